@@ -181,8 +181,9 @@ typedef struct mdet_params {
                                      rows left of it in input order.  1 x 1 pivots only: a
                                      block whose diagonal is exhausted by zeros ([[0, 1],
                                      [1, 0]]) ends the call with MDET_ESINGULAR.  Costs one
-                                     small launch per elimination step (about 0.3 ms per 64
-                                     columns) and workspace for two b x b arrays and one
+                                     launch of one workgroup per 64 columns (about 70 us) for
+                                     b <= 512, one small launch per elimination step (about
+                                     0.3 ms per 64 columns) beyond, and workspace for two b x b arrays and one
                                      (n - b) x b array, counted by mdet_plan; every entry
                                      point takes it; not with MDET_FLAG_PIVOT,
                                      MDET_FLAG_ASSUME_SPD or MDET_FLAG_GENERAL (MDET_EINVAL),

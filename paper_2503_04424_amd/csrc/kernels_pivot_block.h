@@ -12,12 +12,13 @@
 // taken before it.  The scheme is the blocked one with a running diagonal: the diagonal
 // block is kept as a full symmetric matrix S in the workspace, brought up to date with 64
 // pivots at a time (one product S -= L_p D L_p^T on the matrix cores); inside such a group
-// of 64 each step is one small launch over the block's rows,
+// of 64 a step works on the block's rows,
 //     v_i   = S[p][i] - sum_{k < j, this group} L[i][k] (d_k L[p][k])      (column of pivot p)
 //     l_ij  = v_i / d_j,      d_j = running diagonal of p,
 //     diag_i <- diag_i - l_ij v_i,
-// and leaves the partial maxima from which the next launch picks its pivot.  Nothing is
-// swapped while the block is eliminated: rows keep their input positions, columns are in
+// all steps in one launch where one workgroup holds the block's rows (pb_group_kernel), one
+// small launch a step otherwise, which leaves the partial maxima from which the next one
+// picks its pivot (pb_step_kernel).  Nothing is swapped while the block is eliminated: rows keep their input positions, columns are in
 // pivot order (`Lfull`), and the rows below the diagonal block get their 64 new columns by
 // a gather of the pivots' columns, a product with everything solved before (matrix cores),
 // and the leaf solve of the unpivoted path.  At the end the factor is put in place in
@@ -162,6 +163,176 @@ __global__ __launch_bounds__(PB_THREADS) void pb_step_kernel(
   }
   const PbCand best = pb_block_best(next, red);
   if (threadIdx.x == 0) part_out[blockIdx.x] = best;
+}
+
+// All steps of a group of up to 64 pivots in one launch of one workgroup, thread i holding
+// row i (w <= NT): its running diagonal and its multipliers of this group stay in registers.
+// Per step: every wavefront's best candidate to LDS (one barrier), the overall best found by
+// every wavefront alone; the pivot's row of S requested; the thread that holds the pivot puts
+// its multipliers into LDS meanwhile (second barrier); then v, l and the new diagonal as in
+// pb_step_kernel, with the 16 products of a block of multipliers taking the pivot's entries
+// from the lanes of the row (one instruction each).  Same rule, same order of the terms, same
+// outputs as a sequence of pb_step_kernel launches, where a launch and its memory round trips
+// made a step 5.7 us; here it is 1.1 (w = 256, fp64; n = 3000 21.9 -> 6.1 ms).
+// The multipliers of 512 rows are what a compute unit's registers hold (128 of 256 per
+// thread in fp64): larger blocks take a launch per step.
+constexpr int PB_GROUP_ROWS = 512;
+
+// v -= sum_k h[k] w_k, w_k in lane k of each row of 16 lanes (the wait covers the instruction
+// that made w, see MDET_STEP)
+#define MDET_PB_TERM(K, H) MDET_FMAC " %0, -%1, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define MDET_PB_APPLY(TYPE)                                                                              \
+  __device__ __forceinline__ void pb_apply16(TYPE& v, const TYPE (&h)[16], TYPE w) {                    \
+    asm("s_nop 1\n\t" MDET_PB_TERM("0", "2") MDET_PB_TERM("1", "3") MDET_PB_TERM("2", "4")              \
+            MDET_PB_TERM("3", "5") MDET_PB_TERM("4", "6") MDET_PB_TERM("5", "7") MDET_PB_TERM("6", "8") \
+                MDET_PB_TERM("7", "9") MDET_PB_TERM("8", "10") MDET_PB_TERM("9", "11")                  \
+                    MDET_PB_TERM("10", "12") MDET_PB_TERM("11", "13") MDET_PB_TERM("12", "14")          \
+                        MDET_PB_TERM("13", "15") MDET_PB_TERM("14", "16") MDET_PB_TERM("15", "17")      \
+        : "+v"(v)                                                                                       \
+        : "v"(w), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "v"(h[4]), "v"(h[5]), "v"(h[6]),          \
+          "v"(h[7]), "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11]), "v"(h[12]), "v"(h[13]), "v"(h[14]),  \
+          "v"(h[15]));                                                                                  \
+  }
+#define MDET_FMAC "v_fmac_f64_dpp"
+MDET_PB_APPLY(double)
+#undef MDET_FMAC
+#define MDET_FMAC "v_fmac_f32_dpp"
+MDET_PB_APPLY(float)
+#undef MDET_FMAC
+#undef MDET_PB_APPLY
+#undef MDET_PB_TERM
+
+// The lane with the largest key, the lowest one on ties; `top` = that key (0: no candidate,
+// lane 0).  Must be reached by all 64 lanes.
+__device__ __forceinline__ int pb_wave_best(unsigned long long key, unsigned long long& top) {
+  const unsigned hi = (unsigned)(key >> 32), lo = (unsigned)key;
+  const unsigned top_hi = wave_max_u32(hi);
+  unsigned long long hit = __ballot(hi == top_hi);
+  // the upper words nearly always decide
+  if (hit & (hit - 1ull)) {
+    const unsigned top_lo = wave_max_u32(hi == top_hi ? lo : 0u);
+    hit = __ballot(hi == top_hi && lo == top_lo);
+  }
+  const int lane = __ffsll((long long)hit) - 1;
+  top = ((unsigned long long)top_hi << 32) | (unsigned)__builtin_amdgcn_readlane((int)lo, lane);
+  return lane;
+}
+// fp32 keys in the upper word, where pb_wave_best looks first
+__device__ __forceinline__ unsigned long long pb_wave_key(double v) { return pb_key(v); }
+__device__ __forceinline__ unsigned long long pb_wave_key(float v) { return pb_key(v) << 32; }
+
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, int64_t lds, T* __restrict__ Lfull,
+                                                      int64_t ldl, T* __restrict__ dg, int* __restrict__ active,
+                                                      int* __restrict__ piv, T* __restrict__ dvec,
+                                                      T* __restrict__ dinv, int* __restrict__ perm, int w, int c0,
+                                                      int lw, long long pivot0, DevFlags* flags) {
+  constexpr int NW = NT / 64;
+  using vec_t = typename Mfma<T>::vec_t;
+  constexpr int VEC = Mfma<T>::VEC;
+  __shared__ unsigned long long s_key[2][NW];    // two steps in turn
+  __shared__ int s_row[2][NW];
+  __shared__ T s_diag[2][NW];
+  __shared__ __attribute__((aligned(16))) T s_mult[2][LEAF];
+  const int i = threadIdx.x, lane = i & 63, l16 = i & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(i >> 6);
+  T diag = i < w ? dg[i] : T(0);
+  bool live = i < w && active[i] != 0;
+  // multipliers of the finished blocks of 16 steps and of the current one (0: not taken yet);
+  // pivots likewise, step k of a block in lane k of each row of lanes
+  T h[3][SUB], cur[SUB], dh[3], dcur = T(0);
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    dh[b] = T(0);
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) h[b][k] = T(0);
+  }
+#pragma unroll 1
+  for (int m = 0; 16 * m < lw; ++m) {
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) cur[k] = T(0);
+    dcur = T(0);
+#pragma unroll
+    for (int j = 0; j < SUB; ++j) {
+      const int jj = 16 * m + j, par = j & 1;
+      if (jj < lw) {
+        unsigned long long top;
+        const int best = pb_wave_best(live ? pb_wave_key(diag) : 0ull, top);
+        if (lane == best) {
+          s_key[par][wave] = top;
+          s_row[par][wave] = i;
+          s_diag[par][wave] = diag;
+        }
+        __syncthreads();
+        const int from = pb_wave_best(lane < NW ? s_key[par][lane < NW ? lane : 0] : 0ull, top);
+        const int p = __builtin_amdgcn_readfirstlane(s_row[par][from]);
+        const T d = s_diag[par][from];
+        const T sv = i < w ? S[(int64_t)p * lds + i] : T(0);
+        if (i == p) {
+          T* to = s_mult[par];
+          vec_t v;
+#pragma unroll
+          for (int b = 0; b < 3; ++b)
+            if (m > b)
+#pragma unroll
+              for (int k = 0; k < SUB; k += VEC) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[e] = h[b][k + e];
+                *reinterpret_cast<vec_t*>(to + SUB * b + k) = v;
+              }
+#pragma unroll
+          for (int k = 0; k < SUB; k += VEC) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) v[e] = cur[k + e];
+            *reinterpret_cast<vec_t*>(to + SUB * m + k) = v;
+          }
+          piv[c0 + jj] = p;
+          dvec[c0 + jj] = d;
+          dinv[c0 + jj] = T(1) / d;
+          perm[c0 + jj] = (int)pivot0 + p;
+          const bool zero = d == T(0);
+          const bool finite = fabs((double)d) <= 1.7976931348623157e308;
+          if (zero || !finite) {
+            const unsigned long long idx = (unsigned long long)(pivot0 + c0 + jj);
+            const unsigned long long old = atomicMin(&flags->first_bad, idx);
+            if (idx <= old) atomicExch(&flags->bad_kind, zero ? 1ull : 2ull);
+          }
+        }
+        __syncthreads();
+        T v = sv;
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          if (m > b) pb_apply16(v, h[b], s_mult[par][SUB * b + l16] * dh[b]);
+        if (j > 0) pb_apply16(v, cur, s_mult[par][SUB * m + l16] * dcur);
+        if (l16 == j) dcur = d;
+        live = live && i != p;
+        const T l = live ? v / d : T(0);
+        diag = fma(-l, v, diag);
+        cur[j] = l;
+      }
+    }
+    if (i < w) {
+      T* to = Lfull + (int64_t)i * ldl + c0 + SUB * m;
+#pragma unroll
+      for (int k = 0; k < SUB; k += VEC) {
+        vec_t v;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = cur[k + e];
+        *reinterpret_cast<vec_t*>(to + k) = v;
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+      if (m == b) {
+        dh[b] = dcur;
+#pragma unroll
+        for (int k = 0; k < SUB; ++k) h[b][k] = cur[k];
+      }
+  }
+  if (i < w) {
+    dg[i] = diag;
+    active[i] = live ? 1 : 0;
+  }
 }
 
 // The group's own lw x lw leaf in pivot order (strictly lower part; 64 x 64, leading

@@ -481,12 +481,23 @@ struct Launcher {
     int rc = MDET_OK;
     for (int64_t c0 = 0; c0 < w && rc == MDET_OK; c0 += LEAF) {
       const int lw = (int)(w - c0 < LEAF ? w - c0 : LEAF);
-      for (int jj = 0; jj < lw; ++jj) {
-        hipLaunchKernelGGL((pb_step_kernel<T>), dim3((unsigned)nparts), dim3(PB_THREADS), 0, st, (const T*)pb.S, ldl,
-                           pb.Lfull, ldl, pb.dg, pb.active, (const PbCand*)part[cur], part[cur ^ 1], nparts, pb.piv,
-                           dvec + d0, dinv + d0, perm + d0, (int)w, (int)c0, jj, (long long)d0, flags);
-        cur ^= 1;
+      // a block whose rows one workgroup holds: the whole group in one launch
+      if (w <= PB_GROUP_ROWS) {
+#define MDET_LAUNCH_GROUP(NT)                                                                                       \
+  hipLaunchKernelGGL((pb_group_kernel<T, NT>), dim3(1), dim3(NT), 0, st, (const T*)pb.S, ldl, pb.Lfull, ldl, pb.dg, \
+                     pb.active, pb.piv, dvec + d0, dinv + d0, perm + d0, (int)w, (int)c0, lw, (long long)d0, flags)
+        if (w <= PB_GROUP_ROWS / 2) MDET_LAUNCH_GROUP(PB_GROUP_ROWS / 2);
+        else MDET_LAUNCH_GROUP(PB_GROUP_ROWS);
+#undef MDET_LAUNCH_GROUP
         ++launches;
+      } else {
+        for (int jj = 0; jj < lw; ++jj) {
+          hipLaunchKernelGGL((pb_step_kernel<T>), dim3((unsigned)nparts), dim3(PB_THREADS), 0, st, (const T*)pb.S, ldl,
+                             pb.Lfull, ldl, pb.dg, pb.active, (const PbCand*)part[cur], part[cur ^ 1], nparts, pb.piv,
+                             dvec + d0, dinv + d0, perm + d0, (int)w, (int)c0, jj, (long long)d0, flags);
+          cur ^= 1;
+          ++launches;
+        }
       }
       fail->check(hipGetLastError());
       fma += (double)w * lw * (lw - 1) / 2.0;
