@@ -298,70 +298,58 @@ struct Diag16 {
   }
 };
 
-// Inverse of the unit-lower diagonal sub-block b of the leaf in `tile` -> linv.
-// Lane (l16, g) computes column l16: x_i = delta_{i,l16} - sum_{k<i} L[i][k] x_k, the
-// terms in the order k = 0, 1, ...; the entries of L are same-address LDS reads,
-// requested a group of rows ahead of the group being computed.  Left to itself the
-// compiler either puts each read next to its use, so that the latency of every one
-// shows, or issues all 120 at once and needs 300 registers: each group therefore
-// reads through an index the compiler cannot see through (a zero that has passed an
-// empty asm statement), which ties the reads to the place where they are written.
-__device__ __forceinline__ int opaque_zero() {
-  int z = 0;
-  asm volatile("" : "+v"(z));
-  return z;
-}
-template <typename T, int I0, int I1>
-__device__ __forceinline__ void invert_fetch(const T* Lb, T (&l)[SUB * (SUB - 1) / 2]) {
-  const T* p = Lb + opaque_zero();
-#pragma unroll
-  for (int i = I0; i < I1; ++i)
-#pragma unroll
-    for (int k = 0; k < i; ++k) l[i * (i - 1) / 2 + k] = p[i * LEAF_PAD + k];
-}
-template <typename T, int I0, int I1>
-__device__ __forceinline__ void invert_rows(const T (&l)[SUB * (SUB - 1) / 2], T (&x)[SUB],
-                                            const int l16) {
-#pragma unroll
-  for (int i = I0; i < I1; ++i) {
-    T v = i == l16 ? T(1) : T(0);
-#pragma unroll
-    for (int k = 0; k < i; ++k) v -= l[i * (i - 1) / 2 + k] * x[k];
-    x[i] = v;
+// Inverse of a unit-lower 16 x 16 block -> linv (16 x 16, row-major), by one wavefront: nl[k]
+// of lane (c, g) is minus entry (c, k) of the block below the diagonal (c > k), 0 elsewhere.
+// As in Diag16, row c in lane c, the columns dealt out to the four rows of lanes: step k adds
+// nl_ck times row k, read from lane k by the multiply-add itself.  64 instructions and no
+// memory in between; substituting column by column with the block's entries as LDS broadcasts
+// took 3000 clocks, ten times as long.  (Four registers in turn, so that none is read from
+// another lane within two instructions of being written.)
+#define MDET_INV_ROW(K, N)                                                                           \
+  MDET_FMAC " %0, %0, %" N MDET_DPP(K) MDET_FMAC " %1, %1, %" N MDET_DPP(K)                          \
+      MDET_FMAC " %2, %2, %" N MDET_DPP(K) MDET_FMAC " %3, %3, %" N MDET_DPP(K)
+#define MDET_INVERT16(TYPE)                                                                          \
+  __device__ __forceinline__ void invert16_rows(TYPE (&x)[4], const TYPE (&nl)[SUB]) {               \
+    asm("s_nop 1\n\t" MDET_INV_ROW("0", "4") MDET_INV_ROW("1", "5") MDET_INV_ROW("2", "6")           \
+            MDET_INV_ROW("3", "7") MDET_INV_ROW("4", "8") MDET_INV_ROW("5", "9")                     \
+                MDET_INV_ROW("6", "10") MDET_INV_ROW("7", "11") MDET_INV_ROW("8", "12")              \
+                    MDET_INV_ROW("9", "13") MDET_INV_ROW("10", "14") MDET_INV_ROW("11", "15")        \
+                        MDET_INV_ROW("12", "16") MDET_INV_ROW("13", "17") MDET_INV_ROW("14", "18")   \
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])                                             \
+        : "v"(nl[0]), "v"(nl[1]), "v"(nl[2]), "v"(nl[3]), "v"(nl[4]), "v"(nl[5]), "v"(nl[6]),        \
+          "v"(nl[7]), "v"(nl[8]), "v"(nl[9]), "v"(nl[10]), "v"(nl[11]), "v"(nl[12]), "v"(nl[13]),    \
+          "v"(nl[14]));                                                                              \
   }
+#define MDET_FMAC "v_fmac_f64_dpp"
+MDET_INVERT16(double)
+#undef MDET_FMAC
+#define MDET_FMAC "v_fmac_f32_dpp"
+MDET_INVERT16(float)
+#undef MDET_FMAC
+#undef MDET_INVERT16
+#undef MDET_INV_ROW
+template <typename T>
+__device__ __forceinline__ void invert16(const T (&nl)[SUB], T* __restrict__ linv, const int lane) {
+  const int c = lane & 15;
+  T x[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) x[s] = Mfma<T>::acc_row(lane, s) == c ? T(1) : T(0);
+  invert16_rows(x, nl);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) linv[c * SUB + Mfma<T>::acc_row(lane, s)] = x[s];
 }
+// The same for diagonal sub-block b of the unit-lower leaf in `tile` -> its place in linv.
 template <typename T>
 __device__ __forceinline__ void leaf_invert_sub(const T* tile, T* __restrict__ linv, const int b,
-                                                const int l16) {
-  const T* Lb = tile + (b * SUB) * LEAF_PAD + b * SUB;
-  T l[SUB * (SUB - 1) / 2], x[SUB];
-  // groups of rows with about 20 entries each; two groups are in flight at a time
-  invert_fetch<T, 1, 6>(Lb, l);
-  invert_fetch<T, 6, 9>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 0, 6>(l, x, l16);
-  invert_fetch<T, 9, 11>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 6, 9>(l, x, l16);
-  invert_fetch<T, 11, 13>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 9, 11>(l, x, l16);
-  invert_fetch<T, 13, 14>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 11, 13>(l, x, l16);
-  invert_fetch<T, 14, 15>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 13, 14>(l, x, l16);
-  invert_fetch<T, 15, 16>(Lb, l);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 14, 15>(l, x, l16);
-  __builtin_amdgcn_sched_barrier(0);
-  invert_rows<T, 15, 16>(l, x, l16);
-  // all four groups of 16 lanes hold the same columns and store the same values (a
-  // store by one group only would let the compiler move the arithmetic into that
-  // branch, behind all the reads)
+                                                const int lane) {
+  const int c = lane & 15;
+  const T* row = tile + (b * SUB + c) * LEAF_PAD + b * SUB;
+  T nl[SUB];
 #pragma unroll
-  for (int i = 0; i < SUB; ++i) linv[(b * SUB + i) * SUB + l16] = x[i];
+  for (int k = 0; k < SUB; ++k) nl[k] = row[k];
+#pragma unroll
+  for (int k = 0; k < SUB; ++k) nl[k] = c > k ? -nl[k] : T(0);
+  invert16<T>(nl, linv + b * SUB * SUB, lane);
 }
 
 // Four wavefronts factor one leaf held in LDS, on 16 x 16 sub-blocks.  Sub-block (i, j) of the
@@ -757,7 +745,7 @@ __global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_pivoted_kernel(
     const int r = e >> 6, c = e & 63;
     if (r < w && c <= r) A[(int64_t)r * ld + c] = tile[r * LEAF_PAD + c];
   }
-  leaf_invert_sub<T>(tile, linv, wave, l16);
+  leaf_invert_sub<T>(tile, linv, wave, lane);
   if (wave == 0) {
     const T myd = dl[lane];
     const bool zero = myd == T(0);
@@ -792,142 +780,189 @@ __global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_pivoted_kernel(
 // elimination with the pivot of column j taken among the leaf's rows not taken before
 // (largest magnitude; the lowest row of the input on ties).  Rows stay where they are
 // while the elimination runs: lane r of every wavefront holds row r, wavefront q its
-// columns 16q .. 16q+15, in registers.  At step j the wavefront that owns column j picks
-// the pivot row and hands the multipliers and the row's number to the others through LDS
-// (one barrier per step); each wavefront then reads the pivot row's entries of its own
-// columns from the pivot lane's registers.  The rows are put into the order of their
-// choice at the end.  On return Pl holds L below the diagonal and D on it, Qu holds U^T
+// columns CW q .. CW q + CW - 1, in registers.  The wavefront that owns column j picks the
+// pivot row, leaves the multipliers and then the row's number in LDS, in places of their own
+// for every step, and goes on with its next column at once; the wavefronts with later columns
+// follow at their own pace, each waiting for a step's row number (a wavefront's LDS
+// operations complete in the order they were issued, so the multipliers are there when the
+// number is) and reading the pivot row's entries of its own columns from the pivot lane's
+// registers.  No step has a barrier, and a wavefront is through with the earlier columns
+// about one LDS round trip after their owner.  Every wait ends: the owner of a column waits
+// only for earlier columns, and all wavefronts of the one workgroup are on the compute unit.
+// The rows are put into the order of their choice at the end.  On return Pl holds L below the
+// diagonal and D on it, Qu holds U^T
 // (strictly lower, unit diagonal implied), dvec / dinv the pivots and their reciprocals,
 // linvL / linvU the inverses of the 16 x 16 diagonal sub-blocks of L and of U^T (for
 // leaf_solve_kernel: rows below in Pl are solved against U^T, rows below in Qu against L
 // with the leaf's row order as their column gather), perm[j] = pivot0 + (row of the leaf
 // taken at step j); flags->odd_leaves is raised by one if that order is an odd permutation.
-// NW wavefronts (4, 8 or 16): wavefront q holds columns q CW .. q CW + CW - 1, CW = 64 / NW.
-// A step costs its wavefront about 60 clocks per column held (two v_readlane of about 20
-// clocks each, the multiply-add and the live-row select), which is most of the step with
-// 16 columns; 16 wavefronts of 4 columns each spread that over the compute unit's SIMDs.
-constexpr int LU_WAVES = 16;   // n = 8192 as a general matrix: 15.02 ms with 4, 13.97 with 8, 13.56 with 16
+// Bound by the owner's chain: search (six exchanges, a ballot), pivot, estimate, quotient,
+// the next column's update, 425 clocks a step.  Measured, fp64: 18.7 us alone, 19.4 in a run
+// of n = 2900, against 33.5 and 34 with a barrier per step and 16 wavefronts of four columns
+// (n = 2900 3.35 -> 2.74 ms, n = 8192 13.2 -> 11.5 ms).
+constexpr int LU_WAVES = 8;
+// LDS that wavefronts exchange without a barrier: accesses stay in the order they are written
+// in, and in LDS instructions (through a generic pointer they would be memory instructions,
+// each waited for).
+template <typename T>
+using lds_volatile = volatile __attribute__((address_space(3))) T;
+
+// The lane of `cand` whose v is largest in magnitude, the lowest one on ties; cand is not
+// empty.  As pick_pivot, on the bit patterns without their sign (that of a NaN is above all
+// others by itself).
+__device__ __forceinline__ int pick_lane(double v, unsigned long long cand) {
+  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
+  const unsigned hi = (unsigned)__double2hiint(v) & 0x7fffffffu;
+  const unsigned top_hi = wave_max_u32(mine ? hi : 0u);
+  unsigned long long hit = __builtin_amdgcn_ballot_w64(hi == top_hi) & cand;
+  // the upper words (exponent, 20 bits of the fraction) nearly always decide
+  if (__builtin_expect((hit & (hit - 1ull)) != 0ull, 0)) {
+    const bool level = __builtin_amdgcn_inverse_ballot_w64(hit);
+    const unsigned lo = (unsigned)__double2loint(v);
+    const unsigned top_lo = wave_max_u32(level ? lo : 0u);
+    hit &= __builtin_amdgcn_ballot_w64(lo == top_lo);
+  }
+  return __builtin_ctzll(hit);
+}
+__device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
+  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
+  const unsigned key = __float_as_uint(v) & 0x7fffffffu;
+  const unsigned top = wave_max_u32(mine ? key : 0u);
+  return __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == top) & cand);
+}
+
 template <typename T, int NW>
 __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
     T* __restrict__ Pl, T* __restrict__ Qu, int64_t ld, int w, T* __restrict__ dvec,
     T* __restrict__ dinv, T* __restrict__ linvL, T* __restrict__ linvU, int* __restrict__ perm,
     long long pivot0, DevFlags* flags) {
   constexpr int CW = LEAF / NW;          // columns per wavefront
-  constexpr int NT = 64 * NW;            // threads
-  __shared__ T S[LEAF_TILE];      // the rows in their final order: L below, D U on and above
-  __shared__ T Lm[LEAF_TILE];     // multipliers by input row; afterwards U^T
-  __shared__ T lbuf[2][LEAF];            // a step's multipliers, for the other wavefronts
-  __shared__ int pbuf[2];                // and its pivot row
-  __shared__ int ord[LEAF];
-  __builtin_amdgcn_s_setprio(3);
+  static_assert(NW == 2 * NSUB, "one diagonal sub-block of L or U^T to invert per wavefront");
+  __shared__ T S[LEAF_TILE];             // the leaf; afterwards, rows in pivot order: L below, D U on and above
+  __shared__ T mult[LEAF][LEAF];         // minus the multipliers of every step, by input row
+  __shared__ int row_of[LEAF];           // row taken at a step; -1: not yet
+  __shared__ int pos[LEAF];              // step at which a row was taken
+  __builtin_amdgcn_s_setprio(2);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15;
   const int c0 = wave * CW;
-  constexpr int PER = LEAF * LEAF / NT;
+  {
+    // rows of both halves, one row a load: (r, c) of the lower half, (c, r) of the upper;
+    // the padding of a narrow leaf is the identity
+    T p[CW], q[CW];
+#pragma unroll
+    for (int k = 0; k < CW; ++k) {
+      const int r = NW * k + wave;
+      p[k] = (r < w && lane <= r) ? Pl[(int64_t)r * ld + lane] : (r == lane ? T(1) : T(0));
+      q[k] = (r < w && lane < r) ? Qu[(int64_t)r * ld + lane] : T(0);
+    }
+#pragma unroll
+    for (int k = 0; k < CW; ++k) {
+      const int r = NW * k + wave;
+      if (lane <= r) S[r * LEAF_PAD + lane] = p[k];
+      if (lane < r) S[lane * LEAF_PAD + r] = q[k];
+    }
+  }
+  if (tid < LEAF) row_of[tid] = -1;
+  __syncthreads();
   T a[CW];
 #pragma unroll
-  for (int k = 0; k < CW; ++k) {
-    // (r, c) of the lower half and (c, r) of the upper half come from the same place of
-    // the two arrays: row max(r, c), column min(r, c)
-    const int r = lane, c = c0 + k;
-    const int hi = r > c ? r : c, lo = r > c ? c : r;
-    a[k] = (r < w && c < w) ? (c <= r ? Pl[(int64_t)hi * ld + lo] : Qu[(int64_t)hi * ld + lo])
-                            : (r == c ? T(1) : T(0));
-  }
-#pragma unroll
-  for (int q = 0; q < PER; ++q) Lm[((q * NT + tid) >> 6) * LEAF_PAD + (tid & 63)] = T(0);
-  if (tid < LEAF) ord[tid] = tid;
-  __syncthreads();                            // Lm is clear before the first multiplier lands in it
-  unsigned long long taken = 0ull;            // the same in every lane and wavefront
-  int mypos = lane;                           // where this lane's row ends
+  for (int k = 0; k < CW; ++k) a[k] = S[lane * LEAF_PAD + c0 + k];
+  // rows still to be taken: those of the leaf, then (w < 64) those of the padding, whose
+  // pivots are their own ones and eliminate nothing
+  unsigned long long left = ~0ull;
+  const unsigned long long real = w < LEAF ? (1ull << w) - 1ull : ~0ull;
+  int odd = 0;                           // parity of the row order so far
+  auto take = [&](const int p) {
+    odd ^= __popcll(left & ((1ull << p) - 1ull)) & 1;      // rows still to come that stand before p
+    left &= ~(1ull << p);
+  };
+  // the earlier columns' steps
 #pragma unroll 1
-  for (int jb = 0; jb < NW; ++jb) {
+  for (int j = 0; j < c0; ++j) {
+    lds_volatile<int>* number = (lds_volatile<int>*)&row_of[j];
+    lds_volatile<T>* from = (lds_volatile<T>*)&mult[j][lane];
+    int p;
+    T nl;
+    do {
+      p = *number;
+      nl = *from;
+      p = __builtin_amdgcn_readfirstlane(p);
+    } while (p < 0);
+    T pv[CW];
 #pragma unroll
-    for (int jj = 0; jj < CW; ++jj) {
-      const int j = jb * CW + jj;
-      if (j < w) {
-        if (wave == jb) {
-          const T cj = a[jj];
-          const bool cand = lane < w && !((taken >> lane) & 1ull);
-          const int pp = pick_pivot(cj, cand);
-          const T rd = fast_rcp(lane_value(cj, pp));
-          const T lj = (cand && lane != pp) ? cj * rd : T(0);
-          lbuf[j & 1][lane] = lj;
-          Lm[lane * LEAF_PAD + j] = lj;
-          if (lane == 0) {
-            pbuf[j & 1] = pp;
-            ord[j] = pp;
-          }
-        }
-        __syncthreads();
-        const T l = lbuf[j & 1][lane];
-        const int p = __builtin_amdgcn_readfirstlane(pbuf[j & 1]);
-        taken |= 1ull << p;
-        if (lane == p) mypos = j;
-        const bool live = lane < w && !((taken >> lane) & 1ull);
-        if (wave >= jb) {
+    for (int k = 0; k < CW; ++k) pv[k] = lane_value(a[k], p);
 #pragma unroll
-          for (int k = 0; k < CW; ++k) {
-            if (wave > jb || k > jj) {
-              const T pv = lane_value(a[k], p);
-              a[k] = live ? fma(-l, pv, a[k]) : a[k];
-            }
-          }
-        }
-      }
-    }
+    for (int k = 0; k < CW; ++k) a[k] = fma(nl, pv[k], a[k]);
+    take(p);
   }
-  // every row to the place of its turn; its entries left of the diagonal are replaced below
+  // its own
+  __builtin_amdgcn_s_setprio(3);
+  int ps[CW];
+  unsigned long long mine_left = left;
 #pragma unroll
-  for (int k = 0; k < CW; ++k) S[mypos * LEAF_PAD + c0 + k] = a[k];
+  for (int jj = 0; jj < CW; ++jj) {
+    const int j = c0 + jj;
+    const T cj = a[jj];
+    const unsigned long long cand = mine_left & (j < w ? real : ~0ull);
+    const int p = pick_lane(cj, cand);
+    const T d = lane_value(cj, p);
+    const T est = rcp_estimate(d);
+    mine_left &= ~(1ull << p);
+    const bool below = __builtin_amdgcn_inverse_ballot_w64(cand & ~(1ull << p));
+    const T np = -(cj * est);
+    const T nl = below ? fma(np, quotient_tail(d, est), np) : T(0);
+    *(lds_volatile<T>*)&mult[j][lane] = nl;
+    *(lds_volatile<int>*)&row_of[j] = p;                   // (every lane: the same value)
+    *(lds_volatile<int>*)&pos[p] = j;
+#pragma unroll
+    for (int k = jj + 1; k < CW; ++k) a[k] = fma(nl, lane_value(a[k], p), a[k]);
+    a[jj] = below ? -nl : cj;
+    ps[jj] = p;
+  }
+  __builtin_amdgcn_s_setprio(2);
+  if (wave == NW - 1) {
+#pragma unroll
+    for (int jj = 0; jj < CW; ++jj) take(ps[jj]);
+    if (lane == 0 && odd) atomicAdd(&flags->odd_leaves, 1ull);
+  }
   __syncthreads();
   {
-    T v[PER];
+    const int to = pos[lane];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = q * NT + tid, r = e >> 6, c = e & 63;
-      const int from = r < w ? ord[r] : r;
-      v[q] = c < r ? Lm[from * LEAF_PAD + c] : S[r * LEAF_PAD + c];
-    }
-    __syncthreads();
-    // L into place; U = D U~: rows of the upper part divided by their pivot, and its
-    // transpose with a unit diagonal
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = q * NT + tid, r = e >> 6, c = e & 63;
-      if (c < r) S[r * LEAF_PAD + c] = v[q];
-      T u = r == c ? T(1) : T(0);
-      if (c > r && c < w) u = v[q] * fast_rcp(S[r * LEAF_PAD + r]);
-      if (c >= r) Lm[c * LEAF_PAD + r] = u;
-    }
+    for (int k = 0; k < CW; ++k) S[to * LEAF_PAD + c0 + k] = a[k];
   }
   __syncthreads();
-  for (int e = tid; e < LEAF * LEAF; e += NT) {
-    const int r = e >> 6, c = e & 63;
-    if (r < w && c <= r) Pl[(int64_t)r * ld + c] = S[r * LEAF_PAD + c];
-    if (r < w && c < r) Qu[(int64_t)r * ld + c] = Lm[r * LEAF_PAD + c];
+  const T myd = S[lane * LEAF_PAD + lane];
+  const T myr = fast_rcp(myd);
+  // L below the diagonal, D on it; U = D U~, transposed
+#pragma unroll
+  for (int k = 0; k < CW; ++k) {
+    const int r = NW * k + wave;
+    if (r < w && lane <= r) Pl[(int64_t)r * ld + lane] = S[r * LEAF_PAD + lane];
+    if (r < w && lane < r) Qu[(int64_t)r * ld + lane] = S[lane * LEAF_PAD + r] * myr;
   }
+  // the inverses of the diagonal sub-blocks, L by the first wavefronts, U~^T by the others
   if (wave < NSUB) {
-    leaf_invert_sub<T>(S, linvL, wave, l16);
-    leaf_invert_sub<T>(Lm, linvU, wave, l16);
+    leaf_invert_sub<T>(S, linvL, wave, lane);
+  } else {
+    const int b = wave - NSUB, c = lane & 15;
+    T nl[SUB];
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) nl[k] = S[(b * SUB + k) * LEAF_PAD + b * SUB + c] * lane_value(myr, b * SUB + k);
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) nl[k] = c > k ? -nl[k] : T(0);
+    invert16<T>(nl, linvU + b * SUB * SUB, lane);
   }
   if (wave == 0) {
-    const T myd = S[lane * LEAF_PAD + lane];
     const bool zero = myd == T(0);
     const bool finite = fabs((double)myd) <= 1.7976931348623157e308;
     const bool bad = lane < w && (zero || !finite);
-    const int mine = ord[lane];
     if (lane < w) {
       dvec[lane] = myd;
-      dinv[lane] = fast_rcp(myd);
-      perm[lane] = (int)pivot0 + mine;
+      dinv[lane] = myr;
+      perm[lane] = (int)pivot0 + row_of[lane];
     }
-    // sign of the order: parity of the number of pairs that stand the wrong way round
-    int inv = 0;
-    for (int k = 0; k < LEAF; ++k) inv += (k > lane && ord[k] < mine) ? 1 : 0;
-    const unsigned long long odd_lanes = __ballot(inv & 1);
-    if (lane == 0 && (__popcll(odd_lanes) & 1)) atomicAdd(&flags->odd_leaves, 1ull);
     const unsigned long long mask = __ballot(bad);
     if (mask != 0ull) {
       const int first = __ffsll((long long)mask) - 1;

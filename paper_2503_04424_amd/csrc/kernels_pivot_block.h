@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void pb_leaf_kernel(const T* __restrict__ Lful
                                                       const int* __restrict__ piv, int c0, int lw,
                                                       T* __restrict__ leaf, T* __restrict__ linv) {
   __shared__ T tile[LEAF * LEAF_PAD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int e = tid; e < LEAF * LEAF; e += 256) {
     const int r = e >> 6, c = e & 63;
     const T v = (r < lw && c < r) ? Lfull[(int64_t)piv[c0 + r] * ldl + c0 + c] : T(0);
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(256) void pb_leaf_kernel(const T* __restrict__ Lful
     leaf[r * LEAF + c] = v;
   }
   __syncthreads();
-  leaf_invert_sub<T>(tile, linv, wave, l16);
+  leaf_invert_sub<T>(tile, linv, wave, lane);
 }
 
 // Rows below the diagonal block: their columns of the group's pivots, side by side in pivot
