@@ -298,6 +298,30 @@ struct Diag16 {
   }
 };
 
+// v -= sum_k h[k] w_k, w_k in lane k of each row of 16 lanes (the wait covers the instruction
+// that made w, see MDET_STEP)
+#define MDET_APPLY_TERM(K, H) MDET_FMAC " %0, -%1, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define MDET_APPLY16(TYPE)                                                                              \
+  __device__ __forceinline__ void apply16(TYPE& v, const TYPE (&h)[16], TYPE w) {                    \
+    asm("s_nop 1\n\t" MDET_APPLY_TERM("0", "2") MDET_APPLY_TERM("1", "3") MDET_APPLY_TERM("2", "4")              \
+            MDET_APPLY_TERM("3", "5") MDET_APPLY_TERM("4", "6") MDET_APPLY_TERM("5", "7") MDET_APPLY_TERM("6", "8") \
+                MDET_APPLY_TERM("7", "9") MDET_APPLY_TERM("8", "10") MDET_APPLY_TERM("9", "11")                  \
+                    MDET_APPLY_TERM("10", "12") MDET_APPLY_TERM("11", "13") MDET_APPLY_TERM("12", "14")          \
+                        MDET_APPLY_TERM("13", "15") MDET_APPLY_TERM("14", "16") MDET_APPLY_TERM("15", "17")      \
+        : "+v"(v)                                                                                       \
+        : "v"(w), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "v"(h[4]), "v"(h[5]), "v"(h[6]),          \
+          "v"(h[7]), "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11]), "v"(h[12]), "v"(h[13]), "v"(h[14]),  \
+          "v"(h[15]));                                                                                  \
+  }
+#define MDET_FMAC "v_fmac_f64_dpp"
+MDET_APPLY16(double)
+#undef MDET_FMAC
+#define MDET_FMAC "v_fmac_f32_dpp"
+MDET_APPLY16(float)
+#undef MDET_FMAC
+#undef MDET_APPLY16
+#undef MDET_APPLY_TERM
+
 // Inverse of a unit-lower 16 x 16 block -> linv (16 x 16, row-major), by one wavefront: nl[k]
 // of lane (c, g) is minus entry (c, k) of the block below the diagonal (c > k), 0 elsewhere.
 // As in Diag16, row c in lane c, the columns dealt out to the four rows of lanes: step k adds
@@ -580,173 +604,173 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
   return (unsigned)__builtin_amdgcn_readlane(m, 63);
 }
 
-// The pivot rule: among the lanes with `candidate` set, the one whose `diag` is largest in
-// magnitude (the lowest lane on ties; a NaN counts as the largest, so that it is taken
-// and reported).  Magnitudes of IEEE numbers order like their bit patterns.  Returns 0 if
-// there is no candidate.  Must be reached by all 64 lanes.
-__device__ __forceinline__ int pick_pivot(double diag, bool candidate) {
-  unsigned long long key = (unsigned long long)__double_as_longlong(fabs(diag));
-  if (!(diag == diag)) key = 0x7ff0000000000000ull;
-  if (!candidate) key = 0ull;
-  const unsigned hi = (unsigned)(key >> 32), lo = (unsigned)key;
-  const unsigned top_hi = wave_max_u32(hi);
-  unsigned long long hit = __ballot(candidate && hi == top_hi);
-  // the upper words (exponent, 20 bits of the fraction) nearly always decide
-  if (hit & (hit - 1ull)) {
-    const unsigned top_lo = wave_max_u32(hi == top_hi ? lo : 0u);
-    hit = __ballot(candidate && hi == top_hi && lo == top_lo);
-  }
-  return hit ? __ffsll((long long)hit) - 1 : 0;
-}
-__device__ __forceinline__ int pick_pivot(float diag, bool candidate) {
-  unsigned key = (unsigned)__float_as_int(fabsf(diag));
-  if (!(diag == diag)) key = 0x7f800000u;
-  if (!candidate) key = 0u;
-  const unsigned top = wave_max_u32(key);
-  const unsigned long long hit = __ballot(candidate && key == top);
-  return hit ? __ffsll((long long)hit) - 1 : 0;
-}
-
-// a[idx] for an index that is the same in all lanes, without a memory round trip: four
-// levels of two-way selects on the bits of idx.  Written as C++ conditionals the
-// compiler recognises an indexed array, moves the array to scratch memory and stores
-// all of it every time it changes; the select instruction itself keeps the 16 values
-// in the registers they live in.
-__device__ __forceinline__ int select_word(int x0, int x1, unsigned long long take1) {
-  int r;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(x0), "v"(x1), "s"(take1));
-  return r;
-}
-__device__ __forceinline__ double select_value(double x0, double x1, unsigned long long take1) {
-  return __hiloint2double(select_word(__double2hiint(x0), __double2hiint(x1), take1),
-                          select_word(__double2loint(x0), __double2loint(x1), take1));
-}
-__device__ __forceinline__ float select_value(float x0, float x1, unsigned long long take1) {
-  return __int_as_float(select_word(__float_as_int(x0), __float_as_int(x1), take1));
-}
+// LDS that wavefronts exchange without a barrier: accesses stay in the order they are written
+// in, and in LDS instructions (through a generic pointer they would be memory instructions,
+// each waited for).
 template <typename T>
-__device__ __forceinline__ T select16(const T (&a)[SUB], int idx) {
-  const unsigned long long b0 = (idx & 1) ? ~0ull : 0ull, b1 = (idx & 2) ? ~0ull : 0ull;
-  const unsigned long long b2 = (idx & 4) ? ~0ull : 0ull, b3 = (idx & 8) ? ~0ull : 0ull;
-  T t8[8], t4[4], t2[2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) t8[k] = select_value(a[2 * k], a[2 * k + 1], b0);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) t4[k] = select_value(t8[2 * k], t8[2 * k + 1], b1);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) t2[k] = select_value(t4[2 * k], t4[2 * k + 1], b2);
-  return select_value(t2[0], t2[1], b3);
+using lds_volatile = volatile __attribute__((address_space(3))) T;
+
+// The pivot rule: the lane of `cand` (not empty) whose v is largest in magnitude, the lowest
+// one on ties.  Magnitudes of IEEE numbers order like their bit patterns without the sign; a
+// NaN is above all others, so that it is taken and reported.  Must be reached by all 64 lanes.
+__device__ __forceinline__ int pick_lane(double v, unsigned long long cand) {
+  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
+  const unsigned hi = (unsigned)__double2hiint(v) & 0x7fffffffu;
+  const unsigned top_hi = wave_max_u32(mine ? hi : 0u);
+  unsigned long long hit = __builtin_amdgcn_ballot_w64(hi == top_hi) & cand;
+  // the upper words (exponent, 20 bits of the fraction) nearly always decide
+  if (__builtin_expect((hit & (hit - 1ull)) != 0ull, 0)) {
+    const bool level = __builtin_amdgcn_inverse_ballot_w64(hit);
+    const unsigned lo = (unsigned)__double2loint(v);
+    const unsigned top_lo = wave_max_u32(level ? lo : 0u);
+    hit &= __builtin_amdgcn_ballot_w64(lo == top_lo);
+  }
+  return __builtin_ctzll(hit);
+}
+__device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
+  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
+  const unsigned key = __float_as_uint(v) & 0x7fffffffu;
+  const unsigned top = wave_max_u32(mine ? key : 0u);
+  return __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == top) & cand);
 }
 
 // One leaf, P A P^T = L D L^T with P chosen inside the leaf: at every step the largest
-// remaining diagonal entry of the Schur complement is the pivot.  Nothing is swapped
-// while the elimination runs.  The leaf is held as a full symmetric matrix, column c in
-// lane c of each of the four wavefronts, wavefront q holding rows 16 q .. 16 q + 15 in
-// registers.  Step j, pivot p: row p is one register of wavefront p / 16, a value per
-// lane, and goes to LDS in one store; from there every lane reads w_c, its own column's
-// entry, and the entries w_r of its wavefront's 16 rows (row p is column p, by symmetry);
-// l_r = w_r / d; a_rc -= l_r w_c.  The chain from one step to the next is short: the pivot
-// d itself comes from the owner lane's register before the exchange, so its reciprocal
-// is ready when w_c arrives; then one product and one fused multiply-add give the lane's
-// new diagonal entry, which every wavefront keeps with the same arithmetic as the
-// entry in the matrix, so that each finds the next pivot by itself and no decision is
-// exchanged.  The multipliers are collected by original row; once every row knows the
-// step at which it was taken they move to that row of the result.  Rows and columns of
-// pivots already taken keep being updated with values that nothing reads.
+// remaining diagonal entry of the Schur complement is the pivot.  Nothing is swapped while the
+// elimination runs; lane c stands for row and column c.  The leaf is a full symmetric matrix
+// in LDS, brought up to date with 16 steps at a time on the matrix cores by all wavefronts;
+// the steps themselves are wavefront 0's.  Step j, pivot p: row p is read from LDS, v_c; the
+// steps of the same 16 are applied to it, v_c -= l_kc (l_kp d_k), with l_kc in registers and the
+// bracket from lane k of the row of lanes; l_c = v_c / d for the rows still to come; the running diagonal, in registers,
+// receives -l_c v_c.  So a row that has been taken keeps its pivot there, and the next
+// pivot can be looked for at once.  The multipliers are kept by step and input row, and put
+// into the order in which the rows were taken when they are written to memory.
 // Outputs as leaf_factor_kernel (L and D in pivot order into A, pivots, reciprocals,
 // inverses of the diagonal sub-blocks of L), and perm[j] = pivot0 + (row taken at step j).
+// Bound by the chain of one step (460 clocks: search, row from LDS, its 16 terms, quotient);
+// the three products between cost 2300 clocks each.  Measured, fp64, alone: 20.1 us against
+// 32.3 with the matrix in the registers of four wavefronts and a barrier and an exchange of
+// the pivot row per step (n = 4096 4.39 -> 3.70 ms).
+constexpr int PIVOT_WAVES = 8;
 template <typename T>
-__global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_pivoted_kernel(
+__global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
     T* __restrict__ A, int64_t ld, int w, T* __restrict__ dvec, T* __restrict__ dinv,
     T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags) {
-  __shared__ T tile[LEAF_TILE];
-  __shared__ T prow[2][LEAF];     // the pivot row, two steps alternating
+  using X = Mfma<T>;
+  using acc_t = typename X::acc_t;
+  constexpr int NW = PIVOT_WAVES;
+  __shared__ T S[LEAF_TILE];
+  __shared__ T mult[LEAF_TILE];   // multipliers: by step, input row (0 for rows taken before)
   __shared__ T dl[LEAF];          // pivots in the order taken
-  __shared__ int pos[LEAF];       // step at which a row was taken
-  __shared__ int src[LEAF];       // row taken at a step
+  __shared__ int row_of[LEAF];    // row taken at a step
   __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15;
-  constexpr int PER = LEAF * LEAF / FACTOR_THREADS;
   {
-    T v[PER];
+    // one row a load; the padding of a narrow leaf is the identity
+    T v[LEAF / NW];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = q * FACTOR_THREADS + tid, r = e >> 6, c = e & 63;
-      v[q] = (r < w && c <= r) ? A[(int64_t)r * ld + c] : T(0);
+    for (int k = 0; k < LEAF / NW; ++k) {
+      const int r = NW * k + wave;
+      v[k] = (r < w && lane <= r) ? A[(int64_t)r * ld + lane] : (r == lane ? T(1) : T(0));
     }
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = q * FACTOR_THREADS + tid, r = e >> 6, c = e & 63;
-      tile[r * LEAF_PAD + c] = v[q];
-    }
-  }
-  __syncthreads();
-  T a[SUB];        // a[k] = entry (16 wave + k, lane)
-#pragma unroll
-  for (int k = 0; k < SUB; ++k) {
-    const int r = wave * SUB + k;
-    a[k] = lane <= r ? tile[r * LEAF_PAD + lane] : tile[lane * LEAF_PAD + r];
-  }
-  T diag = tile[lane * LEAF_PAD + lane];
-  __syncthreads();
-  for (int e = tid; e < LEAF_TILE; e += FACTOR_THREADS) tile[e] = T(0);
-  if (wave == 0) {
-    pos[lane] = lane;      // rows of the padding (w < 64) stay where they are
-    src[lane] = lane;
-    dl[lane] = T(1);
-  }
-  bool taken = lane >= w;
-  int p = pick_pivot(diag, !taken);
-#pragma unroll 1
-  for (int j = 0; j < w; ++j) {
-    T* pr = prow[j & 1];
-    if (wave == (p >> 4)) pr[lane] = select16<T>(a, p & 15);
-    const T d = lane_value(diag, p);
-    const T rd = fast_rcp(d);
-    // also orders the clearing of the tile before the first multiplier written to it
-    __syncthreads();
-    const T wc = pr[lane];
-    T wr[SUB];
-#pragma unroll
-    for (int k = 0; k < SUB; ++k) wr[k] = pr[wave * SUB + k];
-    const bool live = !taken && lane != p;
-    const T lc = live ? wc * rd : T(0);
-    diag = fma(-lc, wc, diag);      // the same operands as this column's diagonal entry in a[]
-    if (wave == 0) {
-      if (live) tile[lane * LEAF_PAD + j] = lc;
-      if (lane == p) {
-        pos[lane] = j;
-        src[j] = lane;
-        dl[j] = d;
+    for (int k = 0; k < LEAF / NW; ++k) {
+      const int r = NW * k + wave;
+      if (lane <= r) {
+        S[r * LEAF_PAD + lane] = v[k];
+        S[lane * LEAF_PAD + r] = v[k];
       }
     }
-    if (lane == p) taken = true;
-    p = pick_pivot(diag, !taken);
-#pragma unroll
-    for (int k = 0; k < SUB; ++k) a[k] = fma(-(wr[k] * rd), wc, a[k]);
   }
+  for (int e = tid; e < LEAF_TILE; e += 64 * NW) mult[e] = T(0);
   __syncthreads();
-  // rows into the order in which they were taken; row r has multipliers in columns < pos[r]
-  {
-    T v[PER];
+  T diag = S[lane * LEAF_PAD + lane];
+  // rows still to be taken: those of the leaf, then (w < 64) those of the padding, whose
+  // pivots are their own ones and eliminate nothing
+  unsigned long long left = ~0ull;
+  const unsigned long long real = w < LEAF ? (1ull << w) - 1ull : ~0ull;
+#pragma unroll 1
+  for (int m = 0; m < NSUB; ++m) {
+    if (wave == 0) {
+      // dm, pm: pivot and row of step k of the 16 in lane k of each row of lanes
+      T l[SUB], dm = T(0);
+      int pm = 0, mine = l16;
+      asm volatile("" : "+v"(mine));         // compared here, not kept as 16 masks in scalar registers
 #pragma unroll
-    for (int q = 0; q < PER; ++q) v[q] = tile[((q * FACTOR_THREADS + tid) >> 6) * LEAF_PAD + (tid & 63)];
+      for (int k = 0; k < SUB; ++k) l[k] = T(0);
+#pragma unroll
+      for (int j = 0; j < SUB; ++j) {
+        const int jj = m * SUB + j;
+        const int p = pick_lane(diag, left & (jj < w ? real : ~0ull));
+        T v = S[p * LEAF_PAD + lane];
+        const T lp = mult[(m * SUB + l16) * LEAF_PAD + p];
+        const T d = lane_value(diag, p);
+        const T est = rcp_estimate(d);
+        const T tail = quotient_tail(d, est);
+        left &= ~(1ull << p);
+        if (j > 0) apply16(v, l, lp * dm);
+        dm = mine == j ? d : dm;
+        const T q = v * est;
+        l[j] = __builtin_amdgcn_inverse_ballot_w64(left) ? fma(q, tail, q) : T(0);
+        diag = fma(-l[j], v, diag);
+        mult[jj * LEAF_PAD + lane] = l[j];
+        pm = mine == j ? p : pm;
+      }
+      dl[m * SUB + l16] = dm;                // (the four rows of lanes: the same values)
+      row_of[m * SUB + l16] = pm;
+    }
     __syncthreads();
+    if (m + 1 < NSUB) {
+      // S -= L D L^T of these 16 steps, all of it: row p is wanted, whatever p.  Two of the
+      // 16 sub-blocks a wavefront, side by side
+      static_assert(2 * PIVOT_WAVES == NSUB * NSUB, "two sub-blocks a wavefront");
+      const int R = (wave >> 1) * SUB, C = (wave & 1) * 2 * SUB;
+      acc_t acc[2];
+      T aop[4], bop[2][4];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int r = (q * FACTOR_THREADS + tid) >> 6, c = tid & 63, to = pos[r];
-      tile[to * LEAF_PAD + c] = c == to ? dl[to] : v[q];
+      for (int s = 0; s < 4; ++s) {
+        const int k = m * SUB + X::acc_row(lane, s);
+        aop[s] = -(mult[k * LEAF_PAD + R + l16] * dl[k]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          bop[t][s] = mult[k * LEAF_PAD + C + t * SUB + l16];
+          acc[t][s] = S[(R + X::acc_row(lane, s)) * LEAF_PAD + C + t * SUB + l16];
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = X::mfma(aop[s], bop[t][s], acc[t]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) S[(R + X::acc_row(lane, s)) * LEAF_PAD + C + t * SUB + l16] = acc[t][s];
+      __syncthreads();
     }
   }
-  __syncthreads();
-  for (int e = tid; e < LEAF * LEAF; e += FACTOR_THREADS) {
-    const int r = e >> 6, c = e & 63;
-    if (r < w && c <= r) A[(int64_t)r * ld + c] = tile[r * LEAF_PAD + c];
+  // L and D in the order in which the rows were taken
+  {
+    T v[LEAF / NW];
+#pragma unroll
+    for (int k = 0; k < LEAF / NW; ++k) v[k] = mult[lane * LEAF_PAD + row_of[NW * k + wave]];
+    const T myd = dl[lane];
+#pragma unroll
+    for (int k = 0; k < LEAF / NW; ++k) {
+      const int r = NW * k + wave;
+      if (r < w && lane <= r) A[(int64_t)r * ld + lane] = lane == r ? myd : v[k];
+    }
   }
-  leaf_invert_sub<T>(tile, linv, wave, lane);
-  if (wave == 0) {
+  if (wave < NSUB) {
+    const int c = row_of[wave * SUB + l16];
+    T nl[SUB];
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) nl[k] = mult[(wave * SUB + k) * LEAF_PAD + c];
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) nl[k] = l16 > k ? -nl[k] : T(0);
+    invert16<T>(nl, linv + wave * SUB * SUB, lane);
+  }
+  if (wave == NW - 1) {
     const T myd = dl[lane];
     const bool zero = myd == T(0);
     const bool finite = fabs((double)myd) <= 1.7976931348623157e308;
@@ -754,7 +778,7 @@ __global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_pivoted_kernel(
     if (lane < w) {
       dvec[lane] = myd;
       dinv[lane] = fast_rcp(myd);
-      perm[lane] = (int)pivot0 + src[lane];
+      perm[lane] = (int)pivot0 + row_of[lane];
     }
     const unsigned long long mask = __ballot(bad);
     if (mask != 0ull) {
@@ -801,36 +825,6 @@ __global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_pivoted_kernel(
 // of n = 2900, against 33.5 and 34 with a barrier per step and 16 wavefronts of four columns
 // (n = 2900 3.35 -> 2.74 ms, n = 8192 13.2 -> 11.5 ms).
 constexpr int LU_WAVES = 8;
-// LDS that wavefronts exchange without a barrier: accesses stay in the order they are written
-// in, and in LDS instructions (through a generic pointer they would be memory instructions,
-// each waited for).
-template <typename T>
-using lds_volatile = volatile __attribute__((address_space(3))) T;
-
-// The lane of `cand` whose v is largest in magnitude, the lowest one on ties; cand is not
-// empty.  As pick_pivot, on the bit patterns without their sign (that of a NaN is above all
-// others by itself).
-__device__ __forceinline__ int pick_lane(double v, unsigned long long cand) {
-  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
-  const unsigned hi = (unsigned)__double2hiint(v) & 0x7fffffffu;
-  const unsigned top_hi = wave_max_u32(mine ? hi : 0u);
-  unsigned long long hit = __builtin_amdgcn_ballot_w64(hi == top_hi) & cand;
-  // the upper words (exponent, 20 bits of the fraction) nearly always decide
-  if (__builtin_expect((hit & (hit - 1ull)) != 0ull, 0)) {
-    const bool level = __builtin_amdgcn_inverse_ballot_w64(hit);
-    const unsigned lo = (unsigned)__double2loint(v);
-    const unsigned top_lo = wave_max_u32(level ? lo : 0u);
-    hit &= __builtin_amdgcn_ballot_w64(lo == top_lo);
-  }
-  return __builtin_ctzll(hit);
-}
-__device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
-  const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
-  const unsigned key = __float_as_uint(v) & 0x7fffffffu;
-  const unsigned top = wave_max_u32(mine ? key : 0u);
-  return __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == top) & cand);
-}
-
 template <typename T, int NW>
 __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
     T* __restrict__ Pl, T* __restrict__ Qu, int64_t ld, int w, T* __restrict__ dvec,
@@ -935,12 +929,18 @@ __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
   __syncthreads();
   const T myd = S[lane * LEAF_PAD + lane];
   const T myr = fast_rcp(myd);
+  T up[CW];
   // L below the diagonal, D on it; U = D U~, transposed
 #pragma unroll
   for (int k = 0; k < CW; ++k) {
+    a[k] = S[(NW * k + wave) * LEAF_PAD + lane];
+    up[k] = S[lane * LEAF_PAD + NW * k + wave] * myr;
+  }
+#pragma unroll
+  for (int k = 0; k < CW; ++k) {
     const int r = NW * k + wave;
-    if (r < w && lane <= r) Pl[(int64_t)r * ld + lane] = S[r * LEAF_PAD + lane];
-    if (r < w && lane < r) Qu[(int64_t)r * ld + lane] = S[lane * LEAF_PAD + r] * myr;
+    if (r < w && lane <= r) Pl[(int64_t)r * ld + lane] = a[k];
+    if (r < w && lane < r) Qu[(int64_t)r * ld + lane] = up[k];
   }
   // the inverses of the diagonal sub-blocks, L by the first wavefronts, U~^T by the others
   if (wave < NSUB) {

@@ -178,30 +178,6 @@ __global__ __launch_bounds__(PB_THREADS) void pb_step_kernel(
 // thread in fp64): larger blocks take a launch per step.
 constexpr int PB_GROUP_ROWS = 512;
 
-// v -= sum_k h[k] w_k, w_k in lane k of each row of 16 lanes (the wait covers the instruction
-// that made w, see MDET_STEP)
-#define MDET_PB_TERM(K, H) MDET_FMAC " %0, -%1, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
-#define MDET_PB_APPLY(TYPE)                                                                              \
-  __device__ __forceinline__ void pb_apply16(TYPE& v, const TYPE (&h)[16], TYPE w) {                    \
-    asm("s_nop 1\n\t" MDET_PB_TERM("0", "2") MDET_PB_TERM("1", "3") MDET_PB_TERM("2", "4")              \
-            MDET_PB_TERM("3", "5") MDET_PB_TERM("4", "6") MDET_PB_TERM("5", "7") MDET_PB_TERM("6", "8") \
-                MDET_PB_TERM("7", "9") MDET_PB_TERM("8", "10") MDET_PB_TERM("9", "11")                  \
-                    MDET_PB_TERM("10", "12") MDET_PB_TERM("11", "13") MDET_PB_TERM("12", "14")          \
-                        MDET_PB_TERM("13", "15") MDET_PB_TERM("14", "16") MDET_PB_TERM("15", "17")      \
-        : "+v"(v)                                                                                       \
-        : "v"(w), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "v"(h[4]), "v"(h[5]), "v"(h[6]),          \
-          "v"(h[7]), "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11]), "v"(h[12]), "v"(h[13]), "v"(h[14]),  \
-          "v"(h[15]));                                                                                  \
-  }
-#define MDET_FMAC "v_fmac_f64_dpp"
-MDET_PB_APPLY(double)
-#undef MDET_FMAC
-#define MDET_FMAC "v_fmac_f32_dpp"
-MDET_PB_APPLY(float)
-#undef MDET_FMAC
-#undef MDET_PB_APPLY
-#undef MDET_PB_TERM
-
 // The lane with the largest key, the lowest one on ties; `top` = that key (0: no candidate,
 // lane 0).  Must be reached by all 64 lanes.
 __device__ __forceinline__ int pb_wave_best(unsigned long long key, unsigned long long& top) {
@@ -302,8 +278,8 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
         T v = sv;
 #pragma unroll
         for (int b = 0; b < 3; ++b)
-          if (m > b) pb_apply16(v, h[b], s_mult[par][SUB * b + l16] * dh[b]);
-        if (j > 0) pb_apply16(v, cur, s_mult[par][SUB * m + l16] * dcur);
+          if (m > b) apply16(v, h[b], s_mult[par][SUB * b + l16] * dh[b]);
+        if (j > 0) apply16(v, cur, s_mult[par][SUB * m + l16] * dcur);
         if (l16 == j) dcur = d;
         live = live && i != p;
         const T l = live ? v / d : T(0);

@@ -375,7 +375,7 @@ struct Launcher {
     if (w <= LEAF) {
       if (perm) {
         if (spd) return MDET_EINVAL;
-        hipLaunchKernelGGL((leaf_factor_pivoted_kernel<T>), dim3(1), dim3(FACTOR_THREADS), 0, st, P, ld,
+        hipLaunchKernelGGL((leaf_factor_pivoted_kernel<T>), dim3(1), dim3(64 * PIVOT_WAVES), 0, st, P, ld,
                            (int)w, dvec + d0, dinv + d0, linv_of(d0), perm + d0, (long long)d0, flags);
         fail->check(hipGetLastError());
         ++launches;
