@@ -13,8 +13,11 @@ using namespace mdet;
 inline uint64_t up256(uint64_t x) { return (x + 255) / 256 * 256; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// workspace of mdet_principal_logdets: one double per chunk
-inline uint64_t scan_bytes(int64_t n) { return up256((uint64_t)(n > 0 ? ceil_div(n, SEQ_CHUNK) : 1) * 8); }
+// workspace of mdet_principal_logdets: one double per chunk, of the fine ones where they are few
+// enough to be used
+inline int64_t scan_chunks(int64_t n, int per) { return n > 0 ? ceil_div(n, (int64_t)SEQ_THREADS * per) : 1; }
+inline uint64_t scan_bytes(int64_t n, int per) { return up256((uint64_t)scan_chunks(n, per) * 8); }
+inline bool scan_fine(int64_t n) { return scan_chunks(n, SEQ_PER_FINE) <= SEQ_FINE_CHUNKS; }
 
 // workspace of mdet_flodance_fit: the R factors of two consecutive levels of the tree
 struct FitLayout {
@@ -30,6 +33,25 @@ inline FitLayout fit_layout(int64_t rows, int ncols) {
   return f;
 }
 
+template <typename T, int PER>
+void scan(const T* d, int64_t n, double* ell, double* sums, hipStream_t st) {
+  const int64_t chunks = scan_chunks(n, PER);
+  const dim3 grid((unsigned)chunks), block(SEQ_THREADS);
+  hipLaunchKernelGGL((seq_chunk_sums_kernel<T, PER>), grid, block, 0, st, d, n, sums);
+  if constexpr (PER != SEQ_PER_FINE) hipLaunchKernelGGL(seq_chunk_offsets_kernel, dim3(1), block, 0, st, sums, chunks);
+  hipLaunchKernelGGL((seq_running_sum_kernel<T, PER>), grid, block, 0, st, d, n, (const double*)sums, ell);
+}
+
+// One level of the tree: `blocks` workgroups, the kernel for ncols columns.
+template <int NC>
+void qr_level(int ncols, int64_t blocks, const FloProblem& pb, const double* in, int64_t nrows, double* out,
+              double* coef, hipStream_t st) {
+  if (ncols == NC)
+    hipLaunchKernelGGL(flo_qr_kernel<NC>, dim3((unsigned)blocks), dim3(FLO_THREADS), 0, st, pb, in, nrows, out, coef);
+  else if constexpr (NC < FLO_MAX_COLS)
+    qr_level<NC + 1>(ncols, blocks, pb, in, nrows, out, coef, st);
+}
+
 inline int launch_status() { return hipGetLastError() == hipSuccess ? MDET_OK : MDET_EHIP; }
 
 }  // namespace
@@ -40,7 +62,7 @@ int mdet_sequence_workspace_query(int64_t n, int64_t rows, int32_t q, uint64_t* 
   if (!bytes || n < 0 || rows < 0 || q < 0 || q > FLO_MAX_Q) return MDET_EINVAL;
   const FitLayout f = fit_layout(rows, q + 3);
   const uint64_t fit = f.bytes0 + f.bytes1;
-  const uint64_t scan = scan_bytes(n);
+  const uint64_t scan = scan_bytes(n, scan_fine(n) ? SEQ_PER_FINE : SEQ_PER_COARSE);
   *bytes = fit > scan ? fit : scan;
   return MDET_OK;
 }
@@ -50,23 +72,17 @@ int mdet_principal_logdets(int32_t dtype, const void* d, int64_t n, double* ell,
   if (n < 0 || (dtype != MDET_F32 && dtype != MDET_F64)) return MDET_EINVAL;
   if (n == 0) return MDET_OK;
   if (!d || !ell || !workspace) return MDET_EINVAL;
-  if (workspace_bytes < scan_bytes(n)) return MDET_ENOMEM_DEVICE;
-  const int64_t chunks = ceil_div(n, SEQ_CHUNK);
-  if (chunks > INT32_MAX) return MDET_EINVAL;
+  if (workspace_bytes < scan_bytes(n, SEQ_PER_COARSE)) return MDET_ENOMEM_DEVICE;
+  // (a workspace that holds the coarse chunks only is as good as ever)
+  const bool fine = scan_fine(n) && workspace_bytes >= scan_bytes(n, SEQ_PER_FINE);
+  if (scan_chunks(n, SEQ_PER_COARSE) > INT32_MAX) return MDET_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  double* sums = (double*)workspace;
   if (dtype == MDET_F64) {
-    hipLaunchKernelGGL((seq_chunk_sums_kernel<double>), dim3((unsigned)chunks), dim3(SEQ_THREADS), 0, st,
-                       (const double*)d, n, sums);
-    hipLaunchKernelGGL(seq_chunk_offsets_kernel, dim3(1), dim3(SEQ_THREADS), 0, st, sums, chunks);
-    hipLaunchKernelGGL((seq_running_sum_kernel<double>), dim3((unsigned)chunks), dim3(SEQ_THREADS), 0, st,
-                       (const double*)d, n, (const double*)sums, ell);
+    if (fine) scan<double, SEQ_PER_FINE>((const double*)d, n, ell, (double*)workspace, st);
+    else scan<double, SEQ_PER_COARSE>((const double*)d, n, ell, (double*)workspace, st);
   } else {
-    hipLaunchKernelGGL((seq_chunk_sums_kernel<float>), dim3((unsigned)chunks), dim3(SEQ_THREADS), 0, st,
-                       (const float*)d, n, sums);
-    hipLaunchKernelGGL(seq_chunk_offsets_kernel, dim3(1), dim3(SEQ_THREADS), 0, st, sums, chunks);
-    hipLaunchKernelGGL((seq_running_sum_kernel<float>), dim3((unsigned)chunks), dim3(SEQ_THREADS), 0, st,
-                       (const float*)d, n, (const double*)sums, ell);
+    if (fine) scan<float, SEQ_PER_FINE>((const float*)d, n, ell, (double*)workspace, st);
+    else scan<float, SEQ_PER_COARSE>((const float*)d, n, ell, (double*)workspace, st);
   }
   return launch_status();
 }
@@ -87,15 +103,12 @@ int mdet_flodance_fit(const double* ell, int64_t len, int64_t d, int64_t n0, int
   const FloProblem pb{ell, d, n0, ns, (int)q};
   // level 0 builds its rows; every further level factors the stacked R's of the one below
   int64_t blocks = f.blocks0;
-  hipLaunchKernelGGL(flo_qr_kernel, dim3((unsigned)blocks), dim3(FLO_ROWS), 0, st, pb,
-                     (const double*)nullptr, rows, ncols, buf[0], blocks == 1 ? coef : (double*)nullptr);
+  qr_level<3>(ncols, blocks, pb, nullptr, rows, buf[0], blocks == 1 ? coef : nullptr, st);
   int cur = 0;
   while (blocks > 1) {
     const int64_t nrows = blocks * ncols;
     blocks = ceil_div(nrows, FLO_ROWS);
-    hipLaunchKernelGGL(flo_qr_kernel, dim3((unsigned)blocks), dim3(FLO_ROWS), 0, st, pb,
-                       (const double*)buf[cur], nrows, ncols, buf[cur ^ 1],
-                       blocks == 1 ? coef : (double*)nullptr);
+    qr_level<3>(ncols, blocks, pb, buf[cur], nrows, buf[cur ^ 1], blocks == 1 ? coef : nullptr, st);
     cur ^= 1;
   }
   return launch_status();

@@ -1,0 +1,52 @@
+"""The scan and the regression tree at the sizes where they change shape: around a chunk of the
+fine scan (1024), where the coarse one takes over (2048 chunks; also by a workspace that holds
+coarse chunks only), and around one, two and three levels of the tree (1024 rows each), every
+number of columns.
+
+Tolerances as in the sequence tests: ell within 8 eps sum |log|d||; the fitted curve at and beyond
+the fitted range within max(1e-9, 2000 eps cond) of the oracle's, cond that of the column-scaled
+covariates.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import flodance_oracle as F
+
+pytestmark = pytest.mark.gpu
+EPS = np.finfo(np.float64).eps
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 262145, 2048 * 1024, 2048 * 1024 + 1])
+@pytest.mark.parametrize("coarse", [False, True])
+def test_running_sum(n, coarse):
+    import paper_2503_04424_amd as M
+    M.load()
+    d = np.random.default_rng(n).uniform(0.1, 3.0, n) * np.where(np.arange(n) % 3 == 0, -1.0, 1.0)
+    want = np.cumsum(np.log(np.abs(d)).astype(np.longdouble))
+    ws = torch.empty(max(256, (-(-n // 4096) * 8 + 255) // 256 * 256), dtype=torch.uint8, device="cuda") if coarse else None
+    got = M.mdet_principal_logdets(torch.from_numpy(d).cuda(), workspace=ws).cpu().numpy()
+    bound = 8 * EPS * np.cumsum(np.abs(np.log(np.abs(d))))
+    assert np.all(np.abs(got - want) <= bound + 1e-300)
+
+
+@pytest.mark.parametrize("q,rows", [(0, 2), (0, 1023), (1, 1024), (2, 1025), (3, 2049), (4, 40000), (5, 1500), (6, 9000),
+                                    (7, 1100), (8, 3000), (9, 1025), (10, 80000)])
+def test_fit_on_every_tree(q, rows):
+    import paper_2503_04424_amd as M
+    M.load()
+    n0 = 50
+    ns = n0 + rows
+    rng = np.random.default_rng(rows + q)
+    ell = np.cumsum(-0.6 * np.log(np.arange(1, ns + 1)) + 0.2 * rng.standard_normal(ns))
+    fit = F.fit(ell, 1, n0, ns, q)
+    coef = M.mdet_flodance_fit(torch.from_numpy(ell).cuda(), 1, n0, ns, q)
+    at = np.array([ns, 2 * ns, 10 * ns], dtype=np.float64)
+    lhat = M.mdet_flodance_eval(coef, q, torch.from_numpy(at).cuda()).cpu().numpy()
+    j = np.arange(n0 + 1, ns + 1, dtype=np.float64)
+    lg = torch.lgamma(torch.from_numpy(j + 1)).numpy()
+    x = np.stack([np.sqrt(j - 1)] + [lg * j ** (1.0 - i) / np.sqrt(j - 1) for i in range(1, q + 2)], 1)
+    cond = np.linalg.cond(x / np.linalg.norm(x, axis=0))
+    want = np.array([float(fit.eval(a)) for a in at])
+    assert np.all(np.abs(lhat - want) <= max(1e-9, 2000 * EPS * cond) * np.maximum(1.0, np.abs(want)))
