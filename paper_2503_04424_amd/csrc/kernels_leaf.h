@@ -1012,11 +1012,17 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // leaf solve
 // ---------------------------------------------------------------------------
 // Rows below a factored leaf: X (m x w, in place) <- X L^-T D^-1.
-// 256 threads = 4 wavefronts, each owning 16 rows as four 16 x 16 sub-blocks held
-// in MFMA accumulator layout.  Sub-block b:  T_b = X_b - sum_{p<b} W_p L[b,p]^T
-// (products on the matrix cores, terms in the order p = 0, 1, ...), then
-// W_b = T_b L_bb^-T with the inverse of the unit-lower diagonal sub-block prepared
-// by the factor kernel, then L_b = W_b D_b^-1 goes back to memory.
+// 256 threads = 4 wavefronts, each owning 16 rows, row r in lane r of every row of 16 lanes;
+// row g of lanes has columns 4 g .. 4 g + 3 of each 16-column sub-block (four consecutive
+// entries a load).  Sub-block b:  T_b = X_b - sum_{p<b} W_p L[b,p]^T, then W_b = T_b L_bb^-T
+// with the inverse of the unit-lower diagonal sub-block prepared by the factor kernel, then
+// L_b = W_b D_b^-1 goes back to memory.  The products are formed transposed, L[b,p] W_p^T and
+// so on: what a lane holds of X is then both an accumulator and a right operand of the matrix
+// instructions (their output row i stands for column solve_col(i) of the sub-block, and the
+// left operands, the leaf's rows, are read in that order), so the sub-blocks follow each other
+// in registers.  20 KB of LDS in fp64 for the leaf.  Measured, a launch on average, against
+// every change of layout in LDS (60 KB in fp64): fp64 n = 1500 7.1 -> 6.6 us, n = 8192 (beside
+// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.
 // perm (or null): the leaf was factored with pivoting; perm[j] - perm0 is the column of
 // the panel that belongs at position j.  A wavefront reads all 64 columns of its rows
 // before it writes any of them.
@@ -1025,28 +1031,139 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // block outside this launch's own rows and columns.
 constexpr int SOLVE_ROWS = 64;   // rows per workgroup
 
+// Column of a sub-block that output row i of a 16 x 16 product stands for: accumulator register
+// r of row g of lanes holds output row acc_row, and column 4 g + r.
+template <typename T> __device__ __forceinline__ int solve_col(int i);
+template <> __device__ __forceinline__ int solve_col<double>(int i) { return 4 * (i & 3) + (i >> 2); }
+template <> __device__ __forceinline__ int solve_col<float>(int i) { return i; }
+
+// Four consecutive entries, of which those from `left` on are missing (zero).
+template <typename T>
+__device__ __forceinline__ void load4(const T* p, const int left, T (&v)[4]) {
+  // aligned to an entry only: the memory system takes it
+  typedef T four __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  if (left >= 4) {
+    const four f = *reinterpret_cast<const four*>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = f[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = e < left ? p[e] : T(0);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void store4(T* p, const int left, const T (&v)[4]) {
+  typedef T four __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  if (left >= 4) {
+    *reinterpret_cast<four*>(p) = four{v[0], v[1], v[2], v[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < left) p[e] = v[e];
+  }
+}
+
+// What every wavefront of a solve needs of the leaf, as left operands: minus L[b, p], p < b, and
+// the inverses of the diagonal sub-blocks.  The four wavefronts of a workgroup fetch them
+// between them, and keep them in LDS in the order in which they are used, 16 bytes a lane: held
+// by each wavefront in registers, four times the traffic and 80 registers more, a solve of
+// fp64 rows took 7.5 us, and the pair kernel spilled.
+template <typename T>
+struct LeafOperands {
+  static constexpr int COUNT = NSUB * (NSUB - 1) / 2 + NSUB;      // sub-blocks: minus L, then the inverses
+  static constexpr int ELEMS = COUNT * 4 * 64;
+  static constexpr int VEC = Mfma<T>::VEC;
+  using vec_t = typename Mfma<T>::vec_t;
+  T* lds;
+
+  static constexpr int lower(int b, int p) { return b * (b - 1) / 2 + p; }
+  // place of entries [VEC h, VEC h + VEC) of this lane's four of sub-block q
+  __device__ __forceinline__ vec_t* at(int q, int h, int lane) const {
+    return reinterpret_cast<vec_t*>(lds + ((q * (4 / VEC) + h) * 64 + lane) * VEC);
+  }
+  // this wavefront's share; the caller's barrier publishes it
+  __device__ __forceinline__ void stage(const T* __restrict__ Lleaf, int64_t ldl, int w, const T* __restrict__ linv,
+                                        const int wave, const int lane) {
+    const int g = lane >> 4, row = solve_col<T>(lane & 15);
+    T v[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int q = 4 * k + wave;
+      if (q < COUNT) {
+        if (q < COUNT - NSUB) {
+          int b = 1;
+          while (lower(b + 1, 0) <= q) ++b;
+          const int r = b * SUB + row;
+          load4(Lleaf + (int64_t)r * ldl + (q - lower(b, 0)) * SUB + 4 * g, r < w ? 4 : 0, v[k]);
+        } else {
+          load4(linv + ((q - (COUNT - NSUB)) * SUB + row) * SUB + 4 * g, 4, v[k]);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int q = 4 * k + wave;
+      const bool minus = q < COUNT - NSUB;
+      if (q < COUNT) {
+#pragma unroll
+        for (int h = 0; h < 4 / VEC; ++h) {
+          vec_t o;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[e] = minus ? -v[k][VEC * h + e] : v[k][VEC * h + e];
+          *at(q, h, lane) = o;
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void fetch(int q, int lane, T (&v)[4]) const {
+#pragma unroll
+    for (int h = 0; h < 4 / VEC; ++h) {
+      const vec_t o = *at(q, h, lane);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[VEC * h + e] = o[e];
+    }
+  }
+  // x[b] of N sets of 16 rows <- their W_b (undivided)
+  template <int N>
+  __device__ __forceinline__ void solve(typename Mfma<T>::acc_t (&x)[N][NSUB], const int lane) const {
+    using X = Mfma<T>;
+    using acc_t = typename X::acc_t;
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) {
+      T op[4];
+#pragma unroll
+      for (int p = 0; p < b; ++p) {
+        fetch(lower(b, p), lane, op);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int n = 0; n < N; ++n) x[n][b] = X::mfma(op[s], x[n][p][s], x[n][b]);
+      }
+      fetch(COUNT - NSUB + b, lane, op);
+      acc_t wb[N];
+#pragma unroll
+      for (int n = 0; n < N; ++n) wb[n] = acc_t{0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int n = 0; n < N; ++n) wb[n] = X::mfma(op[s], x[n][b][s], wb[n]);
+#pragma unroll
+      for (int n = 0; n < N; ++n) x[n][b] = wb[n];
+    }
+  }
+};
+
 template <typename T>
 __device__ __forceinline__ void leaf_solve_body(
     T* __restrict__ Xg, int64_t ld, int m, int w, const T* __restrict__ Lleaf, int64_t ldl,
     const T* __restrict__ dinv, const T* __restrict__ linv, T* __restrict__ Wg, int64_t ldw,
     const T* __restrict__ dvec, int wfrom, const int* __restrict__ perm, int perm0,
     const T* __restrict__ fix_src, T* __restrict__ fix_dst, int64_t fix_ld) {
-  using X = Mfma<T>;
-  using acc_t = typename X::acc_t;
-  // Only the sub-blocks L[b, p], p < b, and the solved W_p, p < NSUB - 1, are ever
-  // multiplied: rows 16.. and columns ..47 of the leaf.  Keeping just those holds the
-  // workgroup's LDS (60 KB in fp64) below that of a trailing-update workgroup, so
-  // that it fits whichever half of a compute unit such a workgroup has just left.
-  constexpr int LW = LEAF - SUB;                // rows of L kept = columns of L and W kept
-  constexpr int LW_PAD = LW + 1;
-  __shared__ T Ls[LW * LW_PAD];                 // L[16.., ..47], strictly lower part
-  __shared__ T Li[NSUB * SUB * SUB_PAD];        // inverses of its diagonal sub-blocks
-  __shared__ T rinv[LEAF];
-  __shared__ T dsc[LEAF];                       // pivots (only read when Wg is given)
-  __shared__ T wsc[4][SUB * LW_PAD];            // per wavefront: solved W, row-major
-  __shared__ T tsc[4][SUB * SUB_PAD];           // per wavefront: layout change of T_b
+  using acc_t = typename Mfma<T>::acc_t;
   __builtin_amdgcn_s_setprio(2);                // on the chain of dependent launches
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(16))) T lds[LeafOperands<T>::ELEMS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
 
   // a 64 x 64 block that an earlier launch left beside its place (leaf_pair_kernel): the
@@ -1062,91 +1179,48 @@ __device__ __forceinline__ void leaf_solve_body(
     }
     return;
   }
-  // this wavefront's rows, straight into accumulator layout (16 lanes = 128 bytes of a row)
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * SUB;
-  acc_t xb[NSUB];
-#pragma unroll
-  for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + X::acc_row(lane, r);
-      const int col = b * SUB + l16;
-      // with a permutation of the leaf, column `col` of the result is the column that
-      // was taken at that step
-      const int from = (perm != nullptr && col < w) ? perm[col] - perm0 : col;
-      xb[b][r] = (row < m && col < w) ? Xg[row * ld + from] : T(0);
-    }
-  // leaf data shared by the four wavefronts
-  {
-    T v[LEAF * LEAF / 256];
-#pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) {
-      const int e = q * 256 + tid, r = e >> 6, c = e & 63;
-      v[q] = (r < w && c < r) ? Lleaf[(int64_t)r * ldl + c] : T(0);
-    }
-    T u[NSUB * SUB * SUB / 256];
-#pragma unroll
-    for (int q = 0; q < NSUB * SUB * SUB / 256; ++q) u[q] = linv[q * 256 + tid];
-    const T myr = (tid < LEAF && tid < w) ? dinv[tid < LEAF ? tid : 0] : T(0);
-    const T myd = (Wg != nullptr && tid < LEAF && tid < w) ? dvec[tid < LEAF ? tid : 0] : T(0);
-#pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) {
-      const int e = q * 256 + tid, r = e >> 6, c = e & 63;
-      if (r >= SUB && c < LW) Ls[(r - SUB) * LW_PAD + c] = v[q];
-    }
-#pragma unroll
-    for (int q = 0; q < NSUB * SUB * SUB / 256; ++q) {
-      const int e = q * 256 + tid, blk = e >> 8, i = (e >> 4) & 15, k = e & 15;
-      Li[(blk * SUB + i) * SUB_PAD + k] = u[q];
-    }
-    if (tid < LEAF) { rinv[tid] = myr; dsc[tid] = myd; }
-  }
-  __syncthreads();
-  // with a permutation a store below may hit an entry that another lane of this wavefront
-  // loads above: every load has returned before the first store is issued (free here:
-  // the leaf data, requested after the rows, has already arrived)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-  T* ws = wsc[wave];
-  T* ts = tsc[wave];
+  const int64_t row = ((int64_t)blockIdx.x * 4 + wave) * SUB + l16;
+  const bool in = row < m;
+  T* xrow = Xg + row * ld;
+  acc_t x[1][NSUB];
 #pragma unroll
   for (int b = 0; b < NSUB; ++b) {
-    acc_t acc = xb[b];
-    // T_b = X_b - sum_{p<b} W_p L[b,p]^T
-#pragma unroll 1
-    for (int p = 0; p < b; ++p) {
+    const int col = b * SUB + 4 * g;
+    T v[4];
+    if (perm == nullptr) {
+      load4((const T*)xrow + col, in ? w - col : 0, v);
+    } else {
+      // column `col` of the result is the column that was taken at that step
 #pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) {
-        const int k = p * SUB + 4 * s4 + g;
-        const T aop = -ws[l16 * LW_PAD + k];
-        const T bop = Ls[((b - 1) * SUB + l16) * LW_PAD + k];
-        acc = X::mfma(aop, bop, acc);
-      }
+      for (int e = 0; e < 4; ++e) v[e] = (in && col + e < w) ? xrow[perm[col + e] - perm0] : T(0);
     }
-    // accumulator layout -> operand layout through LDS
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ts[X::acc_row(lane, r) * SUB_PAD + l16] = acc[r];
-    // (ts and ws belong to this wavefront alone, and a wavefront's LDS operations
-    // complete in the order they were issued: no barrier between these steps)
-    // W_b = T_b L_bb^-T
-    acc_t wb = acc_t{0, 0, 0, 0};
+    for (int e = 0; e < 4; ++e) x[0][b][e] = v[e];
+  }
+  LeafOperands<T> ops{lds};
+  ops.stage(Lleaf, ldl, w, linv, wave, lane);
+  T rinv[NSUB][4];
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      const int k = 4 * s4 + g;
-      wb = X::mfma(ts[l16 * SUB_PAD + k], Li[(b * SUB + l16) * SUB_PAD + k], wb);
-    }
-    const T rj = rinv[b * SUB + l16];
-    const T dj = dsc[b * SUB + l16];
+  for (int b = 0; b < NSUB; ++b) load4(dinv + b * SUB + 4 * g, w - b * SUB - 4 * g, rinv[b]);
+  __syncthreads();
+  // with a permutation a store below may hit an entry that another lane of this wavefront
+  // loads above: every load has returned before the first store is issued
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  ops.template solve<1>(x, lane);
+  if (in) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row16 = X::acc_row(lane, r);
-      if (b < NSUB - 1) ws[row16 * LW_PAD + b * SUB + l16] = wb[r];
-      const int64_t row = r0 + row16;
-      const int col = b * SUB + l16;
-      if (row < m && col < w) {
-        const T lv = wb[r] * rj;
-        Xg[row * ld + col] = lv;
-        if (Wg != nullptr && row >= wfrom) Wg[row * ldw + col] = lv * dj;
+    for (int b = 0; b < NSUB; ++b) {
+      const int col = b * SUB + 4 * g;
+      T v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = x[0][b][e] * rinv[b][e];
+      store4(xrow + col, w - col, v);
+      if (Wg != nullptr && row >= wfrom) {
+        T d[4];
+        load4(dvec + col, w - col, d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= d[e];
+        store4(Wg + row * ldw + col, w - col, v);
       }
     }
   }

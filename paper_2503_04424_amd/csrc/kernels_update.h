@@ -672,207 +672,135 @@ MDET_GENERAL_UPDATE_KERNEL(panel_update64_general_kernel, 2, 1, 1)
 //         fused factorisation of the second leaf writes, fl.linv: workgroups start at
 //         different times)
 //   Wg    as in leaf_solve_kernel
-// The update's left operand is the solved row before its division by the pivots,
-// w = l d, which the solve keeps in LDS anyway; its right operand the second leaf's rows
+// The update's left operand is the solved row before its division by the pivots, w = l d;
+// its right operand the second leaf's rows
 // l (SCALED, the positive-definite form, where dinv holds d^(-1/2) and l stands for the
 // row of the Cholesky factor: l d^(-1/2), so that the product is again w (1/d) w^T).
-// LDS: 94 KB in fp64, which fits beside one workgroup of the trailing update on a
-// compute unit, so that the launch need not wait for whole units to drain.
+// A wavefront's 16 solved rows are in its registers in the layout of a left operand
+// (leaf_solve_body), and it updates just those rows' 16 x 64 block of C; the second leaf's
+// rows go from the four wavefronts that solve them to all through LDS, once, register by
+// register, and both sets of rows are solved side by side.  52 KB of LDS in fp64.
+// Measured, a launch on average, against every change of layout in LDS (94 KB in fp64): fp64
+// n = 1500 18.4 -> 15.8 us, n = 8192 24.0 -> 21.5, fp32 n = 10000 25.4 -> 19.2.
 template <typename T, bool SCALED = false>
-__global__ __launch_bounds__(256) void leaf_pair_kernel(
+__global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
     T* __restrict__ Xg, int64_t ld, int m, const T* __restrict__ Lleaf, int64_t ldl,
     const T* __restrict__ dinv, const T* __restrict__ linv, const T* __restrict__ dvec,
     T* __restrict__ Wg, int64_t ldw, int wfrom, T* __restrict__ l10, FusedLeaf<T> fl) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
-  using vec_t = typename X::vec_t;
-  constexpr int VEC = X::VEC, BK = X::BK, KS = BK / 4;
-  constexpr int KT = 64;
-  constexpr int S = (KT * (int)sizeof(T) + 16) / (int)sizeof(T);   // padded LDS row of an operand
-  constexpr int LW = LEAF - SUB;
-  constexpr int LW_PAD = LW + 1;
-  __shared__ T Ls[LW * LW_PAD];                 // first leaf: L[16.., ..47], strictly lower part
-  __shared__ T Li[NSUB * SUB * SUB_PAD];        // inverses of its diagonal sub-blocks
-  __shared__ T rinv[LEAF];
-  __shared__ T dsc[LEAF];
-  // As: the solved rows w of the workgroup, 16 per wavefront (while a wavefront solves the
-  // second leaf's rows, theirs); Bs: the second leaf's rows l; later the second leaf itself
-  __shared__ __attribute__((aligned(16))) T ops[2 * 64 * S];
-  static_assert(2 * 64 * S >= FACTOR_LDS_ELEMS, "the fused leaf needs the operand buffers");
-  T* As = ops;
-  T* Bs = ops + 64 * S;
+  // the second leaf's rows: [wavefront that solved them][sub-block][register][lane]; later the
+  // second leaf itself
+  constexpr int ROWS_ELEMS = LEAF * LEAF;
+  __shared__ __attribute__((aligned(16))) T lds[ROWS_ELEMS + LeafOperands<T>::ELEMS];
+  static_assert(ROWS_ELEMS + LeafOperands<T>::ELEMS >= FACTOR_LDS_ELEMS, "the fused leaf needs the operand buffers");
   __builtin_amdgcn_s_setprio(2);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int blk = blockIdx.x;
   const bool first = blk == 0;                  // this workgroup's rows are the second leaf's
 
-  // the block of C: rows 64 blk .. of the region, columns 64 .. 127 of the strip; its
-  // (0, 0) for blk = 0 is on the matrix diagonal
-  T* C = Xg + LEAF;
-  const int row0 = blk * 64;
-  const int wm = wave >> 1, wn = wave & 1;
-  const bool active = !(row0 + wm * 32 + 31 < wn * 32);
-  acc_t acc[2][2];
+  // rows to solve, a row a lane: this wavefront's 16 of the workgroup's own and its 16 of the
+  // second leaf's
+  const int64_t row = ((int64_t)blk * 4 + wave) * SUB + l16;
+  const int leaf_row = wave * SUB + l16;
+  T* xrow = Xg + row * ld;
+  acc_t x[2][NSUB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int b = 0; b < NSUB; ++b) {
+    const int col = b * SUB + 4 * g;
+    T v[4], u[4];
+    load4((const T*)xrow + col, row < m ? 4 : 0, v);
+    load4((const T*)Xg + (int64_t)leaf_row * ld + col, !first && leaf_row < m ? 4 : 0, u);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
-  if (active) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int grow = row0 + wm * 32 + i * 16 + X::acc_row(lane, r);
-        if (grow >= m) continue;
-        const T* crow = C + (int64_t)grow * ld;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int gcol = wn * 32 + j * 16 + l16;
-          if (gcol <= grow) acc[i][j][r] = crow[gcol];
-        }
-      }
+    for (int e = 0; e < 4; ++e) {
+      x[0][b][e] = v[e];
+      x[1][b][e] = u[e];
+    }
   }
-  // rows to solve, in accumulator layout: this wavefront's 16 of the workgroup's own
-  // rows and its 16 of the second leaf's
-  const int64_t r_own = ((int64_t)blk * 4 + wave) * SUB, r_leaf = (int64_t)wave * SUB;
-  acc_t x_own[NSUB], x_leaf[NSUB];
+  LeafOperands<T> ops{lds + ROWS_ELEMS};
+  ops.stage(Lleaf, ldl, LEAF, linv, wave, lane);
+  // this wavefront's 16 x 64 block of C: its (0, 0) for blk = 0, wave = 0 is on the matrix
+  // diagonal, columns behind a row's own are above it
+  T* C = Xg + LEAF;
+  const int row0 = blk * SOLVE_ROWS + wave * SUB;
+  const int tiles = first ? wave + 1 : NSUB;    // 16-column tiles with entries on or below the diagonal
+  acc_t acc[NSUB];
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b)
+  for (int t = 0; t < NSUB; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int col = b * SUB + l16;
-      const int64_t ro = r_own + X::acc_row(lane, r), rl = r_leaf + X::acc_row(lane, r);
-      x_own[b][r] = ro < m ? Xg[ro * ld + col] : T(0);
-      x_leaf[b][r] = (!first && rl < m) ? Xg[rl * ld + col] : T(0);
+      const int grow = row0 + X::acc_row(lane, r), gcol = t * SUB + l16;
+      acc[t][r] = (t < tiles && grow < m && gcol <= grow) ? C[(int64_t)grow * ld + gcol] : T(0);
     }
-  {
-    T v[LEAF * LEAF / 256];
+  T rinv[NSUB][4];
 #pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) {
-      const int e = q * 256 + tid, r = e >> 6, c = e & 63;
-      v[q] = c < r ? Lleaf[(int64_t)r * ldl + c] : T(0);
-    }
-    T u[NSUB * SUB * SUB / 256];
+  for (int b = 0; b < NSUB; ++b) load4(dinv + b * SUB + 4 * g, 4, rinv[b]);
+  __syncthreads();
+  if (first) {
+    acc_t (&own)[1][NSUB] = *reinterpret_cast<acc_t (*)[1][NSUB]>(&x[0]);
+    ops.template solve<1>(own, lane);
 #pragma unroll
-    for (int q = 0; q < NSUB * SUB * SUB / 256; ++q) u[q] = linv[q * 256 + tid];
-    const T myr = tid < LEAF ? dinv[tid < LEAF ? tid : 0] : T(0);
-    const T myd = tid < LEAF ? dvec[tid < LEAF ? tid : 0] : T(0);
-#pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) {
-      const int e = q * 256 + tid, r = e >> 6, c = e & 63;
-      if (r >= SUB && c < LW) Ls[(r - SUB) * LW_PAD + c] = v[q];
-    }
-#pragma unroll
-    for (int q = 0; q < NSUB * SUB * SUB / 256; ++q) {
-      const int e = q * 256 + tid, bq = e >> 8, i = (e >> 4) & 15, k = e & 15;
-      Li[(bq * SUB + i) * SUB_PAD + k] = u[q];
-    }
-    if (tid < LEAF) { rinv[tid] = myr; dsc[tid] = myd; }
+    for (int b = 0; b < NSUB; ++b) x[1][b] = x[0][b];
+  } else {
+    ops.template solve<2>(x, lane);
   }
-  __syncthreads();
-
-  // X L^-T D^-1 for 16 rows, as leaf_solve_kernel; the wavefront's 16 rows of As hold the
-  // solved sub-blocks, and sub-block b's columns of them also serve for the change of
-  // layout of T_b (a wavefront's LDS operations complete in order).  own: the
-  // workgroup's rows (stored, As keeps them as the left operand); otherwise the second
-  // leaf's rows (right operand only).
-  T* ws = As + wave * SUB * S;
-  auto solve16 = [&](acc_t (&x)[NSUB], const int64_t r0, const bool own) {
 #pragma unroll
-    for (int b = 0; b < NSUB; ++b) {
-      acc_t a = x[b];
-#pragma unroll 1
-      for (int p = 0; p < b; ++p) {
+  for (int b = 0; b < NSUB; ++b) {
+    const int col = b * SUB + 4 * g;
+    T v[4];
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-          const int k = p * SUB + 4 * s4 + g;
-          a = X::mfma(-ws[l16 * S + k], Ls[((b - 1) * SUB + l16) * LW_PAD + k], a);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ws[X::acc_row(lane, r) * S + b * SUB + l16] = a[r];
-      acc_t wb = acc_t{0, 0, 0, 0};
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) {
-        const int k = 4 * s4 + g;
-        wb = X::mfma(ws[l16 * S + b * SUB + k], Li[(b * SUB + l16) * SUB_PAD + k], wb);
-      }
-      const T rj = rinv[b * SUB + l16];
-      const T dj = dsc[b * SUB + l16];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row16 = X::acc_row(lane, r);
-        ws[row16 * S + b * SUB + l16] = wb[r];
-        const int64_t row = r0 + row16;
-        const int col = b * SUB + l16;
-        const T lv = wb[r] * rj;
-        if (own && row < m) {
-          if (first) l10[(int)row * LEAF + col] = lv;
-          else Xg[row * ld + col] = lv;
-          if (Wg != nullptr && row >= wfrom) Wg[row * ldw + col] = lv * dj;
-        }
-        if (!own || first) Bs[(wave * SUB + row16) * S + col] = SCALED ? lv * rj : lv;
-      }
+    for (int e = 0; e < 4; ++e) {
+      const T rj = rinv[b][e];
+      v[e] = x[0][b][e] * rj;
+      const T lv = x[1][b][e] * rj;
+      lds[((wave * NSUB + b) * 4 + e) * 64 + lane] = SCALED ? lv * rj : lv;
     }
-  };
-  if (!first) solve16(x_leaf, r_leaf, false);
-  solve16(x_own, r_own, true);
-  __syncthreads();
-
-  if (active) {
+    if (row < m) {
+      store4(first ? l10 + (int)row * LEAF + col : xrow + col, 4, v);
+      if (Wg != nullptr && row >= wfrom) {
+        T d[4];
+        load4(dvec + col, 4, d);
 #pragma unroll
-    for (int slab = 0; slab < KT / BK; ++slab) {
-      const T* as = &As[(wm * 32 + l16) * S + slab * BK + g * KS];
-      const T* bs = &Bs[(wn * 32 + l16) * S + slab * BK + g * KS];
-#pragma unroll
-      for (int h = 0; h < KS / VEC; ++h) {
-        vec_t fa[2], fb[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          fa[t] = -*reinterpret_cast<const vec_t*>(as + t * 16 * S + h * VEC);
-          fb[t] = *reinterpret_cast<const vec_t*>(bs + t * 16 * S + h * VEC);
-        }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = X::mfma(fa[i][e], fb[j][e], acc[i][j]);
+        for (int e = 0; e < 4; ++e) v[e] *= d[e];
+        store4(Wg + row * ldw + col, 4, v);
       }
     }
   }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NSUB; ++t)
+    if (t < tiles) {
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b) {
+        T bop[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) bop[s] = lds[((t * NSUB + b) * 4 + s) * 64 + lane];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[t] = X::mfma(-x[0][b][s], bop[s], acc[t]);
+      }
+    }
   const bool fuse = first && fl.w > 0;
   const int wleaf = fuse ? fl.w : 0;
   if (fuse) {
     __syncthreads();   // everybody is done with the operands
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int t = 0; t < NSUB; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          leaf_tile_put<T>(ops, wm * 32 + i * 16 + X::acc_row(lane, r), wn * 32 + j * 16 + l16, wleaf,
-                           acc[i][j][r]);
+        leaf_tile_put<T>(lds, row0 + X::acc_row(lane, r), t * SUB + l16, wleaf, acc[t][r]);
   }
-  if (active) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int t = 0; t < NSUB; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int grow = row0 + wm * 32 + i * 16 + X::acc_row(lane, r);
-        if (grow >= m) continue;
-        T* crow = C + (int64_t)grow * ld;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int gcol = wn * 32 + j * 16 + l16;
-          if (gcol <= grow && !(grow < wleaf && gcol < wleaf)) crow[gcol] = acc[i][j][r];
-        }
-      }
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int grow = row0 + X::acc_row(lane, r), gcol = t * SUB + l16;
+      if (t < tiles && grow < m && gcol <= grow && !(grow < wleaf && gcol < wleaf)) C[(int64_t)grow * ld + gcol] = acc[t][r];
+    }
   if (fuse) {
     __syncthreads();
-    leaf_factor_body<T, true>(C, ld, fl.w, fl.dvec, fl.dinv, fl.linv, fl.pivot0, fl.flags, ops, fl.spd);
+    leaf_factor_body<T, true>(C, ld, fl.w, fl.dvec, fl.dinv, fl.linv, fl.pivot0, fl.flags, lds, fl.spd);
   }
 }
 
