@@ -82,7 +82,12 @@ typedef struct mdet_params {
                                 still synchronises before returning.               */
   void* dev_workspace;       /* optional caller-owned device scratch (e.g. a
                                 torch.empty buffer); NULL = the library hipMallocs
-                                what it needs (within the budget) and frees it.     */
+                                what it needs (within the budget) and frees it, but
+                                for one buffer of at most 512 MiB per device that a
+                                call without a budget may leave for the next one; it
+                                is freed by a call with a budget, by one that needs
+                                more, when memory runs out, or after 32 calls without
+                                a use for it.                                       */
   uint64_t dev_workspace_bytes;
   void* host_scratch;        /* out-of-core with overwrite=0 only: pinned host
                                 memory of at least mdet_workspace_query()'s

@@ -719,6 +719,7 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
 // ---------------------------------------------------------------------------
 // result collection
 // ---------------------------------------------------------------------------
+// As SmallArea places them: one copy reads both.
 struct DeviceOut {
   double out[3];
   DevFlags flags;
@@ -759,31 +760,107 @@ static void init_result(mdet_result* r, const Plan& pl) {
   r->num_superpanels = (int32_t)pl.panels.size();
 }
 
+// One device buffer per GPU kept between calls: allocating and freeing a workspace costs 25 us
+// at 2 MB and 300 us from about 64 MB on (unmapping), a tenth of a call at n = 3000 .. 4000.
+// At most WORKSPACE_KEPT bytes; lent to one call at a time (others allocate as ever), and only
+// put back by a call whose device work has finished.  Given back to the device when a call needs
+// more than it holds, has a memory budget (nothing may be held beside the call's own memory
+// then), finds no memory, or when WORKSPACE_IDLE calls in a row had no use for it.
+constexpr uint64_t WORKSPACE_KEPT = 512ull << 20;
+constexpr int WORKSPACE_IDLE = 32;
+struct KeptWorkspace {
+  void* p = nullptr;
+  uint64_t bytes = 0;
+  int idle = 0;
+};
+static KeptWorkspace g_kept[64];
+
+// The kept buffer if it holds `need` bytes and is not much larger; a buffer that is to go is
+// freed (with the device current that it belongs to).
+static void* kept_take(int dev, uint64_t need, uint64_t* bytes) {
+  if (dev < 0 || dev >= 64) return nullptr;
+  void* out = nullptr;
+  void* drop = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    KeptWorkspace& k = g_kept[dev];
+    if (k.p && need <= k.bytes && k.bytes / 4 <= need + (16ull << 20)) {
+      out = k.p;
+      *bytes = k.bytes;
+      k = KeptWorkspace{};
+    } else if (k.p && (k.bytes < need || ++k.idle >= WORKSPACE_IDLE)) {
+      drop = k.p;
+      k = KeptWorkspace{};
+    }
+  }
+  if (drop) (void)hipFree(drop);
+  return out;
+}
+static void kept_drop(int dev) {
+  if (dev < 0 || dev >= 64) return;
+  void* drop = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    drop = g_kept[dev].p;
+    g_kept[dev] = KeptWorkspace{};
+  }
+  if (drop) (void)hipFree(drop);
+}
+static bool kept_put(int dev, void* p, uint64_t bytes) {
+  if (dev < 0 || dev >= 64 || bytes > WORKSPACE_KEPT) return false;
+  std::lock_guard<std::mutex> lk(g_mu);
+  KeptWorkspace& k = g_kept[dev];
+  if (k.p) return false;
+  k.p = p;
+  k.bytes = bytes;
+  k.idle = 0;
+  return true;
+}
+
 // Workspace: either the caller's buffer or a library allocation.
 struct Workspace {
   char* base = nullptr;
   uint64_t bytes = 0;
   bool owned = false;
+  bool keep = false;       // set by a call that has waited for all of its device work
+  bool may_keep = false;
+  int dev = 0;
   int acquire(const mdet_params& p, uint64_t need, HipFail& f) {
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
     if (p.dev_workspace) {
       if (p.dev_workspace_bytes < need || ((uintptr_t)p.dev_workspace & 255u)) return MDET_ENOMEM_DEVICE;
       base = (char*)p.dev_workspace;
       bytes = p.dev_workspace_bytes;
       return MDET_OK;
     }
+    if (need == 0) need = 256;
+    may_keep = p.mem_budget_bytes == 0 && need <= WORKSPACE_KEPT;
     void* q = nullptr;
-    hipError_t e = hipMalloc(&q, need ? need : 256);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      f.code = e;
-      return MDET_ENOMEM_DEVICE;
+    if (may_keep) q = kept_take(dev, need, &need);
+    else kept_drop(dev);
+    if (!q) {
+      hipError_t e = hipMalloc(&q, need);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        kept_drop(dev);
+        e = hipMalloc(&q, need);
+      }
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        f.code = e;
+        return MDET_ENOMEM_DEVICE;
+      }
     }
     base = (char*)q;
     bytes = need;
     owned = true;
     return MDET_OK;
   }
-  ~Workspace() { if (owned && base) (void)hipFree(base); }
+  ~Workspace() {
+    if (!owned || !base) return;
+    if (keep && may_keep && kept_put(dev, base, bytes)) return;
+    (void)hipFree(base);
+  }
 };
 
 // The plan's workspace; if it cannot be had and the plan holds the pivot-scaled copies
@@ -952,12 +1029,10 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
   }
   DeviceOut o;
   std::memset(&o, 0, sizeof(o));
-  if (rc == MDET_OK) {
-    MDET_HIP(fail, hipMemcpyAsync(o.out, out, sizeof(o.out), hipMemcpyDeviceToHost, s0));
-    MDET_HIP(fail, hipMemcpyAsync(&o.flags, L.flags, sizeof(DevFlags), hipMemcpyDeviceToHost, s0));
-  }
+  if (rc == MDET_OK) MDET_HIP(fail, hipMemcpyAsync(&o, out, sizeof(o), hipMemcpyDeviceToHost, s0));
   MDET_HIP(fail, hipStreamSynchronize(s1));
   MDET_HIP(fail, hipStreamSynchronize(s0));
+  ws.keep = fail.ok();
   res->flops = 2.0 * L.fma;
   res->kernel_launches = L.launches;
   L.collect_profile(res);
@@ -1123,7 +1198,8 @@ class CopyThreads {
   std::atomic<bool> failed{false};
 
  private:
-  static constexpr size_t PART = 4u << 20;
+  // small enough that a block of 1024 x 1024 doubles occupies all threads
+  static constexpr size_t PART = 1u << 20;
   struct Job {
     int op;                 // 0 memcpy, 1 file -> memory, 2 memory -> file
     char* dst;
@@ -1201,10 +1277,14 @@ class CopyThreads {
 // copy goes through the chunks; with memory, small copies are left to the runtime.
 class HostStager {
  public:
-  static constexpr size_t CHUNK = 32u << 20;
+  // A chunk holds one block, up to 32 MiB: pinned memory costs 16 us a MiB to have and to touch
+  // for the first time, for every call anew.
+  static constexpr size_t CHUNK_MIN = 4u << 20, CHUNK_MAX = 32u << 20;
   static constexpr int NCHUNK = 4;
   static constexpr size_t DIRECT_BELOW = 1u << 20;
-  HostStager(HipFail* f, int fd) : fail_(f), fd_(fd) {}
+  HostStager(HipFail* f, int fd, uint64_t block_bytes)
+      : chunk_((size_t)std::min<uint64_t>(std::max<uint64_t>(round_up((int64_t)block_bytes, 1 << 20), CHUNK_MIN), CHUNK_MAX)),
+        fail_(f), fd_(fd) {}
   ~HostStager() {
     for (int c = 0; c < NCHUNK; ++c) {
       if (ev_[c]) { (void)hipEventSynchronize(ev_[c]); (void)hipEventDestroy(ev_[c]); }
@@ -1233,9 +1313,9 @@ class HostStager {
       return;
     }
     if (!ready()) { broken_ = true; return; }
-    const size_t rows_per = flat ? rows : (CHUNK / row_bytes ? CHUNK / row_bytes : 1);
-    const size_t step = flat ? CHUNK : rows_per * row_bytes;
-    if (step > CHUNK) { broken_ = true; return; }
+    const size_t rows_per = flat ? rows : (chunk_ / row_bytes ? chunk_ / row_bytes : 1);
+    const size_t step = flat ? chunk_ : rows_per * row_bytes;
+    if (step > chunk_) { broken_ = true; return; }
     for (size_t off = 0; off < bytes; off += step) {
       const size_t len = bytes - off < step ? bytes - off : step;
       const int c = take();
@@ -1262,9 +1342,9 @@ class HostStager {
       return;
     }
     if (!ready()) { broken_ = true; return; }
-    const size_t rows_per = flat ? rows : (CHUNK / row_bytes ? CHUNK / row_bytes : 1);
-    const size_t step = flat ? CHUNK : rows_per * row_bytes;
-    if (step > CHUNK) { broken_ = true; return; }
+    const size_t rows_per = flat ? rows : (chunk_ / row_bytes ? chunk_ / row_bytes : 1);
+    const size_t step = flat ? chunk_ : rows_per * row_bytes;
+    if (step > chunk_) { broken_ = true; return; }
     int prev = -1;
     size_t prev_off = 0, prev_len = 0;
     auto drain = [&] {
@@ -1298,7 +1378,7 @@ class HostStager {
     if (state_ != 0) return state_ > 0;
     state_ = -1;
     for (int c = 0; c < NCHUNK; ++c) {
-      if (hipHostMalloc(&buf_[c], CHUNK, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); buf_[c] = nullptr; return false; }
+      if (hipHostMalloc(&buf_[c], chunk_, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); buf_[c] = nullptr; return false; }
       if (hipEventCreateWithFlags(&ev_[c], hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); ev_[c] = nullptr; return false; }
     }
     unsigned hw = std::thread::hardware_concurrency();
@@ -1315,6 +1395,7 @@ class HostStager {
     if (busy_[c]) { fail_->check(hipEventSynchronize(ev_[c])); busy_[c] = false; }
     return c;
   }
+  const size_t chunk_;      // bytes of one chunk
   HipFail* fail_;
   int fd_;
   bool broken_ = false;
@@ -1438,7 +1519,7 @@ static int logdet_host_t(const mdet_params& p, const Plan& plan, T* hA, T* hOut,
   cprof.fail = &fail;
   auto host_col = [&](T* base, int64_t j) { return base + pl.col_offset(j); };
   // pageable host memory goes through pinned chunks (see HostStager)
-  HostStager stager_in(&fail, fd_in), stager_out(&fail, fd_out);
+  HostStager stager_in(&fail, fd_in, pl.tile_bytes), stager_out(&fail, fd_out, pl.tile_bytes);
   const bool from_provider = source && source->provider;
   const bool from_device = source && source->provider_dev;
   const bool narrow = source && !from_provider && !from_device && pl.widen;
@@ -1804,8 +1885,7 @@ static int logdet_host_t(const mdet_params& p, const Plan& plan, T* hA, T* hOut,
   DeviceOut o;
   std::memset(&o, 0, sizeof(o));
   if (rc == MDET_OK) {
-    MDET_HIP(fail, hipMemcpyAsync(o.out, out, sizeof(o.out), hipMemcpyDeviceToHost, s0));
-    MDET_HIP(fail, hipMemcpyAsync(&o.flags, L.flags, sizeof(DevFlags), hipMemcpyDeviceToHost, s0));
+    MDET_HIP(fail, hipMemcpyAsync(&o, out, sizeof(o), hipMemcpyDeviceToHost, s0));
     if (diag_host && n > 0)
       MDET_HIP(fail, hipMemcpyAsync(diag_host, L.dvec, n * sizeof(T), hipMemcpyDeviceToHost, s0));
     if (L.perm && p.perm && n > 0)
@@ -1815,6 +1895,7 @@ static int logdet_host_t(const mdet_params& p, const Plan& plan, T* hA, T* hOut,
   MDET_HIP(fail, hipStreamSynchronize(s1));
   MDET_HIP(fail, hipStreamSynchronize(s0));
   MDET_HIP(fail, hipStreamSynchronize(sd));
+  ws.keep = fail.ok();
   res->flops = 2.0 * L.fma;
   res->kernel_launches = L.launches;
   L.collect_profile(res);

@@ -92,9 +92,8 @@ inline SmallArea small_area(int64_t n, int64_t T, int beta, bool pivot) {
   a.dinv = o; o += align256((uint64_t)(n > 0 ? n : 1) * beta);
   a.linv = o; o += 2 * align256((uint64_t)64 * 16 * beta);   // inverse diagonal sub-blocks of two leaves
   a.l10 = o; o += align256((uint64_t)64 * 64 * beta);        // a 64 x 64 block on its way into place
-  a.flags = o; o += 256;
   a.partial = o; o += align256((uint64_t)(T > 0 ? T : 1) * 3 * 8);
-  a.out = o; o += 256;
+  a.out = o; a.flags = o + 24; o += 256;                     // what a call reads back, side by side
   a.running = o; o += align256((uint64_t)(T > 0 ? T : 1) * 8);
   a.perm = o; if (pivot) o += align256((uint64_t)(n > 0 ? n : 1) * 4);
   a.total = o;
