@@ -167,56 +167,51 @@ __global__ __launch_bounds__(PB_THREADS) void pb_step_kernel(
 
 // All steps of a group of up to 64 pivots in one launch of one workgroup, thread i holding
 // row i (w <= NT): its running diagonal and its multipliers of this group stay in registers.
-// Per step: every wavefront's best candidate to LDS (one barrier), the overall best found by
-// every wavefront alone; the pivot's row of S requested; the thread that holds the pivot puts
-// its multipliers into LDS meanwhile (second barrier); then v, l and the new diagonal as in
-// pb_step_kernel, with the 16 products of a block of multipliers taking the pivot's entries
-// from the lanes of the row (one instruction each).  Same rule, same order of the terms, same
-// outputs as a sequence of pb_step_kernel launches, where a launch and its memory round trips
-// made a step 5.7 us; here it is 1.1 (w = 256, fp64; n = 3000 21.9 -> 6.1 ms).
+// Per step: every wavefront's best candidate to LDS (one barrier), its row of S requested in
+// advance; the overall best found by every thread alone; the pivot's row of S read; the thread
+// that holds the pivot puts its multipliers into LDS meanwhile (second barrier); then v, l and
+// the new diagonal as in pb_step_kernel, with the 16 products of a block of multipliers taking
+// the pivot's entries from the lanes of the row (one instruction each).  At the end the group's
+// leaf, in pivot order, with the inverses of its diagonal sub-blocks (as pb_leaf_kernel).  Same
+// rule, same order of the terms, same outputs as a sequence of pb_step_kernel launches, where a
+// launch and its memory round trips made a step 5.7 us; here it is 1.1 us (w = 256, fp64;
+// n = 3000 21.9 -> 5.3 ms).  Bound by a step's chain: search 300 clocks, exchange, row of S
+// 1100, products, quotient.
 // The multipliers of 512 rows are what a compute unit's registers hold (128 of 256 per
 // thread in fp64): larger blocks take a launch per step.
 constexpr int PB_GROUP_ROWS = 512;
 
-// The lane with the largest key, the lowest one on ties; `top` = that key (0: no candidate,
-// lane 0).  Must be reached by all 64 lanes.
-__device__ __forceinline__ int pb_wave_best(unsigned long long key, unsigned long long& top) {
-  const unsigned hi = (unsigned)(key >> 32), lo = (unsigned)key;
-  const unsigned top_hi = wave_max_u32(hi);
-  unsigned long long hit = __ballot(hi == top_hi);
-  // the upper words nearly always decide
-  if (hit & (hit - 1ull)) {
-    const unsigned top_lo = wave_max_u32(hi == top_hi ? lo : 0u);
-    hit = __ballot(hi == top_hi && lo == top_lo);
-  }
-  const int lane = __ffsll((long long)hit) - 1;
-  top = ((unsigned long long)top_hi << 32) | (unsigned)__builtin_amdgcn_readlane((int)lo, lane);
-  return lane;
+// Magnitudes as integers that order alike (a NaN above all others).
+__device__ __forceinline__ unsigned long long pb_magnitude(double v) {
+  return (unsigned long long)__double_as_longlong(v) & 0x7fffffffffffffffull;
 }
-// fp32 keys in the upper word, where pb_wave_best looks first
-__device__ __forceinline__ unsigned long long pb_wave_key(double v) { return pb_key(v); }
-__device__ __forceinline__ unsigned long long pb_wave_key(float v) { return pb_key(v) << 32; }
+__device__ __forceinline__ unsigned long long pb_magnitude(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, int64_t lds, T* __restrict__ Lfull,
                                                       int64_t ldl, T* __restrict__ dg, int* __restrict__ active,
                                                       int* __restrict__ piv, T* __restrict__ dvec,
                                                       T* __restrict__ dinv, int* __restrict__ perm, int w, int c0,
-                                                      int lw, long long pivot0, DevFlags* flags) {
+                                                      int lw, long long pivot0, DevFlags* flags,
+                                                      T* __restrict__ leaf, T* __restrict__ linv) {
   constexpr int NW = NT / 64;
   using vec_t = typename Mfma<T>::vec_t;
   constexpr int VEC = Mfma<T>::VEC;
-  __shared__ unsigned long long s_key[2][NW];    // two steps in turn
-  __shared__ int s_row[2][NW];
-  __shared__ T s_diag[2][NW];
+  constexpr int LINE = 128 / (int)sizeof(T);
+  __shared__ T s_diag[2][NW];                    // every wavefront's best candidate; two steps in turn
+  __shared__ int s_row[2][NW];                   // its row; -1: none
   __shared__ __attribute__((aligned(16))) T s_mult[2][LEAF];
+  __shared__ T tile[LEAF_TILE];                  // the group's leaf, at the end
   const int i = threadIdx.x, lane = i & 63, l16 = i & 15;
   const int wave = __builtin_amdgcn_readfirstlane(i >> 6);
+  for (int e = i; e < LEAF_TILE; e += NT) tile[e] = T(0);
   T diag = i < w ? dg[i] : T(0);
   bool live = i < w && active[i] != 0;
+  int mypos = -1;                                // step at which this row was taken
   // multipliers of the finished blocks of 16 steps and of the current one (0: not taken yet);
-  // pivots likewise, step k of a block in lane k of each row of lanes
+  // pivots and rows likewise, step k of a block in lane k of each row of lanes
   T h[3][SUB], cur[SUB], dh[3], dcur = T(0);
+  int pcur = 0;
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
     dh[b] = T(0);
@@ -228,21 +223,37 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
 #pragma unroll
     for (int k = 0; k < SUB; ++k) cur[k] = T(0);
     dcur = T(0);
+    int mine = l16;
+    asm volatile("" : "+v"(mine));               // compared here, not kept as 16 masks in scalar registers
 #pragma unroll
     for (int j = 0; j < SUB; ++j) {
       const int jj = 16 * m + j, par = j & 1;
       if (jj < lw) {
-        unsigned long long top;
-        const int best = pb_wave_best(live ? pb_wave_key(diag) : 0ull, top);
-        if (lane == best) {
-          s_key[par][wave] = top;
-          s_row[par][wave] = i;
-          s_diag[par][wave] = diag;
-        }
+        const unsigned long long cand = __builtin_amdgcn_ballot_w64(live);
+        const int best = cand != 0ull ? pick_lane(diag, cand) : 0;
+        const int brow = 64 * wave + best;
+        // this wavefront's candidate may be the pivot: its row of S on the way to this compute unit
+        const T ahead = S[(int64_t)min(brow, w - 1) * lds + min((lane & (LEAF / 2 - 1)) * LINE, w - 1)];
+        s_diag[par][wave] = lane_value(diag, best);          // (every lane: the same values)
+        s_row[par][wave] = cand != 0ull ? brow : -1;
         __syncthreads();
-        const int from = pb_wave_best(lane < NW ? s_key[par][lane < NW ? lane : 0] : 0ull, top);
-        const int p = __builtin_amdgcn_readfirstlane(s_row[par][from]);
-        const T d = s_diag[par][from];
+        T cd[NW];
+        int cr[NW];
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          cd[q] = s_diag[par][q];
+          cr[q] = s_row[par][q];
+        }
+        T d = cd[0];
+        int p = cr[0];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) {
+          // larger magnitude wins, the smaller row on ties
+          const bool better = cr[q] >= 0 && (p < 0 || pb_magnitude(cd[q]) > pb_magnitude(d));
+          d = better ? cd[q] : d;
+          p = better ? cr[q] : p;
+        }
+        p = __builtin_amdgcn_readfirstlane(p);
         const T sv = i < w ? S[(int64_t)p * lds + i] : T(0);
         if (i == p) {
           T* to = s_mult[par];
@@ -262,27 +273,22 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
             for (int e = 0; e < VEC; ++e) v[e] = cur[k + e];
             *reinterpret_cast<vec_t*>(to + SUB * m + k) = v;
           }
-          piv[c0 + jj] = p;
-          dvec[c0 + jj] = d;
-          dinv[c0 + jj] = T(1) / d;
-          perm[c0 + jj] = (int)pivot0 + p;
-          const bool zero = d == T(0);
-          const bool finite = fabs((double)d) <= 1.7976931348623157e308;
-          if (zero || !finite) {
-            const unsigned long long idx = (unsigned long long)(pivot0 + c0 + jj);
-            const unsigned long long old = atomicMin(&flags->first_bad, idx);
-            if (idx <= old) atomicExch(&flags->bad_kind, zero ? 1ull : 2ull);
-          }
+          mypos = jj;
+          live = false;
         }
+        const T rd = T(1) / d;                   // while the row is on its way
         __syncthreads();
         T v = sv;
+        asm volatile("" ::"v"(ahead));
 #pragma unroll
         for (int b = 0; b < 3; ++b)
           if (m > b) apply16(v, h[b], s_mult[par][SUB * b + l16] * dh[b]);
         if (j > 0) apply16(v, cur, s_mult[par][SUB * m + l16] * dcur);
-        if (l16 == j) dcur = d;
-        live = live && i != p;
-        const T l = live ? v / d : T(0);
+        dcur = mine == j ? d : dcur;
+        pcur = mine == j ? p : pcur;
+        // v / d: the product with the rounded reciprocal, and one correction
+        const T q = v * rd;
+        const T l = live ? fma(fma(-d, q, v), rd, q) : T(0);
         diag = fma(-l, v, diag);
         cur[j] = l;
       }
@@ -297,6 +303,29 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
         *reinterpret_cast<vec_t*>(to + k) = v;
       }
     }
+    if (wave == 0) {
+      const int jj = SUB * m + l16;
+      const bool mine_out = lane < SUB && jj < lw;
+      const bool zero = dcur == T(0);
+      const bool finite = fabs((double)dcur) <= 1.7976931348623157e308;
+      if (mine_out) {
+        piv[c0 + jj] = pcur;
+        dvec[c0 + jj] = dcur;
+        dinv[c0 + jj] = T(1) / dcur;
+        perm[c0 + jj] = (int)pivot0 + pcur;
+      }
+      const unsigned long long bad = __builtin_amdgcn_ballot_w64(mine_out && (zero || !finite));
+      if (bad != 0ull && lane == __builtin_ctzll(bad)) {
+        const unsigned long long idx = (unsigned long long)(pivot0 + c0 + jj);
+        const unsigned long long old = atomicMin(&flags->first_bad, idx);
+        if (idx <= old) atomicExch(&flags->bad_kind, zero ? 1ull : 2ull);
+      }
+    }
+    if (mypos >= 0) {
+      // the rows taken so far are rows of the leaf; multipliers behind a row's own step are zero
+#pragma unroll
+      for (int k = 0; k < SUB; ++k) tile[mypos * LEAF_PAD + SUB * m + k] = cur[k];
+    }
 #pragma unroll
     for (int b = 0; b < 3; ++b)
       if (m == b) {
@@ -309,6 +338,20 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
     dg[i] = diag;
     active[i] = live ? 1 : 0;
   }
+  // rows that were taken in a later block than their multipliers
+  if (mypos >= 0) {
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+      if (mypos >= SUB * (b + 1))
+#pragma unroll
+        for (int k = 0; k < SUB; ++k) tile[mypos * LEAF_PAD + SUB * b + k] = h[b][k];
+  }
+  __syncthreads();
+  for (int e = i; e < LEAF * LEAF; e += NT) {
+    const int r = e >> 6, c = e & 63;
+    leaf[e] = c < r ? tile[r * LEAF_PAD + c] : T(0);
+  }
+  if (wave < NSUB) leaf_invert_sub<T>(tile, linv, wave, lane);
 }
 
 // The group's own lw x lw leaf in pivot order (strictly lower part; 64 x 64, leading

@@ -485,7 +485,8 @@ struct Launcher {
       if (w <= PB_GROUP_ROWS) {
 #define MDET_LAUNCH_GROUP(NT)                                                                                       \
   hipLaunchKernelGGL((pb_group_kernel<T, NT>), dim3(1), dim3(NT), 0, st, (const T*)pb.S, ldl, pb.Lfull, ldl, pb.dg, \
-                     pb.active, pb.piv, dvec + d0, dinv + d0, perm + d0, (int)w, (int)c0, lw, (long long)d0, flags)
+                     pb.active, pb.piv, dvec + d0, dinv + d0, perm + d0, (int)w, (int)c0, lw, (long long)d0, flags,  \
+                     pb.leaf, pb.linv)
         if (w <= PB_GROUP_ROWS / 2) MDET_LAUNCH_GROUP(PB_GROUP_ROWS / 2);
         else MDET_LAUNCH_GROUP(PB_GROUP_ROWS);
 #undef MDET_LAUNCH_GROUP
@@ -498,13 +499,13 @@ struct Launcher {
           cur ^= 1;
           ++launches;
         }
+        hipLaunchKernelGGL((pb_leaf_kernel<T>), dim3(1), dim3(256), 0, st, (const T*)pb.Lfull, ldl, (const int*)pb.piv,
+                           (int)c0, lw, pb.leaf, pb.linv);
+        fail->check(hipGetLastError());
+        ++launches;
       }
       fail->check(hipGetLastError());
       fma += (double)w * lw * (lw - 1) / 2.0;
-      hipLaunchKernelGGL((pb_leaf_kernel<T>), dim3(1), dim3(256), 0, st, (const T*)pb.Lfull, ldl, (const int*)pb.piv,
-                         (int)c0, lw, pb.leaf, pb.linv);
-      fail->check(hipGetLastError());
-      ++launches;
       // candidates remain: the diagonal block up to date with this group's 64 pivots
       if (c0 + lw < w)
         rc = update(st, pb.S, ldl, pb.Lfull + c0, ldl, pb.Lfull + c0, ldl, dvec + d0 + c0, w, w, LEAF, false);
