@@ -671,7 +671,8 @@ MDET_GENERAL_UPDATE_KERNEL(panel_update64_general_kernel, 2, 1, 1)
 //         the inverses of its diagonal sub-blocks (linv must not be the array that the
 //         fused factorisation of the second leaf writes, fl.linv: workgroups start at
 //         different times)
-//   Wg    as in leaf_solve_kernel
+//   Wg, perm, perm0: as in leaf_solve_kernel
+// With pivoting the second leaf is factored by a launch of its own (fl.w = 0).
 // The update's left operand is the solved row before its division by the pivots, w = l d;
 // its right operand the second leaf's rows
 // l (SCALED, the positive-definite form, where dinv holds d^(-1/2) and l stands for the
@@ -686,7 +687,8 @@ template <typename T, bool SCALED = false>
 __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
     T* __restrict__ Xg, int64_t ld, int m, const T* __restrict__ Lleaf, int64_t ldl,
     const T* __restrict__ dinv, const T* __restrict__ linv, const T* __restrict__ dvec,
-    T* __restrict__ Wg, int64_t ldw, int wfrom, T* __restrict__ l10, FusedLeaf<T> fl) {
+    T* __restrict__ Wg, int64_t ldw, int wfrom, T* __restrict__ l10, const int* __restrict__ perm, int perm0,
+    FusedLeaf<T> fl) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   // the second leaf's rows: [wavefront that solved them][sub-block][register][lane]; later the
@@ -711,8 +713,19 @@ __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
   for (int b = 0; b < NSUB; ++b) {
     const int col = b * SUB + 4 * g;
     T v[4], u[4];
-    load4((const T*)xrow + col, row < m ? 4 : 0, v);
-    load4((const T*)Xg + (int64_t)leaf_row * ld + col, !first && leaf_row < m ? 4 : 0, u);
+    const bool own = row < m, other = !first && leaf_row < m;
+    const T* lrow = Xg + (int64_t)leaf_row * ld;
+    if (perm == nullptr) {
+      load4((const T*)xrow + col, own ? 4 : 0, v);
+      load4(lrow + col, other ? 4 : 0, u);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int from = perm[col + e] - perm0;
+        v[e] = own ? xrow[from] : T(0);
+        u[e] = other ? lrow[from] : T(0);
+      }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       x[0][b][e] = v[e];
@@ -738,6 +751,9 @@ __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
 #pragma unroll
   for (int b = 0; b < NSUB; ++b) load4(dinv + b * SUB + 4 * g, 4, rinv[b]);
   __syncthreads();
+  // with a permutation a store below may hit an entry that another lane of this wavefront
+  // loads above: every load has returned before the first store is issued
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (first) {
     acc_t (&own)[1][NSUB] = *reinterpret_cast<acc_t (*)[1][NSUB]>(&x[0]);
     ops.template solve<1>(own, lane);

@@ -336,6 +336,14 @@ struct Launcher {
   // The array that holds the inverses of the leaf whose first pivot has index d0.
   T* linv_of(int64_t d0) const { return l10 ? linv + ((d0 / LEAF) & 1) * (LEAF * SUB) : linv; }
 
+  // The leaf of width w at P, first pivot d0, with pivoting.
+  void factor_leaf_pivoted(hipStream_t st, T* P, int64_t ld, int64_t w, int64_t d0) {
+    hipLaunchKernelGGL((leaf_factor_pivoted_kernel<T>), dim3(1), dim3(64 * PIVOT_WAVES), 0, st, P, ld, (int)w,
+                       dvec + d0, dinv + d0, linv_of(d0), perm + d0, (long long)d0, flags);
+    fail->check(hipGetLastError());
+    ++launches;
+  }
+
   // Factor block column: P at its diagonal entry, m rows, w columns (w <= m).
   // d0: index of its first pivot in dvec/dinv.  first_done: the first leaf has
   // been factored already, by the update launch that produced it.
@@ -375,10 +383,7 @@ struct Launcher {
     if (w <= LEAF) {
       if (perm) {
         if (spd) return MDET_EINVAL;
-        hipLaunchKernelGGL((leaf_factor_pivoted_kernel<T>), dim3(1), dim3(64 * PIVOT_WAVES), 0, st, P, ld,
-                           (int)w, dvec + d0, dinv + d0, linv_of(d0), perm + d0, (long long)d0, flags);
-        fail->check(hipGetLastError());
-        ++launches;
+        factor_leaf_pivoted(st, P, ld, w, d0);
       } else if (!first_done) {
         hipLaunchKernelGGL((leaf_factor_kernel<T>), dim3(1), dim3(FACTOR_THREADS), 0, st, P, ld,
                            (int)w, dvec + d0, dinv + d0, linv_of(d0), (long long)d0, flags, spd ? 1 : 0);
@@ -407,25 +412,31 @@ struct Launcher {
     // second leaf's columns and the second leaf's factorisation are one launch.  The
     // solve launch of the second leaf, which must exist, puts a block in place that this
     // one leaves aside.
-    if (w == 2 * LEAF && m > w && l10 && !perm && m - LEAF <= INT32_MAX) {
-      if (!first_done) {
+    // With pivoting the leaves have launches of their own, and the pair's solve and update
+    // are the one launch (instead of two: n = 4096, fp64, 3.20 -> 3.05 ms).
+    if (w == 2 * LEAF && m > w && l10 && qoff == 0 && m - LEAF <= INT32_MAX) {
+      if (perm) {
+        if (spd) return MDET_EINVAL;
+        factor_leaf_pivoted(st, P, ld, LEAF, d0);
+      } else if (!first_done) {
         hipLaunchKernelGGL((leaf_factor_kernel<T>), dim3(1), dim3(FACTOR_THREADS), 0, st, P, ld, (int)LEAF,
                            dvec + d0, dinv + d0, linv_of(d0), (long long)d0, flags, spd ? 1 : 0);
         ++launches;
       }
       const int64_t below = m - LEAF;
-      const FusedLeaf<T> fl = fused_leaf(LEAF, d0 + LEAF);
+      const FusedLeaf<T> fl = fused_leaf(perm ? 0 : LEAF, d0 + LEAF);
+      const int* order = perm ? (const int*)(perm + d0) : (const int*)nullptr;
       const dim3 grid((unsigned)((below + SOLVE_ROWS - 1) / SOLVE_ROWS)), block(256);
       T* Wrows = Wp ? Wp + LEAF * wld : (T*)nullptr;
       const int wfrom = (int)(wskip > LEAF ? wskip - LEAF : 0);
       if (spd)
         hipLaunchKernelGGL((leaf_pair_kernel<T, true>), grid, block, 0, st, P + LEAF * ld, ld, (int)below,
                            (const T*)P, ld, (const T*)(dinv + d0), (const T*)linv_of(d0),
-                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, fl);
+                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, order, (int)d0, fl);
       else
         hipLaunchKernelGGL((leaf_pair_kernel<T, false>), grid, block, 0, st, P + LEAF * ld, ld, (int)below,
                            (const T*)P, ld, (const T*)(dinv + d0), (const T*)linv_of(d0),
-                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, fl);
+                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, order, (int)d0, fl);
       fail->check(hipGetLastError());
       ++launches;
       fma += ((double)LEAF * LEAF * LEAF - (double)LEAF) / 6.0;                 // first leaf

@@ -49,3 +49,21 @@ def test_candidates_that_differ_in_the_last_bits():
     r, d, p = run(a)
     assert list(o.perm[:3]) == [17, 40, 63] and np.array_equal(p, np.asarray(o.perm))
     assert r.sign == o.sign == 1 and np.array_equal(d, np.asarray(o.diag, dtype=np.float64))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [130, 143, 191, 192, 193, 300, 513])
+def test_pairs_of_leaves_with_rows_below(n, dtype):
+    """The first leaf's order is undone while its rows are read: rows of every remainder, as above."""
+    rng = np.random.default_rng(n)
+    a = rng.uniform(-1, 1, (n, n)) / (8 * n)
+    a = a + a.T
+    np.fill_diagonal(a, (3 + 0.01 * rng.permutation(n)) * rng.choice([-1, 1], n))
+    a = a.astype(np.float64 if dtype == "f64" else np.float32)
+    o = oracle.ldlt_pivoted(a)
+    r, d, p = run(a)
+    assert r.status == 0 and r.sign == o.sign and r.negative_pivots == o.negative_pivots
+    assert np.array_equal(p, np.asarray(o.perm))
+    # an off-diagonal entry of the wrong column changes a pivot by about 1 / (4 n)^2 / 3 > 8e-8;
+    # fp32 rounds the pivot itself by 6e-8 relative, so only fp64 can show it
+    assert np.max(np.abs(d - o.diag) / np.abs(o.diag)) < (1e-12 if dtype == "f64" else 1e-5)
