@@ -42,7 +42,6 @@ constexpr int SUB = 16;               // sub-block order = MFMA tile order
 constexpr int NSUB = LEAF / SUB;
 constexpr int LEAF_PAD = LEAF + 1;    // LDS row stride of a leaf tile
 constexpr int LEAF_TILE = LEAF * LEAF_PAD;
-constexpr int SUB_PAD = SUB + 1;
 
 // Device-side status words shared by all kernels of one call.
 struct DevFlags {
@@ -59,35 +58,6 @@ __device__ __forceinline__ double lane_value(double v, int src) {
 }
 __device__ __forceinline__ float lane_value(float v, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
-}
-
-// Coalesced movement of a rows x cols tile (<= 64 x 64) from global memory into an
-// LDS array with row stride `stride`, by one wavefront, in two halves of 32 rows.
-// tile_fetch issues the 32 independent loads of one half (so their latencies
-// overlap, and the loads of two different tiles can be in flight together);
-// tile_put writes them to LDS.  Missing rows/columns read as 0 (diagonal entries
-// of the padding as 1 when unit_pad is set).  With TRANSPOSE the element (r, c)
-// lands at lds[c * stride + r].
-constexpr int TILE_HALF = 32;   // rows per half = loads per lane per half
-
-template <typename T, bool STRICT_LOWER>
-__device__ __forceinline__ void tile_fetch(T (&v)[TILE_HALF], int half, const T* g, int64_t ld,
-                                           int rows, int cols, bool unit_pad, int lane) {
-#pragma unroll
-  for (int q = 0; q < TILE_HALF; ++q) {
-    const int r = half * TILE_HALF + q, c = lane;
-    const bool in = r < rows && c < cols && (!STRICT_LOWER || c < r);
-    v[q] = in ? g[(int64_t)r * ld + c] : ((unit_pad && r == c) ? T(1) : T(0));
-  }
-}
-template <typename T, bool TRANSPOSE>
-__device__ __forceinline__ void tile_put(const T (&v)[TILE_HALF], int half, T* lds, int stride,
-                                         int lane) {
-#pragma unroll
-  for (int q = 0; q < TILE_HALF; ++q) {
-    const int r = half * TILE_HALF + q, c = lane;
-    lds[TRANSPOSE ? c * stride + r : r * stride + c] = v[q];
-  }
 }
 
 // ---------------------------------------------------------------------------

@@ -55,7 +55,6 @@ constexpr int UPD_THREADS = 256;
 // free for the kernels of another stream).
 constexpr int UPD_SUPER = 8;
 constexpr int UPD_SUPER_LOG2 = 3;
-constexpr int UPD_SUPER_TRI = UPD_SUPER * (UPD_SUPER + 1) / 2;   // blocks of a diagonal super-tile
 
 struct UpdGrid {
   int64_t per;       // block numbers per XCD; a full launch has 8 * per workgroups
