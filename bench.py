@@ -239,7 +239,7 @@ def kernel_report(reps=5):
                 "unit": "GB/s", "achieved": gb / (ms * 1e-3), "frac": gb / (ms * 1e-3) / HBM})
     coef = torch.empty(q + 4, dtype=torch.float64, device="cuda")
     ms = timed(lambda: M.mdet_flodance_fit(ell, dd, n0, n_s, q, coef=coef, workspace=ws))
-    out.append({"kernel": "flo_qr_kernel (3 levels)", "dtype": "f64",
+    out.append({"kernel": "flo_qr_kernel (all levels)", "dtype": "f64",
                 "shape": f"rows={n_s - n0} cols={q + 3}", "ms": ms,
                 "note": "latency-bound: 13 dependent reflections per level, one block reduction each"})
     nv = torch.logspace(2, 6, 100000, dtype=torch.float64, device="cuda")
