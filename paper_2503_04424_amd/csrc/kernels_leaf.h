@@ -992,7 +992,8 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // left operands, the leaf's rows, are read in that order), so the sub-blocks follow each other
 // in registers.  20 KB of LDS in fp64 for the leaf.  Measured, a launch on average, against
 // every change of layout in LDS (60 KB in fp64): fp64 n = 1500 7.1 -> 6.6 us, n = 8192 (beside
-// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.
+// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.  Alone on 32704 rows 11.7 -> 11.8 us, on
+// 131008 34.5 -> 36 (bound by memory there, in pieces of 32 bytes a lane; 2 ms of the 11.9 s of n = 131072).
 // perm (or null): the leaf was factored with pivoting; perm[j] - perm0 is the column of
 // the panel that belongs at position j.  A wavefront reads all 64 columns of its rows
 // before it writes any of them.
