@@ -13,11 +13,9 @@ using namespace mdet;
 inline uint64_t up256(uint64_t x) { return (x + 255) / 256 * 256; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// workspace of mdet_principal_logdets: one double per chunk, of the fine ones where they are few
-// enough to be used
-inline int64_t scan_chunks(int64_t n, int per) { return n > 0 ? ceil_div(n, (int64_t)SEQ_THREADS * per) : 1; }
-inline uint64_t scan_bytes(int64_t n, int per) { return up256((uint64_t)scan_chunks(n, per) * 8); }
-inline bool scan_fine(int64_t n) { return scan_chunks(n, SEQ_PER_FINE) <= SEQ_FINE_CHUNKS; }
+// workspace of mdet_principal_logdets: one double per chunk
+inline int64_t scan_chunks(int64_t n) { return n > 0 ? ceil_div(n, SEQ_CHUNK) : 1; }
+inline uint64_t scan_bytes(int64_t n) { return up256((uint64_t)scan_chunks(n) * 8); }
 
 // workspace of mdet_flodance_fit: the R factors of two consecutive levels of the tree
 struct FitLayout {
@@ -33,13 +31,17 @@ inline FitLayout fit_layout(int64_t rows, int ncols) {
   return f;
 }
 
-template <typename T, int PER>
+template <typename T>
 void scan(const T* d, int64_t n, double* ell, double* sums, hipStream_t st) {
-  const int64_t chunks = scan_chunks(n, PER);
+  const int64_t chunks = scan_chunks(n);
   const dim3 grid((unsigned)chunks), block(SEQ_THREADS);
-  hipLaunchKernelGGL((seq_chunk_sums_kernel<T, PER>), grid, block, 0, st, d, n, sums);
-  if constexpr (PER != SEQ_PER_FINE) hipLaunchKernelGGL(seq_chunk_offsets_kernel, dim3(1), block, 0, st, sums, chunks);
-  hipLaunchKernelGGL((seq_running_sum_kernel<T, PER>), grid, block, 0, st, d, n, (const double*)sums, ell);
+  hipLaunchKernelGGL((seq_chunk_sums_kernel<T>), grid, block, 0, st, d, n, sums);
+  if (chunks <= SEQ_DIRECT_CHUNKS) {
+    hipLaunchKernelGGL((seq_running_sum_kernel<T, true>), grid, block, 0, st, d, n, (const double*)sums, ell);
+  } else {
+    hipLaunchKernelGGL(seq_chunk_offsets_kernel, dim3(1), dim3(SEQ_OFFSET_THREADS), 0, st, sums, chunks);
+    hipLaunchKernelGGL((seq_running_sum_kernel<T, false>), grid, block, 0, st, d, n, (const double*)sums, ell);
+  }
 }
 
 // One level of the tree: `blocks` workgroups, the kernel for ncols columns.
@@ -47,7 +49,7 @@ template <int NC>
 void qr_level(int ncols, int64_t blocks, const FloProblem& pb, const double* in, int64_t nrows, double* out,
               double* coef, hipStream_t st) {
   if (ncols == NC)
-    hipLaunchKernelGGL(flo_qr_kernel<NC>, dim3((unsigned)blocks), dim3(FLO_THREADS), 0, st, pb, in, nrows, out, coef);
+    hipLaunchKernelGGL(flo_qr_kernel<NC>, dim3((unsigned)blocks), dim3(FLO_ROWS), 0, st, pb, in, nrows, out, coef);
   else if constexpr (NC < FLO_MAX_COLS)
     qr_level<NC + 1>(ncols, blocks, pb, in, nrows, out, coef, st);
 }
@@ -62,7 +64,7 @@ int mdet_sequence_workspace_query(int64_t n, int64_t rows, int32_t q, uint64_t* 
   if (!bytes || n < 0 || rows < 0 || q < 0 || q > FLO_MAX_Q) return MDET_EINVAL;
   const FitLayout f = fit_layout(rows, q + 3);
   const uint64_t fit = f.bytes0 + f.bytes1;
-  const uint64_t scan = scan_bytes(n, scan_fine(n) ? SEQ_PER_FINE : SEQ_PER_COARSE);
+  const uint64_t scan = scan_bytes(n);
   *bytes = fit > scan ? fit : scan;
   return MDET_OK;
 }
@@ -72,18 +74,11 @@ int mdet_principal_logdets(int32_t dtype, const void* d, int64_t n, double* ell,
   if (n < 0 || (dtype != MDET_F32 && dtype != MDET_F64)) return MDET_EINVAL;
   if (n == 0) return MDET_OK;
   if (!d || !ell || !workspace) return MDET_EINVAL;
-  if (workspace_bytes < scan_bytes(n, SEQ_PER_COARSE)) return MDET_ENOMEM_DEVICE;
-  // (a workspace that holds the coarse chunks only is as good as ever)
-  const bool fine = scan_fine(n) && workspace_bytes >= scan_bytes(n, SEQ_PER_FINE);
-  if (scan_chunks(n, SEQ_PER_COARSE) > INT32_MAX) return MDET_EINVAL;
+  if (workspace_bytes < scan_bytes(n)) return MDET_ENOMEM_DEVICE;
+  if (scan_chunks(n) > INT32_MAX) return MDET_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == MDET_F64) {
-    if (fine) scan<double, SEQ_PER_FINE>((const double*)d, n, ell, (double*)workspace, st);
-    else scan<double, SEQ_PER_COARSE>((const double*)d, n, ell, (double*)workspace, st);
-  } else {
-    if (fine) scan<float, SEQ_PER_FINE>((const float*)d, n, ell, (double*)workspace, st);
-    else scan<float, SEQ_PER_COARSE>((const float*)d, n, ell, (double*)workspace, st);
-  }
+  if (dtype == MDET_F64) scan<double>((const double*)d, n, ell, (double*)workspace, st);
+  else scan<float>((const float*)d, n, ell, (double*)workspace, st);
   return launch_status();
 }
 

@@ -1,7 +1,7 @@
-"""The scan and the regression tree at the sizes where they change shape: around a chunk of the
-fine scan (1024), where the coarse one takes over (2048 chunks; also by a workspace that holds
-coarse chunks only), and around one, two and three levels of the tree (1024 rows each), every
-number of columns.
+"""The scan and the regression tree at the sizes where they change shape: around the entries one
+thread adds up (16), around a chunk (4096), where the offsets get a pass of their own (more than
+512 chunks; with the library's workspace and with one of exactly the size the chunks need), and
+around one, two and three levels of the tree (256 rows each), every number of columns.
 
 Tolerances as in the sequence tests: ell within 8 eps sum |log|d||; the fitted curve at and beyond
 the fitted range within max(1e-9, 2000 eps cond) of the oracle's, cond that of the column-scaled
@@ -18,20 +18,20 @@ pytestmark = pytest.mark.gpu
 EPS = np.finfo(np.float64).eps
 
 
-@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 262145, 2048 * 1024, 2048 * 1024 + 1])
-@pytest.mark.parametrize("coarse", [False, True])
-def test_running_sum(n, coarse):
+@pytest.mark.parametrize("n", [1, 15, 17, 1023, 1024, 1025, 4095, 4096, 4097, 262145, 2048 * 1024, 2048 * 1024 + 1])
+@pytest.mark.parametrize("exact", [False, True])
+def test_running_sum(n, exact):
     import paper_2503_04424_amd as M
     M.load()
     d = np.random.default_rng(n).uniform(0.1, 3.0, n) * np.where(np.arange(n) % 3 == 0, -1.0, 1.0)
     want = np.cumsum(np.log(np.abs(d)).astype(np.longdouble))
-    ws = torch.empty(max(256, (-(-n // 4096) * 8 + 255) // 256 * 256), dtype=torch.uint8, device="cuda") if coarse else None
+    ws = torch.empty(max(256, (-(-n // 4096) * 8 + 255) // 256 * 256), dtype=torch.uint8, device="cuda") if exact else None
     got = M.mdet_principal_logdets(torch.from_numpy(d).cuda(), workspace=ws).cpu().numpy()
     bound = 8 * EPS * np.cumsum(np.abs(np.log(np.abs(d))))
     assert np.all(np.abs(got - want) <= bound + 1e-300)
 
 
-@pytest.mark.parametrize("q,rows", [(0, 2), (0, 1023), (1, 1024), (2, 1025), (3, 2049), (4, 40000), (5, 1500), (6, 9000),
+@pytest.mark.parametrize("q,rows", [(0, 2), (0, 255), (0, 257), (1, 513), (0, 1023), (1, 1024), (2, 1025), (3, 2049), (4, 40000), (5, 1500), (6, 9000),
                                     (7, 1100), (8, 3000), (9, 1025), (10, 80000)])
 def test_fit_on_every_tree(q, rows):
     import paper_2503_04424_amd as M
