@@ -85,9 +85,11 @@ typedef struct mdet_params {
                                 what it needs (within the budget) and frees it, but
                                 for one buffer of at most 512 MiB per device that a
                                 call without a budget may leave for the next one; it
-                                is freed by a call with a budget, by one that needs
-                                more, when memory runs out, or after 32 calls without
-                                a use for it.                                       */
+                                is freed by a call with a budget (with or without a
+                                workspace of the caller's), by one that needs more,
+                                when memory runs out, or after 32 calls without a use
+                                for it, those with a caller's workspace among them
+                                (mdet_logdet_device_noalloc leaves it alone).       */
   uint64_t dev_workspace_bytes;
   void* host_scratch;        /* out-of-core with overwrite=0 only: pinned host
                                 memory of at least mdet_workspace_query()'s

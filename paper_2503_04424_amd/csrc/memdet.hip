@@ -777,7 +777,10 @@ static void init_result(mdet_result* r, const Plan& pl) {
 // At most WORKSPACE_KEPT bytes; lent to one call at a time (others allocate as ever), and only
 // put back by a call whose device work has finished.  Given back to the device when a call needs
 // more than it holds, has a memory budget (nothing may be held beside the call's own memory
-// then), finds no memory, or when WORKSPACE_IDLE calls in a row had no use for it.
+// then), finds no memory, or when WORKSPACE_IDLE calls in a row had no use for it; calls with a
+// workspace of the caller's are such calls, and their budget counts as well.  The bound is a
+// choice: a call that needs more takes 6 ms and longer (fp64, n = 8192), of which allocating
+// is 5 % and less.
 constexpr uint64_t WORKSPACE_KEPT = 512ull << 20;
 constexpr int WORKSPACE_IDLE = 32;
 struct KeptWorkspace {
@@ -808,15 +811,18 @@ static void* kept_take(int dev, uint64_t need, uint64_t* bytes) {
   if (drop) (void)hipFree(drop);
   return out;
 }
-static void kept_drop(int dev) {
+// A call that has no use for the buffer: it goes if it `must`, or if this was the last of too many.
+static void kept_pass(int dev, bool must) {
   if (dev < 0 || dev >= 64) return;
   void* drop = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_mu);
-    drop = g_kept[dev].p;
-    g_kept[dev] = KeptWorkspace{};
+    KeptWorkspace& k = g_kept[dev];
+    if (!k.p || (!must && ++k.idle < WORKSPACE_IDLE)) return;
+    drop = k.p;
+    k = KeptWorkspace{};
   }
-  if (drop) (void)hipFree(drop);
+  (void)hipFree(drop);
 }
 static bool kept_put(int dev, void* p, uint64_t bytes) {
   if (dev < 0 || dev >= 64 || bytes > WORKSPACE_KEPT) return false;
@@ -840,6 +846,7 @@ struct Workspace {
   int acquire(const mdet_params& p, uint64_t need, HipFail& f) {
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
     if (p.dev_workspace) {
+      kept_pass(dev, p.mem_budget_bytes != 0);
       if (p.dev_workspace_bytes < need || ((uintptr_t)p.dev_workspace & 255u)) return MDET_ENOMEM_DEVICE;
       base = (char*)p.dev_workspace;
       bytes = p.dev_workspace_bytes;
@@ -849,12 +856,12 @@ struct Workspace {
     may_keep = p.mem_budget_bytes == 0 && need <= WORKSPACE_KEPT;
     void* q = nullptr;
     if (may_keep) q = kept_take(dev, need, &need);
-    else kept_drop(dev);
+    else kept_pass(dev, true);
     if (!q) {
       hipError_t e = hipMalloc(&q, need);
       if (e != hipSuccess) {
         (void)hipGetLastError();
-        kept_drop(dev);
+        kept_pass(dev, true);
         e = hipMalloc(&q, need);
       }
       if (e != hipSuccess) {

@@ -53,6 +53,33 @@ def test_bounded_and_given_back(M):
     assert base - free() <= 16 * MIB
 
 
+@pytest.mark.parametrize("host", [False, True])
+def test_calls_with_their_own_workspace(M, host):
+    """A budget frees the buffer whoever owns the call's workspace, and calls with a workspace of
+    their own count as calls without a use for it."""
+    n, bs = 700, 128
+    small, mid = spd(n), spd(5000)
+    packed = M.pack_lower_block_columns(small.cpu(), bs)
+
+    def call(budget):
+        ws, _ = M.mdet_workspace_query(n, torch.float64, bs, budget, overwrite=False, for_device_input=not host)
+        buf = torch.empty(ws, dtype=torch.uint8, device="cuda")
+        held = free()
+        for _ in range(1 if budget else 31):
+            if host:
+                M.mdet_logdet_host(packed, n, bs, mem_budget=budget, overwrite=False, workspace=buf)
+            else:
+                M.mdet_logdet_device(small, block_size=bs, mem_budget=budget, overwrite=False, workspace=buf)
+        return free() - held                              # what the calls gave back
+
+    call(1 << 40)
+    M.mdet_logdet_device(mid)                             # leaves 200 MB
+    assert call(1 << 40) >= 150 * MIB
+    M.mdet_logdet_device(mid)
+    assert abs(call(0)) <= 8 * MIB                        # 31 calls: still there
+    assert call(0) >= 150 * MIB                           # the 32nd
+
+
 def test_threads_and_leftovers(M):
     # a buffer full of another call's numbers, NaN among them, changes nothing; several threads
     # at once each get the right result
