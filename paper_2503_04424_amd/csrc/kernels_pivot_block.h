@@ -27,6 +27,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <limits>
+
 #include "kernels_leaf.h"
 
 namespace mdet {
@@ -276,7 +278,12 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
           mypos = jj;
           live = false;
         }
-        const T rd = T(1) / d;                   // while the row is on its way
+        // while the row is on its way: the reciprocal, of a pivot that has been lifted out of the
+        // subnormal range if it was there (the reciprocal of one in the last binades is infinite)
+        const T lift = __builtin_fabs((double)d) < (double)std::numeric_limits<T>::min()
+                           ? T(1) / (std::numeric_limits<T>::epsilon() * std::numeric_limits<T>::epsilon()) : T(1);
+        const T dl = d * lift;
+        const T rd = T(1) / dl;
         __syncthreads();
         T v = sv;
         asm volatile("" ::"v"(ahead));
@@ -287,8 +294,8 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
         dcur = mine == j ? d : dcur;
         pcur = mine == j ? p : pcur;
         // v / d: the product with the rounded reciprocal, and one correction
-        const T q = v * rd;
-        const T l = live ? fma(fma(-d, q, v), rd, q) : T(0);
+        const T vl = v * lift, q = vl * rd;
+        const T l = live ? fma(fma(-dl, q, vl), rd, q) : T(0);
         diag = fma(-l, v, diag);
         cur[j] = l;
       }
