@@ -992,8 +992,9 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // left operands, the leaf's rows, are read in that order), so the sub-blocks follow each other
 // in registers.  20 KB of LDS in fp64 for the leaf.  Measured, a launch on average, against
 // every change of layout in LDS (60 KB in fp64): fp64 n = 1500 7.1 -> 6.6 us, n = 8192 (beside
-// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.  Alone on 32704 rows 11.7 -> 11.8 us, on
-// 131008 34.5 -> 36 (bound by memory there, in pieces of 32 bytes a lane; 2 ms of the 11.9 s of n = 131072).
+// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.  Alone
+// on 32704 rows 12.0 -> 11.7 us in fp64 and 9.2 -> 6.9 in fp32, on 131008 35.2 -> 32.6 (4.1 TB/s:
+// bound by memory there) and 23.5 -> 17.8.
 // perm (or null): the leaf was factored with pivoting; perm[j] - perm0 is the column of
 // the panel that belongs at position j.  A wavefront reads all 64 columns of its rows
 // before it writes any of them.
@@ -1008,29 +1009,51 @@ template <typename T> __device__ __forceinline__ int solve_col(int i);
 template <> __device__ __forceinline__ int solve_col<double>(int i) { return 4 * (i & 3) + (i >> 2); }
 template <> __device__ __forceinline__ int solve_col<float>(int i) { return i; }
 
-// Four consecutive entries, of which those from `left` on are missing (zero).
+// Four consecutive entries (aligned to an entry only: the memory system takes it).
 template <typename T>
-__device__ __forceinline__ void load4(const T* p, const int left, T (&v)[4]) {
-  // aligned to an entry only: the memory system takes it
+__device__ __forceinline__ void load4(const T* p, T (&v)[4]) {
   typedef T four __attribute__((ext_vector_type(4), aligned(sizeof(T))));
-  if (left >= 4) {
-    const four f = *reinterpret_cast<const four*>(p);
+  const four f = *reinterpret_cast<const four*>(p);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = f[e];
+  for (int e = 0; e < 4; ++e) v[e] = f[e];
+}
+template <typename T>
+__device__ __forceinline__ void store4(T* p, const T (&v)[4]) {
+  typedef T four __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  *reinterpret_cast<four*>(p) = four{v[0], v[1], v[2], v[3]};
+}
+// A lane's four of every sub-block of a row that starts at p: columns 16 b + 4 g + e < w, the
+// others zero.  Whole rows (w = LEAF, the same in all lanes) have a path of their own, in which
+// the loads follow each other with nothing in between: with a condition on each of them a solve of
+// 131008 rows took 36.4 us in fp64 and 26.0 in fp32, now 32.6 and 17.8.
+template <typename T>
+__device__ __forceinline__ void load_row(const T* p, const int g, const int w, T (&v)[NSUB][4]) {
+  if (w >= LEAF) {
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) load4(p + b * SUB + 4 * g, v[b]);
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = e < left ? p[e] : T(0);
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int col = b * SUB + 4 * g + e;
+        v[b][e] = col < w ? p[col] : T(0);
+      }
   }
 }
 template <typename T>
-__device__ __forceinline__ void store4(T* p, const int left, const T (&v)[4]) {
-  typedef T four __attribute__((ext_vector_type(4), aligned(sizeof(T))));
-  if (left >= 4) {
-    *reinterpret_cast<four*>(p) = four{v[0], v[1], v[2], v[3]};
+__device__ __forceinline__ void store_row(T* p, const int g, const int w, const T (&v)[NSUB][4]) {
+  if (w >= LEAF) {
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) store4(p + b * SUB + 4 * g, v[b]);
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (e < left) p[e] = v[e];
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int col = b * SUB + 4 * g + e;
+        if (col < w) p[col] = v[b][e];
+      }
   }
 }
 
@@ -1065,9 +1088,14 @@ struct LeafOperands {
           int b = 1;
           while (lower(b + 1, 0) <= q) ++b;
           const int r = b * SUB + row;
-          load4(Lleaf + (int64_t)r * ldl + (q - lower(b, 0)) * SUB + 4 * g, r < w ? 4 : 0, v[k]);
+          if (r < w) {
+            load4(Lleaf + (int64_t)r * ldl + (q - lower(b, 0)) * SUB + 4 * g, v[k]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[k][e] = T(0);
+          }
         } else {
-          load4(linv + ((q - (COUNT - NSUB)) * SUB + row) * SUB + 4 * g, 4, v[k]);
+          load4(linv + ((q - (COUNT - NSUB)) * SUB + row) * SUB + 4 * g, v[k]);
         }
       }
     }
@@ -1154,45 +1182,53 @@ __device__ __forceinline__ void leaf_solve_body(
   const bool in = row < m;
   T* xrow = Xg + row * ld;
   acc_t x[1][NSUB];
+  {
+    T v[NSUB][4];
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b) {
-    const int col = b * SUB + 4 * g;
-    T v[4];
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[b][e] = T(0);
     if (perm == nullptr) {
-      load4((const T*)xrow + col, in ? w - col : 0, v);
+      if (in) load_row((const T*)xrow, g, w, v);
     } else {
       // column `col` of the result is the column that was taken at that step
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (in && col + e < w) ? xrow[perm[col + e] - perm0] : T(0);
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int col = b * SUB + 4 * g + e;
+          if (in && col < w) v[b][e] = xrow[perm[col] - perm0];
+        }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[0][b][e] = v[e];
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[0][b][e] = v[b][e];
   }
   LeafOperands<T> ops{lds};
   ops.stage(Lleaf, ldl, w, linv, wave, lane);
   T rinv[NSUB][4];
-#pragma unroll
-  for (int b = 0; b < NSUB; ++b) load4(dinv + b * SUB + 4 * g, w - b * SUB - 4 * g, rinv[b]);
+  load_row(dinv, g, w, rinv);
   __syncthreads();
   // with a permutation a store below may hit an entry that another lane of this wavefront
   // loads above: every load has returned before the first store is issued
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   ops.template solve<1>(x, lane);
   if (in) {
+    T v[NSUB][4];
 #pragma unroll
-    for (int b = 0; b < NSUB; ++b) {
-      const int col = b * SUB + 4 * g;
-      T v[4];
+    for (int b = 0; b < NSUB; ++b)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = x[0][b][e] * rinv[b][e];
-      store4(xrow + col, w - col, v);
-      if (Wg != nullptr && row >= wfrom) {
-        T d[4];
-        load4(dvec + col, w - col, d);
+      for (int e = 0; e < 4; ++e) v[b][e] = x[0][b][e] * rinv[b][e];
+    store_row(xrow, g, w, v);
+    if (Wg != nullptr && row >= wfrom) {
+      T d[NSUB][4];
+      load_row(dvec, g, w, d);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] *= d[e];
-        store4(Wg + row * ldw + col, w - col, v);
-      }
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[b][e] *= d[b][e];
+      store_row(Wg + row * ldw, g, w, v);
     }
   }
 }

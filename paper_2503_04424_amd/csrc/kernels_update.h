@@ -708,28 +708,34 @@ __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
   const int leaf_row = wave * SUB + l16;
   T* xrow = Xg + row * ld;
   acc_t x[2][NSUB];
-#pragma unroll
-  for (int b = 0; b < NSUB; ++b) {
-    const int col = b * SUB + 4 * g;
-    T v[4], u[4];
+  {
     const bool own = row < m, other = !first && leaf_row < m;
     const T* lrow = Xg + (int64_t)leaf_row * ld;
+    T v[NSUB][4], u[NSUB][4];
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[b][e] = u[b][e] = T(0);
     if (perm == nullptr) {
-      load4((const T*)xrow + col, own ? 4 : 0, v);
-      load4(lrow + col, other ? 4 : 0, u);
+      if (own) load_row((const T*)xrow, g, LEAF, v);
+      if (other) load_row(lrow, g, LEAF, u);
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int from = perm[col + e] - perm0;
-        v[e] = own ? xrow[from] : T(0);
-        u[e] = other ? lrow[from] : T(0);
-      }
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int from = perm[b * SUB + 4 * g + e] - perm0;
+          if (own) v[b][e] = xrow[from];
+          if (other) u[b][e] = lrow[from];
+        }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      x[0][b][e] = v[e];
-      x[1][b][e] = u[e];
-    }
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[0][b][e] = v[b][e];
+        x[1][b][e] = u[b][e];
+      }
   }
   LeafOperands<T> ops{lds + ROWS_ELEMS};
   ops.stage(Lleaf, ldl, LEAF, linv, wave, lane);
@@ -747,8 +753,7 @@ __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
       acc[t][r] = (t < tiles && grow < m && gcol <= grow) ? C[(int64_t)grow * ld + gcol] : T(0);
     }
   T rinv[NSUB][4];
-#pragma unroll
-  for (int b = 0; b < NSUB; ++b) load4(dinv + b * SUB + 4 * g, 4, rinv[b]);
+  load_row(dinv, g, LEAF, rinv);
   __syncthreads();
   // with a permutation a store below may hit an entry that another lane of this wavefront
   // loads above: every load has returned before the first store is issued
@@ -761,26 +766,26 @@ __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
   } else {
     ops.template solve<2>(x, lane);
   }
+  T v[NSUB][4];
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b) {
-    const int col = b * SUB + 4 * g;
-    T v[4];
+  for (int b = 0; b < NSUB; ++b)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const T rj = rinv[b][e];
-      v[e] = x[0][b][e] * rj;
+      v[b][e] = x[0][b][e] * rj;
       const T lv = x[1][b][e] * rj;
       lds[((wave * NSUB + b) * 4 + e) * 64 + lane] = SCALED ? lv * rj : lv;
     }
-    if (row < m) {
-      store4(first ? l10 + (int)row * LEAF + col : xrow + col, 4, v);
-      if (Wg != nullptr && row >= wfrom) {
-        T d[4];
-        load4(dvec + col, 4, d);
+  if (row < m) {
+    store_row(first ? l10 + (int)row * LEAF : xrow, g, LEAF, v);
+    if (Wg != nullptr && row >= wfrom) {
+      T d[NSUB][4];
+      load_row(dvec, g, LEAF, d);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] *= d[e];
-        store4(Wg + row * ldw + col, 4, v);
-      }
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[b][e] *= d[b][e];
+      store_row(Wg + row * ldw, g, LEAF, v);
     }
   }
   __syncthreads();
