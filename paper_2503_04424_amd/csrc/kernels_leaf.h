@@ -23,12 +23,12 @@
 // transpose_strict_kernel : the entries above the diagonal of a general matrix into their
 //                      transposed store, and back.
 //
-// leaf_factor_kernel and leaf_solve_kernel work on 16-column sub-blocks: the sequential part
-// (elimination inside a 16 x 16 diagonal sub-block) runs on the vector ALUs with one matrix
-// row per lane, everything else (the substitution against already solved sub-blocks with the
-// inverse of the diagonal one, updates inside the leaf) is 16 x 16 x 16 products on the
-// matrix cores.  The loops over sub-blocks are real loops, so the code stays small enough for
-// the instruction cache.
+// The leaf kernels work on 16-column sub-blocks: the sequential part (elimination inside a
+// 16 x 16 diagonal sub-block) runs on the vector ALUs with one matrix row per lane, everything
+// else (the substitution against already solved sub-blocks with the inverse of the diagonal one,
+// updates inside the leaf) is 16 x 16 x 16 products on the matrix cores.  The loops over the
+// sub-blocks of a leaf that is factored are real loops around an unrolled elimination; those of
+// a solve are unrolled, since its sub-blocks stay in registers.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -617,9 +617,9 @@ __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
 // Outputs as leaf_factor_kernel (L and D in pivot order into A, pivots, reciprocals,
 // inverses of the diagonal sub-blocks of L), and perm[j] = pivot0 + (row taken at step j).
 // Bound by the chain of one step (460 clocks: search, row from LDS, its 16 terms, quotient);
-// the three products between cost 2300 clocks each.  Measured, fp64, alone: 20.1 us against
-// 32.3 with the matrix in the registers of four wavefronts and a barrier and an exchange of
-// the pivot row per step (n = 4096 4.39 -> 3.70 ms).
+// the three products between cost 2300 clocks each.  Measured, fp64, launches back to back: 20.1 us
+// each (a launch alone 20.6 to 22.6) against 32.3 with the matrix in the registers of four
+// wavefronts and a barrier and an exchange of the pivot row per step (n = 4096 4.41 -> 3.63 ms).
 constexpr int PIVOT_WAVES = 8;
 template <typename T>
 __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
@@ -991,10 +991,9 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // instructions (their output row i stands for column solve_col(i) of the sub-block, and the
 // left operands, the leaf's rows, are read in that order), so the sub-blocks follow each other
 // in registers.  20 KB of LDS in fp64 for the leaf.  Measured, a launch on average, against
-// every change of layout in LDS (60 KB in fp64): fp64 n = 1500 7.1 -> 6.6 us, n = 8192 (beside
-// the bulk update) 13.2 -> 9.7, fp32 n = 10000 14.7 -> 10.3.  Alone
-// on 32704 rows 12.0 -> 11.7 us in fp64 and 9.2 -> 6.9 in fp32, on 131008 35.2 -> 32.6 (4.1 TB/s:
-// bound by memory there) and 23.5 -> 17.8.
+// every change of layout in LDS (60 KB in fp64): fp64 n = 1500 7.1 -> 6.0 us, n = 8192 (beside
+// the bulk update) 13.2 -> 8.5, fp32 n = 10000 14.7 -> 8.3.  Alone on 32704 rows 12.0 -> 11.7 us in
+// fp64 and 9.2 -> 6.9 in fp32, on 131008 35.2 -> 32.6 (4.1 TB/s: bound by memory there) and 23.5 -> 17.8.
 // perm (or null): the leaf was factored with pivoting; perm[j] - perm0 is the column of
 // the panel that belongs at position j.  A wavefront reads all 64 columns of its rows
 // before it writes any of them.

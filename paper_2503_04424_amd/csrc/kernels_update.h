@@ -681,7 +681,7 @@ MDET_GENERAL_UPDATE_KERNEL(panel_update64_general_kernel, 2, 1, 1)
 // rows go from the four wavefronts that solve them to all through LDS, once, register by
 // register, and both sets of rows are solved side by side.  52 KB of LDS in fp64.
 // Measured, a launch on average, against every change of layout in LDS (94 KB in fp64): fp64
-// n = 1500 18.4 -> 15.8 us, n = 8192 24.0 -> 21.5, fp32 n = 10000 25.4 -> 19.2.
+// n = 1500 18.4 -> 15.5 us, n = 8192 24.0 -> 20.6, fp32 n = 10000 25.4 -> 17.9.
 template <typename T, bool SCALED = false>
 __global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
     T* __restrict__ Xg, int64_t ld, int m, const T* __restrict__ Lleaf, int64_t ldl,
