@@ -1,0 +1,747 @@
+// A block column factored by ONE launch: the leaves, the solves below them and the updates
+// between them as tasks that wait for each other, instead of a chain of launches (leaf, solve,
+// update, leaf, ...; Sec. 2.2, the symmetric forms without pivoting).
+//
+// The column is cut into tiles of 64 x 64 entries, tile (i, j) in tile row i and tile column j.
+// A workgroup takes the next task by number:
+//   diagonal task j:  tiles (j, j-1) and (j, j) reduced by everything left of them; then, once
+//                     leaf j-1 is there, tile (j, j-1) solved against it and its product taken off
+//                     tile (j, j); then that factored;
+//   row task (p, j):  the tiles of tile rows 2p and 2p + 1 in column j that no diagonal task has
+//                     (rows from j + 2 on; from j + 1 in the last tile column) reduced; then, once
+//                     leaf j is there, solved.
+// Everything a task reads except its own tiles is final, and was written by tasks with lower
+// numbers (tile column by tile column, the diagonal task first): whoever holds the lowest
+// number that is not through can always go on, however many workgroups the device holds at a
+// time, and a launch beside it may have the rest.  (A wait gives up after FLOW_PATIENCE all the
+// same: the call then fails, it does not hang.)
+//
+// What bounds it, where a matrix is small: the chain of leaves.  From one leaf to the next are the
+// hand-over through memory, the solve of the 64 rows below it, the product of these and the
+// elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
+// that.  Between launches the same steps also wait for every workgroup of the launch before and
+// for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
+// against the chain of launches, whole calls: fp64 n = 512 230 -> 164 us, n = 1500 620 -> 371, n = 5555
+// 3030 -> 1563, n = 8192 5889 -> 4110, fp32 n = 10000 5948 -> 4191; block columns of 2048 beside a bulk
+// update, n = 32768, 191.1 -> 187.5 ms.  Where a matrix is large: the matrix cores, 4.2 us for the
+// 128 x 64 x 64 products of a tile in fp64 (positive-definite form 3.9; 3.4 at their peak).
+// One workgroup of eight wavefronts has a compute unit to itself (its LDS sees to that): two
+// of four wavefronts each slow each other's leaves down, whose single wavefront then waits for
+// the other's matrix instructions (n = 8192: 10.8 us a leaf instead of 6.7), and the sums of a
+// diagonal task take twice as long.
+//
+// Memory.  The chiplets' L2 caches do not see each other's writes.  What one task hands to
+// another is written through (stores at device scope) and complete before the tile row's
+// counter says so; a task's own tiles are read past the caches; and finished tiles are read by
+// ordinary loads: they cannot be in any cache from before, as long as no 128-byte line holds
+// entries of two tiles.  Where the array's rows do not start on such lines (`lines` = false) the
+// operands are read past the caches as well.
+//
+// Order of the products of one entry: k rising in slabs of 128 bytes, inside a slab as
+// schur_update_block takes them, each term (l d) l: what the update kernels do, so results do not
+// depend on where a block column ends.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels_leaf.h"
+#include "kernels_update.h"
+#include "mfma.h"
+
+namespace mdet {
+
+constexpr int FLOW_WAVES = 8;
+constexpr int FLOW_THREADS = 64 * FLOW_WAVES;
+constexpr int FLOW_ROWS = SUB * FLOW_WAVES;           // rows of a row task: two tile rows
+constexpr int FLOW_STAGES = 4;                        // slabs in LDS: one in use, the next there, two on their way
+constexpr unsigned long long FLOW_PATIENCE = 60ull * 100000000ull;   // of the 100 MHz counter
+
+// Words of device memory a launch needs, zero when it starts: the next task, failure, and per
+// tile row the number of its finished tiles.
+struct FlowSync {
+  unsigned ticket;
+  unsigned failed;
+  unsigned done[1];
+};
+static inline int64_t flow_words(int64_t m) { return 2 + (m + LEAF - 1) / LEAF; }
+
+// Tasks before tile column j (j < ntc) of ntr tile rows, ntp = ceil(ntr / 2) pairs of them: in each
+// column c a diagonal task and the pairs from (c + 2) / 2 on.
+__host__ __device__ __forceinline__ int64_t flow_tasks_before(int64_t ntp, int64_t j) {
+  return j <= 0 ? 0 : j * ntp - (j - 1) * (j - 1) / 4;
+}
+// ... and in all of ntc tile columns; the last has the row right below its leaf, too.
+__host__ __device__ __forceinline__ int64_t flow_tasks(int64_t ntr, int64_t ntc) {
+  const int64_t ntp = (ntr + 1) / 2;
+  return flow_tasks_before(ntp, ntc - 1) + 1 + (ntr > ntc ? ntp - ntc / 2 : 0);
+}
+// Column j of task t and its pair of tile rows, or -1: the diagonal task.
+__host__ __device__ __forceinline__ void flow_task(int ntr, int ntc, int t, int& pair, int& j) {
+  const int64_t ntp = (ntr + 1) / 2;
+  // t >= j ntp - (j - 1)^2 / 4 solved for j, then put right
+  const double a = 2.0 * (double)ntp, q = a * a - 4.0 * (double)t;
+  j = (int)(a - sqrt(q > 0.0 ? q : 0.0));
+  if (j > ntc - 1) j = ntc - 1;
+  if (j < 0) j = 0;
+  while (j > 0 && flow_tasks_before(ntp, j) > t) --j;
+  while (j + 1 < ntc && flow_tasks_before(ntp, j + 1) <= t) ++j;
+  const int r = (int)(t - flow_tasks_before(ntp, j));
+  pair = r == 0 ? -1 : (j + 1 < ntc ? (j + 2) / 2 : (j + 1) / 2) + r - 1;
+}
+
+// Four consecutive entries past the caches: `base` is the same in all lanes, `off` bytes from it.
+typedef unsigned flow_u4 __attribute__((ext_vector_type(4)));
+constexpr int FLOW_DEVICE_SCOPE = 16;                 // the sc1 bit of a buffer or LDS-direct access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t flow_rsrc(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffffu, 0x00027000);
+}
+template <typename T>
+__device__ __forceinline__ void flow_load4(__amdgpu_buffer_rsrc_t r, unsigned off, T (&v)[4]) {
+#pragma unroll
+  for (int h = 0; h < (int)sizeof(T) / 4; ++h) {
+    const flow_u4 u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16 * h), 0, FLOW_DEVICE_SCOPE);
+    __builtin_memcpy(&v[h * (16 / (int)sizeof(T))], &u, 16);
+  }
+}
+template <typename T>
+struct FlowShape {
+  static constexpr int BK = Mfma<T>::BK;
+  static constexpr int ROWS = FLOW_ROWS * BK, COLS = LEAF * BK;   // the slabs of the two operands
+  static constexpr int STAGE = ROWS + COLS + BK;                  // both, and the pivots
+  static constexpr int SLABS = FLOW_STAGES * STAGE;
+  // after the sums the same memory holds what a solve needs of its leaf, later the leaf that is
+  // factored, and behind that a solved tile, or 16 solved rows of each wavefront on their way out
+  static constexpr int SOLVED = FACTOR_LDS_ELEMS;
+  static constexpr int ROW_STRIDE = LEAF + 16 / (int)sizeof(T);
+  static constexpr int OUT = SUB * ROW_STRIDE;
+  static constexpr int LATER = SOLVED + FLOW_WAVES * OUT;
+  static_assert(LEAF * LEAF + 4 * OUT <= FLOW_WAVES * OUT, "places in LDS");
+  static constexpr int LDS_ELEMS = SLABS > LATER ? SLABS : LATER;
+  static_assert(SOLVED >= LeafOperands<T>::ELEMS && SOLVED * sizeof(T) % 16 == 0, "places in LDS");
+};
+
+// What all tasks of a launch share.
+template <typename T>
+struct FlowArgs {
+  T* P;                 // the block column's diagonal entry
+  int64_t ld;
+  int m, w;             // rows, columns (w a multiple of LEAF, or m = w)
+  T* dvec;              // its pivots and reciprocal pivots
+  T* dinv;
+  T* W;                 // its pivot-scaled copy (rows from wskip on), or null
+  int64_t wld;
+  int wskip;
+  long long pivot0;
+  DevFlags* flags;
+  FlowSync* sync;
+  int ntr, ntc;
+  bool lines;           // rows start on 128-byte lines
+};
+
+// A wavefront waits until the counter of every lane's tile row (`row` < 0: none) has reached `need`;
+// the smallest of them, or -1 if the launch has failed.  A wait that gives up is reported as pivot
+// 0, kind 8.
+template <typename T>
+__device__ __forceinline__ int flow_wait(const FlowArgs<T>& a, const int row, const int need) {
+  unsigned long long since = 0;
+  for (unsigned spins = 0;; ++spins) {
+    const int v = row >= 0 ? (int)__hip_atomic_load(&a.sync->done[row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                           : INT32_MAX;
+    if (__ballot(v < need) == 0ull) {
+      int least = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+      for (int q = 1; q < 3; ++q) {
+        const int o = __builtin_amdgcn_readlane(v, q);
+        least = o < least ? o : least;
+      }
+      return least;
+    }
+    if ((spins & 255u) == 255u) {
+      if (__hip_atomic_load(&a.sync->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return -1;
+      const unsigned long long now = __builtin_amdgcn_s_memrealtime();
+      if (since == 0) since = now;
+      if (now - since > FLOW_PATIENCE) {
+        if ((threadIdx.x & 63) == 0) {
+          __hip_atomic_store(&a.sync->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          atomicMin(&a.flags->first_bad, 0ull);
+          atomicExch(&a.flags->bad_kind, 8ull);
+        }
+        return -1;
+      }
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+// The same by the first wavefront for all threads of the workgroup, rows r0, r1, r2.
+template <typename T>
+__device__ __forceinline__ int flow_wait_all(const FlowArgs<T>& a, const int r0, const int r1, const int r2, const int need,
+                                             int* shared) {
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const int v = flow_wait(a, lane == 0 ? r0 : (lane == 1 ? r1 : (lane == 2 ? r2 : -1)), need);
+    if (lane == 0) *shared = v;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*shared);
+}
+template <typename T>
+__device__ __forceinline__ void flow_publish(const FlowArgs<T>& a, const int row, const int count) {
+  __hip_atomic_store(&a.sync->done[row], (unsigned)count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The parts of tile (j, j) in a diagonal task: wavefront 0 has sub-block (0, 0), which the
+// elimination starts with, wavefronts 5 to 7 three each of the others (4, on the SIMD of
+// wavefront 0, none).
+struct FlowUnits {
+  int count;
+  int row[3], col[3];
+  __device__ __forceinline__ explicit FlowUnits(const int wave) {
+    count = wave == 0 ? 1 : (wave >= 5 ? 3 : 0);
+    row[0] = wave == 0 ? 0 : (wave == 5 ? 1 : (wave == 6 ? 2 : 3));
+    col[0] = wave == 0 ? 0 : (wave == 5 ? 0 : 1);
+    row[1] = wave == 5 ? 1 : (wave == 6 ? 2 : 3);
+    col[1] = wave == 5 ? 1 : 2;
+    row[2] = wave == 5 ? 2 : 3;
+    col[2] = wave == 7 ? 3 : 0;
+  }
+};
+
+// The sums of a task over the tiles k < nk left of it, slab by slab through LDS.
+// x[t] += L_col D L_row^T (transposed: register r of a lane of row g of lanes is row l16 of this
+// wavefront's 16 and column 16 t + 4 g + r, as in leaf_solve_body), for the 16 rows that start at
+// 16 wave of the rows row0, row0 + 1, ... (rows, at most FLOW_ROWS; `mine`: this wavefront has some).
+// DIAG: rows are the 64 of tile row `rt0`; wavefronts 0 to 3 collect x, and s[u] += L_row D L_row^T
+// of the FlowUnits.  False if the launch has failed.
+template <typename T, bool SCALED, bool DIAG>
+__device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int rt0, const int rt1, const int col,
+                                                const int nk, const bool mine, typename Mfma<T>::acc_t (&x)[NSUB],
+                                                typename Mfma<T>::acc_t (&s)[3], T* __restrict__ lds, int* shared) {
+  using X = Mfma<T>;
+  using vec_t = typename X::vec_t;
+  using Sh = FlowShape<T>;
+  constexpr int BK = Sh::BK, VEC = X::VEC, KS = BK / 4, PER_TILE = LEAF / BK;
+  constexpr int RV = DIAG ? 1 : 2;                     // a wavefront's loads of row operands per slab
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+
+  // LDS-direct loads as in schur_update_block: 8 rows of 128 bytes each, the eight 16-byte chunks
+  // of a row in the order chunk ^ ((row >> 1) & 7).  Load v brings rows 8 wave .. + 7 of tile row v.
+  const int rt = 8 * wave + (lane >> 3);
+  const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
+  const char* base = reinterpret_cast<const char*>(a.P);
+  const char* Rbase[2];
+  unsigned roff[2];
+#pragma unroll
+  for (int v = 0; v < RV; ++v) {
+    const int64_t first = (int64_t)(v == 0 ? rt0 : rt1) * LEAF;
+    Rbase[v] = base + first * a.ld * (int64_t)sizeof(T);
+    const int rr = first + rt < a.m ? rt : (int)(a.m - 1 - first);
+    roff[v] = (unsigned)(((int64_t)rr * a.ld + chunk * VEC) * (int64_t)sizeof(T));
+  }
+  const char* Cbase = base + (int64_t)col * LEAF * a.ld * (int64_t)sizeof(T);
+  const unsigned coff = (unsigned)(((int64_t)rt * a.ld + chunk * VEC) * (int64_t)sizeof(T));
+  auto pinned = [](unsigned o) { asm volatile("" : "+v"(o)); return o; };
+  constexpr int LOADS = RV + 1 + (SCALED ? 0 : 1);     // a wavefront's, per slab
+  auto request = [&](const int slab, const int stage, auto scope) {
+    constexpr int SCOPE = decltype(scope)::value;
+    T* to = lds + stage * Sh::STAGE;
+    const unsigned kb = __builtin_amdgcn_readfirstlane((unsigned)slab * 128u);
+#pragma unroll
+    for (int v = 0; v < RV; ++v)
+      __builtin_amdgcn_global_load_lds((upd_global_ptr)(Rbase[v] + kb + pinned(roff[v])),
+                                       (upd_lds_ptr)(to + (v * LEAF + wave * 8) * BK), 16, 0, SCOPE);
+    __builtin_amdgcn_global_load_lds((upd_global_ptr)(Cbase + kb + pinned(coff)),
+                                     (upd_lds_ptr)(to + Sh::ROWS + wave * 8 * BK), 16, 0, SCOPE);
+    if constexpr (!SCALED) {
+      // the slab's pivots: 128 bytes, every wavefront the same
+      if (lane < 32)
+        __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(a.dvec) + kb + 4 * lane),
+                                         (upd_lds_ptr)(to + Sh::ROWS + Sh::COLS), 4, 0, 0);
+    }
+  };
+  auto request_any = [&](const int slab, const int stage) {
+    if (a.lines) request(slab, stage, std::integral_constant<int, 0>{});
+    else request(slab, stage, std::integral_constant<int, FLOW_DEVICE_SCOPE>{});
+  };
+
+  const int own_sw = (l16 >> 1) & 7;
+  const int pc = solve_col<T>(l16), pc_sw = (pc >> 1) & 7;
+  auto fetch = [&](T (&f)[KS], const T* from, const int sw) {
+    const vec_t v0 = *reinterpret_cast<const vec_t*>(from + (((2 * g) ^ sw) * VEC));
+    const vec_t v1 = *reinterpret_cast<const vec_t*>(from + (((2 * g + 1) ^ sw) * VEC));
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
+  };
+  const FlowUnits units(wave);
+  // The first operands of a slab, fetched while the slab before is multiplied.
+  struct First { T row[KS], col[KS], d[KS]; } next;
+  const bool sums = mine && (!DIAG || wave < 4);
+  auto scale = [&](T (&f)[KS], const T (&d)[KS]) {
+    if constexpr (!SCALED) {
+#pragma unroll
+      for (int e = 0; e < KS; ++e) f[e] *= d[e];
+    }
+  };
+  auto prefetch = [&](const int stage) {
+    const T* rs = lds + stage * Sh::STAGE;
+    if constexpr (!SCALED) {
+#pragma unroll
+      for (int h = 0; h < KS / VEC; ++h) {
+        const vec_t v = *reinterpret_cast<const vec_t*>(rs + Sh::ROWS + Sh::COLS + g * KS + h * VEC);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) next.d[h * VEC + e] = v[e];
+      }
+    }
+    if (sums) {
+      fetch(next.row, rs + (wave * SUB + l16) * BK, own_sw);
+      fetch(next.col, rs + Sh::ROWS + pc * BK, pc_sw);
+    }
+  };
+  // Operands are waited for in front of the fetch of the next ones and not, as the compiler
+  // would have it where it has lost count, behind it.
+  auto arrived = [&](T (&f)[KS]) {
+#pragma unroll
+    for (int e = 0; e < KS; ++e) asm volatile("" : "+v"(f[e]));
+  };
+  // the first operands are there: scaled in front of the barrier, not behind it
+  auto ready = [&] {
+    if constexpr (!SCALED) arrived(next.d);
+    if (sums) {
+      arrived(next.row);
+      arrived(next.col);
+      scale(next.row, next.d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // (`behind`: what is to go out while the first products run)
+  auto multiply = [&](const int stage, const int following, auto behind) {
+    const T* rs = lds + stage * Sh::STAGE;
+    const T* cs = rs + Sh::ROWS;
+    T nd[KS];
+    if constexpr (DIAG && !SCALED) {
+#pragma unroll
+      for (int e = 0; e < KS; ++e) nd[e] = next.d[e];
+    }
+    if (sums) {
+      T fr[KS], fc[NSUB][KS];
+#pragma unroll
+      for (int e = 0; e < KS; ++e) {
+        fr[e] = next.row[e];
+        fc[0][e] = next.col[e];
+      }
+#pragma unroll
+      for (int t = 0; t < NSUB; ++t) {
+        if (t > 0) arrived(fc[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < NSUB) fetch(fc[t + 1], cs + ((t + 1) * SUB + pc) * BK, pc_sw);
+        else if (!DIAG) prefetch(following);           // (behind the last slab: whatever is there)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < KS; ++e) x[t] = X::mfma(fc[t][e], fr[e], x[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t == 0) behind();
+      }
+    } else {
+      behind();
+    }
+    if constexpr (DIAG) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < units.count) {
+          T fr[KS], fc[KS];
+          fetch(fr, rs + (units.row[u] * SUB + l16) * BK, own_sw);
+          fetch(fc, rs + (units.col[u] * SUB + l16) * BK, own_sw);
+          scale(fr, nd);
+#pragma unroll
+          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e], fc[e], s[u]);
+        }
+      prefetch(following);
+    }
+    ready();
+  };
+  // All but the newest slab's loads (`late`; or really all) of this wavefront have landed, and behind
+  // the barrier those of all.
+  auto landed = [](const bool late) {
+    if (!late) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    else if constexpr (LOADS == 4) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+    else if constexpr (LOADS == 3) asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  int k = 0;
+  while (k < nk) {
+    int upto = flow_wait_all(a, rt0, rt1, col, k + 1, shared);
+    if (upto < 0) return false;
+    if (upto > nk) upto = nk;
+    const int s0 = k * PER_TILE, s1 = upto * PER_TILE;
+    request_any(s0, 0);
+    request_any(s0 + 1, 1);                            // (a tile has at least two slabs)
+    if (s0 + 2 < s1) request_any(s0 + 2, 2);
+    landed(s0 + 2 < s1);
+    prefetch(0);
+    ready();
+    // slab by slab; the next one has landed, for all wavefronts after the barrier, which also says
+    // that all are through with the slab before this one: its place takes the third from here
+    for (int slab = s0; slab < s1; slab += FLOW_STAGES) {
+#pragma unroll
+      for (int q = 0; q < FLOW_STAGES; ++q) {
+        if (PER_TILE % FLOW_STAGES != 0 && q % PER_TILE == 0 && slab + q >= s1) break;
+        if (slab + q > s0) landed(slab + q + 2 < s1);
+        multiply(q, (q + 1) % FLOW_STAGES, [&] {
+          if (slab + q + 3 < s1) request_any(slab + q + 3, (q + 3) % FLOW_STAGES);
+        });
+      }
+    }
+    __syncthreads();                                   // the slabs' places are free
+    k = upto;
+  }
+  return true;
+}
+
+// What the solve against a leaf needs, into LDS: as LeafOperands::stage, the inverses of the
+// diagonal sub-blocks (wavefronts 0 to 3, one each) formed here from the leaf itself: the same
+// operations in the same order as the elimination carries along, and no array of them for every
+// leaf in flight.
+template <typename T>
+__device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, const T* __restrict__ leaf, const int64_t ld,
+                                                const int wave, const int lane) {
+  using L = LeafOperands<T>;
+  constexpr int LOW = L::COUNT - NSUB, VEC = L::VEC;
+  const int c = lane & 15, g = lane >> 4, row = solve_col<T>(c);
+  if (wave < 4) {
+    T nl[SUB], inv[4];
+    const T* mine = leaf + (int64_t)(wave * SUB + c) * ld + wave * SUB;
+#pragma unroll
+    for (int k = 0; k < SUB; k += 4) {
+      T f[4];
+      load4(mine + k, f);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) nl[k + e] = f[e];
+    }
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) nl[k] = c > k ? -nl[k] : T(0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) inv[s] = Mfma<T>::acc_row(lane, s) == c ? T(1) : T(0);
+    invert16_rows(inv, nl);
+    // entry (c, k) belongs to the lane whose operand row is c (solve_col is its own inverse)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = Mfma<T>::acc_row(lane, s), e = k & 3;
+      ops.lds[(((LOW + wave) * (4 / VEC) + e / VEC) * 64 + (k >> 2) * 16 + row) * VEC + e % VEC] = inv[s];
+    }
+  } else {
+    T v[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int q = 4 * k + wave - 4;
+      if (q < LOW) {
+        const int b = q < 1 ? 1 : (q < 3 ? 2 : 3);
+        load4(leaf + (int64_t)(b * SUB + row) * ld + (q - L::lower(b, 0)) * SUB + 4 * g, v[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int q = 4 * k + wave - 4;
+      if (q < LOW) {
+#pragma unroll
+        for (int h = 0; h < 4 / VEC; ++h) {
+          typename L::vec_t o;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[e] = -v[k][VEC * h + e];
+          *ops.at(q, h, lane) = o;
+        }
+      }
+    }
+  }
+}
+
+// 16 solved, divided rows from r16 on (this lane's share of them, columns of tile column col) to
+// memory and, scaled by the pivots, to the copy.  The first through LDS (`out`, this wavefront's), so
+// that a store writes whole rows: in 16-byte pieces as the lanes hold them a row task's 64 KB
+// took 2.9 us to arrive.
+template <typename T>
+__device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, const int64_t r16, const int col,
+                                                const T (&v)[NSUB][4], T* __restrict__ out, const int lane) {
+  using vec_t = typename Mfma<T>::vec_t;
+  constexpr int VEC = Mfma<T>::VEC, STRIDE = FlowShape<T>::ROW_STRIDE;
+  constexpr int PIECES = LEAF / VEC, ROWS = 64 / PIECES;         // 16-byte pieces of a row, rows of a store
+  const int l16 = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int h = 0; h < 4 / VEC; ++h) {
+      vec_t o;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) o[e] = v[b][VEC * h + e];
+      *reinterpret_cast<vec_t*>(out + l16 * STRIDE + b * SUB + 4 * g + VEC * h) = o;
+    }
+  const __amdgpu_buffer_rsrc_t to = flow_rsrc(a.P + r16 * a.ld + (int64_t)col * LEAF);
+  const int r0 = lane / PIECES, c = (lane % PIECES) * VEC;
+#pragma unroll
+  for (int q = 0; q < SUB / ROWS; ++q) {
+    const int r = q * ROWS + r0;
+    const vec_t o = *reinterpret_cast<const vec_t*>(out + r * STRIDE + c);
+    flow_u4 u;
+    __builtin_memcpy(&u, &o, 16);
+    if (r16 + r < a.m)
+      __builtin_amdgcn_raw_buffer_store_b128(u, to, (int)(unsigned)(((int64_t)r * a.ld + c) * (int64_t)sizeof(T)), 0,
+                                             FLOW_DEVICE_SCOPE);
+  }
+  if (a.W != nullptr && r16 + l16 < a.m && r16 + l16 >= a.wskip) {
+    T d[NSUB][4];
+    load_row((const T*)(a.dvec + (int64_t)col * LEAF), g, LEAF, d);
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[b][e] *= v[b][e];
+    store_row(a.W + (r16 + l16) * a.wld + (int64_t)col * LEAF, g, LEAF, d);
+  }
+}
+
+// 16 rows of tile column col, negated, as flow_accumulate collects them.
+template <typename T>
+__device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const int64_t r16, const int col,
+                                               typename Mfma<T>::acc_t (&x)[NSUB], const int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  const __amdgpu_buffer_rsrc_t from = flow_rsrc(a.P + r16 * a.ld + (int64_t)col * LEAF);
+  const unsigned off = (unsigned)(((int64_t)l16 * a.ld + 4 * g) * (int64_t)sizeof(T));
+  T v[NSUB][4];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[b][e] = T(0);
+  if (r16 + l16 < a.m) {
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) flow_load4(from, off + (unsigned)(b * SUB * sizeof(T)), v[b]);
+  }
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[b][e] = -v[b][e];
+}
+
+// Solve of this wavefront's 16 rows against the staged leaf, its operands fetched ahead: x from
+// minus the reduced rows to the solved ones, undivided.  (The operations of LeafOperands::solve.)
+template <typename T>
+__device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename Mfma<T>::acc_t (&x)[NSUB], const int lane) {
+  using X = Mfma<T>;
+  using L = LeafOperands<T>;
+  using acc_t = typename X::acc_t;
+  constexpr int LOW = L::COUNT - NSUB;
+  T op[L::COUNT][4];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b) {
+#pragma unroll
+    for (int p = 0; p < b; ++p) ops.fetch(L::lower(b, p), lane, op[L::lower(b, p)]);
+    ops.fetch(LOW + b, lane, op[LOW + b]);
+  }
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b) x[b] = -x[b];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b) {
+#pragma unroll
+    for (int p = 0; p < b; ++p)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x[b] = X::mfma(op[L::lower(b, p)][s], x[p][s], x[b]);
+    acc_t wb = acc_t{0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) wb = X::mfma(op[LOW + b][s], x[b][s], wb);
+    x[b] = wb;
+  }
+}
+
+template <typename T, bool SCALED>
+__device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pair, const int j, T* __restrict__ lds,
+                                              int* shared) {
+  using acc_t = typename Mfma<T>::acc_t;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // of the pair's two tile rows those that this task has; the other one, whose entries left of
+  // column j need not be final, is not read at all
+  const int first = j + 1 < a.ntc ? j + 2 : j + 1;
+  const bool low = 2 * pair >= first, high = 2 * pair + 1 < a.ntr;
+  if (!low && !high) return;                           // (the last pair, of an odd number of rows)
+  const int rt0 = low ? 2 * pair : 2 * pair + 1, rt1 = high ? 2 * pair + 1 : 2 * pair;
+  const int64_t r16 = (int64_t)pair * FLOW_ROWS + wave * SUB;
+  const bool mine = (wave < 4 ? low : high) && r16 < a.m;
+  acc_t x[NSUB], none[3];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
+  if (mine) flow_load_rows(a, r16, j, x, lane);
+  if (!flow_accumulate<T, SCALED, false>(a, rt0, rt1, j, j, mine, x, none, lds, shared)) return;
+  if (flow_wait_all(a, j, -1, -1, j + 1, shared) < 0) return;
+  const LeafOperands<T> ops{lds};
+  flow_stage_leaf(ops, (const T*)(a.P + (int64_t)j * LEAF * (a.ld + 1)), a.ld, wave, lane);
+  T rinv[NSUB][4];
+  load_row((const T*)(a.dinv + (int64_t)j * LEAF), lane >> 4, LEAF, rinv);
+  __syncthreads();
+  if (mine) {
+    flow_solve(ops, x, lane);
+    T v[NSUB][4];
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[b][e] = x[b][e] * rinv[b][e];
+    flow_store_rows(a, r16, j, v, lds + FlowShape<T>::SOLVED + wave * FlowShape<T>::OUT, lane);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    flow_publish(a, rt0, j + 1);
+    if (rt1 != rt0) flow_publish(a, rt1, j + 1);
+  }
+}
+
+template <typename T, bool SCALED>
+__device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T>& a, const int j, T* __restrict__ lds, int* shared) {
+  using X = Mfma<T>;
+  using acc_t = typename X::acc_t;
+  using vec_t = typename X::vec_t;
+  constexpr int VEC = X::VEC;
+  __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int64_t j0 = (int64_t)j * LEAF;
+  const int wl = a.w - j0 < LEAF ? (int)(a.w - j0) : LEAF;       // the leaf's order
+  const FlowUnits units(wave);
+  acc_t x[NSUB], s[3];
+  // entries of the leaf on and below its diagonal
+  T* const leaf = a.P + j0 * (a.ld + 1);
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int grow = units.row[u] * SUB + X::acc_row(lane, r), gcol = units.col[u] * SUB + l16;
+      s[u][r] = (u < units.count && grow < wl && gcol <= grow)
+                    ? -__hip_atomic_load(leaf + (int64_t)grow * a.ld + gcol, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                    : T(0);
+    }
+  if (j > 0) {
+    T* const solved = lds + FlowShape<T>::SOLVED;
+    // place of entries [VEC h, VEC h + VEC) of lane l's four of sub-block (q, b) of the solved tile
+    auto at = [&](const int q, const int b, const int h, const int l) {
+      return reinterpret_cast<vec_t*>(solved + (((q * NSUB + b) * (4 / VEC) + h) * 64 + l) * VEC);
+    };
+    auto fetch = [&](const int q, const int b, const int l, T (&f)[4]) {
+#pragma unroll
+      for (int h = 0; h < 4 / VEC; ++h) {
+        const vec_t o = *at(q, b, h, l);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f[VEC * h + e] = o[e];
+      }
+    };
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
+    if (wave < 4) flow_load_rows(a, j0 + wave * SUB, j - 1, x, lane);
+    if (!flow_accumulate<T, SCALED, true>(a, j, j, j - 1, j - 1, true, x, s, lds, shared)) return;
+    if (flow_wait_all(a, j - 1, -1, -1, j, shared) < 0) return;
+    const LeafOperands<T> ops{lds};
+    flow_stage_leaf(ops, (const T*)(a.P + (j0 - LEAF) * (a.ld + 1)), a.ld, wave, lane);
+    T rinv[NSUB][4];
+    if (wave < 4) load_row((const T*)(a.dinv + j0 - LEAF), g, LEAF, rinv);
+    constexpr int BK = X::BK, KS = BK / 4;
+    T d[NSUB][4];                    // the pivots in the order of the product below
+    if constexpr (!SCALED) {
+#pragma unroll
+      for (int q = 0; q < NSUB; ++q)
+        load4((const T*)(a.dvec + j0 - LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
+    }
+    __syncthreads();
+    T v[NSUB][4];
+    if (wave < 4) {
+      flow_solve(ops, x, lane);
+      // the solved rows go from the wavefronts that hold them to all through LDS
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int h = 0; h < 4 / VEC; ++h) {
+          vec_t o;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[e] = v[b][VEC * h + e] = x[b][VEC * h + e] * rinv[b][VEC * h + e];
+          *at(wave, b, h, lane) = o;
+        }
+    }
+    __syncthreads();
+    // off the chain: the solved tile to memory (wavefront 0's rows by wavefront 4)
+    if (wave >= 1 && wave <= 4) {
+      if (wave == 4) {
+#pragma unroll
+        for (int b = 0; b < NSUB; ++b) fetch(0, b, lane, v[b]);
+      }
+      flow_store_rows(a, j0 + (wave & 3) * SUB, j - 1, v, solved + LEAF * LEAF + (wave & 3) * FlowShape<T>::OUT, lane);
+    }
+    // its product with itself, the columns in the order of a slab: KS consecutive ones of each
+    // BK to a row of lanes
+#pragma unroll
+    for (int p = 0; p < LEAF / BK; ++p) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < units.count) {
+          T fr[KS], fc[KS];
+#pragma unroll
+          for (int h = 0; h < KS / 4; ++h) {
+            // columns c .. c + 3 are with sub-block c / 16 and row of lanes c / 4 % 4
+            const int c = p * BK + g * KS + 4 * h;
+            T vr[4], vc[4];
+            fetch(units.row[u], c / SUB, (c / 4 % 4) * 16 + l16, vr);
+            fetch(units.col[u], c / SUB, (c / 4 % 4) * 16 + l16, vc);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              fr[4 * h + e] = SCALED ? vr[e] : vr[e] * d[p * (KS / 4) + h][e];
+              fc[4 * h + e] = vc[e];
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e], fc[e], s[u]);
+        }
+    }
+  }
+  // wavefront 0 goes on with its sub-block at once; the others' are there, and tile (j, j - 1) is
+  // in memory, when it is through with that (the first barrier of leaf_factor_body)
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (u < units.count) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        leaf_tile_put<T>(lds, units.row[u] * SUB + X::acc_row(lane, r), units.col[u] * SUB + l16, wl, -s[u][r]);
+    }
+  if (wave != 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  leaf_factor_body<T, true, true>(leaf, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, a.pivot0 + j0, a.flags, lds,
+                                  SCALED ? 1 : 0, &a.sync->done[j], (unsigned)j);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) flow_publish(a, j, j + 1);
+}
+
+// SCALED: the positive-definite form (see leaf_factor_body): rows of the Cholesky factor, whose
+// products need no pivots.
+template <typename T, bool SCALED>
+__global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) T lds[FlowShape<T>::LDS_ELEMS];
+  __shared__ int shared[2];
+  if (threadIdx.x == 0)
+    shared[1] = (int)__hip_atomic_fetch_add(&a.sync->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int t = __builtin_amdgcn_readfirstlane(shared[1]);
+  int pair, j;
+  flow_task(a.ntr, a.ntc, t, pair, j);
+  pair = __builtin_amdgcn_readfirstlane(pair);
+  j = __builtin_amdgcn_readfirstlane(j);
+  if (pair < 0) {
+    flow_diagonal_task<T, SCALED>(a, j, lds, shared);
+  } else {
+    __builtin_amdgcn_s_setprio(2);
+    flow_row_task<T, SCALED>(a, pair, j, lds, shared);
+  }
+}
+
+// The words of FlowSync, n of them, to zero.
+__global__ void flow_reset_kernel(unsigned* words, int n) {
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) words[q] = 0u;
+}
+
+}  // namespace mdet

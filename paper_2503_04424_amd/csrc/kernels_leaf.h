@@ -229,7 +229,13 @@ MDET_STEP(14, "15", MDET_WAIT2, MDET_COLS16, MDET_OPS15, MDET_INVS4)
 // their wait states (3480 clocks); with the exchange as separate moves it is 2590.
 // stored: where entry (c, g) of L and D goes in memory, for c < rows; written four columns at
 // a time.  On return mypiv is pivot c.
-template <typename T>
+// THROUGH: as in leaf_factor_body.
+template <bool THROUGH, typename T>
+__device__ __forceinline__ void leaf_store(T* p, T v) {
+  if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+template <typename T, bool THROUGH = false>
 struct Diag16 {
   using X = Mfma<T>;
   T d[SUB];
@@ -256,7 +262,7 @@ struct Diag16 {
     const T lo = (g & 1) ? nl4[1] : nl4[0], hi = (g & 1) ? nl4[3] : nl4[2];
     const int k = 4 * Q + g;
     const T v = c == k ? mypiv : -((g & 2) ? hi : lo);
-    if (k <= c && c < rows) stored[4 * Q] = v;
+    if (k <= c && c < rows) leaf_store<THROUGH>(stored + 4 * Q, v);
   }
   __device__ __forceinline__ void eliminate(const int lane, T* stored, const int rows) {
     const int c = lane & 15, g = lane >> 4;
@@ -389,10 +395,17 @@ __device__ __forceinline__ void leaf_tile_put(T* __restrict__ lds, int row, int 
 // dinv receives d^(-1/2) instead of 1/d: the rows below the leaf, solved with that
 // scaling, are then rows of the Cholesky factor L D^(1/2), and the updates that use
 // them need no pivots.
-template <typename T, bool IN_LDS = false>
+//
+// THROUGH: what is stored is for workgroups of the same launch, on other chiplets too: stores at
+// device scope, past this chiplet's L2 cache.  They form the inverses themselves (linv is not used).
+// Wavefronts beyond the fourth only keep the barriers company, and the other three may come to the
+// first of them late: only sub-block (0, 0) has to be in LDS, put there by wavefront 0 itself, when
+// that begins.  Behind the first barrier *mid becomes mid_value.
+template <typename T, bool IN_LDS = false, bool THROUGH = false>
 __device__ __forceinline__ void leaf_factor_body(
     T* __restrict__ A, int64_t ld, int w, T* __restrict__ dvec, T* __restrict__ dinv,
-    T* __restrict__ linv, long long pivot0, DevFlags* flags, T* __restrict__ lds, int spd = 0) {
+    T* __restrict__ linv, long long pivot0, DevFlags* flags, T* __restrict__ lds, int spd = 0,
+    unsigned* mid = nullptr, unsigned mid_value = 0u) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   T* tile = lds;
@@ -454,19 +467,19 @@ __device__ __forceinline__ void leaf_factor_body(
     const int r = j * SUB + l16;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      if (r < w) A[(int64_t)r * ld + p * SUB + X::acc_row(lane, s)] = l[s];
+      if (r < w) leaf_store<THROUGH>(A + (int64_t)r * ld + p * SUB + X::acc_row(lane, s), l[s]);
   };
   // the pivots of diagonal block p to memory
   auto store_pivots = [&](const int p) {
     const int i = p * SUB + l16;
     if (g == 0 && i < w) {
       const T d = piv_of[i];
-      dvec[i] = d;
-      dinv[i] = spd != 0 ? T(1) / sqrt(d) : rcp_of[i];
+      leaf_store<THROUGH>(dvec + i, d);
+      leaf_store<THROUGH>(dinv + i, T(spd != 0 ? T(1) / sqrt(d) : rcp_of[i]));
     }
   };
 
-  Diag16<T> dg;
+  Diag16<T, THROUGH> dg;
 #pragma unroll 1
   for (int b = 0; b < NSUB; ++b) {
     const int p = b - 1;                          // the diagonal block done last
@@ -493,9 +506,11 @@ __device__ __forceinline__ void leaf_factor_body(
       for (int s = 0; s < 4; ++s) inv_of[((b & 1) * 4 + s) * 64 + lane] = dg.inv[s];
       piv_of[b * SUB + l16] = dg.mypiv;
       rcp_of[b * SUB + l16] = fast_rcp(dg.mypiv);
+      if constexpr (!THROUGH) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) linv[(b * SUB + l16) * SUB + X::acc_row(lane, s)] = dg.inv[s];
-    } else if (b > 0) {
+        for (int s = 0; s < 4; ++s) linv[(b * SUB + l16) * SUB + X::acc_row(lane, s)] = dg.inv[s];
+      }
+    } else if (b > 0 && (!THROUGH || wave < 4)) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         inv[s] = inv_of[((p & 1) * 4 + s) * 64 + lane];
@@ -529,6 +544,9 @@ __device__ __forceinline__ void leaf_factor_body(
       if (wave == 3) store_pivots(p);
     }
     if (b + 1 < NSUB) __syncthreads();
+    if constexpr (THROUGH) {
+      if (b == 0 && tid == 64) __hip_atomic_store(mid, mid_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
   // the last pivots, and the first zero / non-finite one of all through the flags (wavefront 0
   // reads LDS entries of its own: no barrier)

@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "../../include/memdet.h"
+#include "kernels_flow.h"
 #include "kernels_leaf.h"
 #include "kernels_pivot_block.h"
 #include "kernels_reduce.h"
@@ -140,6 +141,11 @@ struct Launcher {
   // linv is two arrays, used by leaves in turn: that kernel reads one leaf's while one
   // of its workgroups already writes the next leaf's.
   T* l10 = nullptr;
+  // Words for the block columns that are factored by one launch (panel_flow_kernel; none: they
+  // are not): each launch takes the next flow_words of them, all zero at the start of the call and
+  // again whenever they run out.
+  unsigned* sync = nullptr;
+  int64_t sync_words = 0, sync_used = 0;
   const T* fix_src = nullptr; // pending copy for the next solve launch
   T* fix_dst = nullptr;
   int64_t fix_ld = 0;
@@ -344,6 +350,49 @@ struct Launcher {
     ++launches;
   }
 
+  // Whether factor_cols takes a block column of m rows and w columns in one launch.
+  bool flows(int64_t ld, int64_t m, int64_t w) const {
+    return sync != nullptr && flow_words(m) <= sync_words && m <= INT32_MAX && (w % LEAF == 0 || w == m) &&
+           (uint64_t)ld * sizeof(T) * LEAF < (1ull << 31) &&
+           flow_tasks((m + LEAF - 1) / LEAF, (w + LEAF - 1) / LEAF) <= INT32_MAX;
+  }
+  int factor_cols_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip) {
+    const int64_t words = flow_words(m);
+    if (sync_used + words > sync_words) {
+      hipLaunchKernelGGL(flow_reset_kernel, dim3(1), dim3(1024), 0, st, sync, (int)sync_words);
+      ++launches;
+      sync_used = 0;
+    }
+    FlowArgs<T> a;
+    a.P = P;
+    a.ld = ld;
+    a.m = (int)m;
+    a.w = (int)w;
+    a.dvec = dvec + d0;
+    a.dinv = dinv + d0;
+    a.W = Wp;
+    a.wld = wld;
+    a.wskip = (int)wskip;
+    a.pivot0 = d0;
+    a.flags = flags;
+    a.sync = (FlowSync*)(sync + sync_used);
+    a.ntr = (int)((m + LEAF - 1) / LEAF);
+    a.ntc = (int)((w + LEAF - 1) / LEAF);
+    a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0;
+    sync_used += words;
+    const dim3 grid((unsigned)flow_tasks(a.ntr, a.ntc)), block(FLOW_THREADS);
+    if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((panel_flow_kernel<T, false>), grid, block, 0, st, a);
+    fail->check(hipGetLastError());
+    ++launches;
+    for (int64_t j = 0; j < w; j += LEAF) {
+      const double lw = (double)(w - j < LEAF ? w - j : LEAF), below = (double)(m - j) - lw;
+      fma += (lw * lw * lw - lw) / 6.0 + below * (lw * (lw - 1) / 2.0);
+      fma += (lw * (lw + 1) / 2 + below * lw) * (double)j;
+    }
+    return MDET_OK;
+  }
+
   // Factor block column: P at its diagonal entry, m rows, w columns (w <= m).
   // d0: index of its first pivot in dvec/dinv.  first_done: the first leaf has
   // been factored already, by the update launch that produced it.
@@ -356,6 +405,7 @@ struct Launcher {
                   bool first_done = false, T* Wp = nullptr, int64_t wskip = 0) {
     if (w <= 0) return MDET_OK;
     if (pb.S != nullptr) return factor_cols_pivot_block(st, P, ld, m, w, d0);
+    if (!first_done && flows(ld, m, w)) return factor_cols_flow(st, P, ld, m, w, d0, Wp, wskip);
     if (w <= LEAF && qoff != 0) {
       // P A = L D U of the leaf, then the rows below it in both halves: the lower half
       // against U^T, the transposed upper half against L with the leaf's row order
@@ -648,7 +698,8 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
     // every column but the group's first had its first leaf factored by the update
     // launch that finished it
     T* Wk = L.wbuf[0] ? L.wbuf[k & 1] : nullptr;      // this column's pivot-scaled copy
-    int rc = L.factor_cols(s0, cols[k].base, cols[k].ld, mk, wk, k * bs, k > jb, Wk, wk);
+    const bool leaf_done = k > jb && !L.flows(cols[k].ld, mk, wk);
+    int rc = L.factor_cols(s0, cols[k].base, cols[k].ld, mk, wk, k * bs, leaf_done, Wk, wk);
     if (rc != MDET_OK) return rc;
     // left operand of the updates by column k: rows from block row j down
     auto left = [&](int64_t j) -> const T* {
@@ -681,8 +732,9 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
       touch(s0, j);
       const T* B = cols[k].base + (j - k) * bs * cols[k].ld;
       const FusedLeaf<T> fl = L.fused_leaf(pl.col_width(j), j * bs);
+      const bool flow = L.flows(cols[j].ld, n - j * bs, pl.col_width(j));
       rc = L.update(s0, cols[j].base, cols[j].ld, left(j), lda_k, B, cols[k].ld, L.dvec + k * bs,
-                    n - j * bs, pl.col_width(j), wk, true, true, &fl, -1, Wk != nullptr);
+                    n - j * bs, pl.col_width(j), wk, true, true, flow ? nullptr : &fl, -1, Wk != nullptr);
       if (rc != MDET_OK) return rc;
     }
     if (lookahead && k + 2 < je && leave_free >= 0) {
@@ -728,6 +780,26 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
   return MDET_OK;
 }
 
+// The block columns in which a dense matrix of this plan is factored: up to 16 of the plan's at a
+// time where a launch that takes them all (panel_flow_kernel) beats block columns whose bulk
+// update runs beside the next one's factorisation.  Measured, ms, one launch against block
+// columns, symmetric / positive definite: fp64 n = 2900 0.66 / 0.62 against 1.05 / 1.01, n = 8192
+// 4.02 / 3.79 against 5.22 / 4.97, n = 12288 12.8 / 12.3 against 15.3 / 14.5, n = 16384 29.9 / 29.4
+// against 28.0 / 26.6; fp32 n = 10000 4.6 / 3.7 against 5.8 / 5.5, n = 16384 15.4 / 13.7 against 14.9 /
+// 14.3: the launch reads each operand out of memory once for every 64 columns, which from about
+// there on no cache holds.  16 is how many block columns the library makes of such a matrix by
+// itself; a caller who asks for more of them, and for look-ahead between them, gets a launch for
+// every 16.  With MDET_FLAG_PROFILE the updates between block columns are what is looked at.
+template <typename T>
+static Plan dense_plan(const Launcher<T>& L, const Plan& pl, int64_t ld, bool lookahead) {
+  constexpr int64_t ONE_LAUNCH = sizeof(T) == 8 ? 14336 : 16384;
+  Plan f = pl;
+  if (pl.T < 2 || pl.n > ONE_LAUNCH || L.profile || L.wbuf[0] || !L.flows(ld, pl.n, pl.n)) return f;
+  f.bs = lookahead ? 16 * pl.bs : round_up(pl.n, LEAF);
+  f.T = (f.n + f.bs - 1) / f.bs;
+  return f;
+}
+
 // ---------------------------------------------------------------------------
 // result collection
 // ---------------------------------------------------------------------------
@@ -745,6 +817,11 @@ static int finish_result(const DeviceOut& o, mdet_result* r) {
       r->sign = 0;
       r->logabsdet = -HUGE_VAL;
       return MDET_ESINGULAR;
+    }
+    if (o.flags.bad_kind == 8) {           // a wait inside a launch gave up
+      r->sign = 0;
+      r->logabsdet = std::nan("");
+      return MDET_EHIP;
     }
     if (o.flags.bad_kind == 4) {
       r->sign = 0;
@@ -904,6 +981,10 @@ static void bind_small(Launcher<T>& L, char* base, const SmallArea& sa) {
   L.linv_u = L.linv + LEAF * SUB;      // linv is two arrays here
   L.flags = (DevFlags*)(base + sa.flags);
   L.perm = sa.total > sa.perm ? (int*)(base + sa.perm) : nullptr;
+  if (!L.perm) {                       // (nothing else uses that array then)
+    L.sync = (unsigned*)L.l10;
+    L.sync_words = LEAF * LEAF * (int64_t)sizeof(T) / 4;
+  }
   // two workgroups of the trailing update fit one compute unit (registers and LDS)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
@@ -913,7 +994,8 @@ static void bind_small(Launcher<T>& L, char* base, const SmallArea& sa) {
 
 // first_bad = ~0 (none), no odd leaves.  A kernel, not a memset: a caller may record the
 // launches of the allocation-free entry point into a graph.
-__global__ void reset_flags_kernel(DevFlags* f) {
+__global__ void reset_flags_kernel(DevFlags* f, unsigned* sync, int sync_words) {
+  for (int q = threadIdx.x; q < sync_words; q += blockDim.x) sync[q] = 0u;
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     f->first_bad = ~0ull;
     f->bad_kind = ~0ull;
@@ -943,7 +1025,7 @@ static void bind_pivot_block(Launcher<T>& L, char* base, const Plan& pl) {
 
 template <typename T>
 static void reset_flags(Launcher<T>& L, hipStream_t st) {
-  hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, L.flags);
+  hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(L.sync ? 1024 : 64), 0, st, L.flags, L.sync, (int)L.sync_words);
   L.fail->check(hipGetLastError());
 }
 
@@ -1029,10 +1111,11 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
     L.wld = pl.bs;
   }
 
-  std::vector<ColRef<T>> cols((size_t)pl.T);
-  for (int64_t j = 0; j < pl.T; ++j) cols[j] = {W + j * pl.bs * ldw + j * pl.bs, ldw};
   const bool lookahead = !(p.flags & MDET_FLAG_NO_LOOKAHEAD);
-  rc = factor_resident(L, pl, cols, 0, pl.T, true, lookahead, s0, s1, events);
+  const Plan by = dense_plan(L, pl, ldw, lookahead);
+  std::vector<ColRef<T>> cols((size_t)by.T);
+  for (int64_t j = 0; j < by.T; ++j) cols[j] = {W + j * by.bs * ldw + j * by.bs, ldw};
+  rc = factor_resident(L, by, cols, 0, by.T, true, lookahead, s0, s1, events);
   if (rc == MDET_OK) {
     L.reduce(s0, pl.n, pl.bs, pl.T, partial, out, running);
     if (Q && !pl.need_copy) {
@@ -1102,6 +1185,7 @@ __global__ void noalloc_finish_kernel(const double* __restrict__ red, const DevF
     sign = 0.0;
     if (flags->bad_kind == 1ull) { logabs = -HUGE_VAL; status = MDET_ESINGULAR; }
     else if (flags->bad_kind == 4ull) { logabs = __builtin_nan(""); status = MDET_ENOTPOSDEF; }
+    else if (flags->bad_kind == 8ull) { logabs = __builtin_nan(""); status = MDET_EHIP; }
     else { logabs = __builtin_nan(""); status = MDET_ENONFINITE; }
   } else if (!(logabs - logabs == 0.0)) {
     status = MDET_ENONFINITE;
@@ -1129,9 +1213,10 @@ static int logdet_device_noalloc_t(const mdet_params& p, const Plan& pl, char* b
   // everything on the caller's stream, in order: no second stream, no events
   EventPool events(&fail);       // never asked for an event without look-ahead
   reset_flags(L, st);
-  std::vector<ColRef<T>> cols((size_t)pl.T);
-  for (int64_t j = 0; j < pl.T; ++j) cols[j] = {dA + j * pl.bs * ld + j * pl.bs, ld};
-  int rc = factor_resident(L, pl, cols, 0, pl.T, true, false, st, st, events);
+  const Plan by = dense_plan(L, pl, ld, false);
+  std::vector<ColRef<T>> cols((size_t)by.T);
+  for (int64_t j = 0; j < by.T; ++j) cols[j] = {dA + j * by.bs * ld + j * by.bs, ld};
+  int rc = factor_resident(L, by, cols, 0, by.T, true, false, st, st, events);
   if (rc != MDET_OK) return rc;
   L.reduce(st, pl.n, pl.bs, pl.T, partial, red, running);
   hipLaunchKernelGGL(noalloc_finish_kernel, dim3(1), dim3(64), 0, st, (const double*)red,

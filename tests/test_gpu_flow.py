@@ -1,0 +1,59 @@
+"""Block columns factored by one launch (panel_flow_kernel): orders around the edges of tiles and pairs
+of tiles, rows that do not start on 128-byte lines, several launches, the scaled copy.
+
+Tolerance: diagonal 1 .. 4 with either sign (positive for the Cholesky form), off-diagonal entries of
+size 1 / (2 n): every entry of the factor is a sum of at most n products of size <= 1 / n, so an
+elimination in any order is within a few hundred units in the last place, 1e-13 (fp32: 1e-5).
+Whatever the block columns, the products of an entry are summed in one order: same bits.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("form", ["sym", "spd"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [65, 127, 128, 129, 191, 193, 256, 321, 448, 640, 1025])
+def test_orders_around_tile_edges(n, dtype, form):
+    import paper_2503_04424_amd as M
+    M.load()
+    npdt, tol = (np.float64, 1e-13) if dtype == "f64" else (np.float32, 1e-5)
+    rng = np.random.default_rng(n)
+    a = rng.uniform(-1, 1, (n, n)) / (2 * n)
+    a = a + a.T
+    np.fill_diagonal(a, rng.uniform(1, 4, n) * (rng.choice([-1, 1], n) if form == "sym" else 1))
+    a = a.astype(npdt)
+    o = oracle.ldlt_logdet(a.astype(np.float64), want_diag=True)
+    flags = M.FLAG_ASSUME_SPD if form == "spd" else 0
+    got = []
+    # whole lines and rows that straddle them, one launch and several, look-ahead and one stream
+    vec = 16 // np.dtype(npdt).itemsize
+    lds = [(n + 31) // 32 * 32, (n + vec - 1) // vec * vec, (n + 31) // 32 * 32 + vec]
+    for ld, bs, extra in [(lds[0], 1024, 0), (lds[1], 128, 0), (lds[2], 64, 0), (lds[0], 64, M.FLAG_NO_LOOKAHEAD),
+                          (lds[1], 192, M.FLAG_PROFILE), (lds[2], 128, 0 if form == "spd" else M.FLAG_SCALED_COPY)]:
+        buf = torch.full((n, ld), float("nan"), dtype=torch.float64 if dtype == "f64" else torch.float32, device="cuda")
+        buf[:, :n] = torch.from_numpy(np.tril(a)).cuda()
+        buf[:, :n] += torch.triu(torch.full((n, n), float("nan"), dtype=buf.dtype, device="cuda"), 1)
+        diag = torch.empty(n, dtype=buf.dtype, device="cuda")
+        r = M.mdet_logdet_device(buf[:, :n], block_size=bs, overwrite=True, flags=flags | extra, diag=diag)
+        d = diag.cpu().numpy().astype(np.float64)
+        assert r.status == 0 and np.max(np.abs(d - o.diag) / np.abs(o.diag)) < tol, (ld, bs)
+        assert r.flops == pytest.approx(2 * (n ** 3 - n) / 6, rel=1e-12)
+        f = buf[:, :n].cpu().numpy()
+        assert np.isnan(f[np.triu_indices(n, 1)]).all()              # what lies above the diagonal is not used
+        got.append((d, np.tril(f)))
+    for d, f in got[1:]:
+        assert np.array_equal(d, got[0][0]) and np.array_equal(f, got[0][1])
+    # the factor itself, against the matrix
+    low = np.tril(got[0][1].astype(np.float64), -1)
+    if form == "spd":                                                # stored leaves are unit-lower, rows below them L D^(1/2)
+        for k in range(0, n, 64):
+            low[k + 64:, k:k + 64] /= np.sqrt(got[0][0][k:k + 64])
+    low += np.eye(n)
+    err = np.abs(low * got[0][0] @ low.T - a.astype(np.float64))
+    assert err.max() < 8 * tol                                       # entries up to 4
