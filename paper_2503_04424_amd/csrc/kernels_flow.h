@@ -1,6 +1,9 @@
 // A block column factored by ONE launch: the leaves, the solves below them and the updates
 // between them as tasks that wait for each other, instead of a chain of launches (leaf, solve,
-// update, leaf, ...; Sec. 2.2, the symmetric forms without pivoting).
+// update, leaf, ...; Sec. 2.2).  Four forms: symmetric, positive definite (rows of the Cholesky factor,
+// whose products need no pivots), symmetric with the pivots of a leaf taken from its whole
+// diagonal, and general matrices as two lower-triangular arrays (GeneralOperands), every tile of
+// which there is twice: its row tasks are two, its diagonal task has both.
 //
 // The column is cut into tiles of 64 x 64 entries, tile (i, j) in tile row i and tile column j.
 // A workgroup takes the next task by number:
@@ -21,9 +24,10 @@
 // elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
 // that.  Between launches the same steps also wait for every workgroup of the launch before and
 // for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
-// against the chain of launches, whole calls: fp64 n = 512 230 -> 164 us, n = 1500 620 -> 371, n = 5555
+// against the chain of launches, whole calls: symmetric fp64 n = 512 230 -> 164 us, n = 1500 620 -> 371, n = 5555
 // 3030 -> 1563, n = 8192 5889 -> 4110, fp32 n = 10000 5948 -> 4191; block columns of 2048 beside a bulk
-// update, n = 32768, 191.1 -> 187.5 ms.  Where a matrix is large: the matrix cores, 4.2 us for the
+// update, n = 32768, 191.1 -> 187.5 ms; pivots from inside a leaf, n = 4096 3.03 -> 1.69 ms; general
+// n = 2900 2.30 -> 1.39, block columns of 1024 at n = 8192 11.3 -> 10.1 (leaves of 20 us there).  Where a matrix is large: the matrix cores, 4.2 us for the
 // 128 x 64 x 64 products of a tile in fp64 (positive-definite form 3.9; 3.4 at their peak).
 // One workgroup of eight wavefronts has a compute unit to itself (its LDS sees to that): two
 // of four wavefronts each slow each other's leaves down, whose single wavefront then waits for
@@ -57,36 +61,38 @@ constexpr int FLOW_STAGES = 4;                        // slabs in LDS: one in us
 constexpr unsigned long long FLOW_PATIENCE = 60ull * 100000000ull;   // of the 100 MHz counter
 
 // Words of device memory a launch needs, zero when it starts: the next task, failure, and per
-// tile row the number of its finished tiles.
+// tile row the number of its finished tiles (of both arrays of a general matrix, one after the other).
 struct FlowSync {
   unsigned ticket;
   unsigned failed;
   unsigned done[1];
 };
-static inline int64_t flow_words(int64_t m) { return 2 + (m + LEAF - 1) / LEAF; }
+enum FlowForm { FLOW_SYM, FLOW_SPD, FLOW_PIVOT, FLOW_GENERAL };
+static inline int64_t flow_words(int64_t m, int arrays) { return 2 + arrays * ((m + LEAF - 1) / LEAF); }
 
 // Tasks before tile column j (j < ntc) of ntr tile rows, ntp = ceil(ntr / 2) pairs of them: in each
-// column c a diagonal task and the pairs from (c + 2) / 2 on.
-__host__ __device__ __forceinline__ int64_t flow_tasks_before(int64_t ntp, int64_t j) {
-  return j <= 0 ? 0 : j * ntp - (j - 1) * (j - 1) / 4;
+// column c a diagonal task and, for each array, the pairs from (c + 2) / 2 on.
+__host__ __device__ __forceinline__ int64_t flow_tasks_before(int64_t ntp, int arrays, int64_t j) {
+  return j <= 0 ? 0 : j + arrays * (j * (ntp - 1) - (j - 1) * (j - 1) / 4);
 }
 // ... and in all of ntc tile columns; the last has the row right below its leaf, too.
-__host__ __device__ __forceinline__ int64_t flow_tasks(int64_t ntr, int64_t ntc) {
+__host__ __device__ __forceinline__ int64_t flow_tasks(int64_t ntr, int64_t ntc, int arrays) {
   const int64_t ntp = (ntr + 1) / 2;
-  return flow_tasks_before(ntp, ntc - 1) + 1 + (ntr > ntc ? ntp - ntc / 2 : 0);
+  return flow_tasks_before(ntp, arrays, ntc - 1) + 1 + (ntr > ntc ? arrays * (ntp - ntc / 2) : 0);
 }
-// Column j of task t and its pair of tile rows, or -1: the diagonal task.
-__host__ __device__ __forceinline__ void flow_task(int ntr, int ntc, int t, int& pair, int& j) {
+// Column j of task t, its array and its pair of tile rows, or -1: the diagonal task.
+__host__ __device__ __forceinline__ void flow_task(int ntr, int ntc, int arrays, int t, int& pair, int& array, int& j) {
   const int64_t ntp = (ntr + 1) / 2;
-  // t >= j ntp - (j - 1)^2 / 4 solved for j, then put right
-  const double a = 2.0 * (double)ntp, q = a * a - 4.0 * (double)t;
+  // t >= flow_tasks_before(j), about (2 ntp j - j^2 / 2) arrays / 2, solved for j, then put right
+  const double a = 2.0 * (double)ntp, q = a * a - 4.0 * (double)t / (double)arrays;
   j = (int)(a - sqrt(q > 0.0 ? q : 0.0));
   if (j > ntc - 1) j = ntc - 1;
   if (j < 0) j = 0;
-  while (j > 0 && flow_tasks_before(ntp, j) > t) --j;
-  while (j + 1 < ntc && flow_tasks_before(ntp, j + 1) <= t) ++j;
-  const int r = (int)(t - flow_tasks_before(ntp, j));
-  pair = r == 0 ? -1 : (j + 1 < ntc ? (j + 2) / 2 : (j + 1) / 2) + r - 1;
+  while (j > 0 && flow_tasks_before(ntp, arrays, j) > t) --j;
+  while (j + 1 < ntc && flow_tasks_before(ntp, arrays, j + 1) <= t) ++j;
+  const int r = (int)(t - flow_tasks_before(ntp, arrays, j));
+  array = r == 0 ? 0 : (r - 1) % arrays;
+  pair = r == 0 ? -1 : (j + 1 < ntc ? (j + 2) / 2 : (j + 1) / 2) + (r - 1) / arrays;
 }
 
 // Four consecutive entries past the caches: `base` is the same in all lanes, `off` bytes from it.
@@ -103,21 +109,36 @@ __device__ __forceinline__ void flow_load4(__amdgpu_buffer_rsrc_t r, unsigned of
     __builtin_memcpy(&v[h * (16 / (int)sizeof(T))], &u, 16);
   }
 }
-template <typename T>
+template <typename T, FlowForm FORM>
 struct FlowShape {
   static constexpr int BK = Mfma<T>::BK;
-  static constexpr int ROWS = FLOW_ROWS * BK, COLS = LEAF * BK;   // the slabs of the two operands
+  static constexpr int ARRAYS = FORM == FLOW_GENERAL ? 2 : 1;
+  static constexpr int ROWS = FLOW_ROWS * BK, COLS = ARRAYS * LEAF * BK;   // the slabs of the two operands
   static constexpr int STAGE = ROWS + COLS + BK;                  // both, and the pivots
   static constexpr int SLABS = FLOW_STAGES * STAGE;
-  // after the sums the same memory holds what a solve needs of its leaf, later the leaf that is
-  // factored, and behind that a solved tile, or 16 solved rows of each wavefront on their way out
-  static constexpr int SOLVED = FACTOR_LDS_ELEMS;
+  // after the sums the same memory holds what a solve needs of its leaf (of both its halves, one after
+  // the other), later the leaf that is factored, and behind that the solved tiles
+  static constexpr int LEAF_ELEMS =
+      FORM == FLOW_GENERAL ? LU_LDS_ELEMS : (FORM == FLOW_PIVOT ? PIVOT_LDS_ELEMS : FACTOR_LDS_ELEMS);
+  static constexpr int TILES = ARRAYS * LEAF * LEAF;
+  // 16 rows of each wavefront on their way out or into another order of columns: behind what a
+  // solve needs in a row task; in a diagonal task behind the solved tile (general matrices: in the
+  // place of the leaf, with barriers in between)
   static constexpr int ROW_STRIDE = LEAF + 16 / (int)sizeof(T);
   static constexpr int OUT = SUB * ROW_STRIDE;
-  static constexpr int LATER = SOLVED + FLOW_WAVES * OUT;
-  static_assert(LEAF * LEAF + 4 * OUT <= FLOW_WAVES * OUT, "places in LDS");
-  static constexpr int LDS_ELEMS = SLABS > LATER ? SLABS : LATER;
-  static_assert(SOLVED >= LeafOperands<T>::ELEMS && SOLVED * sizeof(T) % 16 == 0, "places in LDS");
+  static constexpr int BEFORE = FORM == FLOW_GENERAL && FLOW_WAVES * OUT > LEAF_ELEMS ? FLOW_WAVES * OUT : LEAF_ELEMS;
+  static constexpr int SOLVED = (BEFORE + 3) / 4 * 4;
+  static constexpr int ROW_OUT = LeafOperands<T>::ELEMS;
+  static constexpr int DIAG_OUT = FORM == FLOW_GENERAL ? 0 : SOLVED + TILES;
+  static constexpr int LATER_ROW = ROW_OUT + FLOW_WAVES * OUT;
+  static constexpr int LATER_DIAG = FORM == FLOW_GENERAL ? SOLVED + TILES : DIAG_OUT + 4 * OUT;
+  static constexpr int LATER = LATER_ROW > LATER_DIAG ? LATER_ROW : LATER_DIAG;
+  // (so much that a compute unit holds one workgroup)
+  static constexpr int ALONE = 96 * 1024 / (int)sizeof(T);
+  static constexpr int MOST = SLABS > LATER ? SLABS : LATER;
+  static constexpr int LDS_ELEMS = MOST > ALONE ? MOST : ALONE;
+  static_assert(SOLVED >= ARRAYS * LeafOperands<T>::ELEMS && LDS_ELEMS * sizeof(T) + 64 <= 160 * 1024,
+                "places in LDS");
 };
 
 // What all tasks of a launch share.
@@ -131,6 +152,8 @@ struct FlowArgs {
   T* W;                 // its pivot-scaled copy (rows from wskip on), or null
   int64_t wld;
   int wskip;
+  int64_t qoff;         // general matrices: elements to the array of the transposed upper triangle
+  int* perm;            // with pivoting: the rows of each leaf in the order taken
   long long pivot0;
   DevFlags* flags;
   FlowSync* sync;
@@ -138,7 +161,7 @@ struct FlowArgs {
   bool lines;           // rows start on 128-byte lines
 };
 
-// A wavefront waits until the counter of every lane's tile row (`row` < 0: none) has reached `need`;
+// A wavefront waits until the counter of every lane (`row` < 0: none) has reached `need`;
 // the smallest of them, or -1 if the launch has failed.  A wait that gives up is reported as pivot
 // 0, kind 8.
 template <typename T>
@@ -150,7 +173,7 @@ __device__ __forceinline__ int flow_wait(const FlowArgs<T>& a, const int row, co
     if (__ballot(v < need) == 0ull) {
       int least = __builtin_amdgcn_readlane(v, 0);
 #pragma unroll
-      for (int q = 1; q < 3; ++q) {
+      for (int q = 1; q < 4; ++q) {
         const int o = __builtin_amdgcn_readlane(v, q);
         least = o < least ? o : least;
       }
@@ -172,13 +195,13 @@ __device__ __forceinline__ int flow_wait(const FlowArgs<T>& a, const int row, co
     __builtin_amdgcn_s_sleep(1);
   }
 }
-// The same by the first wavefront for all threads of the workgroup, rows r0, r1, r2.
+// The same by the first wavefront for all threads of the workgroup, counters r0 to r3.
 template <typename T>
-__device__ __forceinline__ int flow_wait_all(const FlowArgs<T>& a, const int r0, const int r1, const int r2, const int need,
-                                             int* shared) {
+__device__ __forceinline__ int flow_wait_all(const FlowArgs<T>& a, const int r0, const int r1, const int r2, const int r3,
+                                             const int need, int* shared) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
-    const int v = flow_wait(a, lane == 0 ? r0 : (lane == 1 ? r1 : (lane == 2 ? r2 : -1)), need);
+    const int v = flow_wait(a, lane == 0 ? r0 : (lane == 1 ? r1 : (lane == 2 ? r2 : (lane == 3 ? r3 : -1))), need);
     if (lane == 0) *shared = v;
   }
   __syncthreads();
@@ -189,38 +212,65 @@ __device__ __forceinline__ void flow_publish(const FlowArgs<T>& a, const int row
   __hip_atomic_store(&a.sync->done[row], (unsigned)count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The parts of tile (j, j) in a diagonal task: wavefront 0 has sub-block (0, 0), which the
-// elimination starts with, wavefronts 5 to 7 three each of the others (4, on the SIMD of
-// wavefront 0, none).
+// The sub-blocks of tile (j, j), on and below its diagonal, of each wavefront of a diagonal task.  One
+// array: wavefront 0 has (0, 0), which the elimination starts with, wavefronts 5 to 7 three each of
+// the others (4, on the SIMD of wavefront 0, none).  Two arrays: wavefronts 0 to 3 share those of
+// the first, the others those of the second.
 struct FlowUnits {
   int count;
   int row[3], col[3];
-  __device__ __forceinline__ explicit FlowUnits(const int wave) {
-    count = wave == 0 ? 1 : (wave >= 5 ? 3 : 0);
-    row[0] = wave == 0 ? 0 : (wave == 5 ? 1 : (wave == 6 ? 2 : 3));
-    col[0] = wave == 0 ? 0 : (wave == 5 ? 0 : 1);
-    row[1] = wave == 5 ? 1 : (wave == 6 ? 2 : 3);
-    col[1] = wave == 5 ? 1 : 2;
-    row[2] = wave == 5 ? 2 : 3;
-    col[2] = wave == 7 ? 3 : 0;
+  __device__ __forceinline__ FlowUnits(const int wave, const int arrays) {
+    if (arrays == 1) {
+      count = wave == 0 ? 1 : (wave >= 5 ? 3 : 0);
+      row[0] = wave == 0 ? 0 : (wave == 5 ? 1 : (wave == 6 ? 2 : 3));
+      col[0] = wave == 0 ? 0 : (wave == 5 ? 0 : 1);
+      row[1] = wave == 5 ? 1 : (wave == 6 ? 2 : 3);
+      col[1] = wave == 5 ? 1 : 2;
+      row[2] = wave == 5 ? 2 : 3;
+      col[2] = wave == 7 ? 3 : 0;
+    } else {
+      const int w = wave & 3;
+      count = w >= 2 ? 3 : 2;
+      row[0] = w;
+      col[0] = 0;
+      row[1] = w == 0 ? 3 : w;
+      col[1] = w == 0 ? 3 : 1;
+      row[2] = w;
+      col[2] = 2;
+    }
   }
 };
 
+// What a task reduces its tiles by: operand rows of two tile rows (of P or, general matrices, of the
+// array behind it), in the order in which a slab holds them, and the counters that say how far
+// they are.
+template <typename T>
+struct FlowOperands {
+  const T* row[2];      // tile rows of the row operand; row[1] is not read by a diagonal task of one array
+  const T* col[2];      // and of the column operand; the second one in a diagonal task of two arrays only
+  int left[2];          // rows of the matrix from row[v] on
+  int counter[4];       // -1: none
+};
+
 // The sums of a task over the tiles k < nk left of it, slab by slab through LDS.
-// x[t] += L_col D L_row^T (transposed: register r of a lane of row g of lanes is row l16 of this
-// wavefront's 16 and column 16 t + 4 g + r, as in leaf_solve_body), for the 16 rows that start at
-// 16 wave of the rows row0, row0 + 1, ... (rows, at most FLOW_ROWS; `mine`: this wavefront has some).
-// DIAG: rows are the 64 of tile row `rt0`; wavefronts 0 to 3 collect x, and s[u] += L_row D L_row^T
-// of the FlowUnits.  False if the launch has failed.
-template <typename T, bool SCALED, bool DIAG>
-__device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int rt0, const int rt1, const int col,
-                                                const int nk, const bool mine, typename Mfma<T>::acc_t (&x)[NSUB],
-                                                typename Mfma<T>::acc_t (&s)[3], T* __restrict__ lds, int* shared) {
+// Row task (KIND 0): x[t] += L_col D L_row^T (transposed: register r of a lane of row g of lanes is row
+// l16 of this wavefront's 16 and column 16 t + 4 g + r, as in leaf_solve_body), for 16 of the 128 rows
+// (`mine`: this wavefront has some).
+// Diagonal task (KIND 1): the same by wavefronts 0 to 3 for the 64 rows of row[0], and s[u] += L_row D
+// L_row^T of the FlowUnits.
+// Diagonal task of a general matrix (KIND 2): the 64 rows of row[0] by col[0] and those of row[1] by
+// col[1], and s[u] += row[0] D row[1]^T (wavefronts 0 to 3) and row[1] D row[0]^T (the others).
+// False if the launch has failed.
+template <typename T, FlowForm FORM, int KIND>
+__device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const FlowOperands<T>& of, const int nk, const bool mine,
+                                                typename Mfma<T>::acc_t (&x)[NSUB], typename Mfma<T>::acc_t (&s)[3],
+                                                T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using vec_t = typename X::vec_t;
-  using Sh = FlowShape<T>;
+  using Sh = FlowShape<T, FORM>;
+  constexpr bool SCALED = FORM == FLOW_SPD;
   constexpr int BK = Sh::BK, VEC = X::VEC, KS = BK / 4, PER_TILE = LEAF / BK;
-  constexpr int RV = DIAG ? 1 : 2;                     // a wavefront's loads of row operands per slab
+  constexpr int RV = KIND == 1 ? 1 : 2, CV = KIND == 2 ? 2 : 1;   // a wavefront's loads of each operand per slab
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
@@ -229,30 +279,28 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
   // of a row in the order chunk ^ ((row >> 1) & 7).  Load v brings rows 8 wave .. + 7 of tile row v.
   const int rt = 8 * wave + (lane >> 3);
   const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
-  const char* base = reinterpret_cast<const char*>(a.P);
-  const char* Rbase[2];
-  unsigned roff[2];
+  unsigned roff[2], coff[2];
 #pragma unroll
   for (int v = 0; v < RV; ++v) {
-    const int64_t first = (int64_t)(v == 0 ? rt0 : rt1) * LEAF;
-    Rbase[v] = base + first * a.ld * (int64_t)sizeof(T);
-    const int rr = first + rt < a.m ? rt : (int)(a.m - 1 - first);
+    const int rr = rt < of.left[v] ? rt : of.left[v] - 1;
     roff[v] = (unsigned)(((int64_t)rr * a.ld + chunk * VEC) * (int64_t)sizeof(T));
   }
-  const char* Cbase = base + (int64_t)col * LEAF * a.ld * (int64_t)sizeof(T);
-  const unsigned coff = (unsigned)(((int64_t)rt * a.ld + chunk * VEC) * (int64_t)sizeof(T));
+#pragma unroll
+  for (int v = 0; v < CV; ++v) coff[v] = (unsigned)(((int64_t)rt * a.ld + chunk * VEC) * (int64_t)sizeof(T));
   auto pinned = [](unsigned o) { asm volatile("" : "+v"(o)); return o; };
-  constexpr int LOADS = RV + 1 + (SCALED ? 0 : 1);     // a wavefront's, per slab
+  constexpr int LOADS = RV + CV + (SCALED ? 0 : 1);    // a wavefront's, per slab
   auto request = [&](const int slab, const int stage, auto scope) {
     constexpr int SCOPE = decltype(scope)::value;
     T* to = lds + stage * Sh::STAGE;
     const unsigned kb = __builtin_amdgcn_readfirstlane((unsigned)slab * 128u);
 #pragma unroll
     for (int v = 0; v < RV; ++v)
-      __builtin_amdgcn_global_load_lds((upd_global_ptr)(Rbase[v] + kb + pinned(roff[v])),
+      __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(of.row[v]) + kb + pinned(roff[v])),
                                        (upd_lds_ptr)(to + (v * LEAF + wave * 8) * BK), 16, 0, SCOPE);
-    __builtin_amdgcn_global_load_lds((upd_global_ptr)(Cbase + kb + pinned(coff)),
-                                     (upd_lds_ptr)(to + Sh::ROWS + wave * 8 * BK), 16, 0, SCOPE);
+#pragma unroll
+    for (int v = 0; v < CV; ++v)
+      __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(of.col[v]) + kb + pinned(coff[v])),
+                                       (upd_lds_ptr)(to + Sh::ROWS + (v * LEAF + wave * 8) * BK), 16, 0, SCOPE);
     if constexpr (!SCALED) {
       // the slab's pivots: 128 bytes, every wavefront the same
       if (lane < 32)
@@ -273,10 +321,11 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
 #pragma unroll
     for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
   };
-  const FlowUnits units(wave);
+  const FlowUnits units(wave, KIND == 2 ? 2 : 1);
+  const int half = KIND == 2 ? (wave >> 2) * LEAF * BK : 0;       // which of the column operands
   // The first operands of a slab, fetched while the slab before is multiplied.
   struct First { T row[KS], col[KS], d[KS]; } next;
-  const bool sums = mine && (!DIAG || wave < 4);
+  const bool sums = mine && (KIND != 1 || wave < 4);
   auto scale = [&](T (&f)[KS], const T (&d)[KS]) {
     if constexpr (!SCALED) {
 #pragma unroll
@@ -295,7 +344,7 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
     }
     if (sums) {
       fetch(next.row, rs + (wave * SUB + l16) * BK, own_sw);
-      fetch(next.col, rs + Sh::ROWS + pc * BK, pc_sw);
+      fetch(next.col, rs + Sh::ROWS + half + pc * BK, pc_sw);
     }
   };
   // Operands are waited for in front of the fetch of the next ones and not, as the compiler
@@ -317,9 +366,9 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
   // (`behind`: what is to go out while the first products run)
   auto multiply = [&](const int stage, const int following, auto behind) {
     const T* rs = lds + stage * Sh::STAGE;
-    const T* cs = rs + Sh::ROWS;
+    const T* cs = rs + Sh::ROWS + half;
     T nd[KS];
-    if constexpr (DIAG && !SCALED) {
+    if constexpr (KIND != 0 && !SCALED) {
 #pragma unroll
       for (int e = 0; e < KS; ++e) nd[e] = next.d[e];
     }
@@ -335,7 +384,7 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
         if (t > 0) arrived(fc[t]);
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < NSUB) fetch(fc[t + 1], cs + ((t + 1) * SUB + pc) * BK, pc_sw);
-        else if (!DIAG) prefetch(following);           // (behind the last slab: whatever is there)
+        else if (KIND == 0) prefetch(following);          // (behind the last slab: whatever is there)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < KS; ++e) x[t] = X::mfma(fc[t][e], fr[e], x[t]);
@@ -345,7 +394,7 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
     } else {
       behind();
     }
-    if constexpr (DIAG) {
+    if constexpr (KIND == 1) {
 #pragma unroll
       for (int u = 0; u < 3; ++u)
         if (u < units.count) {
@@ -358,12 +407,27 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
         }
       prefetch(following);
     }
+    if constexpr (KIND == 2) {
+      const int mine0 = (wave >> 2) * LEAF, other0 = LEAF - mine0;
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < units.count) {
+          T fr[KS], fc[KS];
+          fetch(fr, rs + (mine0 + units.row[u] * SUB + l16) * BK, own_sw);
+          fetch(fc, rs + (other0 + units.col[u] * SUB + l16) * BK, own_sw);
+          scale(fr, nd);
+#pragma unroll
+          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e], fc[e], s[u]);
+        }
+      prefetch(following);
+    }
     ready();
   };
   // All but the newest slab's loads (`late`; or really all) of this wavefront have landed, and behind
   // the barrier those of all.
   auto landed = [](const bool late) {
     if (!late) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    else if constexpr (LOADS == 5) asm volatile("s_waitcnt vmcnt(5) lgkmcnt(0)" ::: "memory");
     else if constexpr (LOADS == 4) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
     else if constexpr (LOADS == 3) asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");
@@ -373,7 +437,7 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const int 
 
   int k = 0;
   while (k < nk) {
-    int upto = flow_wait_all(a, rt0, rt1, col, k + 1, shared);
+    int upto = flow_wait_all(a, of.counter[0], of.counter[1], of.counter[2], of.counter[3], k + 1, shared);
     if (upto < 0) return false;
     if (upto > nk) upto = nk;
     const int s0 = k * PER_TILE, s1 = upto * PER_TILE;
@@ -458,15 +522,15 @@ __device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, cons
   }
 }
 
-// 16 solved, divided rows from r16 on (this lane's share of them, columns of tile column col) to
-// memory and, scaled by the pivots, to the copy.  The first through LDS (`out`, this wavefront's), so
+// 16 solved, divided rows of `array` from r16 on (this lane's share of them, columns of tile column col)
+// to memory and, scaled by the pivots, to the copy.  The first through LDS (`out`, this wavefront's), so
 // that a store writes whole rows: in 16-byte pieces as the lanes hold them a row task's 64 KB
 // took 2.9 us to arrive.
 template <typename T>
-__device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, const int64_t r16, const int col,
+__device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, T* array, const int64_t r16, const int col,
                                                 const T (&v)[NSUB][4], T* __restrict__ out, const int lane) {
   using vec_t = typename Mfma<T>::vec_t;
-  constexpr int VEC = Mfma<T>::VEC, STRIDE = FlowShape<T>::ROW_STRIDE;
+  constexpr int VEC = Mfma<T>::VEC, STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
   constexpr int PIECES = LEAF / VEC, ROWS = 64 / PIECES;         // 16-byte pieces of a row, rows of a store
   const int l16 = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -478,7 +542,7 @@ __device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, const int6
       for (int e = 0; e < VEC; ++e) o[e] = v[b][VEC * h + e];
       *reinterpret_cast<vec_t*>(out + l16 * STRIDE + b * SUB + 4 * g + VEC * h) = o;
     }
-  const __amdgpu_buffer_rsrc_t to = flow_rsrc(a.P + r16 * a.ld + (int64_t)col * LEAF);
+  const __amdgpu_buffer_rsrc_t to = flow_rsrc(array + r16 * a.ld + (int64_t)col * LEAF);
   const int r0 = lane / PIECES, c = (lane % PIECES) * VEC;
 #pragma unroll
   for (int q = 0; q < SUB / ROWS; ++q) {
@@ -501,12 +565,12 @@ __device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, const int6
   }
 }
 
-// 16 rows of tile column col, negated, as flow_accumulate collects them.
+// 16 rows of `array` in tile column col, negated, as flow_accumulate collects them.
 template <typename T>
-__device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const int64_t r16, const int col,
+__device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const T* array, const int64_t r16, const int col,
                                                typename Mfma<T>::acc_t (&x)[NSUB], const int lane) {
   const int l16 = lane & 15, g = lane >> 4;
-  const __amdgpu_buffer_rsrc_t from = flow_rsrc(a.P + r16 * a.ld + (int64_t)col * LEAF);
+  const __amdgpu_buffer_rsrc_t from = flow_rsrc(array + r16 * a.ld + (int64_t)col * LEAF);
   const unsigned off = (unsigned)(((int64_t)l16 * a.ld + 4 * g) * (int64_t)sizeof(T));
   T v[NSUB][4];
 #pragma unroll
@@ -553,10 +617,31 @@ __device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename 
   }
 }
 
-template <typename T, bool SCALED>
-__device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pair, const int j, T* __restrict__ lds,
-                                              int* shared) {
+// The columns of this wavefront's 16 rows into the order in which the leaf's rows were taken, through
+// `out` (this wavefront's).
+template <typename T>
+__device__ __forceinline__ void flow_gather(const int* __restrict__ perm, const long long first,
+                                            typename Mfma<T>::acc_t (&x)[NSUB], T* __restrict__ out, const int lane) {
+  constexpr int STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
+  const int l16 = lane & 15, g = lane >> 4;
+  int from[NSUB][4];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b) load4(perm + b * SUB + 4 * g, from[b]);
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[l16 * STRIDE + b * SUB + 4 * g + e] = x[b][e];
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[b][e] = out[l16 * STRIDE + (from[b][e] - (int)first)];
+}
+
+template <typename T, FlowForm FORM>
+__device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pair, const int array, const int j,
+                                              T* __restrict__ lds, int* shared) {
   using acc_t = typename Mfma<T>::acc_t;
+  using Sh = FlowShape<T, FORM>;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // of the pair's two tile rows those that this task has; the other one, whose entries left of
@@ -567,16 +652,34 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pa
   const int rt0 = low ? 2 * pair : 2 * pair + 1, rt1 = high ? 2 * pair + 1 : 2 * pair;
   const int64_t r16 = (int64_t)pair * FLOW_ROWS + wave * SUB;
   const bool mine = (wave < 4 ? low : high) && r16 < a.m;
+  // general matrices: the rows of one array by those of the other, and solved against the leaf there
+  T* const rows = a.P + (FORM == FLOW_GENERAL && array != 0 ? a.qoff : 0);
+  T* const cols = a.P + (FORM == FLOW_GENERAL && array == 0 ? a.qoff : 0);
+  const int mine0 = FORM == FLOW_GENERAL ? array * a.ntr : 0, other0 = FORM == FLOW_GENERAL ? (1 - array) * a.ntr : 0;
+  FlowOperands<T> of;
+  of.row[0] = rows + (int64_t)rt0 * LEAF * a.ld;
+  of.row[1] = rows + (int64_t)rt1 * LEAF * a.ld;
+  of.left[0] = a.m - rt0 * LEAF;
+  of.left[1] = a.m - rt1 * LEAF;
+  of.col[0] = of.col[1] = cols + (int64_t)j * LEAF * a.ld;
+  of.counter[0] = mine0 + rt0;
+  of.counter[1] = mine0 + rt1;
+  of.counter[2] = other0 + j;
+  of.counter[3] = -1;
   acc_t x[NSUB], none[3];
 #pragma unroll
   for (int b = 0; b < NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
-  if (mine) flow_load_rows(a, r16, j, x, lane);
-  if (!flow_accumulate<T, SCALED, false>(a, rt0, rt1, j, j, mine, x, none, lds, shared)) return;
-  if (flow_wait_all(a, j, -1, -1, j + 1, shared) < 0) return;
+  if (mine) flow_load_rows(a, (const T*)rows, r16, j, x, lane);
+  if (!flow_accumulate<T, FORM, 0>(a, of, j, mine, x, none, lds, shared)) return;
+  if (flow_wait_all(a, j, -1, -1, -1, j + 1, shared) < 0) return;
   const LeafOperands<T> ops{lds};
-  flow_stage_leaf(ops, (const T*)(a.P + (int64_t)j * LEAF * (a.ld + 1)), a.ld, wave, lane);
+  flow_stage_leaf(ops, (const T*)(cols + (int64_t)j * LEAF * (a.ld + 1)), a.ld, wave, lane);
   T rinv[NSUB][4];
   load_row((const T*)(a.dinv + (int64_t)j * LEAF), lane >> 4, LEAF, rinv);
+  T* const out = lds + Sh::ROW_OUT + wave * Sh::OUT;
+  if (FORM == FLOW_PIVOT || (FORM == FLOW_GENERAL && array != 0)) {
+    if (mine) flow_gather((const int*)(a.perm + (int64_t)j * LEAF), a.pivot0 + (long long)j * LEAF, x, out, lane);
+  }
   __syncthreads();
   if (mine) {
     flow_solve(ops, x, lane);
@@ -585,29 +688,77 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pa
     for (int b = 0; b < NSUB; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[b][e] = x[b][e] * rinv[b][e];
-    flow_store_rows(a, r16, j, v, lds + FlowShape<T>::SOLVED + wave * FlowShape<T>::OUT, lane);
+    flow_store_rows(a, rows, r16, j, v, out, lane);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    flow_publish(a, rt0, j + 1);
-    if (rt1 != rt0) flow_publish(a, rt1, j + 1);
+    flow_publish(a, mine0 + rt0, j + 1);
+    if (rt1 != rt0) flow_publish(a, mine0 + rt1, j + 1);
   }
 }
 
-template <typename T, bool SCALED>
+// Place in LDS of entries [VEC h, VEC h + VEC) of lane l's four of sub-block (q, b) of a solved tile.
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::vec_t* flow_solved_at(T* solved, const int q, const int b, const int h,
+                                                                   const int l) {
+  constexpr int VEC = Mfma<T>::VEC;
+  return reinterpret_cast<typename Mfma<T>::vec_t*>(solved + (((q * NSUB + b) * (4 / VEC) + h) * 64 + l) * VEC);
+}
+template <typename T>
+__device__ __forceinline__ void flow_solved_fetch(T* solved, const int q, const int b, const int l, T (&f)[4]) {
+  constexpr int VEC = Mfma<T>::VEC;
+#pragma unroll
+  for (int h = 0; h < 4 / VEC; ++h) {
+    const typename Mfma<T>::vec_t o = *flow_solved_at(solved, q, b, h, l);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) f[VEC * h + e] = o[e];
+  }
+}
+// This wavefront's solved rows, divided (v), to the others.
+template <typename T>
+__device__ __forceinline__ void flow_solved_put(T* solved, const int q, const typename Mfma<T>::acc_t (&x)[NSUB],
+                                                const T (&rinv)[NSUB][4], T (&v)[NSUB][4], const int lane) {
+  constexpr int VEC = Mfma<T>::VEC;
+#pragma unroll
+  for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+    for (int h = 0; h < 4 / VEC; ++h) {
+      typename Mfma<T>::vec_t o;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) o[e] = v[b][VEC * h + e] = x[b][VEC * h + e] * rinv[b][VEC * h + e];
+      *flow_solved_at(solved, q, b, h, lane) = o;
+    }
+}
+// Operands of slab p (KS consecutive columns of each BK to a row of lanes) from 16 solved rows.
+template <typename T, int KS>
+__device__ __forceinline__ void flow_solved_slab(T* solved, const int q, const int p, const int l16, const int g, T (&f)[KS]) {
+#pragma unroll
+  for (int h = 0; h < KS / 4; ++h) {
+    // columns c .. c + 3 are with sub-block c / 16 and row of lanes c / 4 % 4
+    const int c = p * 4 * KS + g * KS + 4 * h;
+    T v[4];
+    flow_solved_fetch(solved, q, c / SUB, (c / 4 % 4) * 16 + l16, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[4 * h + e] = v[e];
+  }
+}
+
+// The symmetric forms.
+template <typename T, FlowForm FORM>
 __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T>& a, const int j, T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
-  using vec_t = typename X::vec_t;
-  constexpr int VEC = X::VEC;
+  using Sh = FlowShape<T, FORM>;
+  constexpr bool SCALED = FORM == FLOW_SPD, PIVOT = FORM == FLOW_PIVOT;
+  constexpr int BK = X::BK, KS = BK / 4;
   __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int64_t j0 = (int64_t)j * LEAF;
   const int wl = a.w - j0 < LEAF ? (int)(a.w - j0) : LEAF;       // the leaf's order
-  const FlowUnits units(wave);
+  const FlowUnits units(wave, 1);
   acc_t x[NSUB], s[3];
   // entries of the leaf on and below its diagonal
   T* const leaf = a.P + j0 * (a.ld + 1);
@@ -621,121 +772,227 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T>& a, const i
                     : T(0);
     }
   if (j > 0) {
-    T* const solved = lds + FlowShape<T>::SOLVED;
-    // place of entries [VEC h, VEC h + VEC) of lane l's four of sub-block (q, b) of the solved tile
-    auto at = [&](const int q, const int b, const int h, const int l) {
-      return reinterpret_cast<vec_t*>(solved + (((q * NSUB + b) * (4 / VEC) + h) * 64 + l) * VEC);
-    };
-    auto fetch = [&](const int q, const int b, const int l, T (&f)[4]) {
-#pragma unroll
-      for (int h = 0; h < 4 / VEC; ++h) {
-        const vec_t o = *at(q, b, h, l);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) f[VEC * h + e] = o[e];
-      }
-    };
+    T* const solved = lds + Sh::SOLVED;
+    T* const out = lds + Sh::DIAG_OUT + (wave & 3) * Sh::OUT;
 #pragma unroll
     for (int b = 0; b < NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
-    if (wave < 4) flow_load_rows(a, j0 + wave * SUB, j - 1, x, lane);
-    if (!flow_accumulate<T, SCALED, true>(a, j, j, j - 1, j - 1, true, x, s, lds, shared)) return;
-    if (flow_wait_all(a, j - 1, -1, -1, j, shared) < 0) return;
+    if (wave < 4) flow_load_rows(a, (const T*)a.P, j0 + wave * SUB, j - 1, x, lane);
+    FlowOperands<T> of;
+    of.row[0] = of.row[1] = a.P + j0 * a.ld;
+    of.left[0] = of.left[1] = (int)(a.m - j0);
+    of.col[0] = of.col[1] = a.P + (j0 - LEAF) * a.ld;
+    of.counter[0] = j;
+    of.counter[1] = j - 1;
+    of.counter[2] = of.counter[3] = -1;
+    if (!flow_accumulate<T, FORM, 1>(a, of, j - 1, true, x, s, lds, shared)) return;
+    if (flow_wait_all(a, j - 1, -1, -1, -1, j, shared) < 0) return;
     const LeafOperands<T> ops{lds};
     flow_stage_leaf(ops, (const T*)(a.P + (j0 - LEAF) * (a.ld + 1)), a.ld, wave, lane);
     T rinv[NSUB][4];
     if (wave < 4) load_row((const T*)(a.dinv + j0 - LEAF), g, LEAF, rinv);
-    constexpr int BK = X::BK, KS = BK / 4;
     T d[NSUB][4];                    // the pivots in the order of the product below
     if constexpr (!SCALED) {
 #pragma unroll
       for (int q = 0; q < NSUB; ++q)
         load4((const T*)(a.dvec + j0 - LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
     }
+    if (PIVOT && wave < 4) flow_gather((const int*)(a.perm + j0 - LEAF), a.pivot0 + j0 - LEAF, x, out, lane);
     __syncthreads();
     T v[NSUB][4];
     if (wave < 4) {
       flow_solve(ops, x, lane);
       // the solved rows go from the wavefronts that hold them to all through LDS
-#pragma unroll
-      for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-        for (int h = 0; h < 4 / VEC; ++h) {
-          vec_t o;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) o[e] = v[b][VEC * h + e] = x[b][VEC * h + e] * rinv[b][VEC * h + e];
-          *at(wave, b, h, lane) = o;
-        }
+      flow_solved_put(solved, wave, x, rinv, v, lane);
     }
     __syncthreads();
     // off the chain: the solved tile to memory (wavefront 0's rows by wavefront 4)
     if (wave >= 1 && wave <= 4) {
       if (wave == 4) {
 #pragma unroll
-        for (int b = 0; b < NSUB; ++b) fetch(0, b, lane, v[b]);
+        for (int b = 0; b < NSUB; ++b) flow_solved_fetch(solved, 0, b, lane, v[b]);
       }
-      flow_store_rows(a, j0 + (wave & 3) * SUB, j - 1, v, solved + LEAF * LEAF + (wave & 3) * FlowShape<T>::OUT, lane);
+      flow_store_rows(a, a.P, j0 + (wave & 3) * SUB, j - 1, v, out, lane);
     }
-    // its product with itself, the columns in the order of a slab: KS consecutive ones of each
-    // BK to a row of lanes
+    // its product with itself, the columns in the order of a slab
 #pragma unroll
     for (int p = 0; p < LEAF / BK; ++p) {
 #pragma unroll
       for (int u = 0; u < 3; ++u)
         if (u < units.count) {
           T fr[KS], fc[KS];
+          flow_solved_slab<T, KS>(solved, units.row[u], p, l16, g, fr);
+          flow_solved_slab<T, KS>(solved, units.col[u], p, l16, g, fc);
 #pragma unroll
-          for (int h = 0; h < KS / 4; ++h) {
-            // columns c .. c + 3 are with sub-block c / 16 and row of lanes c / 4 % 4
-            const int c = p * BK + g * KS + 4 * h;
-            T vr[4], vc[4];
-            fetch(units.row[u], c / SUB, (c / 4 % 4) * 16 + l16, vr);
-            fetch(units.col[u], c / SUB, (c / 4 % 4) * 16 + l16, vc);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              fr[4 * h + e] = SCALED ? vr[e] : vr[e] * d[p * (KS / 4) + h][e];
-              fc[4 * h + e] = vc[e];
-            }
-          }
-#pragma unroll
-          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e], fc[e], s[u]);
+          for (int e = 0; e < KS; ++e)
+            s[u] = X::mfma(SCALED ? fr[e] : fr[e] * d[p * (KS / 4) + e / 4][e % 4], fc[e], s[u]);
         }
     }
   }
-  // wavefront 0 goes on with its sub-block at once; the others' are there, and tile (j, j - 1) is
-  // in memory, when it is through with that (the first barrier of leaf_factor_body)
+  if constexpr (PIVOT) {
+    // the whole leaf has to be there before the first pivot is looked for
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 64) flow_publish(a, j, j);                        // tile (j, j - 1)
 #pragma unroll
-  for (int u = 0; u < 3; ++u)
-    if (u < units.count) {
+    for (int u = 0; u < 3; ++u)
+      if (u < units.count) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        leaf_tile_put<T>(lds, units.row[u] * SUB + X::acc_row(lane, r), units.col[u] * SUB + l16, wl, -s[u][r]);
-    }
-  if (wave != 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  leaf_factor_body<T, true, true>(leaf, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, a.pivot0 + j0, a.flags, lds,
-                                  SCALED ? 1 : 0, &a.sync->done[j], (unsigned)j);
+        for (int r = 0; r < 4; ++r) {
+          const int row = units.row[u] * SUB + X::acc_row(lane, r), col = units.col[u] * SUB + l16;
+          if (col <= row) {
+            leaf_tile_put<T>(lds, row, col, wl, -s[u][r]);
+            leaf_tile_put<T>(lds, col, row, wl, -s[u][r]);
+          }
+        }
+      }
+    leaf_factor_pivoted_body<T, true, true>(leaf, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, a.perm + j0, a.pivot0 + j0,
+                                            a.flags, lds);
+  } else {
+    // wavefront 0 goes on with its sub-block at once; the others' are there, and tile (j, j - 1) is
+    // in memory, when it is through with that (the first barrier of leaf_factor_body)
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (u < units.count) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          leaf_tile_put<T>(lds, units.row[u] * SUB + X::acc_row(lane, r), units.col[u] * SUB + l16, wl, -s[u][r]);
+      }
+    if (wave != 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    leaf_factor_body<T, true, true>(leaf, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, a.pivot0 + j0, a.flags, lds,
+                                    SCALED ? 1 : 0, &a.sync->done[j], (unsigned)j);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) flow_publish(a, j, j + 1);
 }
 
-// SCALED: the positive-definite form (see leaf_factor_body): rows of the Cholesky factor, whose
-// products need no pivots.
-template <typename T, bool SCALED>
+// General matrices: P M = L D U of the leaf, and the tiles left of it in both arrays, L's by
+// wavefronts 0 to 3, U^T's by the others.
+template <typename T>
+__device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, const int j, T* __restrict__ lds, int* shared) {
+  using X = Mfma<T>;
+  using acc_t = typename X::acc_t;
+  using Sh = FlowShape<T, FLOW_GENERAL>;
+  constexpr int BK = X::BK, KS = BK / 4;
+  __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int64_t j0 = (int64_t)j * LEAF;
+  const int wl = a.w - j0 < LEAF ? (int)(a.w - j0) : LEAF;       // the leaf's order
+  T* const Q = a.P + a.qoff;
+  acc_t x[NSUB], s[3];
+  T* const leaf = a.P + j0 * (a.ld + 1);
+  const FlowUnits units(wave, 2);
+  const int low = wave < 4 ? 0 : 1;                    // entries on the diagonal are the first array's
+  {
+    const T* D = leaf + (wave < 4 ? 0 : a.qoff);
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = units.row[u] * SUB + X::acc_row(lane, r), col = units.col[u] * SUB + l16;
+        s[u][r] = u < units.count && row < wl && col + low <= row
+                      ? -__hip_atomic_load(D + (int64_t)row * a.ld + col, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                      : T(0);
+      }
+  }
+  if (j > 0) {
+    T* const solved = lds + Sh::SOLVED;
+    T* const out = lds + Sh::DIAG_OUT + wave * Sh::OUT;
+    T* const rows = wave < 4 ? a.P : Q;
+    const int64_t r16 = j0 + (wave & 3) * SUB;
+    flow_load_rows(a, (const T*)rows, r16, j - 1, x, lane);
+    FlowOperands<T> of;
+    of.row[0] = a.P + j0 * a.ld;
+    of.row[1] = Q + j0 * a.ld;
+    of.left[0] = of.left[1] = (int)(a.m - j0);
+    of.col[0] = Q + (j0 - LEAF) * a.ld;
+    of.col[1] = a.P + (j0 - LEAF) * a.ld;
+    of.counter[0] = j;
+    of.counter[1] = a.ntr + j;
+    of.counter[2] = j - 1;
+    of.counter[3] = a.ntr + j - 1;
+    if (!flow_accumulate<T, FLOW_GENERAL, 2>(a, of, j - 1, true, x, s, lds, shared)) return;
+    if (flow_wait_all(a, j - 1, -1, -1, -1, j, shared) < 0) return;
+    const LeafOperands<T> opsL{lds}, opsU{lds + LeafOperands<T>::ELEMS};
+    const T* const before = a.P + (j0 - LEAF) * (a.ld + 1);
+    flow_stage_leaf(opsL, before, a.ld, wave, lane);
+    flow_stage_leaf(opsU, before + a.qoff, a.ld, wave, lane);
+    T rinv[NSUB][4], d[NSUB][4];
+    load_row((const T*)(a.dinv + j0 - LEAF), g, LEAF, rinv);
+#pragma unroll
+    for (int q = 0; q < NSUB; ++q)
+      load4((const T*)(a.dvec + j0 - LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
+    // (the places of the solved tiles are free)
+    if (wave >= 4)
+      flow_gather((const int*)(a.perm + j0 - LEAF), a.pivot0 + j0 - LEAF, x, solved + (wave & 3) * Sh::OUT, lane);
+    __syncthreads();
+    flow_solve(wave < 4 ? opsU : opsL, x, lane);
+    T v[NSUB][4];
+    flow_solved_put(solved, wave, x, rinv, v, lane);
+    __syncthreads();
+    flow_store_rows(a, rows, r16, j - 1, v, out, lane);
+    // their product, the columns in the order of a slab
+    const int mine0 = wave & 4, other0 = 4 - mine0;
+#pragma unroll
+    for (int p = 0; p < LEAF / BK; ++p) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (u < units.count) {
+          T fr[KS], fc[KS];
+          flow_solved_slab<T, KS>(solved, mine0 + units.row[u], p, l16, g, fr);
+          flow_solved_slab<T, KS>(solved, other0 + units.col[u], p, l16, g, fc);
+#pragma unroll
+          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e] * d[p * (KS / 4) + e / 4][e % 4], fc[e], s[u]);
+        }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 64) {                                               // tiles (j, j - 1)
+    flow_publish(a, j, j);
+    flow_publish(a, a.ntr + j, j);
+  }
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (u < units.count) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = units.row[u] * SUB + X::acc_row(lane, r), col = units.col[u] * SUB + l16;
+        if (col + low <= row) leaf_tile_put<T>(lds, low ? col : row, low ? row : col, wl, -s[u][r]);
+      }
+    }
+  leaf_lu_body<T, FLOW_WAVES, true, true>(leaf, leaf + a.qoff, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, nullptr,
+                                          a.perm + j0, a.pivot0 + j0, a.flags, lds);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    flow_publish(a, a.ntr + j, j + 1);
+    flow_publish(a, j, j + 1);
+  }
+}
+
+template <typename T, FlowForm FORM>
 __global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a) {
-  __shared__ __attribute__((aligned(16))) T lds[FlowShape<T>::LDS_ELEMS];
+  __shared__ __attribute__((aligned(16))) T lds[FlowShape<T, FORM>::LDS_ELEMS];
   __shared__ int shared[2];
   if (threadIdx.x == 0)
     shared[1] = (int)__hip_atomic_fetch_add(&a.sync->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   const int t = __builtin_amdgcn_readfirstlane(shared[1]);
-  int pair, j;
-  flow_task(a.ntr, a.ntc, t, pair, j);
+  int pair, array, j;
+  flow_task(a.ntr, a.ntc, FlowShape<T, FORM>::ARRAYS, t, pair, array, j);
   pair = __builtin_amdgcn_readfirstlane(pair);
+  array = __builtin_amdgcn_readfirstlane(array);
   j = __builtin_amdgcn_readfirstlane(j);
-  if (pair < 0) {
-    flow_diagonal_task<T, SCALED>(a, j, lds, shared);
-  } else {
+  if (pair >= 0) {
     __builtin_amdgcn_s_setprio(2);
-    flow_row_task<T, SCALED>(a, pair, j, lds, shared);
+    flow_row_task<T, FORM>(a, pair, array, j, lds, shared);
+  } else if constexpr (FORM == FLOW_GENERAL) {
+    flow_diagonal_general<T>(a, j, lds, shared);
+  } else {
+    flow_diagonal_task<T, FORM>(a, j, lds, shared);
   }
 }
 

@@ -638,23 +638,26 @@ __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
 // the three products between cost 2300 clocks each.  Measured, fp64, launches back to back: 20.1 us
 // each (a launch alone 20.6 to 22.6) against 32.3 with the matrix in the registers of four
 // wavefronts and a barrier and an exchange of the pivot row per step (n = 4096 4.41 -> 3.63 ms).
+// IN_LDS, THROUGH: as for leaf_factor_body; `lds` has PIVOT_LDS_ELEMS elements, of which with IN_LDS
+// the first LEAF_TILE hold the leaf, both triangles, row stride LEAF_PAD.
 constexpr int PIVOT_WAVES = 8;
-template <typename T>
-__global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
+constexpr int PIVOT_LDS_ELEMS = 2 * LEAF_TILE + 2 * LEAF;
+template <typename T, bool IN_LDS = false, bool THROUGH = false>
+__device__ __forceinline__ void leaf_factor_pivoted_body(
     T* __restrict__ A, int64_t ld, int w, T* __restrict__ dvec, T* __restrict__ dinv,
-    T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags) {
+    T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags, T* __restrict__ lds) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   constexpr int NW = PIVOT_WAVES;
-  __shared__ T S[LEAF_TILE];
-  __shared__ T mult[LEAF_TILE];   // multipliers: by step, input row (0 for rows taken before)
-  __shared__ T dl[LEAF];          // pivots in the order taken
-  __shared__ int row_of[LEAF];    // row taken at a step
+  T* const S = lds;
+  T* const mult = S + LEAF_TILE;  // multipliers: by step, input row (0 for rows taken before)
+  T* const dl = mult + LEAF_TILE; // pivots in the order taken
+  int* const row_of = reinterpret_cast<int*>(dl + LEAF);   // row taken at a step
   __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15;
-  {
+  if constexpr (!IN_LDS) {
     // one row a load; the padding of a narrow leaf is the identity
     T v[LEAF / NW];
 #pragma unroll
@@ -746,10 +749,10 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
 #pragma unroll
     for (int k = 0; k < LEAF / NW; ++k) {
       const int r = NW * k + wave;
-      if (r < w && lane <= r) A[(int64_t)r * ld + lane] = lane == r ? myd : v[k];
+      if (r < w && lane <= r) leaf_store<THROUGH>(A + (int64_t)r * ld + lane, lane == r ? myd : v[k]);
     }
   }
-  if (wave < NSUB) {
+  if (!THROUGH && wave < NSUB) {
     const int c = row_of[wave * SUB + l16];
     T nl[SUB];
 #pragma unroll
@@ -764,9 +767,9 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
     const bool finite = fabs((double)myd) <= 1.7976931348623157e308;
     const bool bad = lane < w && (zero || !finite);
     if (lane < w) {
-      dvec[lane] = myd;
-      dinv[lane] = fast_rcp(myd);
-      perm[lane] = (int)pivot0 + row_of[lane];
+      leaf_store<THROUGH>(dvec + lane, myd);
+      leaf_store<THROUGH>(dinv + lane, fast_rcp(myd));
+      leaf_store<THROUGH>(perm + lane, (int)pivot0 + row_of[lane]);
     }
     const unsigned long long mask = __ballot(bad);
     if (mask != 0ull) {
@@ -779,6 +782,13 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
     }
   }
   __builtin_amdgcn_s_setprio(0);
+}
+template <typename T>
+__global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
+    T* __restrict__ A, int64_t ld, int w, T* __restrict__ dvec, T* __restrict__ dinv,
+    T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags) {
+  __shared__ T lds[PIVOT_LDS_ELEMS];
+  leaf_factor_pivoted_body<T>(A, ld, w, dvec, dinv, linv, perm, pivot0, flags, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -812,23 +822,26 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
 // the next column's update, 425 clocks a step.  Measured, fp64: 18.7 us alone, 19.4 in a run
 // of n = 2900, against 33.5 and 34 with a barrier per step and 16 wavefronts of four columns
 // (n = 2900 3.35 -> 2.74 ms, n = 8192 13.2 -> 11.5 ms).
+// IN_LDS, THROUGH: as for leaf_factor_body; `lds` has LU_LDS_ELEMS elements, of which with IN_LDS the
+// first LEAF_TILE hold the leaf, row stride LEAF_PAD.
 constexpr int LU_WAVES = 8;
-template <typename T, int NW>
-__global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
+constexpr int LU_LDS_ELEMS = LEAF_TILE + LEAF * LEAF + 2 * LEAF;
+template <typename T, int NW, bool IN_LDS = false, bool THROUGH = false>
+__device__ __forceinline__ void leaf_lu_body(
     T* __restrict__ Pl, T* __restrict__ Qu, int64_t ld, int w, T* __restrict__ dvec,
     T* __restrict__ dinv, T* __restrict__ linvL, T* __restrict__ linvU, int* __restrict__ perm,
-    long long pivot0, DevFlags* flags) {
+    long long pivot0, DevFlags* flags, T* __restrict__ lds) {
   constexpr int CW = LEAF / NW;          // columns per wavefront
   static_assert(NW == 2 * NSUB, "one diagonal sub-block of L or U^T to invert per wavefront");
-  __shared__ T S[LEAF_TILE];             // the leaf; afterwards, rows in pivot order: L below, D U on and above
-  __shared__ T mult[LEAF][LEAF];         // minus the multipliers of every step, by input row
-  __shared__ int row_of[LEAF];           // row taken at a step; -1: not yet
-  __shared__ int pos[LEAF];              // step at which a row was taken
+  T* const S = lds;                      // the leaf; afterwards, rows in pivot order: L below, D U on and above
+  T (* const mult)[LEAF] = reinterpret_cast<T (*)[LEAF]>(S + LEAF_TILE);   // minus the multipliers of every step, by input row
+  int* const row_of = reinterpret_cast<int*>(S + LEAF_TILE + LEAF * LEAF); // row taken at a step; -1: not yet
+  int* const pos = row_of + LEAF;        // step at which a row was taken
   __builtin_amdgcn_s_setprio(2);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c0 = wave * CW;
-  {
+  if constexpr (!IN_LDS) {
     // rows of both halves, one row a load: (r, c) of the lower half, (c, r) of the upper;
     // the padding of a narrow leaf is the identity
     T p[CW], q[CW];
@@ -927,11 +940,12 @@ __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
 #pragma unroll
   for (int k = 0; k < CW; ++k) {
     const int r = NW * k + wave;
-    if (r < w && lane <= r) Pl[(int64_t)r * ld + lane] = a[k];
-    if (r < w && lane < r) Qu[(int64_t)r * ld + lane] = up[k];
+    if (r < w && lane <= r) leaf_store<THROUGH>(Pl + (int64_t)r * ld + lane, a[k]);
+    if (r < w && lane < r) leaf_store<THROUGH>(Qu + (int64_t)r * ld + lane, up[k]);
   }
   // the inverses of the diagonal sub-blocks, L by the first wavefronts, U~^T by the others
-  if (wave < NSUB) {
+  if (THROUGH) {
+  } else if (wave < NSUB) {
     leaf_invert_sub<T>(S, linvL, wave, lane);
   } else {
     const int b = wave - NSUB, c = lane & 15;
@@ -947,9 +961,9 @@ __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
     const bool finite = fabs((double)myd) <= 1.7976931348623157e308;
     const bool bad = lane < w && (zero || !finite);
     if (lane < w) {
-      dvec[lane] = myd;
-      dinv[lane] = myr;
-      perm[lane] = (int)pivot0 + row_of[lane];
+      leaf_store<THROUGH>(dvec + lane, myd);
+      leaf_store<THROUGH>(dinv + lane, myr);
+      leaf_store<THROUGH>(perm + lane, (int)pivot0 + row_of[lane]);
     }
     const unsigned long long mask = __ballot(bad);
     if (mask != 0ull) {
@@ -962,6 +976,15 @@ __global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
     }
   }
   __builtin_amdgcn_s_setprio(0);
+}
+
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void leaf_lu_kernel(
+    T* __restrict__ Pl, T* __restrict__ Qu, int64_t ld, int w, T* __restrict__ dvec,
+    T* __restrict__ dinv, T* __restrict__ linvL, T* __restrict__ linvU, int* __restrict__ perm,
+    long long pivot0, DevFlags* flags) {
+  __shared__ T lds[LU_LDS_ELEMS];
+  leaf_lu_body<T, NW>(Pl, Qu, ld, w, dvec, dinv, linvL, linvU, perm, pivot0, flags, lds);
 }
 
 // Moves the strict upper triangle of a general matrix into its transposed store, or back,

@@ -352,12 +352,15 @@ struct Launcher {
 
   // Whether factor_cols takes a block column of m rows and w columns in one launch.
   bool flows(int64_t ld, int64_t m, int64_t w) const {
-    return sync != nullptr && flow_words(m) <= sync_words && m <= INT32_MAX && (w % LEAF == 0 || w == m) &&
-           (uint64_t)ld * sizeof(T) * LEAF < (1ull << 31) &&
-           flow_tasks((m + LEAF - 1) / LEAF, (w + LEAF - 1) / LEAF) <= INT32_MAX;
+    const int arrays = qoff != 0 ? 2 : 1;
+    return sync != nullptr && pb.S == nullptr && flow_words(m, arrays) <= sync_words && m <= INT32_MAX &&
+           (w % LEAF == 0 || w == m) && (uint64_t)ld * sizeof(T) * LEAF < (1ull << 31) &&
+           flow_tasks((m + LEAF - 1) / LEAF, (w + LEAF - 1) / LEAF, arrays) <= INT32_MAX;
   }
   int factor_cols_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip) {
-    const int64_t words = flow_words(m);
+    if (spd && (perm || qoff != 0)) return MDET_EINVAL;
+    const int arrays = qoff != 0 ? 2 : 1;
+    const int64_t words = flow_words(m, arrays);
     if (sync_used + words > sync_words) {
       hipLaunchKernelGGL(flow_reset_kernel, dim3(1), dim3(1024), 0, st, sync, (int)sync_words);
       ++launches;
@@ -373,22 +376,27 @@ struct Launcher {
     a.W = Wp;
     a.wld = wld;
     a.wskip = (int)wskip;
+    a.qoff = qoff;
+    a.perm = perm ? perm + d0 : nullptr;
     a.pivot0 = d0;
     a.flags = flags;
     a.sync = (FlowSync*)(sync + sync_used);
     a.ntr = (int)((m + LEAF - 1) / LEAF);
     a.ntc = (int)((w + LEAF - 1) / LEAF);
-    a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0;
+    a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0 &&
+              (uint64_t)qoff * sizeof(T) % 128 == 0;
     sync_used += words;
-    const dim3 grid((unsigned)flow_tasks(a.ntr, a.ntc)), block(FLOW_THREADS);
-    if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((panel_flow_kernel<T, false>), grid, block, 0, st, a);
+    const dim3 grid((unsigned)flow_tasks(a.ntr, a.ntc, arrays)), block(FLOW_THREADS);
+    if (qoff != 0) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_GENERAL>), grid, block, 0, st, a);
+    else if (perm) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_PIVOT>), grid, block, 0, st, a);
+    else if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SPD>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SYM>), grid, block, 0, st, a);
     fail->check(hipGetLastError());
     ++launches;
     for (int64_t j = 0; j < w; j += LEAF) {
       const double lw = (double)(w - j < LEAF ? w - j : LEAF), below = (double)(m - j) - lw;
-      fma += (lw * lw * lw - lw) / 6.0 + below * (lw * (lw - 1) / 2.0);
-      fma += (lw * (lw + 1) / 2 + below * lw) * (double)j;
+      fma += arrays * ((lw * lw * lw - lw) / 6.0 + below * (lw * (lw - 1) / 2.0));
+      fma += arrays * (lw * (lw + 1) / 2 + below * lw) * (double)j;
     }
     return MDET_OK;
   }
@@ -406,6 +414,7 @@ struct Launcher {
     if (w <= 0) return MDET_OK;
     if (pb.S != nullptr) return factor_cols_pivot_block(st, P, ld, m, w, d0);
     if (!first_done && flows(ld, m, w)) return factor_cols_flow(st, P, ld, m, w, d0, Wp, wskip);
+    sync_used = sync_words;
     if (w <= LEAF && qoff != 0) {
       // P A = L D U of the leaf, then the rows below it in both halves: the lower half
       // against U^T, the transposed upper half against L with the leaf's row order
@@ -787,12 +796,15 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
 // 4.02 / 3.79 against 5.22 / 4.97, n = 12288 12.8 / 12.3 against 15.3 / 14.5, n = 16384 29.9 / 29.4
 // against 28.0 / 26.6; fp32 n = 10000 4.6 / 3.7 against 5.8 / 5.5, n = 16384 15.4 / 13.7 against 14.9 /
 // 14.3: the launch reads each operand out of memory once for every 64 columns, which from about
-// there on no cache holds.  16 is how many block columns the library makes of such a matrix by
+// there on no cache holds; pivots from inside a leaf, n = 12288 12.6; general matrices (twice the
+// data) fp64 n = 6144 5.5 against 7.0, n = 8192 11.9 against 11.5, fp32 6144 3.1 against 4.3, 8192 6.9
+// against 6.7.  16 is how many block columns the library makes of such a matrix by
 // itself; a caller who asks for more of them, and for look-ahead between them, gets a launch for
 // every 16.  With MDET_FLAG_PROFILE the updates between block columns are what is looked at.
 template <typename T>
 static Plan dense_plan(const Launcher<T>& L, const Plan& pl, int64_t ld, bool lookahead) {
-  constexpr int64_t ONE_LAUNCH = sizeof(T) == 8 ? 14336 : 16384;
+  constexpr int64_t SYMMETRIC = sizeof(T) == 8 ? 14336 : 16384, GENERAL = sizeof(T) == 8 ? 7168 : 8192;
+  const int64_t ONE_LAUNCH = L.qoff != 0 ? GENERAL : SYMMETRIC;
   Plan f = pl;
   if (pl.T < 2 || pl.n > ONE_LAUNCH || L.profile || L.wbuf[0] || !L.flows(ld, pl.n, pl.n)) return f;
   f.bs = lookahead ? 16 * pl.bs : round_up(pl.n, LEAF);
@@ -981,10 +993,8 @@ static void bind_small(Launcher<T>& L, char* base, const SmallArea& sa) {
   L.linv_u = L.linv + LEAF * SUB;      // linv is two arrays here
   L.flags = (DevFlags*)(base + sa.flags);
   L.perm = sa.total > sa.perm ? (int*)(base + sa.perm) : nullptr;
-  if (!L.perm) {                       // (nothing else uses that array then)
-    L.sync = (unsigned*)L.l10;
-    L.sync_words = LEAF * LEAF * (int64_t)sizeof(T) / 4;
-  }
+  L.sync = (unsigned*)L.l10;           // (leaf_pair_kernel's array: a launch that uses it ends the words)
+  L.sync_words = LEAF * LEAF * (int64_t)sizeof(T) / 4;
   // two workgroups of the trailing update fit one compute unit (registers and LDS)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
@@ -1027,6 +1037,37 @@ template <typename T>
 static void reset_flags(Launcher<T>& L, hipStream_t st) {
   hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(L.sync ? 1024 : 64), 0, st, L.flags, L.sync, (int)L.sync_words);
   L.fail->check(hipGetLastError());
+}
+
+// The pivots and the permutation to where the caller wants them, in one launch if that is memory of
+// a device (two copies by the runtime are two launches and 10 us of a call; n = 512).
+template <typename T>
+__global__ void copy_out_kernel(const T* __restrict__ dvec, T* __restrict__ diag, const int* __restrict__ perm,
+                                int* __restrict__ perm_out, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (diag) diag[i] = dvec[i];
+  if (perm_out) perm_out[i] = perm[i];
+}
+static bool device_memory(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return a.type == hipMemoryTypeDevice;
+}
+template <typename T>
+static void copy_out(Launcher<T>& L, hipStream_t st, int64_t n, T* diag, int32_t* perm_out) {
+  if (!L.perm) perm_out = nullptr;
+  if (n <= 0 || (!diag && !perm_out)) return;
+  if ((diag && (!device_memory(diag) || (uintptr_t)diag % sizeof(T))) ||
+      (perm_out && (!device_memory(perm_out) || (uintptr_t)perm_out % 4))) {
+    if (diag) L.fail->check(hipMemcpyAsync(diag, L.dvec, n * sizeof(T), hipMemcpyDeviceToDevice, st));
+    if (perm_out) L.fail->check(hipMemcpyAsync(perm_out, L.perm, n * sizeof(int), hipMemcpyDeviceToDevice, st));
+    return;
+  }
+  hipLaunchKernelGGL((copy_out_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const T*)L.dvec, diag,
+                     (const int*)L.perm, (int*)perm_out, n);
+  L.fail->check(hipGetLastError());
+  ++L.launches;
 }
 
 // ---------------------------------------------------------------------------
@@ -1124,10 +1165,7 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
                          dim3(256), 0, s0, (const T*)Q, W, ldw, pl.n, nb64, 1);
       MDET_HIP(fail, hipGetLastError());
     }
-    if (diag && pl.n > 0)
-      MDET_HIP(fail, hipMemcpyAsync(diag, L.dvec, pl.n * sizeof(T), hipMemcpyDeviceToDevice, s0));
-    if (L.perm && p.perm && pl.n > 0)
-      MDET_HIP(fail, hipMemcpyAsync(p.perm, L.perm, pl.n * sizeof(int), hipMemcpyDeviceToDevice, s0));
+    copy_out(L, s0, pl.n, diag, (int32_t*)p.perm);
   }
   DeviceOut o;
   std::memset(&o, 0, sizeof(o));

@@ -10,25 +10,30 @@ using namespace mdet;
 
 int main() {
   long bad = 0, cases = 0;
-  for (int ntr = 1; ntr <= 140; ntr += ntr < 40 ? 1 : 9)
+  for (int arrays = 1; arrays <= 2; ++arrays)
+   for (int ntr = 1; ntr <= 140; ntr += ntr < 40 ? 1 : 9)
     for (int ntc = 1; ntc <= ntr; ntc += ntc < 20 || ntc + 7 > ntr ? 1 : 5) {
-      const int64_t tasks = flow_tasks(ntr, ntc);
-      std::vector<int64_t> owner((size_t)ntr * ntc, -1);
-      auto own = [&](int i, int j, int64_t t) {
-        if (i >= ntr || j >= ntc || owner[(size_t)i * ntc + j] >= 0) ++bad;
-        else owner[(size_t)i * ntc + j] = t;
+      const int64_t tasks = flow_tasks(ntr, ntc, arrays);
+      std::vector<int64_t> owner((size_t)arrays * ntr * ntc, -1);
+      auto place = [&](int y, int i, int j) -> int64_t& { return owner[((size_t)y * ntr + i) * ntc + j]; };
+      auto own = [&](int y, int i, int j, int64_t t) {
+        if (y >= arrays || i >= ntr || j >= ntc || place(y, i, j) >= 0) ++bad;
+        else place(y, i, j) = t;
       };
       for (int pass = 0; pass < 2; ++pass)
         for (int64_t t = 0; t < tasks; ++t) {
-          int pair, j;
-          flow_task(ntr, ntc, (int)t, pair, j);
-          auto before = [&](int i, int k) {
-            if (owner[(size_t)i * ntc + k] >= t) ++bad;
+          int pair, y, j;
+          flow_task(ntr, ntc, arrays, (int)t, pair, y, j);
+          auto before = [&](int i, int k) {              // in every array: each needs the other's rows
+            for (int q = 0; q < arrays; ++q)
+              if (place(q, i, k) >= t) ++bad;
           };
           if (pair < 0) {
             if (pass == 0) {
-              own(j, j, t);
-              if (j > 0) own(j, j - 1, t);
+              for (int q = 0; q < arrays; ++q) {
+                own(q, j, j, t);
+                if (j > 0) own(q, j, j - 1, t);
+              }
               continue;
             }
             for (int k = 0; k + 1 < j; ++k) { before(j, k); before(j - 1, k); }
@@ -38,14 +43,18 @@ int main() {
           const int first = j + 1 < ntc ? j + 2 : j + 1;
           for (int i = 2 * pair; i < 2 * pair + 2; ++i) {
             if (i < first || i >= ntr) continue;
-            if (pass == 0) { own(i, j, t); continue; }
+            if (pass == 0) { own(y, i, j, t); continue; }
             before(j, j);
-            for (int k = 0; k < j; ++k) { before(i, k); before(j, k); }
+            for (int k = 0; k < j; ++k) {
+              if (place(y, i, k) >= t) ++bad;
+              before(j, k);
+            }
           }
         }
       for (int i = 0; i < ntr; ++i)
         for (int j = 0; j < ntc && j <= i; ++j)
-          if (owner[(size_t)i * ntc + j] < 0) ++bad;
+          for (int q = 0; q < arrays; ++q)
+            if (place(q, i, j) < 0) ++bad;
       if (bad && cases >= 0) std::printf("rows %d columns %d: bad %ld\n", ntr, ntc, bad);
       ++cases;
     }

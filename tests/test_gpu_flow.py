@@ -57,3 +57,63 @@ def test_orders_around_tile_edges(n, dtype, form):
     low += np.eye(n)
     err = np.abs(low * got[0][0] @ low.T - a.astype(np.float64))
     assert err.max() < 8 * tol                                       # entries up to 4
+
+
+@pytest.mark.parametrize("form", ["gen", "pivot"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 193, 320, 449, 1025])
+def test_pivoting_forms_around_tile_edges(n, dtype, form):
+    """Pivots that stand in the first place of no leaf: the largest of each leaf's columns (diagonals) is in
+    its last rows.  The factor multiplied out gives the matrix, and the block columns change no bit."""
+    import paper_2503_04424_amd as M
+    M.load()
+    npdt, tol = (np.float64, 1e-13) if dtype == "f64" else (np.float32, 1e-5)
+    rng = np.random.default_rng(n + 1)
+    a = rng.uniform(-1, 1, (n, n)) / (2 * n)
+    if form == "pivot":
+        a = a + a.T
+        np.fill_diagonal(a, (1 + np.arange(n) % 64 / 21.0) * rng.choice([-1, 1], n))     # 1 .. 4, the last the largest
+    else:
+        np.fill_diagonal(a, rng.uniform(1, 4, n))
+        rows = np.arange(n)
+        for k in range(0, n, 64):
+            rows[k:k + 64] = rows[k:k + 64][::-1]
+        a = a[rows]
+    a = a.astype(npdt)
+    vec = 16 // np.dtype(npdt).itemsize
+    got = []
+    for ld, bs, extra in [((n + 31) // 32 * 32, 1024, 0), ((n + vec - 1) // vec * vec, 128, 0),
+                          ((n + 31) // 32 * 32 + vec, 64, 0), ((n + 31) // 32 * 32, 192, M.FLAG_PROFILE)]:
+        buf = torch.zeros((n, ld), dtype=torch.float64 if dtype == "f64" else torch.float32, device="cuda")
+        buf[:, :n] = torch.from_numpy(a).cuda()
+        diag = torch.empty(n, dtype=buf.dtype, device="cuda")
+        perm = torch.empty(n, dtype=torch.int32, device="cuda")
+        r = M.mdet_logdet_device(buf[:, :n], block_size=bs, overwrite=True, diag=diag, perm=perm,
+                                 flags=extra | (M.FLAG_GENERAL if form == "gen" else M.FLAG_PIVOT))
+        assert r.status == 0 and r.flops == pytest.approx((4 if form == "gen" else 2) * (n ** 3 - n) / 6, rel=1e-12)
+        got.append((diag.cpu().numpy(), perm.cpu().numpy(), buf[:, :n].cpu().numpy()))
+    for d, p, f in got[1:]:
+        assert np.array_equal(d, got[0][0]) and np.array_equal(p, got[0][1])
+        assert np.array_equal(*(f_ if form == "gen" else np.tril(f_) for f_ in (f, got[0][2])))
+    d, p, f = got[0][0].astype(np.float64), got[0][1], got[0][2].astype(np.float64)
+    assert not np.array_equal(p[:64], np.arange(min(n, 64)))
+    if form == "gen":
+        want = np.linalg.slogdet(a.astype(np.float64))
+        assert r.sign == want[0] and abs(r.logabsdet - want[1]) <= 10 * n * tol
+    # rows of a later leaf stay in their input order in the columns of the leaves before it
+    low = np.tril(f, -1)
+    up = np.triu(f, 1) if form == "gen" else low.T
+    exact = a.astype(np.float64)
+    s = exact.copy()
+    for k in range(0, n, 64):
+        e = min(n, k + 64)
+        q = p[k:e]
+        l11, u11 = low[k:e, k:e] + np.eye(e - k), up[k:e, k:e] + np.eye(e - k)
+        lead = s[k:e, k:e][q - k] if form == "gen" else s[k:e, k:e][np.ix_(q - k, q - k)]
+        assert np.abs(l11 * d[k:e] @ u11 - lead).max() < 8 * tol
+        l21, u12 = low[e:, k:e], up[k:e, e:]
+        cols = s[e:, k:e] if form == "gen" else s[e:, k:e][:, q - k]
+        assert e == n or np.abs(l21 * d[k:e] @ u11 - cols).max() < 8 * tol
+        right = s[k:e, e:][q - k]
+        assert e == n or np.abs(l11 * d[k:e] @ u12 - right).max() < 8 * tol
+        s[e:, e:] -= l21 * d[k:e] @ u12
