@@ -92,7 +92,22 @@ __global__ __launch_bounds__(256) void widen_lower_kernel(const S* __restrict__ 
   for (int64_t j = threadIdx.x; j < end; j += 256) dst[i * ldd + j] = widen_exact(src[i * lds + j]);
 }
 
-// The same for a rows x cols rectangle (a piece of a block column on its way from host
+// The same without a change of type, V elements (rows of whole V) at a time: half of what copying the
+// square moves.
+template <typename E, int V>
+__global__ __launch_bounds__(256) void copy_lower_kernel(const E* __restrict__ src, int64_t lds, E* __restrict__ dst,
+                                                         int64_t ldd, int64_t n) {
+  const int64_t i = blockIdx.x;
+  int64_t end = (i / 64 + 1) * 64;
+  if (end > n) end = n;
+  end = (end + V - 1) / V;             // (no further than lds, which is whole)
+  const E* from = src + i * lds;
+  E* to = dst + i * ldd;
+#pragma unroll 4
+  for (int64_t j = threadIdx.x; j < end; j += 256) to[j] = from[j];
+}
+
+// widen_lower_kernel for a rows x cols rectangle (a piece of a block column on its way from host
 // memory): src with leading dimension lds, dst with ldd.
 template <typename S>
 __global__ __launch_bounds__(256) void widen_rows_kernel(const S* __restrict__ src, int64_t lds,

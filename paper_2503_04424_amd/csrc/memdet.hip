@@ -971,10 +971,16 @@ struct Workspace {
   }
 };
 
-// The plan's workspace; if it cannot be had and the plan holds the pivot-scaled copies
-// without having been asked for them, once more without them.
+// The plan's workspace; if it cannot be had, once more with the copy's rows no longer than they have
+// to be, and if the plan holds the pivot-scaled copies without having been asked for them, once
+// more without them.
 static int acquire_workspace(Workspace& ws, const mdet_params& p, Plan& pl, HipFail& fail) {
   int rc = ws.acquire(p, pl.dev_bytes, fail);
+  if (rc == MDET_ENOMEM_DEVICE && pl.copy_ld > narrow_copy_ld(pl)) {
+    place_copy(pl, narrow_copy_ld(pl), pl.copy_ld);
+    fail.code = hipSuccess;
+    rc = ws.acquire(p, pl.dev_bytes, fail);
+  }
   if (rc == MDET_ENOMEM_DEVICE && pl.wcopy_optional && pl.wcopy_bytes) {
     pl.dev_bytes -= pl.wcopy_bytes;
     pl.wcopy_bytes = 0;
@@ -1112,8 +1118,7 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
   T* W = dA;
   int64_t ldw = ld;
   if (pl.need_copy && pl.n > 0) {
-    constexpr int vec = 16 / (int)sizeof(T);
-    ldw = round_up(pl.n, vec);
+    ldw = pl.copy_ld;
     W = (T*)(ws.base + fixed);
     if (widen_from) {
       const dim3 grid((unsigned)pl.n), block(256);
@@ -1127,9 +1132,18 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
         hipLaunchKernelGGL((widen_lower_kernel<float>), grid, block, 0, s0, (const float*)widen_from,
                            ld, (double*)W, ldw, pl.n);
       MDET_HIP(fail, hipGetLastError());
-    } else {
+    } else if (pl.general) {
       MDET_HIP(fail, hipMemcpy2DAsync(W, ldw * sizeof(T), dA, ld * sizeof(T), pl.n * sizeof(T), pl.n,
                                       hipMemcpyDeviceToDevice, s0));
+    } else {
+      const dim3 grid((unsigned)pl.n), block(256);
+      if (ld % (16 / (int)sizeof(T)) == 0)
+        hipLaunchKernelGGL((copy_lower_kernel<typename Mfma<T>::vec_t, Mfma<T>::VEC>), grid, block, 0, s0,
+                           (const typename Mfma<T>::vec_t*)dA, ld / Mfma<T>::VEC, (typename Mfma<T>::vec_t*)W,
+                           ldw / Mfma<T>::VEC, pl.n);
+      else
+        hipLaunchKernelGGL((copy_lower_kernel<T, 1>), grid, block, 0, s0, (const T*)dA, ld, W, ldw, pl.n);
+      MDET_HIP(fail, hipGetLastError());
     }
   }
   reset_flags(L, s0);
