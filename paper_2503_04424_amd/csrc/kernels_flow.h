@@ -24,11 +24,12 @@
 // elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
 // that.  Between launches the same steps also wait for every workgroup of the launch before and
 // for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
-// against the chain of launches, whole calls: symmetric fp64 n = 512 230 -> 164 us, n = 1500 620 -> 371, n = 5555
-// 3030 -> 1563, n = 8192 5889 -> 4110, fp32 n = 10000 5948 -> 4191; block columns of 2048 beside a bulk
-// update, n = 32768, 191.1 -> 187.5 ms; pivots from inside a leaf, n = 4096 3.03 -> 1.69 ms; general
-// n = 2900 2.30 -> 1.39, block columns of 1024 at n = 8192 11.3 -> 10.1 (leaves of 20 us there).  Where a matrix is large: the matrix cores, 4.2 us for the
-// 128 x 64 x 64 products of a tile in fp64 (positive-definite form 3.9; 3.4 at their peak).
+// against the chain of launches, whole calls: symmetric fp64 n = 512 230 -> 160 us, n = 1500 (positive
+// definite) 620 -> 360, n = 5555 3030 -> 1530, n = 8192 5889 -> 3850, fp32 n = 10000 5948 -> 3560; block columns
+// of 2048 beside a bulk update, n = 32768, 191 -> 178 ms; pivots from inside a leaf, n = 4096 3.03 -> 1.69
+// ms; general n = 2900 2.30 -> 1.36, n = 8192 11.3 -> 7.8 (leaves of 20 us).  Where a matrix is large: the
+// matrix cores, in fp64 4.2 us for the 128 x 64 x 64 products of a row task of one column and 7.7 for
+// 128 x 128 x 64 of two (positive-definite form 3.9 and 7.5; 3.4 and 6.8 at their peak).
 // One workgroup of eight wavefronts has a compute unit to itself (its LDS sees to that): two
 // of four wavefronts each slow each other's leaves down, whose single wavefront then waits for
 // the other's matrix instructions (n = 8192: 10.8 us a leaf instead of 6.7), and the sums of a
@@ -56,7 +57,7 @@ namespace mdet {
 
 constexpr int FLOW_WAVES = 8;
 constexpr int FLOW_THREADS = 64 * FLOW_WAVES;
-constexpr int FLOW_ROWS = SUB * FLOW_WAVES;           // rows of a row task: two tile rows
+constexpr int FLOW_ROWS_HELD = SUB * FLOW_WAVES;      // rows of a row task: two tile rows
 constexpr int FLOW_STAGES = 4;                        // slabs in LDS: one in use, the next there, two on their way
 constexpr unsigned long long FLOW_PATIENCE = 60ull * 100000000ull;   // of the 100 MHz counter
 
@@ -70,29 +71,83 @@ struct FlowSync {
 enum FlowForm { FLOW_SYM, FLOW_SPD, FLOW_PIVOT, FLOW_GENERAL };
 static inline int64_t flow_words(int64_t m, int arrays) { return 2 + arrays * ((m + LEAF - 1) / LEAF); }
 
-// Tasks before tile column j (j < ntc) of ntr tile rows, ntp = ceil(ntr / 2) pairs of them: in each
-// column c a diagonal task and, for each array, the pairs from (c + 2) / 2 on.
-__host__ __device__ __forceinline__ int64_t flow_tasks_before(int64_t ntp, int arrays, int64_t j) {
-  return j <= 0 ? 0 : j + arrays * (j * (ntp - 1) - (j - 1) * (j - 1) / 4);
+// The tasks in their order, two tile columns j0 = 2 J and j1 = j0 + 1 at a time (ntr tile rows, ntp = ceil(ntr
+// / 2) pairs of them, pair p tile rows 2 p and 2 p + 1; `arrays` tasks for each row task).  J < two:
+//   diagonal task j0, row task (pair J + 1, column j0), diagonal task j1, row task (pair J + 1, column
+//   j1), row tasks (pairs from J + 2 on, both columns);
+// the others:
+//   diagonal task j0, row tasks (pairs from J + 1 on, column j0), and the same for j1;
+// and if the last tile column is a j0: its diagonal task, row tasks (pairs from J on, that column).
+// Row tasks of both columns read their rows once for 128 columns and multiply twice as long between two
+// barriers, but are twice as long: where few are left (flow_two) they would be waited for.  Those next
+// to the diagonal, which the next diagonal tasks wait for, have one.
+enum FlowKind { FLOW_DIAGONAL, FLOW_ROWS, FLOW_ROWS2, FLOW_NOTHING };
+struct FlowOrder {
+  int ntr, ntc, arrays, two;
+  __host__ __device__ __forceinline__ int64_t pairs() const { return (ntr + 1) / 2; }
+  // tasks in front of column pair J
+  __host__ __device__ __forceinline__ int64_t before(int64_t J) const {
+    const int64_t A = J < two ? J : two, ntp = pairs();
+    const int64_t both = A * (2 + arrays * ntp) - arrays * (A * (A - 1) / 2);
+    return both + (J - A) * (2 + 2 * arrays * (ntp - 1)) - arrays * (J * (J - 1) - A * (A - 1));
+  }
+  __host__ __device__ __forceinline__ int64_t tasks() const {
+    const int64_t J = (ntc - 1) / 2;
+    if (ntr == ntc) return before(J) + (ntc % 2 == 0 ? 2 : 1);
+    return ntc % 2 == 0 ? before(J + 1) : before(J) + 1 + arrays * (pairs() - J);
+  }
+  // column (the first of two), array and pair of task t
+  __host__ __device__ __forceinline__ FlowKind task(const int t, int& pair, int& array, int& j) const {
+    const int last = (ntc - 1) / 2;
+    int J = 0;
+    for (int step = 1 << 24; step != 0; step >>= 1)
+      if (J + step <= last && before(J + step) <= t) J += step;
+    int r = (int)(t - before(J));
+    j = 2 * J;
+    pair = array = 0;
+    if (r == 0) return FLOW_DIAGONAL;
+    --r;
+    const int below = arrays * (int)(pairs() - J - 1);   // row tasks of one column
+    if (j + 1 >= ntc) {                                  // the last column, alone
+      array = r % arrays;
+      pair = J + r / arrays;
+    } else if (J == last && ntr == ntc) {                // no rows below the last two
+      ++j;
+      return FLOW_DIAGONAL;
+    } else {
+      const int first = J < two ? arrays : below;        // row tasks of j0 in front of diagonal task j1
+      if (r == first) {
+        ++j;
+        return FLOW_DIAGONAL;
+      }
+      if (r > 2 * first) {
+        array = (r - 2 * first - 1) % arrays;
+        pair = J + 2 + (r - 2 * first - 1) / arrays;
+        return FLOW_ROWS2;
+      }
+      if (r > first) {
+        ++j;
+        r -= first + 1;
+      }
+      array = r % arrays;
+      pair = J + 1 + r / arrays;
+    }
+    // (the last pair, of an odd number of rows, may have none for this column)
+    const int top = j + 1 < ntc ? j + 2 : j + 1;
+    return 2 * pair >= top || 2 * pair + 1 < ntr ? FLOW_ROWS : FLOW_NOTHING;
+  }
+};
+// Column pairs with row tasks of both: while 28 row tasks of each column are left.  Measured with none, a
+// quarter, 0.4, 0.6, three quarters and all of the pairs: fp64 n = 4096 0.90 0.94 0.89 0.94 0.93 0.98 ms, n
+// = 8192 3.99 3.90 3.90 3.86 3.84 4.18, n = 12300 13.3 12.9 12.5 12.1 12.2 12.4; fp32 n = 10000 4.28 4.02
+// 3.84 3.63 3.60 3.53.
+static inline int flow_two(int64_t m, int64_t w, int arrays) {
+  const int64_t pairs = (m + 2 * LEAF - 1) / (2 * LEAF), columns = (w + 2 * LEAF - 1) / (2 * LEAF);
+  const int64_t two = pairs - 28 / arrays;
+  return (int)(two < 0 ? 0 : (two < columns ? two : columns));
 }
-// ... and in all of ntc tile columns; the last has the row right below its leaf, too.
-__host__ __device__ __forceinline__ int64_t flow_tasks(int64_t ntr, int64_t ntc, int arrays) {
-  const int64_t ntp = (ntr + 1) / 2;
-  return flow_tasks_before(ntp, arrays, ntc - 1) + 1 + (ntr > ntc ? arrays * (ntp - ntc / 2) : 0);
-}
-// Column j of task t, its array and its pair of tile rows, or -1: the diagonal task.
-__host__ __device__ __forceinline__ void flow_task(int ntr, int ntc, int arrays, int t, int& pair, int& array, int& j) {
-  const int64_t ntp = (ntr + 1) / 2;
-  // t >= flow_tasks_before(j), about (2 ntp j - j^2 / 2) arrays / 2, solved for j, then put right
-  const double a = 2.0 * (double)ntp, q = a * a - 4.0 * (double)t / (double)arrays;
-  j = (int)(a - sqrt(q > 0.0 ? q : 0.0));
-  if (j > ntc - 1) j = ntc - 1;
-  if (j < 0) j = 0;
-  while (j > 0 && flow_tasks_before(ntp, arrays, j) > t) --j;
-  while (j + 1 < ntc && flow_tasks_before(ntp, arrays, j + 1) <= t) ++j;
-  const int r = (int)(t - flow_tasks_before(ntp, arrays, j));
-  array = r == 0 ? 0 : (r - 1) % arrays;
-  pair = r == 0 ? -1 : (j + 1 < ntc ? (j + 2) / 2 : (j + 1) / 2) + (r - 1) / arrays;
+static inline FlowOrder flow_order(int64_t m, int64_t w, int arrays, int two) {
+  return FlowOrder{(int)((m + LEAF - 1) / LEAF), (int)((w + LEAF - 1) / LEAF), arrays, two};
 }
 
 // Four consecutive entries past the caches: `base` is the same in all lanes, `off` bytes from it.
@@ -113,7 +168,7 @@ template <typename T, FlowForm FORM>
 struct FlowShape {
   static constexpr int BK = Mfma<T>::BK;
   static constexpr int ARRAYS = FORM == FLOW_GENERAL ? 2 : 1;
-  static constexpr int ROWS = FLOW_ROWS * BK, COLS = ARRAYS * LEAF * BK;   // the slabs of the two operands
+  static constexpr int ROWS = FLOW_ROWS_HELD * BK, COLS = 2 * LEAF * BK;   // the slabs of the two operands
   static constexpr int STAGE = ROWS + COLS + BK;                  // both, and the pivots
   static constexpr int SLABS = FLOW_STAGES * STAGE;
   // after the sums the same memory holds what a solve needs of its leaf (of both its halves, one after
@@ -130,13 +185,12 @@ struct FlowShape {
   static constexpr int SOLVED = (BEFORE + 3) / 4 * 4;
   static constexpr int ROW_OUT = LeafOperands<T>::ELEMS;
   static constexpr int DIAG_OUT = FORM == FLOW_GENERAL ? 0 : SOLVED + TILES;
-  static constexpr int LATER_ROW = ROW_OUT + FLOW_WAVES * OUT;
+  static constexpr int ROW_TILE = ROW_OUT + FLOW_WAVES * OUT;     // a tile as a column operand
+  static constexpr int LATER_ROW = ROW_TILE + LEAF * LEAF;
   static constexpr int LATER_DIAG = FORM == FLOW_GENERAL ? SOLVED + TILES : DIAG_OUT + 4 * OUT;
   static constexpr int LATER = LATER_ROW > LATER_DIAG ? LATER_ROW : LATER_DIAG;
   // (so much that a compute unit holds one workgroup)
-  static constexpr int ALONE = 96 * 1024 / (int)sizeof(T);
-  static constexpr int MOST = SLABS > LATER ? SLABS : LATER;
-  static constexpr int LDS_ELEMS = MOST > ALONE ? MOST : ALONE;
+  static constexpr int LDS_ELEMS = SLABS > LATER ? SLABS : LATER;
   static_assert(SOLVED >= ARRAYS * LeafOperands<T>::ELEMS && LDS_ELEMS * sizeof(T) + 64 <= 160 * 1024,
                 "places in LDS");
 };
@@ -157,7 +211,7 @@ struct FlowArgs {
   long long pivot0;
   DevFlags* flags;
   FlowSync* sync;
-  int ntr, ntc;
+  FlowOrder order;
   bool lines;           // rows start on 128-byte lines
 };
 
@@ -247,7 +301,7 @@ struct FlowUnits {
 template <typename T>
 struct FlowOperands {
   const T* row[2];      // tile rows of the row operand; row[1] is not read by a diagonal task of one array
-  const T* col[2];      // and of the column operand; the second one in a diagonal task of two arrays only
+  const T* col[2];      // and of the column operand; the second one of KIND 2 and 3 only
   int left[2];          // rows of the matrix from row[v] on
   int counter[4];       // -1: none
 };
@@ -260,17 +314,19 @@ struct FlowOperands {
 // L_row^T of the FlowUnits.
 // Diagonal task of a general matrix (KIND 2): the 64 rows of row[0] by col[0] and those of row[1] by
 // col[1], and s[u] += row[0] D row[1]^T (wavefronts 0 to 3) and row[1] D row[0]^T (the others).
+// Row task of two columns (KIND 3): as KIND 0, x[NSUB + t] by col[1].
 // False if the launch has failed.
 template <typename T, FlowForm FORM, int KIND>
 __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const FlowOperands<T>& of, const int nk, const bool mine,
-                                                typename Mfma<T>::acc_t (&x)[NSUB], typename Mfma<T>::acc_t (&s)[3],
-                                                T* __restrict__ lds, int* shared) {
+                                                typename Mfma<T>::acc_t (&x)[KIND == 3 ? 2 * NSUB : NSUB],
+                                                typename Mfma<T>::acc_t (&s)[3], T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using vec_t = typename X::vec_t;
   using Sh = FlowShape<T, FORM>;
   constexpr bool SCALED = FORM == FLOW_SPD;
   constexpr int BK = Sh::BK, VEC = X::VEC, KS = BK / 4, PER_TILE = LEAF / BK;
-  constexpr int RV = KIND == 1 ? 1 : 2, CV = KIND == 2 ? 2 : 1;   // a wavefront's loads of each operand per slab
+  constexpr int RV = KIND == 1 ? 1 : 2, CV = KIND >= 2 ? 2 : 1;   // a wavefront's loads of each operand per slab
+  constexpr int NT = KIND == 3 ? 2 * NSUB : NSUB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
@@ -368,23 +424,23 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const Flow
     const T* rs = lds + stage * Sh::STAGE;
     const T* cs = rs + Sh::ROWS + half;
     T nd[KS];
-    if constexpr (KIND != 0 && !SCALED) {
+    if constexpr ((KIND == 1 || KIND == 2) && !SCALED) {
 #pragma unroll
       for (int e = 0; e < KS; ++e) nd[e] = next.d[e];
     }
     if (sums) {
-      T fr[KS], fc[NSUB][KS];
+      T fr[KS], fc[NT][KS];
 #pragma unroll
       for (int e = 0; e < KS; ++e) {
         fr[e] = next.row[e];
         fc[0][e] = next.col[e];
       }
 #pragma unroll
-      for (int t = 0; t < NSUB; ++t) {
+      for (int t = 0; t < NT; ++t) {
         if (t > 0) arrived(fc[t]);
         __builtin_amdgcn_sched_barrier(0);
-        if (t + 1 < NSUB) fetch(fc[t + 1], cs + ((t + 1) * SUB + pc) * BK, pc_sw);
-        else if (KIND == 0) prefetch(following);          // (behind the last slab: whatever is there)
+        if (t + 1 < NT) fetch(fc[t + 1], cs + ((t + 1) * SUB + pc) * BK, pc_sw);
+        else if (KIND == 0 || KIND == 3) prefetch(following);          // (behind the last slab: whatever is there)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < KS; ++e) x[t] = X::mfma(fc[t][e], fr[e], x[t]);
@@ -568,7 +624,7 @@ __device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, T* array, 
 // 16 rows of `array` in tile column col, negated, as flow_accumulate collects them.
 template <typename T>
 __device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const T* array, const int64_t r16, const int col,
-                                               typename Mfma<T>::acc_t (&x)[NSUB], const int lane) {
+                                               typename Mfma<T>::acc_t* x, const int lane) {
   const int l16 = lane & 15, g = lane >> 4;
   const __amdgpu_buffer_rsrc_t from = flow_rsrc(array + r16 * a.ld + (int64_t)col * LEAF);
   const unsigned off = (unsigned)(((int64_t)l16 * a.ld + 4 * g) * (int64_t)sizeof(T));
@@ -590,7 +646,7 @@ __device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const T* ar
 // Solve of this wavefront's 16 rows against the staged leaf, its operands fetched ahead: x from
 // minus the reduced rows to the solved ones, undivided.  (The operations of LeafOperands::solve.)
 template <typename T>
-__device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename Mfma<T>::acc_t (&x)[NSUB], const int lane) {
+__device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename Mfma<T>::acc_t* x, const int lane) {
   using X = Mfma<T>;
   using L = LeafOperands<T>;
   using acc_t = typename X::acc_t;
@@ -621,7 +677,7 @@ __device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename 
 // `out` (this wavefront's).
 template <typename T>
 __device__ __forceinline__ void flow_gather(const int* __restrict__ perm, const long long first,
-                                            typename Mfma<T>::acc_t (&x)[NSUB], T* __restrict__ out, const int lane) {
+                                            typename Mfma<T>::acc_t* x, T* __restrict__ out, const int lane) {
   constexpr int STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
   const int l16 = lane & 15, g = lane >> 4;
   int from[NSUB][4];
@@ -646,16 +702,15 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pa
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // of the pair's two tile rows those that this task has; the other one, whose entries left of
   // column j need not be final, is not read at all
-  const int first = j + 1 < a.ntc ? j + 2 : j + 1;
-  const bool low = 2 * pair >= first, high = 2 * pair + 1 < a.ntr;
-  if (!low && !high) return;                           // (the last pair, of an odd number of rows)
+  const int first = j + 1 < a.order.ntc ? j + 2 : j + 1;
+  const bool low = 2 * pair >= first, high = 2 * pair + 1 < a.order.ntr;
   const int rt0 = low ? 2 * pair : 2 * pair + 1, rt1 = high ? 2 * pair + 1 : 2 * pair;
-  const int64_t r16 = (int64_t)pair * FLOW_ROWS + wave * SUB;
+  const int64_t r16 = (int64_t)pair * FLOW_ROWS_HELD + wave * SUB;
   const bool mine = (wave < 4 ? low : high) && r16 < a.m;
   // general matrices: the rows of one array by those of the other, and solved against the leaf there
   T* const rows = a.P + (FORM == FLOW_GENERAL && array != 0 ? a.qoff : 0);
   T* const cols = a.P + (FORM == FLOW_GENERAL && array == 0 ? a.qoff : 0);
-  const int mine0 = FORM == FLOW_GENERAL ? array * a.ntr : 0, other0 = FORM == FLOW_GENERAL ? (1 - array) * a.ntr : 0;
+  const int mine0 = FORM == FLOW_GENERAL ? array * a.order.ntr : 0, other0 = FORM == FLOW_GENERAL ? (1 - array) * a.order.ntr : 0;
   FlowOperands<T> of;
   of.row[0] = rows + (int64_t)rt0 * LEAF * a.ld;
   of.row[1] = rows + (int64_t)rt1 * LEAF * a.ld;
@@ -695,6 +750,133 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pa
   if (tid == 0) {
     flow_publish(a, mine0 + rt0, j + 1);
     if (rt1 != rt0) flow_publish(a, mine0 + rt1, j + 1);
+  }
+}
+
+// A row task of columns j and j + 1, the tile rows of the pair whole and far from the diagonal: behind the
+// solve of the first column's tiles their products with tile (j + 1, j) come off the second's.
+template <typename T, FlowForm FORM>
+__device__ __forceinline__ void flow_row2_task(const FlowArgs<T>& a, const int pair, const int array, const int j,
+                                               T* __restrict__ lds, int* shared) {
+  using X = Mfma<T>;
+  using acc_t = typename X::acc_t;
+  using vec_t = typename X::vec_t;
+  using Sh = FlowShape<T, FORM>;
+  constexpr bool SCALED = FORM == FLOW_SPD;
+  constexpr int BK = X::BK, VEC = X::VEC, KS = BK / 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int rt0 = 2 * pair, rt1 = rt0 + 1 < a.order.ntr ? rt0 + 1 : rt0;
+  const int64_t r16 = (int64_t)pair * FLOW_ROWS_HELD + wave * SUB;
+  const bool mine = r16 < a.m;
+  T* const rows = a.P + (FORM == FLOW_GENERAL && array != 0 ? a.qoff : 0);
+  T* const cols = a.P + (FORM == FLOW_GENERAL && array == 0 ? a.qoff : 0);
+  const int mine0 = FORM == FLOW_GENERAL ? array * a.order.ntr : 0, other0 = FORM == FLOW_GENERAL ? (1 - array) * a.order.ntr : 0;
+  const bool gather = FORM == FLOW_PIVOT || (FORM == FLOW_GENERAL && array != 0);
+  FlowOperands<T> of;
+  of.row[0] = rows + (int64_t)rt0 * LEAF * a.ld;
+  of.row[1] = rows + (int64_t)rt1 * LEAF * a.ld;
+  of.left[0] = a.m - rt0 * LEAF;
+  of.left[1] = a.m - rt1 * LEAF;
+  of.col[0] = cols + (int64_t)j * LEAF * a.ld;
+  of.col[1] = of.col[0] + LEAF * a.ld;
+  of.counter[0] = mine0 + rt0;
+  of.counter[1] = mine0 + rt1;
+  of.counter[2] = other0 + j;
+  of.counter[3] = other0 + j + 1;
+  acc_t x[2 * NSUB], none[3];
+#pragma unroll
+  for (int b = 0; b < 2 * NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
+  if (mine) {
+    flow_load_rows(a, (const T*)rows, r16, j, x, lane);
+    flow_load_rows(a, (const T*)rows, r16, j + 1, x + NSUB, lane);
+  }
+  if (!flow_accumulate<T, FORM, 3>(a, of, j, mine, x, none, lds, shared)) return;
+  const LeafOperands<T> ops{lds};
+  T* const out = lds + Sh::ROW_OUT + wave * Sh::OUT;
+  T* const tile = lds + Sh::ROW_TILE;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (flow_wait_all(a, j + c, -1, -1, -1, j + c + 1, shared) < 0) return;
+    flow_stage_leaf(ops, (const T*)(cols + (int64_t)(j + c) * LEAF * (a.ld + 1)), a.ld, wave, lane);
+    T rinv[NSUB][4];
+    load_row((const T*)(a.dinv + (int64_t)(j + c) * LEAF), g, LEAF, rinv);
+    if (gather && mine)
+      flow_gather((const int*)(a.perm + (int64_t)(j + c) * LEAF), a.pivot0 + (long long)(j + c) * LEAF, x + c * NSUB, out, lane);
+    __syncthreads();
+    if (mine) {
+      flow_solve(ops, x + c * NSUB, lane);
+      T v[NSUB][4];
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[b][e] = x[c * NSUB + b][e] * rinv[b][e];
+      flow_store_rows(a, rows, r16, j + c, v, out, lane);
+    }
+    if (c == 0) {
+      // tile (j + 1, j) as slabs of a column operand
+      if (flow_wait_all(a, other0 + j + 1, -1, -1, -1, j + 1, shared) < 0) return;
+      const int rt = 8 * wave + (lane >> 3);
+      const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
+      const T* from = of.col[1] + (int64_t)rt * a.ld + (int64_t)j * LEAF + chunk * VEC;
+#pragma unroll
+      for (int p = 0; p < LEAF / BK; ++p) {
+        if (a.lines)
+          __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
+                                           0, 0);
+        else
+          __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
+                                           0, FLOW_DEVICE_SCOPE);
+      }
+      T d[NSUB][4];                    // the pivots in the order of the product
+      if constexpr (!SCALED) {
+#pragma unroll
+        for (int q = 0; q < NSUB; ++q)
+          load4((const T*)(a.dvec + (int64_t)j * LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the solved rows are out, the tile is in
+      __syncthreads();
+      if (tid == 0) {
+        flow_publish(a, mine0 + rt0, j + 1);
+        if (rt1 != rt0) flow_publish(a, mine0 + rt1, j + 1);
+      }
+      if (mine) {
+        const int pc = solve_col<T>(l16), sw = (pc >> 1) & 7;
+#pragma unroll
+        for (int p = 0; p < LEAF / BK; ++p) {
+          T fr[KS], fc[NSUB][KS];
+#pragma unroll
+          for (int h = 0; h < KS / VEC; ++h) {
+            const vec_t v = *reinterpret_cast<const vec_t*>(out + l16 * Sh::ROW_STRIDE + p * BK + g * KS + h * VEC);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) fr[h * VEC + e] = v[e];
+          }
+#pragma unroll
+          for (int t = 0; t < NSUB; ++t) {
+            const T* at = tile + (p * LEAF + t * SUB + pc) * BK;
+            const vec_t v0 = *reinterpret_cast<const vec_t*>(at + (((2 * g) ^ sw) * VEC));
+            const vec_t v1 = *reinterpret_cast<const vec_t*>(at + (((2 * g + 1) ^ sw) * VEC));
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { fc[t][e] = v0[e]; fc[t][VEC + e] = v1[e]; }
+          }
+          if constexpr (!SCALED) {
+#pragma unroll
+            for (int e = 0; e < KS; ++e) fr[e] *= d[p * (KS / 4) + e / 4][e % 4];
+          }
+#pragma unroll
+          for (int t = 0; t < NSUB; ++t)
+#pragma unroll
+            for (int e = 0; e < KS; ++e) x[NSUB + t] = X::mfma(fc[t][e], fr[e], x[NSUB + t]);
+        }
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    flow_publish(a, mine0 + rt0, j + 2);
+    if (rt1 != rt0) flow_publish(a, mine0 + rt1, j + 2);
   }
 }
 
@@ -910,9 +1092,9 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, cons
     of.col[0] = Q + (j0 - LEAF) * a.ld;
     of.col[1] = a.P + (j0 - LEAF) * a.ld;
     of.counter[0] = j;
-    of.counter[1] = a.ntr + j;
+    of.counter[1] = a.order.ntr + j;
     of.counter[2] = j - 1;
-    of.counter[3] = a.ntr + j - 1;
+    of.counter[3] = a.order.ntr + j - 1;
     if (!flow_accumulate<T, FLOW_GENERAL, 2>(a, of, j - 1, true, x, s, lds, shared)) return;
     if (flow_wait_all(a, j - 1, -1, -1, -1, j, shared) < 0) return;
     const LeafOperands<T> opsL{lds}, opsU{lds + LeafOperands<T>::ELEMS};
@@ -952,7 +1134,7 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, cons
   __syncthreads();
   if (tid == 64) {                                               // tiles (j, j - 1)
     flow_publish(a, j, j);
-    flow_publish(a, a.ntr + j, j);
+    flow_publish(a, a.order.ntr + j, j);
   }
 #pragma unroll
   for (int u = 0; u < 3; ++u)
@@ -968,7 +1150,7 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, cons
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    flow_publish(a, a.ntr + j, j + 1);
+    flow_publish(a, a.order.ntr + j, j + 1);
     flow_publish(a, j, j + 1);
   }
 }
@@ -980,19 +1162,21 @@ __global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a)
   if (threadIdx.x == 0)
     shared[1] = (int)__hip_atomic_fetch_add(&a.sync->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  const int t = __builtin_amdgcn_readfirstlane(shared[1]);
   int pair, array, j;
-  flow_task(a.ntr, a.ntc, FlowShape<T, FORM>::ARRAYS, t, pair, array, j);
+  const int kind = __builtin_amdgcn_readfirstlane(
+      (int)a.order.task(__builtin_amdgcn_readfirstlane(shared[1]), pair, array, j));
   pair = __builtin_amdgcn_readfirstlane(pair);
   array = __builtin_amdgcn_readfirstlane(array);
   j = __builtin_amdgcn_readfirstlane(j);
-  if (pair >= 0) {
+  if (kind == FLOW_DIAGONAL) {
+    if constexpr (FORM == FLOW_GENERAL) flow_diagonal_general<T>(a, j, lds, shared);
+    else flow_diagonal_task<T, FORM>(a, j, lds, shared);
+  } else if (kind == FLOW_ROWS2) {
+    __builtin_amdgcn_s_setprio(2);
+    flow_row2_task<T, FORM>(a, pair, array, j, lds, shared);
+  } else if (kind == FLOW_ROWS) {
     __builtin_amdgcn_s_setprio(2);
     flow_row_task<T, FORM>(a, pair, array, j, lds, shared);
-  } else if constexpr (FORM == FLOW_GENERAL) {
-    flow_diagonal_general<T>(a, j, lds, shared);
-  } else {
-    flow_diagonal_task<T, FORM>(a, j, lds, shared);
   }
 }
 

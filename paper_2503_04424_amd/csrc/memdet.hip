@@ -355,7 +355,7 @@ struct Launcher {
     const int arrays = qoff != 0 ? 2 : 1;
     return sync != nullptr && pb.S == nullptr && flow_words(m, arrays) <= sync_words && m <= INT32_MAX &&
            (w % LEAF == 0 || w == m) && (uint64_t)ld * sizeof(T) * LEAF < (1ull << 31) &&
-           flow_tasks((m + LEAF - 1) / LEAF, (w + LEAF - 1) / LEAF, arrays) <= INT32_MAX;
+           flow_order(m, w, arrays, 0).tasks() <= INT32_MAX;
   }
   int factor_cols_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip) {
     if (spd && (perm || qoff != 0)) return MDET_EINVAL;
@@ -381,12 +381,12 @@ struct Launcher {
     a.pivot0 = d0;
     a.flags = flags;
     a.sync = (FlowSync*)(sync + sync_used);
-    a.ntr = (int)((m + LEAF - 1) / LEAF);
-    a.ntc = (int)((w + LEAF - 1) / LEAF);
+    // row tasks of two columns while at least 28 pairs of tile rows are left (flow_two)
+    a.order = flow_order(m, w, arrays, flow_two(m, w, arrays));
     a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0 &&
               (uint64_t)qoff * sizeof(T) % 128 == 0;
     sync_used += words;
-    const dim3 grid((unsigned)flow_tasks(a.ntr, a.ntc, arrays)), block(FLOW_THREADS);
+    const dim3 grid((unsigned)a.order.tasks()), block(FLOW_THREADS);
     if (qoff != 0) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_GENERAL>), grid, block, 0, st, a);
     else if (perm) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_PIVOT>), grid, block, 0, st, a);
     else if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SPD>), grid, block, 0, st, a);
@@ -728,7 +728,12 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
     // is a chain of small kernels with little work each: the bulk update then runs
     // in rounds that leave them room, and starts once the next column's own update
     // (which wants the whole device) is through.
-    const int leave_free = lookahead && k + 2 < je ? L.leave_free_for(mk - wk) : -1;
+    // A launch that takes the whole block column wants whole compute units, which it does not get
+    // by that: the bulk update is one launch then, and starts beside the next column's own (n = 32768,
+    // fp64, 187 -> 178 ms; general n = 8192 9.9 -> 9.1; units set aside for the block column, 1.5 times its
+    // share of the work, 186 and 9.0).
+    const bool flow_next = L.flows(cols[k + 1].ld, n - (k + 1) * bs, pl.col_width(k + 1));
+    const int leave_free = lookahead && k + 2 < je && !flow_next ? L.leave_free_for(mk - wk) : -1;
     hipEvent_t ev_panel = nullptr;
     if (lookahead && k + 2 < je && leave_free < 0) {
       ev_panel = events.get();
@@ -741,9 +746,8 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
       touch(s0, j);
       const T* B = cols[k].base + (j - k) * bs * cols[k].ld;
       const FusedLeaf<T> fl = L.fused_leaf(pl.col_width(j), j * bs);
-      const bool flow = L.flows(cols[j].ld, n - j * bs, pl.col_width(j));
       rc = L.update(s0, cols[j].base, cols[j].ld, left(j), lda_k, B, cols[k].ld, L.dvec + k * bs,
-                    n - j * bs, pl.col_width(j), wk, true, true, flow ? nullptr : &fl, -1, Wk != nullptr);
+                    n - j * bs, pl.col_width(j), wk, true, true, flow_next ? nullptr : &fl, -1, Wk != nullptr);
       if (rc != MDET_OK) return rc;
     }
     if (lookahead && k + 2 < je && leave_free >= 0) {
@@ -792,21 +796,18 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
 // The block columns in which a dense matrix of this plan is factored: up to 16 of the plan's at a
 // time where a launch that takes them all (panel_flow_kernel) beats block columns whose bulk
 // update runs beside the next one's factorisation.  Measured, ms, one launch against block
-// columns, symmetric / positive definite: fp64 n = 2900 0.66 / 0.62 against 1.05 / 1.01, n = 8192
-// 4.02 / 3.79 against 5.22 / 4.97, n = 12288 12.8 / 12.3 against 15.3 / 14.5, n = 16384 29.9 / 29.4
-// against 28.0 / 26.6; fp32 n = 10000 4.6 / 3.7 against 5.8 / 5.5, n = 16384 15.4 / 13.7 against 14.9 /
-// 14.3: the launch reads each operand out of memory once for every 64 columns, which from about
-// there on no cache holds; pivots from inside a leaf, n = 12288 12.6; general matrices (twice the
-// data) fp64 n = 6144 5.5 against 7.0, n = 8192 11.9 against 11.5, fp32 6144 3.1 against 4.3, 8192 6.9
-// against 6.7.  16 is how many block columns the library makes of such a matrix by
+// columns: symmetric fp64 n = 8192 3.8 against 5.4, 12288 11.3 / 14.2, 16384 25.7 / 27.2, 24000 78.5 / 83.9,
+// fp32 n = 10000 3.6 / 5.1, 24000 39.5 / 42.7; positive definite fp64 24000 76.7 / 79.6, 32768 189 / 183; pivots
+// from inside a leaf 12288 11.6 / 15.7; general 8192 7.8 / 10.0, 16384 54.3 / 53.6, 20480 101 / 109.  From
+// 24576 on the launch is bound by the operands it reads out of memory, and the pivot-scaled copies
+// of block columns pay (make_plan).  16 is how many block columns the library makes of a matrix by
 // itself; a caller who asks for more of them, and for look-ahead between them, gets a launch for
 // every 16.  With MDET_FLAG_PROFILE the updates between block columns are what is looked at.
 template <typename T>
 static Plan dense_plan(const Launcher<T>& L, const Plan& pl, int64_t ld, bool lookahead) {
-  constexpr int64_t SYMMETRIC = sizeof(T) == 8 ? 14336 : 16384, GENERAL = sizeof(T) == 8 ? 7168 : 8192;
-  const int64_t ONE_LAUNCH = L.qoff != 0 ? GENERAL : SYMMETRIC;
+  constexpr int64_t ONE_LAUNCH = 24576;
   Plan f = pl;
-  if (pl.T < 2 || pl.n > ONE_LAUNCH || L.profile || L.wbuf[0] || !L.flows(ld, pl.n, pl.n)) return f;
+  if (pl.T < 2 || pl.n >= ONE_LAUNCH || L.profile || L.wbuf[0] || !L.flows(ld, pl.n, pl.n)) return f;
   f.bs = lookahead ? 16 * pl.bs : round_up(pl.n, LEAF);
   f.T = (f.n + f.bs - 1) / f.bs;
   return f;
