@@ -848,6 +848,41 @@ struct DeviceOut {
   DevFlags flags;
 };
 
+// Pinned host memory that kernels leave a call's results in: 64 places of 64 bytes, one to a call at
+// a time, for the life of the process.  None free (or to be had): the results are copied.
+struct ResultPlace {
+  static constexpr int COUNT = 64;
+  int index = -1;
+  unsigned long long* p = nullptr;
+  ResultPlace() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (!pool && !tried) {
+      tried = true;
+      if (hipHostMalloc(&pool, COUNT * 64, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        pool = nullptr;
+      }
+    }
+    if (!pool || used == ~0ull) return;
+    index = __builtin_ctzll(~used);
+    used |= 1ull << index;
+    p = (unsigned long long*)((char*)pool + 64 * index);
+  }
+  ~ResultPlace() {
+    if (index < 0) return;
+    std::lock_guard<std::mutex> lk(g_mu);
+    used &= ~(1ull << index);
+  }
+  ResultPlace(const ResultPlace&) = delete;
+  ResultPlace& operator=(const ResultPlace&) = delete;
+  static void* pool;
+  static bool tried;
+  static unsigned long long used;
+};
+void* ResultPlace::pool = nullptr;
+bool ResultPlace::tried = false;
+unsigned long long ResultPlace::used = 0;
+
 static int finish_result(const DeviceOut& o, mdet_result* r) {
   r->negative_pivots = (int64_t)o.out[2];
   if (o.flags.first_bad != ~0ull) {
@@ -1210,8 +1245,20 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
   std::vector<ColRef<T>> cols((size_t)by.T);
   for (int64_t j = 0; j < by.T; ++j) cols[j] = {W + j * by.bs * ldw + j * by.bs, ldw};
   rc = factor_resident(L, by, cols, 0, by.T, true, lookahead, s0, s1, events);
+  std::unique_ptr<ResultPlace> place;
+  if (rc == MDET_OK && pl.T > 0 && pl.T <= FINISH_BLOCKS && pl.n < 24576) {
+    place.reset(new ResultPlace);
+    if (!place->p) place.reset();
+  }
   if (rc == MDET_OK) {
-    L.reduce(s0, pl.n, pl.bs, pl.T, partial, out, running);
+    if (place) {
+      hipLaunchKernelGGL((logdet_finish_kernel<T>), dim3(1), dim3(FINISH_SETS * RED_THREADS), 0, s0, (const T*)L.dvec, pl.n,
+                         pl.bs, (int)pl.T, out, (const unsigned long long*)L.flags, place->p);
+      MDET_HIP(fail, hipGetLastError());
+      ++L.launches;
+    } else {
+      L.reduce(s0, pl.n, pl.bs, pl.T, partial, out, running);
+    }
     if (Q && !pl.need_copy) {
       // the caller's array is the output: U back above the diagonal
       hipLaunchKernelGGL((transpose_strict_kernel<T>), dim3((unsigned)((int64_t)nb64 * (nb64 + 1) / 2)),
@@ -1222,9 +1269,10 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
   }
   DeviceOut o;
   std::memset(&o, 0, sizeof(o));
-  if (rc == MDET_OK) MDET_HIP(fail, hipMemcpyAsync(&o, out, sizeof(o), hipMemcpyDeviceToHost, s0));
+  if (rc == MDET_OK && !place) MDET_HIP(fail, hipMemcpyAsync(&o, out, sizeof(o), hipMemcpyDeviceToHost, s0));
   MDET_HIP(fail, hipStreamSynchronize(s1));
   MDET_HIP(fail, hipStreamSynchronize(s0));
+  if (place) std::memcpy(&o, place->p, sizeof(o));
   ws.keep = fail.ok();
   res->flops = 2.0 * L.fma;
   res->kernel_launches = L.launches;
