@@ -117,3 +117,52 @@ def test_pivoting_forms_around_tile_edges(n, dtype, form):
         right = s[k:e, e:][q - k]
         assert e == n or np.abs(l11 * d[k:e] @ u12 - right).max() < 8 * tol
         s[e:, e:] -= l21 * d[k:e] @ u12
+
+
+@pytest.mark.parametrize("form", ["sym", "gen"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [129, 323])
+def test_copy_without_room_for_long_rows(n, dtype, form):
+    """The least budget that the plan accepts, and a workspace of that size, leave no room for rows of the copy
+    on 128-byte lines: same bits by the route that reads past the caches."""
+    import paper_2503_04424_amd as M
+    M.load()
+    flags = M.FLAG_GENERAL if form == "gen" else 0
+    roomy = M.mdet_workspace_query(n, dtype, 64, 0, False, flags, True)[0]
+    low, high = 0, roomy
+    while high - low > 1:
+        mid = (low + high) // 2
+        try:
+            M.mdet_workspace_query(n, dtype, 64, mid, False, flags, True)
+            high = mid
+        except M.MemdetError:
+            low = mid
+    assert high < roomy
+    td = torch.float64 if dtype == "f64" else torch.float32
+    rng = np.random.default_rng(n)
+    a = rng.uniform(-1, 1, (n, n)) / (2 * n)
+    a = a + a.T + np.diag(rng.uniform(1, 4, n))
+    a = torch.from_numpy(a).to(td).cuda()
+    own = torch.empty(high, dtype=torch.uint8, device="cuda")
+    got = []
+    for kw in ({}, {"mem_budget": high}, {"workspace": own}):
+        diag = torch.empty(n, dtype=td, device="cuda")
+        r = M.mdet_logdet_device(a, block_size=64, flags=flags, diag=diag, **kw)
+        assert r.status == 0
+        got.append((diag.cpu().numpy(), r.logabsdet, r.sign))
+    for d, v, s in got[1:]:
+        assert np.array_equal(d, got[0][0]) and (v, s) == got[0][1:]
+
+
+@pytest.mark.parametrize("n", [1, 64, 1023, 1024, 1025, 1040])
+@pytest.mark.parametrize("bs", [64, 128])
+def test_results_of_few_and_many_blocks(n, bs):
+    """The sums of log|d| over block columns, by the one launch of up to 16 of them and by the two of more:
+    a diagonal matrix, whose pivots are exact and one of which is not positive."""
+    import paper_2503_04424_amd as M
+    M.load()
+    d = np.random.default_rng(n).uniform(0.5, 4, n)
+    d[n // 2] *= -1
+    r = M.mdet_logdet_device(torch.from_numpy(np.diag(d)).cuda(), block_size=bs)
+    want = float(np.sum(np.log(np.abs(d).astype(np.longdouble))))
+    assert (r.status, r.sign, r.negative_pivots) == (0, -1, 1) and abs(r.logabsdet - want) <= 4e-16 * n
