@@ -1119,7 +1119,7 @@ static void reset_flags(Launcher<T>& L, hipStream_t st) {
 }
 
 // The pivots and the permutation to where the caller wants them, in one launch if that is memory of
-// a device (two copies by the runtime are two launches and 10 us of a call; n = 512).
+// this device (two copies by the runtime are two launches and 10 us of a call; n = 512).
 template <typename T>
 __global__ void copy_out_kernel(const T* __restrict__ dvec, T* __restrict__ diag, const int* __restrict__ perm,
                                 int* __restrict__ perm_out, int64_t n) {
@@ -1128,10 +1128,15 @@ __global__ void copy_out_kernel(const T* __restrict__ dvec, T* __restrict__ diag
   if (diag) diag[i] = dvec[i];
   if (perm_out) perm_out[i] = perm[i];
 }
+// (Another device's memory is not for a kernel of this one, which may have no access to it.)
 static bool device_memory(const void* p) {
   hipPointerAttribute_t a;
-  if (hipPointerGetAttributes(&a, p) != hipSuccess) { (void)hipGetLastError(); return false; }
-  return a.type == hipMemoryTypeDevice;
+  int current = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&current) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == current;
 }
 template <typename T>
 static void copy_out(Launcher<T>& L, hipStream_t st, int64_t n, T* diag, int32_t* perm_out) {
