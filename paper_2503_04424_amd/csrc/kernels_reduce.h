@@ -151,19 +151,23 @@ __global__ __launch_bounds__(256) void widen_lower_kernel(const S* __restrict__ 
   for (int64_t j = threadIdx.x; j < end; j += 256) dst[i * ldd + j] = widen_exact(src[i * lds + j]);
 }
 
-// The same without a change of type, V elements (rows of whole V) at a time: half of what copying the
-// square moves.
-template <typename E, int V>
-__global__ __launch_bounds__(256) void copy_lower_kernel(const E* __restrict__ src, int64_t lds, E* __restrict__ dst,
+// The same without a change of type, pieces E of several elements at a time (rows start on whole pieces):
+// half of what copying the square moves.  A row's last elements that make no whole piece go one by
+// one: behind the last row's there need not be any memory.
+template <typename T, typename E>
+__global__ __launch_bounds__(256) void copy_lower_kernel(const T* __restrict__ src, int64_t lds, T* __restrict__ dst,
                                                          int64_t ldd, int64_t n) {
+  constexpr int V = sizeof(E) / sizeof(T);
   const int64_t i = blockIdx.x;
   int64_t end = (i / 64 + 1) * 64;
   if (end > n) end = n;
-  end = (end + V - 1) / V;             // (no further than lds, which is whole)
-  const E* from = src + i * lds;
-  E* to = dst + i * ldd;
+  const int64_t pieces = end / V;
+  const E* from = reinterpret_cast<const E*>(src + i * lds);
+  E* to = reinterpret_cast<E*>(dst + i * ldd);
 #pragma unroll 4
-  for (int64_t j = threadIdx.x; j < end; j += 256) to[j] = from[j];
+  for (int64_t j = threadIdx.x; j < pieces; j += 256) to[j] = from[j];
+  const int64_t j = pieces * V + threadIdx.x;
+  if (j < end) dst[i * ldd + j] = src[i * lds + j];
 }
 
 // widen_lower_kernel for a rows x cols rectangle (a piece of a block column on its way from host

@@ -1215,12 +1215,11 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
                                       hipMemcpyDeviceToDevice, s0));
     } else {
       const dim3 grid((unsigned)pl.n), block(256);
-      if (ld % (16 / (int)sizeof(T)) == 0)
-        hipLaunchKernelGGL((copy_lower_kernel<typename Mfma<T>::vec_t, Mfma<T>::VEC>), grid, block, 0, s0,
-                           (const typename Mfma<T>::vec_t*)dA, ld / Mfma<T>::VEC, (typename Mfma<T>::vec_t*)W,
-                           ldw / Mfma<T>::VEC, pl.n);
+      if (ld % Mfma<T>::VEC == 0)
+        hipLaunchKernelGGL((copy_lower_kernel<T, typename Mfma<T>::vec_t>), grid, block, 0, s0, (const T*)dA, ld, W, ldw,
+                           pl.n);
       else
-        hipLaunchKernelGGL((copy_lower_kernel<T, 1>), grid, block, 0, s0, (const T*)dA, ld, W, ldw, pl.n);
+        hipLaunchKernelGGL((copy_lower_kernel<T, T>), grid, block, 0, s0, (const T*)dA, ld, W, ldw, pl.n);
       MDET_HIP(fail, hipGetLastError());
     }
   }

@@ -59,3 +59,52 @@ int main() {
   return bad + (device_memory(nullptr) ? 1 : 0);
 }
 """)
+
+
+def test_copies_read_no_further_than_the_last_entry(tmp_path):
+    """A matrix whose last entry is the last one of its memory (rows longer than the order: a view of some
+    columns): behind it lies a page that cannot be read.  Rows of pieces of 16 bytes, orders around them and
+    around leaves; what arrives is the lower part up to the end of each row's leaf on the diagonal."""
+    run(tmp_path, """
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include <sys/mman.h>
+#define __global__
+#define __launch_bounds__(x)
+#define __restrict__
+struct Index { unsigned x; };
+static Index blockIdx, threadIdx;
+struct f64x2 { double v[2]; };
+struct f32x4 { float v[4]; };
+""" + source_of("kernels_reduce.h", r"template <[^>]*>\n__global__[^\n]*\bcopy_lower_kernel\(") + """
+template <typename T, typename E>
+int check(int64_t n, int64_t ld) {
+  const size_t page = 4096, bytes = ((n - 1) * ld + n) * sizeof(T), room = (bytes + page - 1) / page * page;
+  char* base = (char*)mmap(nullptr, room + page, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0);
+  if (base == MAP_FAILED || mprotect(base + room, page, PROT_NONE)) return 1;
+  T* src = (T*)(base + room - bytes);
+  for (int64_t i = 0; i < n; ++i)
+    for (int64_t j = 0; j < n; ++j) src[i * ld + j] = T(1 + i * n + j);
+  const int64_t ldd = (n + 31) / 32 * 32;
+  std::vector<T> dst((size_t)(n * ldd), T(-1));
+  std::printf("n %ld ld %ld size %zu\\n", (long)n, (long)ld, sizeof(T));
+  std::fflush(stdout);
+  for (blockIdx.x = 0; blockIdx.x < n; ++blockIdx.x)
+    for (threadIdx.x = 0; threadIdx.x < 256; ++threadIdx.x) copy_lower_kernel<T, E>(src, ld, dst.data(), ldd, n);
+  int bad = 0;
+  for (int64_t i = 0; i < n; ++i)
+    for (int64_t j = 0; j < n && j < (i / 64 + 1) * 64; ++j) bad += dst[i * ldd + j] != T(1 + i * n + j);
+  munmap(base, room + page);
+  return bad;
+}
+int main() {
+  int bad = 0;
+  for (int64_t n : {1, 2, 3, 5, 63, 64, 65, 66, 127, 129, 130, 131, 257}) {
+    bad += check<double, f64x2>(n, (n + 1) / 2 * 2) + check<double, f64x2>(n, (n + 1) / 2 * 2 + 2) + check<double, double>(n, n);
+    bad += check<float, f32x4>(n, (n + 3) / 4 * 4) + check<float, f32x4>(n, (n + 3) / 4 * 4 + 4) + check<float, float>(n, n);
+  }
+  return bad != 0;
+}
+""")
