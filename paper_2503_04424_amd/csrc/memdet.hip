@@ -540,6 +540,26 @@ struct Launcher {
     fail->check(hipEventRecord(prof_ref, st));
   }
 
+  // Whether the rows below a diagonal block follow its groups of steps on a stream of their own, up to two
+  // groups behind, with two buffers for the group's leaf: the steps of a group keep one compute unit
+  // busy (w <= PB_GROUP_ROWS), and the next group needs of this one only S.  Events that order only this
+  // device's streams cost 5 us each all the same: from three groups on, and with three only where
+  // there is something to hide.  That stream also carries the bulk update by the block column
+  // before, which a narrow one with many rows below it waits for longer than it gains; and
+  // where every step is a launch (w > PB_GROUP_ROWS), 64 of them to a group, events in between cost
+  // 20 to 40 us a group.  Measured, ms, always on the main stream / always aside / by this rule:
+  // fp64 n = 1500 b = 64 2.43 2.78 2.43, 128 2.44 2.51 2.44, 192 2.49 2.40 2.38, 256 2.53 2.37 2.36; n =
+  // 3000 b = 256 5.20 4.82 4.79, 512 6.48 5.81 5.80; n = 8192 b = 192 15.71 15.73 15.24, 512 19.75 18.46
+  // 18.49; n = 16384 b = 256 50.2 51.1 49.9, 512 59.3 56.9 57.1; n = 20480 b = 256 79.2 84.2 78.8; fp32 n =
+  // 3000 b = 256 4.22 4.00 4.01, n = 20480 b = 512 53.2 53.8 52.4; steps as launches, fp64 n = 1500 b =
+  // 640 9.28 9.85 9.28, n = 4096 b = 2048 29.97 30.90 29.97, n = 8192 b = 1024 65.7 64.3 64.1, fp32 n = 3000 b =
+  // 1024 18.6 19.7 18.7, n = 16384 128.4 125.9 126.2.  A stream for these rows alone: n = 8192 b = 512
+  // 18.2, but n = 3000 b = 256 4.91 and every b above 512 as on the main stream.
+  static bool follows_aside(int64_t w, int64_t below) {
+    if (w > PB_GROUP_ROWS) return below * (int64_t)sizeof(T) >= 24576;
+    return w > 2 * LEAF && below > (w > 3 * LEAF ? 0 : 256) && below <= 32 * w;
+  }
+
   // A whole block column with the pivots taken from anywhere on its w x w diagonal block
   // (MDET_FLAG_PIVOT_BLOCK; the scheme is described in kernels_pivot_block.h).  Same
   // arguments and same result layout as factor_cols: L and D in pivot order in place,
@@ -559,11 +579,7 @@ struct Launcher {
     launches += 2;
     int cur = 0;
     int rc = MDET_OK;
-    // The steps of a group keep one compute unit busy (w <= PB_GROUP_ROWS), and the next group needs
-    // of this one only S: the rows below follow on a stream of their own, up to two groups behind,
-    // with two buffers for the group's leaf (n = 3000, fp64, 12 blocks of 256: 5.27 -> 4.94 ms; with
-    // events that write the caches back to the host 5.16).
-    const hipStream_t sy = pb.beside && below > 0 ? pb.beside : st;
+    const hipStream_t sy = pb.beside && follows_aside(w, below) ? pb.beside : st;
     for (int64_t c0 = 0; c0 < w && rc == MDET_OK; c0 += LEAF) {
       const int lw = (int)(w - c0 < LEAF ? w - c0 : LEAF);
       const int turn = (int)(c0 / LEAF & 1);
