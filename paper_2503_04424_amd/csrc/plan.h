@@ -192,7 +192,13 @@ inline int make_plan(const mdet_params& p, bool device_input, int64_t ld, Plan& 
     // rows of a copy start on 128-byte lines, unless a budget has no room for that (panel_flow_kernel
     // then reads its operands past the caches: n = 5555, fp64, 1.80 ms, instead of 1.65 at n = 5552)
     place_copy(pl, round_up(p.n > 0 ? p.n : 1, 128 / pl.beta), ld);
-    if (budget && pl.dev_bytes > budget) place_copy(pl, narrow_copy_ld(pl), ld);
+    // (or for them beside the pivot-scaled copies, which with a budget are there because they were asked for)
+    if (budget && pl.dev_bytes + wcopy > budget) {
+      const bool fits = pl.dev_bytes <= budget;
+      const int64_t wide = pl.copy_ld;
+      place_copy(pl, narrow_copy_ld(pl), ld);
+      if (fits && pl.dev_bytes + wcopy > budget) place_copy(pl, wide, ld);
+    }
     pl.out_of_core = false;
     if (budget && pl.dev_bytes > budget) return MDET_EBUDGET;
     if (wcopy && (!budget || pl.dev_bytes + wcopy <= budget)) {

@@ -108,3 +108,24 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_scaled_copy_that_was_asked_for_goes_before_long_rows():
+    """A budget with room for the pivot-scaled copies beside a copy of the matrix with its shortest rows holds
+    them; more room, and the rows start on 128-byte lines."""
+    import paper_2503_04424_amd as M
+    M.load()
+    for n, dtype, bs in [(323, "f64", 64), (323, "f32", 64), (1000, "f32", 128), (1001, "f64", 256)]:
+        ask = lambda budget, flags=M.FLAG_SCALED_COPY: M.mdet_workspace_query(n, dtype, bs, budget, False, flags, True)[0]
+        scaled = ask(0) - ask(0, 0)
+        low, high = 0, ask(0, 0)
+        while high - low > 1:
+            mid = (low + high) // 2
+            try:
+                ask(mid, 0)
+                high = mid
+            except M.MemdetError:
+                low = mid
+        assert scaled > 0 and high < ask(0, 0)
+        assert ask(high + scaled) == high + scaled and ask(ask(0)) == ask(0) and ask(ask(0) - 1) == high + scaled
+        assert ask(high) == high and ask(high + scaled - 1) <= high + scaled - 1
