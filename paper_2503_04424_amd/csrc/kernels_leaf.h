@@ -1038,9 +1038,6 @@ __global__ __launch_bounds__(256) void transpose_strict_kernel(const T* __restri
 // perm (or null): the leaf was factored with pivoting; perm[j] - perm0 is the column of
 // the panel that belongs at position j.  A wavefront reads all 64 columns of its rows
 // before it writes any of them.
-// fix_src (or null): the launch has one workgroup more than its rows need, and that one
-// copies the 64 x 64 row-major block at fix_src to fix_dst (leading dimension fix_ld), a
-// block outside this launch's own rows and columns.
 constexpr int SOLVE_ROWS = 64;   // rows per workgroup
 
 // Column of a sub-block that output row i of a 16 x 16 product stands for: accumulator register
@@ -1101,7 +1098,7 @@ __device__ __forceinline__ void store_row(T* p, const int g, const int w, const 
 // the inverses of the diagonal sub-blocks.  The four wavefronts of a workgroup fetch them
 // between them, and keep them in LDS in the order in which they are used, 16 bytes a lane: held
 // by each wavefront in registers, four times the traffic and 80 registers more, a solve of
-// fp64 rows took 7.5 us, and the pair kernel spilled.
+// fp64 rows took 7.5 us.
 template <typename T>
 struct LeafOperands {
   static constexpr int COUNT = NSUB * (NSUB - 1) / 2 + NSUB;      // sub-blocks: minus L, then the inverses
@@ -1162,9 +1159,8 @@ struct LeafOperands {
       for (int e = 0; e < VEC; ++e) v[VEC * h + e] = o[e];
     }
   }
-  // x[b] of N sets of 16 rows <- their W_b (undivided)
-  template <int N>
-  __device__ __forceinline__ void solve(typename Mfma<T>::acc_t (&x)[N][NSUB], const int lane) const {
+  // x[b] of 16 rows <- their W_b (undivided)
+  __device__ __forceinline__ void solve(typename Mfma<T>::acc_t (&x)[NSUB], const int lane) const {
     using X = Mfma<T>;
     using acc_t = typename X::acc_t;
 #pragma unroll
@@ -1174,20 +1170,13 @@ struct LeafOperands {
       for (int p = 0; p < b; ++p) {
         fetch(lower(b, p), lane, op);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int n = 0; n < N; ++n) x[n][b] = X::mfma(op[s], x[n][p][s], x[n][b]);
+        for (int s = 0; s < 4; ++s) x[b] = X::mfma(op[s], x[p][s], x[b]);
       }
       fetch(COUNT - NSUB + b, lane, op);
-      acc_t wb[N];
+      acc_t wb = acc_t{0, 0, 0, 0};
 #pragma unroll
-      for (int n = 0; n < N; ++n) wb[n] = acc_t{0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int n = 0; n < N; ++n) wb[n] = X::mfma(op[s], x[n][b][s], wb[n]);
-#pragma unroll
-      for (int n = 0; n < N; ++n) x[n][b] = wb[n];
+      for (int s = 0; s < 4; ++s) wb = X::mfma(op[s], x[b][s], wb);
+      x[b] = wb;
     }
   }
 };
@@ -1195,9 +1184,7 @@ struct LeafOperands {
 template <typename T>
 __device__ __forceinline__ void leaf_solve_body(
     T* __restrict__ Xg, int64_t ld, int m, int w, const T* __restrict__ Lleaf, int64_t ldl,
-    const T* __restrict__ dinv, const T* __restrict__ linv, T* __restrict__ Wg, int64_t ldw,
-    const T* __restrict__ dvec, int wfrom, const int* __restrict__ perm, int perm0,
-    const T* __restrict__ fix_src, T* __restrict__ fix_dst, int64_t fix_ld) {
+    const T* __restrict__ dinv, const T* __restrict__ linv, const int* __restrict__ perm, int perm0) {
   using acc_t = typename Mfma<T>::acc_t;
   __builtin_amdgcn_s_setprio(2);                // on the chain of dependent launches
   __shared__ __attribute__((aligned(16))) T lds[LeafOperands<T>::ELEMS];
@@ -1205,23 +1192,10 @@ __device__ __forceinline__ void leaf_solve_body(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
 
-  // a 64 x 64 block that an earlier launch left beside its place (leaf_pair_kernel): the
-  // launch then has one workgroup more, which does only this
-  if (fix_src != nullptr && blockIdx.x == gridDim.x - 1) {
-    T v[LEAF * LEAF / 256];
-#pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) v[q] = fix_src[q * 256 + tid];
-#pragma unroll
-    for (int q = 0; q < LEAF * LEAF / 256; ++q) {
-      const int e = q * 256 + tid;
-      fix_dst[(int64_t)(e >> 6) * fix_ld + (e & 63)] = v[q];
-    }
-    return;
-  }
   const int64_t row = ((int64_t)blockIdx.x * 4 + wave) * SUB + l16;
   const bool in = row < m;
   T* xrow = Xg + row * ld;
-  acc_t x[1][NSUB];
+  acc_t x[NSUB];
   {
     T v[NSUB][4];
 #pragma unroll
@@ -1243,7 +1217,7 @@ __device__ __forceinline__ void leaf_solve_body(
 #pragma unroll
     for (int b = 0; b < NSUB; ++b)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[0][b][e] = v[b][e];
+      for (int e = 0; e < 4; ++e) x[b][e] = v[b][e];
   }
   LeafOperands<T> ops{lds};
   ops.stage(Lleaf, ldl, w, linv, wave, lane);
@@ -1253,34 +1227,22 @@ __device__ __forceinline__ void leaf_solve_body(
   // with a permutation a store below may hit an entry that another lane of this wavefront
   // loads above: every load has returned before the first store is issued
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  ops.template solve<1>(x, lane);
+  ops.solve(x, lane);
   if (in) {
     T v[NSUB][4];
 #pragma unroll
     for (int b = 0; b < NSUB; ++b)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[b][e] = x[0][b][e] * rinv[b][e];
+      for (int e = 0; e < 4; ++e) v[b][e] = x[b][e] * rinv[b][e];
     store_row(xrow, g, w, v);
-    if (Wg != nullptr && row >= wfrom) {
-      T d[NSUB][4];
-      load_row(dvec, g, w, d);
-#pragma unroll
-      for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[b][e] *= d[b][e];
-      store_row(Wg + row * ldw, g, w, v);
-    }
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void leaf_solve_kernel(
     T* __restrict__ Xg, int64_t ld, int m, int w, const T* __restrict__ Lleaf, int64_t ldl,
-    const T* __restrict__ dinv, const T* __restrict__ linv, T* __restrict__ Wg, int64_t ldw,
-    const T* __restrict__ dvec, int wfrom, const int* __restrict__ perm, int perm0,
-    const T* __restrict__ fix_src, T* __restrict__ fix_dst, int64_t fix_ld) {
-  leaf_solve_body<T>(Xg, ld, m, w, Lleaf, ldl, dinv, linv, Wg, ldw, dvec, wfrom, perm, perm0, fix_src, fix_dst,
-                     fix_ld);
+    const T* __restrict__ dinv, const T* __restrict__ linv, const int* __restrict__ perm, int perm0) {
+  leaf_solve_body<T>(Xg, ld, m, w, Lleaf, ldl, dinv, linv, perm, perm0);
 }
 
 // The rows below a leaf of a general matrix, both halves in one launch with two rows of
@@ -1291,12 +1253,10 @@ __global__ __launch_bounds__(256) void leaf_solve_kernel(
 template <typename T>
 __global__ __launch_bounds__(256) void leaf_solve_general_kernel(
     T* Xg, int64_t ld, int m, int w, const T* Lleaf, const T* __restrict__ dinv,
-    const T* __restrict__ linvL, const T* __restrict__ linvU, const T* __restrict__ dvec,
-    const int* __restrict__ perm, int perm0, int64_t qoff) {
+    const T* __restrict__ linvL, const T* __restrict__ linvU, const int* __restrict__ perm, int perm0, int64_t qoff) {
   const bool upper = blockIdx.y != 0;
   leaf_solve_body<T>(upper ? Xg + qoff : Xg, ld, m, w, upper ? Lleaf : Lleaf + qoff, ld, dinv,
-                     upper ? linvL : linvU, (T*)nullptr, (int64_t)0, dvec, 0,
-                     upper ? perm : (const int*)nullptr, perm0, (const T*)nullptr, (T*)nullptr, (int64_t)0);
+                     upper ? linvL : linvU, upper ? perm : (const int*)nullptr, perm0);
 }
 
 }  // namespace mdet

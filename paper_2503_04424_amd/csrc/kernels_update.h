@@ -18,9 +18,8 @@
 // current one is multiplied.  The scaling by -d is applied to the A fragments as
 // they are read from LDS; the accumulators are seeded with C.
 //
-// Also here, because they end with the same hand-over of the next leaf:
-// leaf_update_kernel (K = 64, one shot from LDS) and leaf_pair_kernel (a leaf's solve,
-// the K = 64 update by it and the next leaf's factorisation in one launch).
+// Also here, because it ends with the same hand-over of the next leaf: leaf_update_kernel
+// (K = 64, one shot from LDS).
 //
 // The *_general_kernel names run the same bodies for a general matrix (Sec. 2.2, Eq. 1:
 // M = P L U) kept as two lower-triangular arrays, one row of workgroups per array.
@@ -439,8 +438,9 @@ template <typename T, bool SCALED = false>
 __global__ __launch_bounds__(UPD_THREADS, 2) void trailing_update_kernel(
     T* __restrict__ C, int64_t ldc, const T* __restrict__ A, int64_t lda,
     const T* __restrict__ B, int64_t ldb, const T* __restrict__ d, int M, int N, int K, int nsn,
-    int swl, int lower, int per, int k0, FusedLeaf<T> fl) {
-  schur_update_body<T, 4, SCALED>(C, ldc, A, lda, B, ldb, d, M, N, K, nsn, swl, lower != 0, per, k0, fl);
+    int swl, int lower, int per, int k0) {
+  const FusedLeaf<T> none{0, nullptr, nullptr, nullptr, 0, nullptr, 0};
+  schur_update_body<T, 4, SCALED>(C, ldc, A, lda, B, ldb, d, M, N, K, nsn, swl, lower != 0, per, k0, none);
 }
 // The trailing update of a short block column: with 128 x 128 blocks it would have
 // fewer workgroups than the device has compute units and last as long as one
@@ -449,8 +449,9 @@ template <typename T, bool SCALED = false>
 __global__ __launch_bounds__(UPD_THREADS) void trailing_update64_kernel(
     T* __restrict__ C, int64_t ldc, const T* __restrict__ A, int64_t lda,
     const T* __restrict__ B, int64_t ldb, const T* __restrict__ d, int M, int N, int K, int nsn,
-    int swl, int lower, int per, int k0, FusedLeaf<T> fl) {
-  schur_update_body<T, 2, SCALED>(C, ldc, A, lda, B, ldb, d, M, N, K, nsn, swl, lower != 0, per, k0, fl);
+    int swl, int lower, int per, int k0) {
+  const FusedLeaf<T> none{0, nullptr, nullptr, nullptr, 0, nullptr, 0};
+  schur_update_body<T, 2, SCALED>(C, ldc, A, lda, B, ldb, d, M, N, K, nsn, swl, lower != 0, per, k0, none);
 }
 template <typename T, bool SCALED = false>
 __global__ __launch_bounds__(UPD_THREADS, 2) void panel_update_kernel(
@@ -653,175 +654,5 @@ MDET_GENERAL_UPDATE_KERNEL(trailing_update64_general_kernel, 2, 1, 0)
 MDET_GENERAL_UPDATE_KERNEL(panel_update_general_kernel, 4, 2, 1)
 MDET_GENERAL_UPDATE_KERNEL(panel_update64_general_kernel, 2, 1, 1)
 #undef MDET_GENERAL_UPDATE_KERNEL
-
-// Two leaves side by side (a 128-column strip of a block column), the first one
-// factored: one launch solves the rows below the first leaf against it, updates the
-// second leaf's columns of those rows with the result (K = 64), and factors the second
-// leaf.  Separately these are a leaf_solve_kernel and a leaf_update_kernel, the second
-// waiting for all of the first; here a workgroup needs nothing from the others: it
-// solves its own 64 rows and, once more, the 64 rows of the second leaf (rows 0 .. 63
-// below the first), whose solved form is the right operand of everybody's update.
-// Those 64 rows therefore stay as they are in memory during this launch (every
-// workgroup reads them unsolved); workgroup 0, which owns them, puts their solved form
-// into `l10` (64 x 64, row-major) and the solve launch of the second leaf copies it
-// into place (leaf_solve_kernel, fix_src).
-//   Xg    row 0 of the region below the first leaf, column 0 of the strip; m rows
-//   Lleaf the first leaf, factored; dinv, dvec, linv: its reciprocal pivots, pivots and
-//         the inverses of its diagonal sub-blocks (linv must not be the array that the
-//         fused factorisation of the second leaf writes, fl.linv: workgroups start at
-//         different times)
-//   Wg, perm, perm0: as in leaf_solve_kernel
-// With pivoting the second leaf is factored by a launch of its own (fl.w = 0).
-// The update's left operand is the solved row before its division by the pivots, w = l d;
-// its right operand the second leaf's rows
-// l (SCALED, the positive-definite form, where dinv holds d^(-1/2) and l stands for the
-// row of the Cholesky factor: l d^(-1/2), so that the product is again w (1/d) w^T).
-// A wavefront's 16 solved rows are in its registers in the layout of a left operand
-// (leaf_solve_body), and it updates just those rows' 16 x 64 block of C; the second leaf's
-// rows go from the four wavefronts that solve them to all through LDS, once, register by
-// register, and both sets of rows are solved side by side.  52 KB of LDS in fp64.
-// Measured, a launch on average, against every change of layout in LDS (94 KB in fp64): fp64
-// n = 1500 18.4 -> 15.5 us, n = 8192 24.0 -> 20.6, fp32 n = 10000 25.4 -> 17.9.
-template <typename T, bool SCALED = false>
-__global__ __launch_bounds__(256, 2) void leaf_pair_kernel(
-    T* __restrict__ Xg, int64_t ld, int m, const T* __restrict__ Lleaf, int64_t ldl,
-    const T* __restrict__ dinv, const T* __restrict__ linv, const T* __restrict__ dvec,
-    T* __restrict__ Wg, int64_t ldw, int wfrom, T* __restrict__ l10, const int* __restrict__ perm, int perm0,
-    FusedLeaf<T> fl) {
-  using X = Mfma<T>;
-  using acc_t = typename X::acc_t;
-  // the second leaf's rows: [wavefront that solved them][sub-block][register][lane]; later the
-  // second leaf itself
-  constexpr int ROWS_ELEMS = LEAF * LEAF;
-  __shared__ __attribute__((aligned(16))) T lds[ROWS_ELEMS + LeafOperands<T>::ELEMS];
-  static_assert(ROWS_ELEMS + LeafOperands<T>::ELEMS >= FACTOR_LDS_ELEMS, "the fused leaf needs the operand buffers");
-  __builtin_amdgcn_s_setprio(2);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, g = lane >> 4;
-  const int blk = blockIdx.x;
-  const bool first = blk == 0;                  // this workgroup's rows are the second leaf's
-
-  // rows to solve, a row a lane: this wavefront's 16 of the workgroup's own and its 16 of the
-  // second leaf's
-  const int64_t row = ((int64_t)blk * 4 + wave) * SUB + l16;
-  const int leaf_row = wave * SUB + l16;
-  T* xrow = Xg + row * ld;
-  acc_t x[2][NSUB];
-  {
-    const bool own = row < m, other = !first && leaf_row < m;
-    const T* lrow = Xg + (int64_t)leaf_row * ld;
-    T v[NSUB][4], u[NSUB][4];
-#pragma unroll
-    for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[b][e] = u[b][e] = T(0);
-    if (perm == nullptr) {
-      if (own) load_row((const T*)xrow, g, LEAF, v);
-      if (other) load_row(lrow, g, LEAF, u);
-    } else {
-#pragma unroll
-      for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int from = perm[b * SUB + 4 * g + e] - perm0;
-          if (own) v[b][e] = xrow[from];
-          if (other) u[b][e] = lrow[from];
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[0][b][e] = v[b][e];
-        x[1][b][e] = u[b][e];
-      }
-  }
-  LeafOperands<T> ops{lds + ROWS_ELEMS};
-  ops.stage(Lleaf, ldl, LEAF, linv, wave, lane);
-  // this wavefront's 16 x 64 block of C: its (0, 0) for blk = 0, wave = 0 is on the matrix
-  // diagonal, columns behind a row's own are above it
-  T* C = Xg + LEAF;
-  const int row0 = blk * SOLVE_ROWS + wave * SUB;
-  const int tiles = first ? wave + 1 : NSUB;    // 16-column tiles with entries on or below the diagonal
-  acc_t acc[NSUB];
-#pragma unroll
-  for (int t = 0; t < NSUB; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int grow = row0 + X::acc_row(lane, r), gcol = t * SUB + l16;
-      acc[t][r] = (t < tiles && grow < m && gcol <= grow) ? C[(int64_t)grow * ld + gcol] : T(0);
-    }
-  T rinv[NSUB][4];
-  load_row(dinv, g, LEAF, rinv);
-  __syncthreads();
-  // with a permutation a store below may hit an entry that another lane of this wavefront
-  // loads above: every load has returned before the first store is issued
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (first) {
-    acc_t (&own)[1][NSUB] = *reinterpret_cast<acc_t (*)[1][NSUB]>(&x[0]);
-    ops.template solve<1>(own, lane);
-#pragma unroll
-    for (int b = 0; b < NSUB; ++b) x[1][b] = x[0][b];
-  } else {
-    ops.template solve<2>(x, lane);
-  }
-  T v[NSUB][4];
-#pragma unroll
-  for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const T rj = rinv[b][e];
-      v[b][e] = x[0][b][e] * rj;
-      const T lv = x[1][b][e] * rj;
-      lds[((wave * NSUB + b) * 4 + e) * 64 + lane] = SCALED ? lv * rj : lv;
-    }
-  if (row < m) {
-    store_row(first ? l10 + (int)row * LEAF : xrow, g, LEAF, v);
-    if (Wg != nullptr && row >= wfrom) {
-      T d[NSUB][4];
-      load_row(dvec, g, LEAF, d);
-#pragma unroll
-      for (int b = 0; b < NSUB; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[b][e] *= d[b][e];
-      store_row(Wg + row * ldw, g, LEAF, v);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < NSUB; ++t)
-    if (t < tiles) {
-#pragma unroll
-      for (int b = 0; b < NSUB; ++b) {
-        T bop[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) bop[s] = lds[((t * NSUB + b) * 4 + s) * 64 + lane];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acc[t] = X::mfma(-x[0][b][s], bop[s], acc[t]);
-      }
-    }
-  const bool fuse = first && fl.w > 0;
-  const int wleaf = fuse ? fl.w : 0;
-  if (fuse) {
-    __syncthreads();   // everybody is done with the operands
-#pragma unroll
-    for (int t = 0; t < NSUB; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        leaf_tile_put<T>(lds, row0 + X::acc_row(lane, r), t * SUB + l16, wleaf, acc[t][r]);
-  }
-#pragma unroll
-  for (int t = 0; t < NSUB; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int grow = row0 + X::acc_row(lane, r), gcol = t * SUB + l16;
-      if (t < tiles && grow < m && gcol <= grow && !(grow < wleaf && gcol < wleaf)) C[(int64_t)grow * ld + gcol] = acc[t][r];
-    }
-  if (fuse) {
-    __syncthreads();
-    leaf_factor_body<T, true>(C, ld, fl.w, fl.dvec, fl.dinv, fl.linv, fl.pivot0, fl.flags, lds, fl.spd);
-  }
-}
 
 }  // namespace mdet

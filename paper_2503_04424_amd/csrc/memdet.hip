@@ -142,20 +142,12 @@ struct Launcher {
   HipFail* fail;
   T* dvec = nullptr;
   T* dinv = nullptr;
-  T* linv = nullptr;          // inverses of a leaf's diagonal sub-blocks (see linv_of)
-  // 64 x 64 elements (or none): where leaf_pair_kernel leaves the solved rows of the
-  // second leaf of a pair until the next solve launch copies them into place.  With it
-  // linv is two arrays, used by leaves in turn: that kernel reads one leaf's while one
-  // of its workgroups already writes the next leaf's.
-  T* l10 = nullptr;
+  T* linv = nullptr;          // inverses of a leaf's diagonal sub-blocks
   // Words for the block columns that are factored by one launch (panel_flow_kernel; none: they
   // are not): each launch takes the next flow_words of them, all zero at the start of the call and
   // again whenever they run out.
   unsigned* sync = nullptr;
   int64_t sync_words = 0, sync_used = 0;
-  const T* fix_src = nullptr; // pending copy for the next solve launch
-  T* fix_dst = nullptr;
-  int64_t fix_ld = 0;
   DevFlags* flags = nullptr;
   bool spd = false;           // positive-definite form (MDET_FLAG_ASSUME_SPD)
   // n indices (or none): every leaf is factored with the pivot taken from its own
@@ -169,8 +161,8 @@ struct Launcher {
     T* Lfull = nullptr;
     T* Y = nullptr;
     T* Bg = nullptr;
-    T* leaf = nullptr;
-    T* linv = nullptr;
+    T* leaf[2] = {nullptr, nullptr};      // a group's leaf and the inverses of its diagonal
+    T* linv[2] = {nullptr, nullptr};      // sub-blocks, used by groups in turn
     T* dg = nullptr;
     int* active = nullptr;
     int* piv = nullptr;
@@ -211,7 +203,7 @@ struct Launcher {
   // trailing = true marks the Schur update of the trailing matrix by a whole block
   // column (as opposed to the updates inside a block column's own factorisation);
   // it runs the same code under its own kernel name so profiles tell them apart.
-  // fuse: the launch also factors the leaf at C's top-left corner (lower only).
+  // fuse: the launch also factors the leaf at C's top-left corner (lower, not trailing, only).
   // leave_free >= 0 (trailing only): several launches in a row, each that many
   // workgroups short of what the device holds, so that other streams' kernels find room.
   int update(hipStream_t st, T* C, int64_t ldc, const T* A, int64_t lda, const T* B, int64_t ldb,
@@ -258,7 +250,7 @@ struct Launcher {
     if (8 * ug.per > INT32_MAX) return MDET_EINVAL;
     FusedLeaf<T> fl{0, nullptr, nullptr, nullptr, 0, nullptr, 0};
     if (fuse && !perm) {
-      if (!lower || fuse->w > LEAF || fuse->w > N || fuse->w > M) return MDET_EINVAL;
+      if (trailing || !lower || fuse->w > LEAF || fuse->w > N || fuse->w > M) return MDET_EINVAL;
       fl = *fuse;
     }
     // workgroups per launch and XCD: everything at once, or rounds that fill all but
@@ -278,13 +270,14 @@ struct Launcher {
         e1 = timing_event_get(fail);
         fail->check(hipEventRecord(e0, st));
       }
-#define MDET_LAUNCH_UPD_AS(KERNEL, SCALED)                                                         \
-  hipLaunchKernelGGL((KERNEL<T, SCALED>), grid, block, 0, st, C, ldc, A, lda, B, ldb, d, (int)M,  \
-                     (int)N, (int)K, ug.nsn, ug.swl, (int)lower, (int)ug.per, (int)k0, fl)
-#define MDET_LAUNCH_UPD(KERNEL)                                                                   \
+#define MDET_LAUNCH_UPD(KERNEL, ...)                                                               \
   do {                                                                                            \
-    if (scaled) MDET_LAUNCH_UPD_AS(KERNEL, true);                                                 \
-    else MDET_LAUNCH_UPD_AS(KERNEL, false);                                                       \
+    if (scaled)                                                                                   \
+      hipLaunchKernelGGL((KERNEL<T, true>), grid, block, 0, st, C, ldc, A, lda, B, ldb, d, (int)M, \
+                         (int)N, (int)K, ug.nsn, ug.swl, (int)lower, (int)ug.per, (int)k0, ##__VA_ARGS__); \
+    else                                                                                          \
+      hipLaunchKernelGGL((KERNEL<T, false>), grid, block, 0, st, C, ldc, A, lda, B, ldb, d, (int)M, \
+                         (int)N, (int)K, ug.nsn, ug.swl, (int)lower, (int)ug.per, (int)k0, ##__VA_ARGS__); \
   } while (0)
       if (dual == 2) {
         const dim3 grid2((unsigned)(8 * kn), 2);
@@ -308,10 +301,9 @@ struct Launcher {
         else
           hipLaunchKernelGGL((leaf_update_kernel<T, false>), grid, block, 0, st, C, ldc, A, lda, B, ldb,
                              d, (int)M, (int)N, ug.nsn, ug.swl, (int)lower, (int)ug.per, fl);
-      } else if (small) MDET_LAUNCH_UPD(panel_update64_kernel);
-      else MDET_LAUNCH_UPD(panel_update_kernel);
+      } else if (small) MDET_LAUNCH_UPD(panel_update64_kernel, fl);
+      else MDET_LAUNCH_UPD(panel_update_kernel, fl);
 #undef MDET_LAUNCH_UPD
-#undef MDET_LAUNCH_UPD_AS
       ++launches;
       if (timed) {
         fail->check(hipEventRecord(e1, st));
@@ -346,16 +338,13 @@ struct Launcher {
   // What an update launch needs to factor the leaf of width w whose first pivot has
   // index d0 (see FusedLeaf).
   FusedLeaf<T> fused_leaf(int64_t w, int64_t d0) const {
-    return FusedLeaf<T>{(int)(w < LEAF ? w : LEAF), dvec + d0, dinv + d0, linv_of(d0), (long long)d0, flags,
-                        spd ? 1 : 0};
+    return FusedLeaf<T>{(int)(w < LEAF ? w : LEAF), dvec + d0, dinv + d0, linv, (long long)d0, flags, spd ? 1 : 0};
   }
-  // The array that holds the inverses of the leaf whose first pivot has index d0.
-  T* linv_of(int64_t d0) const { return l10 ? linv + ((d0 / LEAF) & 1) * (LEAF * SUB) : linv; }
 
   // The leaf of width w at P, first pivot d0, with pivoting.
   void factor_leaf_pivoted(hipStream_t st, T* P, int64_t ld, int64_t w, int64_t d0) {
     hipLaunchKernelGGL((leaf_factor_pivoted_kernel<T>), dim3(1), dim3(64 * PIVOT_WAVES), 0, st, P, ld, (int)w,
-                       dvec + d0, dinv + d0, linv_of(d0), perm + d0, (long long)d0, flags);
+                       dvec + d0, dinv + d0, linv, perm + d0, (long long)d0, flags);
     fail->check(hipGetLastError());
     ++launches;
   }
@@ -412,19 +401,25 @@ struct Launcher {
   }
 
   // Factor block column: P at its diagonal entry, m rows, w columns (w <= m).
-  // d0: index of its first pivot in dvec/dinv.  first_done: the first leaf has
-  // been factored already, by the update launch that produced it.
+  // d0: index of its first pivot in dvec/dinv.
   // Wp, if given, points at the same entry of the column's pivot-scaled copy (leading
   // dimension wld): the rows from wskip on (those below the block column's diagonal
   // block, which the trailing updates read) are written there too.  The updates inside
   // the column keep scaling on the fly: with one array for both operands they read
   // half as much (measured at n = 8192: 6.66 ms against 6.97).
-  int factor_cols(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0,
-                  bool first_done = false, T* Wp = nullptr, int64_t wskip = 0) {
+  int factor_cols(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp = nullptr,
+                  int64_t wskip = 0) {
     if (w <= 0) return MDET_OK;
     if (pb.S != nullptr) return factor_cols_pivot_block(st, P, ld, m, w, d0);
-    if (!first_done && flows(ld, m, w)) return factor_cols_flow(st, P, ld, m, w, d0, Wp, wskip);
-    sync_used = sync_words;
+    if (flows(ld, m, w)) return factor_cols_flow(st, P, ld, m, w, d0, Wp, wskip);
+    // (rows 2^31 / LEAF bytes apart and more, which update_one refuses as well: a matrix of one leaf needs none)
+    return Wp ? MDET_EINVAL : factor_cols_chain(st, P, ld, m, w, d0, false);
+  }
+
+  // The same by a chain of launches (leaf, solve, update, leaf, ...): the step entry points, which have
+  // no words for one launch.  first_done: the first leaf has been factored already, by the update
+  // launch that produced it.
+  int factor_cols_chain(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, bool first_done) {
     if (w <= LEAF && qoff != 0) {
       // P A = L D U of the leaf, then the rows below it in both halves: the lower half
       // against U^T, the transposed upper half against L with the leaf's row order
@@ -442,7 +437,7 @@ struct Launcher {
         const int64_t nblk = (below + SOLVE_ROWS - 1) / SOLVE_ROWS;
         hipLaunchKernelGGL((leaf_solve_general_kernel<T>), dim3((unsigned)nblk, 2), dim3(256), 0, st, P + w * ld,
                            ld, (int)below, (int)w, (const T*)P, (const T*)(dinv + d0), (const T*)linvL,
-                           (const T*)linvU, (const T*)(dvec + d0), (const int*)(perm + d0), (int)d0, qoff);
+                           (const T*)linvU, (const int*)(perm + d0), (int)d0, qoff);
         fail->check(hipGetLastError());
         ++launches;
         fma += 2.0 * (double)below * ((double)w * (w - 1) / 2.0);
@@ -455,7 +450,7 @@ struct Launcher {
         factor_leaf_pivoted(st, P, ld, w, d0);
       } else if (!first_done) {
         hipLaunchKernelGGL((leaf_factor_kernel<T>), dim3(1), dim3(FACTOR_THREADS), 0, st, P, ld,
-                           (int)w, dvec + d0, dinv + d0, linv_of(d0), (long long)d0, flags, spd ? 1 : 0);
+                           (int)w, dvec + d0, dinv + d0, linv, (long long)d0, flags, spd ? 1 : 0);
         fail->check(hipGetLastError());
         ++launches;
       }
@@ -464,63 +459,19 @@ struct Launcher {
       if (below > 0) {
         if (below > INT32_MAX) return MDET_EINVAL;
         int64_t nblk = (below + SOLVE_ROWS - 1) / SOLVE_ROWS;
-        hipLaunchKernelGGL((leaf_solve_kernel<T>), dim3((unsigned)(nblk + (fix_src ? 1 : 0))), dim3(256), 0,
-                           st, P + w * ld, ld, (int)below, (int)w, (const T*)P, ld,
-                           (const T*)(dinv + d0), (const T*)linv_of(d0), Wp ? Wp + w * wld : (T*)nullptr, wld,
-                           (const T*)(dvec + d0), (int)(wskip > w ? wskip - w : 0),
-                           perm ? (const int*)(perm + d0) : (const int*)nullptr, (int)d0, fix_src, fix_dst,
-                           fix_ld);
-        fix_src = nullptr;
+        hipLaunchKernelGGL((leaf_solve_kernel<T>), dim3((unsigned)nblk), dim3(256), 0, st, P + w * ld, ld,
+                           (int)below, (int)w, (const T*)P, ld, (const T*)(dinv + d0), (const T*)linv,
+                           perm ? (const int*)(perm + d0) : (const int*)nullptr, (int)d0);
         fail->check(hipGetLastError());
         ++launches;
         fma += (double)below * ((double)w * (w - 1) / 2.0);
       }
       return MDET_OK;
     }
-    // Two whole leaves with rows below them: the first leaf's solve, the update of the
-    // second leaf's columns and the second leaf's factorisation are one launch.  The
-    // solve launch of the second leaf, which must exist, puts a block in place that this
-    // one leaves aside.
-    // With pivoting the leaves have launches of their own, and the pair's solve and update
-    // are the one launch (instead of two: n = 4096, fp64, 3.20 -> 3.05 ms).
-    if (w == 2 * LEAF && m > w && l10 && qoff == 0 && m - LEAF <= INT32_MAX) {
-      if (perm) {
-        if (spd) return MDET_EINVAL;
-        factor_leaf_pivoted(st, P, ld, LEAF, d0);
-      } else if (!first_done) {
-        hipLaunchKernelGGL((leaf_factor_kernel<T>), dim3(1), dim3(FACTOR_THREADS), 0, st, P, ld, (int)LEAF,
-                           dvec + d0, dinv + d0, linv_of(d0), (long long)d0, flags, spd ? 1 : 0);
-        ++launches;
-      }
-      const int64_t below = m - LEAF;
-      const FusedLeaf<T> fl = fused_leaf(perm ? 0 : LEAF, d0 + LEAF);
-      const int* order = perm ? (const int*)(perm + d0) : (const int*)nullptr;
-      const dim3 grid((unsigned)((below + SOLVE_ROWS - 1) / SOLVE_ROWS)), block(256);
-      T* Wrows = Wp ? Wp + LEAF * wld : (T*)nullptr;
-      const int wfrom = (int)(wskip > LEAF ? wskip - LEAF : 0);
-      if (spd)
-        hipLaunchKernelGGL((leaf_pair_kernel<T, true>), grid, block, 0, st, P + LEAF * ld, ld, (int)below,
-                           (const T*)P, ld, (const T*)(dinv + d0), (const T*)linv_of(d0),
-                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, order, (int)d0, fl);
-      else
-        hipLaunchKernelGGL((leaf_pair_kernel<T, false>), grid, block, 0, st, P + LEAF * ld, ld, (int)below,
-                           (const T*)P, ld, (const T*)(dinv + d0), (const T*)linv_of(d0),
-                           (const T*)(dvec + d0), Wrows, wld, wfrom, l10, order, (int)d0, fl);
-      fail->check(hipGetLastError());
-      ++launches;
-      fma += ((double)LEAF * LEAF * LEAF - (double)LEAF) / 6.0;                 // first leaf
-      fma += (double)below * ((double)LEAF * (LEAF - 1) / 2.0);                  // its solve
-      fma += ((double)LEAF * (LEAF + 1) / 2 + (double)(below - LEAF) * LEAF) * LEAF;   // the update
-      fix_src = l10;
-      fix_dst = P + LEAF * ld;
-      fix_ld = ld;
-      return factor_cols(st, P + LEAF * ld + LEAF, ld, below, LEAF, d0 + LEAF, true,
-                         Wp ? Wp + LEAF * wld + LEAF : (T*)nullptr, wskip > LEAF ? wskip - LEAF : 0);
-    }
     // split at a multiple of the leaf width nearest the middle
     int64_t leaves = (w + LEAF - 1) / LEAF;
     int64_t w1 = (leaves / 2) * LEAF;
-    int rc = factor_cols(st, P, ld, m, w1, d0, first_done, Wp, wskip);
+    int rc = factor_cols_chain(st, P, ld, m, w1, d0, first_done);
     if (rc != MDET_OK) return rc;
     // columns [w1, w), rows [w1, m)  -=  L[rows, 0:w1] D L[cols, 0:w1]^T, and the
     // first leaf of those columns factored by the same launch
@@ -529,8 +480,7 @@ struct Launcher {
     const FusedLeaf<T> fl = fused_leaf(w - w1, d0 + w1);
     rc = update(st, C, ld, A, ld, A, ld, dvec + d0, m - w1, w - w1, w1, true, false, &fl);
     if (rc != MDET_OK) return rc;
-    return factor_cols(st, C, ld, m - w1, w - w1, d0 + w1, true, Wp ? Wp + w1 * wld + w1 : (T*)nullptr,
-                       wskip > w1 ? wskip - w1 : 0);
+    return factor_cols_chain(st, C, ld, m - w1, w - w1, d0 + w1, true);
   }
 
   // Start of the profiled region (MDET_FLAG_PROFILE): the origin of the launches' time axis.
@@ -583,8 +533,8 @@ struct Launcher {
     for (int64_t c0 = 0; c0 < w && rc == MDET_OK; c0 += LEAF) {
       const int lw = (int)(w - c0 < LEAF ? w - c0 : LEAF);
       const int turn = (int)(c0 / LEAF & 1);
-      T* const leaf = turn ? l10 : pb.leaf;
-      T* const inverses = turn ? linv : pb.linv;
+      T* const leaf = pb.leaf[turn];
+      T* const inverses = pb.linv[turn];
       if (sy != st && c0 >= 2 * LEAF) fail->check(hipStreamWaitEvent(st, pb.solved[turn], 0));
       // a block whose rows one workgroup holds: the whole group in one launch
       if (w <= PB_GROUP_ROWS) {
@@ -630,8 +580,7 @@ struct Launcher {
         const int64_t nblk = (below + SOLVE_ROWS - 1) / SOLVE_ROWS;
         hipLaunchKernelGGL((leaf_solve_kernel<T>), dim3((unsigned)nblk), dim3(256), 0, sy, pb.Y + c0, ldl, (int)below,
                            lw, (const T*)leaf, (int64_t)LEAF, (const T*)(dinv + d0 + c0), (const T*)inverses,
-                           (T*)nullptr, (int64_t)0, (const T*)(dvec + d0 + c0), 0, (const int*)nullptr, 0,
-                           (const T*)nullptr, (T*)nullptr, (int64_t)0);
+                           (const int*)nullptr, 0);
         fail->check(hipGetLastError());
         ++launches;
         fma += (double)below * ((double)lw * (lw - 1) / 2.0);
@@ -746,11 +695,8 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
     const int64_t wk = pl.col_width(k);
     const int64_t mk = n - k * bs;
     touch(s0, k);
-    // every column but the group's first had its first leaf factored by the update
-    // launch that finished it
     T* Wk = L.wbuf[0] ? L.wbuf[k & 1] : nullptr;      // this column's pivot-scaled copy
-    const bool leaf_done = k > jb && !L.flows(cols[k].ld, mk, wk);
-    int rc = L.factor_cols(s0, cols[k].base, cols[k].ld, mk, wk, k * bs, leaf_done, Wk, wk);
+    int rc = L.factor_cols(s0, cols[k].base, cols[k].ld, mk, wk, k * bs, Wk, wk);
     if (rc != MDET_OK) return rc;
     // left operand of the updates by column k: rows from block row j down
     auto left = [&](int64_t j) -> const T* {
@@ -787,9 +733,8 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
       const int64_t j = k + 1;
       touch(s0, j);
       const T* B = cols[k].base + (j - k) * bs * cols[k].ld;
-      const FusedLeaf<T> fl = L.fused_leaf(pl.col_width(j), j * bs);
       rc = L.update(s0, cols[j].base, cols[j].ld, left(j), lda_k, B, cols[k].ld, L.dvec + k * bs,
-                    n - j * bs, pl.col_width(j), wk, true, true, flow_next ? nullptr : &fl, -1, Wk != nullptr);
+                    n - j * bs, pl.col_width(j), wk, true, true, nullptr, -1, Wk != nullptr);
       if (rc != MDET_OK) return rc;
     }
     if (lookahead && k + 2 < je && leave_free >= 0) {
@@ -1073,12 +1018,11 @@ static void bind_small(Launcher<T>& L, char* base, const SmallArea& sa) {
   L.dvec = (T*)(base + sa.dvec);
   L.dinv = (T*)(base + sa.dinv);
   L.linv = (T*)(base + sa.linv);
-  L.l10 = (T*)(base + sa.l10);
   L.linv_u = L.linv + LEAF * SUB;      // linv is two arrays here
   L.flags = (DevFlags*)(base + sa.flags);
   L.perm = sa.total > sa.perm ? (int*)(base + sa.perm) : nullptr;
-  L.sync = (unsigned*)L.l10;           // (leaf_pair_kernel's array: a launch that uses it ends the words)
-  L.sync_words = LEAF * LEAF * (int64_t)sizeof(T) / 4;
+  L.sync = (unsigned*)(base + sa.words);
+  L.sync_words = (int64_t)sa.words_bytes / 4;
   // two workgroups of the trailing update fit one compute unit (registers and LDS)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
@@ -1101,13 +1045,18 @@ __global__ void reset_flags_kernel(DevFlags* f, unsigned* sync, int sync_words) 
 template <typename T>
 static void bind_pivot_block(Launcher<T>& L, char* base, const Plan& pl) {
   if (!pl.pivot_block) return;
+  // (no block column is factored by one launch in this form: the words for that are the second leaf)
+  L.pb.leaf[1] = (T*)L.sync;
+  L.pb.linv[1] = L.linv;
+  L.sync = nullptr;
+  L.sync_words = 0;
   const PivotBlockArea a = pivot_block_area(pl.n, pl.bs, pl.beta);
   L.pb.S = (T*)(base + a.S);
   L.pb.Lfull = (T*)(base + a.Lfull);
   L.pb.Y = (T*)(base + a.Y);
   L.pb.Bg = (T*)(base + a.Bg);
-  L.pb.leaf = (T*)(base + a.leaf);
-  L.pb.linv = (T*)(base + a.linv);
+  L.pb.leaf[0] = (T*)(base + a.leaf);
+  L.pb.linv[0] = (T*)(base + a.linv);
   L.pb.dg = (T*)(base + a.dg);
   L.pb.active = (int*)(base + a.active);
   L.pb.piv = (int*)(base + a.piv);

@@ -83,7 +83,7 @@ inline uint64_t align256(uint64_t x) { return (x + 255) / 256 * 256; }
 
 // Layout of the small scratch area (offsets in bytes from its start).
 struct SmallArea {
-  uint64_t dvec, dinv, linv, l10, flags, partial, out, running, perm, total;
+  uint64_t dvec, dinv, linv, words, words_bytes, flags, partial, out, running, perm, total;
 };
 // pivot: room for the permutation (n 32-bit indices) of MDET_FLAG_PIVOT
 inline SmallArea small_area(int64_t n, int64_t T, int beta, bool pivot) {
@@ -92,7 +92,12 @@ inline SmallArea small_area(int64_t n, int64_t T, int beta, bool pivot) {
   a.dvec = o; o += align256((uint64_t)(n > 0 ? n : 1) * beta);
   a.dinv = o; o += align256((uint64_t)(n > 0 ? n : 1) * beta);
   a.linv = o; o += 2 * align256((uint64_t)64 * 16 * beta);   // inverse diagonal sub-blocks of two leaves
-  a.l10 = o; o += align256((uint64_t)64 * 64 * beta);        // a 64 x 64 block on its way into place
+  // what one launch for a block column of n rows of two arrays counts in (2 + 2 ceil(n / 64) words), for
+  // several launches where n is small; pivoting over the block has a 64 x 64 leaf here
+  a.words_bytes = align256((uint64_t)64 * 64 * beta);
+  const uint64_t words = align256(4 * (2 + 2 * (uint64_t)((n + 63) / 64)));
+  if (words > a.words_bytes) a.words_bytes = words;
+  a.words = o; o += a.words_bytes;
   a.partial = o; o += align256((uint64_t)(T > 0 ? T : 1) * 3 * 8);
   a.out = o; a.flags = o + 24; o += 256;                     // what a call reads back, side by side
   a.running = o; o += align256((uint64_t)(T > 0 ? T : 1) * 8);
