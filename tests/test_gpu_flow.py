@@ -166,3 +166,87 @@ def test_results_of_few_and_many_blocks(n, bs):
     r = M.mdet_logdet_device(torch.from_numpy(np.diag(d)).cuda(), block_size=bs)
     want = float(np.sum(np.log(np.abs(d).astype(np.longdouble))))
     assert (r.status, r.sign, r.negative_pivots) == (0, -1, 1) and abs(r.logabsdet - want) <= 4e-16 * n
+
+
+def multiplied_out(form, a, d, p, f):
+    """Largest difference between the matrix and the factor multiplied out (all fp64, on the GPU); rows of a leaf
+    stand in their input order in the columns of the leaves before it."""
+    n = a.shape[0]
+    low = torch.tril(f, -1)
+    if form in ("sym", "spd"):
+        if form == "spd":                                # stored leaves are unit-lower, rows below them L D^(1/2)
+            for k in range(0, n, 64):
+                low[k + 64:, k:k + 64] /= torch.sqrt(d[k:k + 64])
+        low += torch.eye(n, dtype=f.dtype, device=f.device)
+        return float(torch.abs((low * d) @ low.T.contiguous() - a).max())
+    up = torch.triu(f, 1) if form == "gen" else low.T.contiguous()
+    s, worst = a.clone(), 0.0
+    for k in range(0, n, 64):
+        e = min(n, k + 64)
+        q = p[k:e].long() - k
+        eye = torch.eye(e - k, dtype=f.dtype, device=f.device)
+        l11, u11 = low[k:e, k:e] + eye, up[k:e, k:e] + eye
+        lead = s[k:e, k:e][q] if form == "gen" else s[k:e, k:e][q][:, q]
+        diffs = [(l11 * d[k:e]) @ u11 - lead]
+        if e < n:
+            l21, u12 = low[e:, k:e].contiguous(), up[k:e, e:].contiguous()
+            cols = s[e:, k:e] if form == "gen" else s[e:, k:e][:, q]
+            diffs += [(l21 * d[k:e]) @ u11 - cols, (l11 * d[k:e]) @ u12 - s[k:e, e:][q]]
+            s[e:, e:] -= (l21 * d[k:e]) @ u12
+        worst = max([worst] + [float(torch.abs(x).max()) for x in diffs])
+    return worst
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("form,n", [(f, n) for f in ("sym", "spd", "pivot") for n in (3585, 3713, 3776, 3800, 3841)] +
+                         [("gen", n) for n in (1793, 1921, 1984, 2049, 2113)])
+def test_row_tasks_of_two_columns(form, n, dtype):
+    """Orders from which on row tasks take two tile columns (28 pairs of tile rows and one more, general
+    matrices 14), with an odd and an even number of tile rows, the last of them whole, ragged or of one row; rows on
+    128-byte lines and off them; whole matrices, block columns with and without the scaled copy, and block
+    columns of one tile column, which have no such tasks: the same bits, and the factor multiplied out.
+
+    Off-diagonal entries c u with |u| <= 1, c = 1 / (2 sqrt(n)), diagonal 1 .. 4: the terms of an entry add up to
+    sum |l| |d| |l| <= n c^2 E u^2 = 1/12 beside the diagonal itself, so an elimination in any order
+    leaves |A - L D L^T| <= n u / 12 and a few roundings of numbers up to 5, u the unit roundoff.  64 terms left
+    out or taken twice show as 8 c^2 / 3 = 2 / (3 n) on average: ten times that in fp32."""
+    import paper_2503_04424_amd as M
+    M.load()
+    td, unit = (torch.float64, 2.0 ** -53) if dtype == "f64" else (torch.float32, 2.0 ** -24)
+    tol = unit * (n / 6 + 64)
+    g = torch.Generator().manual_seed(n)
+    a = (torch.rand((n, n), generator=g, dtype=torch.float64) * 2 - 1) / (2 * n ** 0.5)
+    if form != "gen":
+        a = torch.tril(a) + torch.tril(a, -1).T
+    big = (1 + torch.arange(n) % 64 / 21.0).double()                 # in every leaf the last the largest
+    if form in ("sym", "pivot"):
+        big = big * (torch.randint(0, 2, (n,), generator=g) * 2 - 1)
+    a.diagonal().copy_(big)
+    if form == "gen":
+        rows = torch.arange(n)
+        for k in range(0, n, 64):
+            rows[k:k + 64] = rows[k:k + 64].flip(0)
+        a = a[rows]
+    a = a.to(td).cuda()
+    vec = 16 // a.element_size()
+    on, off = (n + 31) // 32 * 32, (n + 31) // 32 * 32 + vec
+    flags = {"sym": 0, "spd": M.FLAG_ASSUME_SPD, "pivot": M.FLAG_PIVOT, "gen": M.FLAG_GENERAL}[form]
+    scaled = M.FLAG_SCALED_COPY if form in ("sym", "pivot") else 0
+    first = None
+    for ld, bs, extra in [(on, 4096, 0), (off, 4096, 0), (off, 64, M.FLAG_NO_LOOKAHEAD), (on, 64, 0), (on, 1024, scaled),
+                          (off, 640, scaled | M.FLAG_PROFILE), (on, 64, M.FLAG_PROFILE)]:
+        w = torch.full((n, ld), float("nan"), dtype=td, device="cuda")[:, :n]
+        w.copy_(a)
+        diag = torch.empty(n, dtype=td, device="cuda")
+        perm = torch.arange(n, dtype=torch.int32, device="cuda")
+        r = M.mdet_logdet_device(w, block_size=bs, overwrite=True, flags=flags | extra, diag=diag, perm=perm)
+        assert r.status == 0, (ld, bs)
+        f = w if form == "gen" else torch.tril(w)
+        if first is None:
+            first = (diag, perm, f.clone(), r.logabsdet, r.sign)
+            if form in ("pivot", "gen"):
+                assert not torch.equal(perm[:64].cpu(), torch.arange(64, dtype=torch.int32))
+            assert multiplied_out(form, a.double(), diag.double(), perm, f.double()) < tol
+        assert all(torch.equal(x, y) for x, y in zip(first[:3], (diag, perm, f))), (ld, bs, extra)
+        # (n terms up to 1.4, added in another order: n / 64 + 10 additions at most to each)
+        assert abs(r.logabsdet - first[3]) <= 1.4 * n * (n / 64 + 10) * 2.0 ** -53 and r.sign == first[4]
