@@ -1155,8 +1155,11 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, cons
   }
 }
 
+// Starts on a page: its 47 to 64 KB of instructions nearly fill the instruction cache, and where in a page
+// the code before it made it start moved the pivoted form in fp64 by 1.4 % (n = 6000, the same
+// instructions 0x600 and 0xb00 behind a page's start 2391 and 2426 us, at its start 2392).
 template <typename T, FlowForm FORM>
-__global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a) {
+__attribute__((aligned(4096))) __global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a) {
   __shared__ __attribute__((aligned(16))) T lds[FlowShape<T, FORM>::LDS_ELEMS];
   __shared__ int shared[2];
   if (threadIdx.x == 0)

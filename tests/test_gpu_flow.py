@@ -59,6 +59,28 @@ def test_orders_around_tile_edges(n, dtype, form):
     assert err.max() < 8 * tol                                       # entries up to 4
 
 
+@pytest.mark.parametrize("form", ["sym", "spd"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("w", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
+def test_leaf_of_any_width_in_a_whole_call(w, dtype, form):
+    """The last leaf of a call, alone and behind whole ones, at three scales (the step entry point's leaf:
+    test_gpu_leaf_edges.py)."""
+    import paper_2503_04424_amd as M
+    M.load()
+    npdt, tol = (np.float64, 1e-13) if dtype == "f64" else (np.float32, 1e-5)
+    for n, scale in [(w, 1.0), (w, 1e12), (w, 1e-12), (64 + w, 1.0), (128 + w, 1.0)]:
+        rng = np.random.default_rng(100 * n + w)
+        a = rng.uniform(-1, 1, (n, n)) / (2 * n)
+        a = a + a.T
+        np.fill_diagonal(a, rng.uniform(1, 4, n) * (rng.choice([-1, 1], n) if form == "sym" else 1))
+        a = (a * scale).astype(npdt)
+        o = oracle.ldlt_logdet(a.astype(np.float64), want_diag=True)
+        diag = torch.empty(n, dtype=torch.float64 if dtype == "f64" else torch.float32, device="cuda")
+        r = M.mdet_logdet_device(torch.from_numpy(a).cuda(), flags=M.FLAG_ASSUME_SPD if form == "spd" else 0, diag=diag)
+        d = diag.cpu().numpy().astype(np.float64)
+        assert r.status == 0 and r.sign == o.sign and np.max(np.abs(d - o.diag) / np.abs(o.diag)) < tol, (n, scale)
+
+
 @pytest.mark.parametrize("form", ["gen", "pivot"])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("n", [64, 65, 128, 129, 193, 320, 449, 1025])

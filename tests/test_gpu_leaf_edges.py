@@ -1,5 +1,6 @@
 """Leaves whose width is not a multiple of the 16-column sub-blocks they are factored in, alone
-and with rows below them, against the oracle's factor.
+and with rows below them, through the step entry point (its chain of launches; whole calls:
+test_gpu_flow.py), against the oracle's factor.
 
 Tolerance: the pivots of these matrices (diagonal 1 .. 4, off-diagonal entries of size
 1/(2 w)) are sums of at most 64 products of size <= 1; a double-precision elimination in any
