@@ -103,9 +103,11 @@ def measured_traffic(workload):
 
 
 def kernel_report(reps=5):
-    """Stand-alone rates of the path's kernels through the single-step entry points:
-    the Schur update against the matrix-core peak, the leaf solve and the log/sign
-    reduction against HBM bandwidth.  One JSON line."""
+    """Stand-alone rates of kernels through the single-step entry points: the Schur
+    update against the matrix-core peak, the leaf solve and the log/sign reduction
+    against HBM bandwidth.  (Whole calls factor their leaves and solve the rows below
+    inside one launch per block column, which no step entry point reaches.)  One JSON
+    line."""
     import torch
     import paper_2503_04424_amd as M
     M.load()

@@ -24,10 +24,11 @@
 // elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
 // that.  Between launches the same steps also wait for every workgroup of the launch before and
 // for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
-// against the chain of launches, whole calls: symmetric fp64 n = 512 230 -> 160 us, n = 1500 (positive
-// definite) 620 -> 360, n = 5555 3030 -> 1530, n = 8192 5889 -> 3850, fp32 n = 10000 5948 -> 3560; block columns
-// of 2048 beside a bulk update, n = 32768, 191 -> 178 ms; pivots from inside a leaf, n = 4096 3.03 -> 1.69
-// ms; general n = 2900 2.30 -> 1.36, n = 8192 11.3 -> 7.8 (leaves of 20 us).  Where a matrix is large: the
+// against the chain of launches, whole calls that keep their input: symmetric fp64 n = 512 229 -> 152 us,
+// n = 1500 (positive definite) 603 -> 361, n = 5555 (positive definite) 3020 -> 1546, n = 8192 5873 -> 3889, fp32
+// n = 10000 5940 -> 3609; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 183.8 ms; pivots from
+// inside a leaf, n = 4096 3.04 -> 1.69 ms; general n = 2900 2.27 -> 1.38, n = 8192 11.3 -> 8.0 (leaves of 20 us).
+// Where a matrix is large: the
 // matrix cores, in fp64 4.2 us for the 128 x 64 x 64 products of a row task of one column and 7.7 for
 // 128 x 128 x 64 of two (positive-definite form 3.9 and 7.5; 3.4 and 6.8 at their peak).
 // One workgroup of eight wavefronts has a compute unit to itself (its LDS sees to that): two
@@ -137,7 +138,8 @@ struct FlowOrder {
     return 2 * pair >= top || 2 * pair + 1 < ntr ? FLOW_ROWS : FLOW_NOTHING;
   }
 };
-// Column pairs with row tasks of both: while 28 row tasks of each column are left.  Measured with none, a
+// Column pairs with row tasks of both: while 28 row tasks of each column are left (general matrices have
+// two to a pair of tile rows, so 14 pairs).  Measured with none, a
 // quarter, 0.4, 0.6, three quarters and all of the pairs: fp64 n = 4096 0.90 0.94 0.89 0.94 0.93 0.98 ms, n
 // = 8192 3.99 3.90 3.90 3.86 3.84 4.18, n = 12300 13.3 12.9 12.5 12.1 12.2 12.4; fp32 n = 10000 4.28 4.02
 // 3.84 3.63 3.60 3.53.

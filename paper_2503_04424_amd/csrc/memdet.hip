@@ -380,7 +380,7 @@ struct Launcher {
     a.pivot0 = d0;
     a.flags = flags;
     a.sync = (FlowSync*)(sync + sync_used);
-    // row tasks of two columns while at least 28 pairs of tile rows are left (flow_two)
+    // row tasks of two columns while flow_two has pairs of tile rows left for them
     a.order = flow_order(m, w, arrays, flow_two(m, w, arrays));
     a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0 &&
               (uint64_t)qoff * sizeof(T) % 128 == 0;
@@ -717,9 +717,9 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
     // in rounds that leave them room, and starts once the next column's own update
     // (which wants the whole device) is through.
     // A launch that takes the whole block column wants whole compute units, which it does not get
-    // by that: the bulk update is one launch then, and starts beside the next column's own (n = 32768,
-    // fp64, 187 -> 178 ms; general n = 8192 9.9 -> 9.1; units set aside for the block column, 1.5 times its
-    // share of the work, 186 and 9.0).
+    // by that: the bulk update is one launch then, and starts beside the next column's own (fp64, rounds
+    // against one launch: n = 8192, b = 1024 5.38 and 4.77 ms, general 10.0 and 9.39, n = 32768, b = 2048 203
+    // and 182).
     const bool flow_next = L.flows(cols[k + 1].ld, n - (k + 1) * bs, pl.col_width(k + 1));
     const int leave_free = lookahead && k + 2 < je && !flow_next ? L.leave_free_for(mk - wk) : -1;
     hipEvent_t ev_panel = nullptr;
@@ -782,14 +782,18 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
 
 // The block columns in which a dense matrix of this plan is factored: up to 16 of the plan's at a
 // time where a launch that takes them all (panel_flow_kernel) beats block columns whose bulk
-// update runs beside the next one's factorisation.  Measured, ms, one launch against block
-// columns: symmetric fp64 n = 8192 3.8 against 5.4, 12288 11.3 / 14.2, 16384 25.7 / 27.2, 24000 78.5 / 83.9,
-// fp32 n = 10000 3.6 / 5.1, 24000 39.5 / 42.7; positive definite fp64 24000 76.7 / 79.6, 32768 189 / 183; pivots
-// from inside a leaf 12288 11.6 / 15.7; general 8192 7.8 / 10.0, 16384 54.3 / 53.6, 20480 101 / 109.  From
-// 24576 on the launch is bound by the operands it reads out of memory, and the pivot-scaled copies
-// of block columns pay (make_plan).  16 is how many block columns the library makes of a matrix by
-// itself; a caller who asks for more of them, and for look-ahead between them, gets a launch for
-// every 16.  With MDET_FLAG_PROFILE the updates between block columns are what is looked at.
+// update runs beside the next one's factorisation.  Measured in place, ms, one launch against block
+// columns, symmetric / general fp64 / symmetric fp32: n = 2048 0.45 0.72 / 0.93 1.21 / 0.33 0.54, 8192 3.68 5.30 /
+// 8.29 10.4 / 2.08 3.08, 16384 24.9 26.3 / 53.4 53.8 / 12.8 13.9, 20480 47.6 53.9 / 101 110 / 24.2 27.8, 24000 75.5
+// 82.3 / 156 167 / 38.4 42.1; positive definite 16384 24.3 25.4, 24000 73.4 78.3; pivots from inside a leaf 24000
+// 75.6 83.8; rows off 128-byte lines, whose operands are read past the caches, 8192 3.78 5.39, 16384 25.3
+// 27.4, 24000 76.8 85.1, general 160 173.  The line lies where the plan begins to take pivot-scaled copies of
+// block columns by itself (make_plan).  It is not where the gain ends: 28000 118 124 / 240 259 / 59.8 63.7, 32768
+// 186 181 / 376 380 / 94.9 92.9, 36000 248 256 / 504 536 / 126 131.  16 is how many block columns the
+// library makes of a matrix by itself; a caller who asks for more of them, and for look-ahead between them,
+// gets a launch for every 16 (n = 8192, b = 128, copied: 4.86 ms; without look-ahead, whole, 4.09; the chain
+// of launches took 9.77).  With MDET_FLAG_PROFILE the updates between block columns are what is looked
+// at.
 template <typename T>
 static Plan dense_plan(const Launcher<T>& L, const Plan& pl, int64_t ld, bool lookahead) {
   constexpr int64_t ONE_LAUNCH = 24576;
@@ -1214,6 +1218,7 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
   std::vector<ColRef<T>> cols((size_t)by.T);
   for (int64_t j = 0; j < by.T; ++j) cols[j] = {W + j * by.bs * ldw + j * by.bs, ldw};
   rc = factor_resident(L, by, cols, 0, by.T, true, lookahead, s0, s1, events);
+  // (from 24576 rows on a call takes 40 ms and more, and the 10 us that this saves are nothing in it)
   std::unique_ptr<ResultPlace> place;
   if (rc == MDET_OK && pl.T > 0 && pl.T <= FINISH_BLOCKS && pl.n < 24576) {
     place.reset(new ResultPlace);

@@ -195,7 +195,7 @@ inline int make_plan(const mdet_params& p, bool device_input, int64_t ld, Plan& 
     const bool aligned = ld % vec == 0;
     pl.need_copy = widen || !p.overwrite || !aligned;
     // rows of a copy start on 128-byte lines, unless a budget has no room for that (panel_flow_kernel
-    // then reads its operands past the caches: n = 5555, fp64, 1.80 ms, instead of 1.65 at n = 5552)
+    // then reads its operands past the caches: n = 5555, fp64, in place, rows of 5556 1.591 ms, of 5568 1.557)
     place_copy(pl, round_up(p.n > 0 ? p.n : 1, 128 / pl.beta), ld);
     // (or for them beside the pivot-scaled copies, which with a budget are there because they were asked for)
     if (budget && pl.dev_bytes + wcopy > budget) {
