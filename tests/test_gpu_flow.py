@@ -176,6 +176,31 @@ def test_copy_without_room_for_long_rows(n, dtype, form):
         assert np.array_equal(d, got[0][0]) and (v, s) == got[0][1:]
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [1, 3, 63, 65, 130, 131, 257])
+def test_copy_of_a_view_of_some_columns(n, dtype):
+    """Rows longer than the order, copied in pieces of 16 bytes and, where they are not whole ones, by entry: the
+    same bits as from rows without a gap, and nothing between the rows is touched or used."""
+    import paper_2503_04424_amd as M
+    M.load()
+    td, vec = (torch.float64, 2) if dtype == "f64" else (torch.float32, 4)
+    rng = np.random.default_rng(n)
+    a = rng.uniform(-1, 1, (n, n)) / (2 * n)
+    a = torch.from_numpy(a + a.T + np.diag(rng.uniform(1, 4, n))).to(td).cuda()
+    got = []
+    for ld in (n, (n + vec - 1) // vec * vec, (n + vec - 1) // vec * vec + vec):
+        flat = torch.full(((n - 1) * ld + n,), float("nan"), dtype=td, device="cuda")
+        view = flat.as_strided((n, n), (ld, 1))
+        view.copy_(a)
+        before = flat.clone()
+        diag = torch.empty(n, dtype=td, device="cuda")
+        r = M.mdet_logdet_device(view, block_size=64, diag=diag)
+        assert r.status == 0 and torch.equal(flat.isnan(), before.isnan()) and torch.equal(view, a)
+        got.append((diag.cpu().numpy(), r.logabsdet))
+    for d, v in got[1:]:
+        assert np.array_equal(d, got[0][0]) and v == got[0][1]
+
+
 @pytest.mark.parametrize("n", [1, 64, 1023, 1024, 1025, 1040])
 @pytest.mark.parametrize("bs", [64, 128])
 def test_results_of_few_and_many_blocks(n, bs):
