@@ -29,8 +29,11 @@
 // n = 10000 5940 -> 3609; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 183.8 ms; pivots from
 // inside a leaf, n = 4096 3.04 -> 1.69 ms; general n = 2900 2.27 -> 1.38, n = 8192 11.3 -> 8.0 (leaves of 20 us).
 // Where a matrix is large: the
-// matrix cores, in fp64 4.2 us for the 128 x 64 x 64 products of a row task of one column and 7.7 for
-// 128 x 128 x 64 of two (positive-definite form 3.9 and 7.5; 3.4 and 6.8 at their peak).
+// matrix cores, in fp64 3.6 us for the 128 x 64 x 64 products of a row task of one column and 7.0 for
+// 128 x 128 x 64 of two (positive-definite form 3.5 and 6.9; 3.4 and 6.8 at their peak; fp32 1.97 and 3.65 of 1.7
+// and 3.4).  That takes a loop over the slabs of the operands with no jump in it but its own: with the loads
+// under conditions and all issued at the start of a slab, where 40 of them keep the wavefronts from
+// their products, it was 4.2 and 7.7 us (fp32 2.2 and 3.95; n = 8192 3.88 -> 3.55 ms, fp32 n = 10000 3.67 -> 3.38).
 // One workgroup of eight wavefronts has a compute unit to itself (its LDS sees to that): two
 // of four wavefronts each slow each other's leaves down, whose single wavefront then waits for
 // the other's matrix instructions (n = 8192: 10.8 us a leaf instead of 6.7), and the sums of a
@@ -166,12 +169,30 @@ __device__ __forceinline__ void flow_load4(__amdgpu_buffer_rsrc_t r, unsigned of
     __builtin_memcpy(&v[h * (16 / (int)sizeof(T))], &u, 16);
   }
 }
+// A wavefront's SIZE bytes a lane from base + off (base the same in all lanes) straight to LDS, lane by lane
+// from byte `at` on (the same in all lanes).  Written out because the compiler, told of the load, waits for it in front of the next
+// read of anything in LDS; the caller counts these loads and waits for them by itself (s_waitcnt vmcnt).
+template <int SIZE, int SCOPE>
+__device__ __forceinline__ void flow_to_lds(const char* base, const unsigned off, const unsigned at) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)base);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)base >> 32));
+  const unsigned long long from = ((unsigned long long)hi << 32) | lo;
+#define MDET_TO_LDS(WIDTH, BITS)                                                                         \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_" WIDTH " %1, %2" BITS                  \
+               :: "s"(at), "v"(off), "s"(from) : "m0")
+  static_assert((SIZE == 16 || SIZE == 4) && (SCOPE == 0 || SCOPE == FLOW_DEVICE_SCOPE), "forms in use");
+  if constexpr (SIZE == 16 && SCOPE == 0) MDET_TO_LDS("dwordx4", "");
+  else if constexpr (SIZE == 16) MDET_TO_LDS("dwordx4", " sc1");
+  else if constexpr (SCOPE == 0) MDET_TO_LDS("dword", "");
+  else MDET_TO_LDS("dword", " sc1");
+#undef MDET_TO_LDS
+}
 template <typename T, FlowForm FORM>
 struct FlowShape {
   static constexpr int BK = Mfma<T>::BK;
   static constexpr int ARRAYS = FORM == FLOW_GENERAL ? 2 : 1;
   static constexpr int ROWS = FLOW_ROWS_HELD * BK, COLS = 2 * LEAF * BK;   // the slabs of the two operands
-  static constexpr int STAGE = ROWS + COLS + BK;                  // both, and the pivots
+  static constexpr int STAGE = ROWS + COLS + 2 * BK;              // both, and the pivots (twice)
   static constexpr int SLABS = FLOW_STAGES * STAGE;
   // after the sums the same memory holds what a solve needs of its leaf (of both its halves, one after
   // the other), later the leaf that is factored, and behind that the solved tiles
@@ -197,9 +218,10 @@ struct FlowShape {
                 "places in LDS");
 };
 
-// What all tasks of a launch share.
-template <typename T>
+// What all tasks of a launch share.  LINES: the arrays' rows start on 128-byte lines.
+template <typename T, bool LINES>
 struct FlowArgs {
+  static constexpr bool lines = LINES;
   T* P;                 // the block column's diagonal entry
   int64_t ld;
   int m, w;             // rows, columns (w a multiple of LEAF, or m = w)
@@ -214,14 +236,13 @@ struct FlowArgs {
   DevFlags* flags;
   FlowSync* sync;
   FlowOrder order;
-  bool lines;           // rows start on 128-byte lines
 };
 
 // A wavefront waits until the counter of every lane (`row` < 0: none) has reached `need`;
 // the smallest of them, or -1 if the launch has failed.  A wait that gives up is reported as pivot
 // 0, kind 8.
-template <typename T>
-__device__ __forceinline__ int flow_wait(const FlowArgs<T>& a, const int row, const int need) {
+template <typename T, bool LINES>
+__device__ __forceinline__ int flow_wait(const FlowArgs<T, LINES>& a, const int row, const int need) {
   unsigned long long since = 0;
   for (unsigned spins = 0;; ++spins) {
     const int v = row >= 0 ? (int)__hip_atomic_load(&a.sync->done[row], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
@@ -252,8 +273,8 @@ __device__ __forceinline__ int flow_wait(const FlowArgs<T>& a, const int row, co
   }
 }
 // The same by the first wavefront for all threads of the workgroup, counters r0 to r3.
-template <typename T>
-__device__ __forceinline__ int flow_wait_all(const FlowArgs<T>& a, const int r0, const int r1, const int r2, const int r3,
+template <typename T, bool LINES>
+__device__ __forceinline__ int flow_wait_all(const FlowArgs<T, LINES>& a, const int r0, const int r1, const int r2, const int r3,
                                              const int need, int* shared) {
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
@@ -263,8 +284,8 @@ __device__ __forceinline__ int flow_wait_all(const FlowArgs<T>& a, const int r0,
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(*shared);
 }
-template <typename T>
-__device__ __forceinline__ void flow_publish(const FlowArgs<T>& a, const int row, const int count) {
+template <typename T, bool LINES>
+__device__ __forceinline__ void flow_publish(const FlowArgs<T, LINES>& a, const int row, const int count) {
   __hip_atomic_store(&a.sync->done[row], (unsigned)count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -318,8 +339,8 @@ struct FlowOperands {
 // col[1], and s[u] += row[0] D row[1]^T (wavefronts 0 to 3) and row[1] D row[0]^T (the others).
 // Row task of two columns (KIND 3): as KIND 0, x[NSUB + t] by col[1].
 // False if the launch has failed.
-template <typename T, FlowForm FORM, int KIND>
-__device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const FlowOperands<T>& of, const int nk, const bool mine,
+template <typename T, FlowForm FORM, int KIND, bool LINES>
+__device__ __forceinline__ bool flow_accumulate(const FlowArgs<T, LINES>& a, const FlowOperands<T>& of, const int nk, const bool mine,
                                                 typename Mfma<T>::acc_t (&x)[KIND == 3 ? 2 * NSUB : NSUB],
                                                 typename Mfma<T>::acc_t (&s)[3], T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
@@ -345,30 +366,24 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const Flow
   }
 #pragma unroll
   for (int v = 0; v < CV; ++v) coff[v] = (unsigned)(((int64_t)rt * a.ld + chunk * VEC) * (int64_t)sizeof(T));
-  auto pinned = [](unsigned o) { asm volatile("" : "+v"(o)); return o; };
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(upd_lds_ptr)lds);
   constexpr int LOADS = RV + CV + (SCALED ? 0 : 1);    // a wavefront's, per slab
-  auto request = [&](const int slab, const int stage, auto scope) {
-    constexpr int SCOPE = decltype(scope)::value;
-    T* to = lds + stage * Sh::STAGE;
-    const unsigned kb = __builtin_amdgcn_readfirstlane((unsigned)slab * 128u);
-#pragma unroll
-    for (int v = 0; v < RV; ++v)
-      __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(of.row[v]) + kb + pinned(roff[v])),
-                                       (upd_lds_ptr)(to + (v * LEAF + wave * 8) * BK), 16, 0, SCOPE);
-#pragma unroll
-    for (int v = 0; v < CV; ++v)
-      __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(of.col[v]) + kb + pinned(coff[v])),
-                                       (upd_lds_ptr)(to + Sh::ROWS + (v * LEAF + wave * 8) * BK), 16, 0, SCOPE);
-    if constexpr (!SCALED) {
-      // the slab's pivots: 128 bytes, every wavefront the same
-      if (lane < 32)
-        __builtin_amdgcn_global_load_lds((upd_global_ptr)(reinterpret_cast<const char*>(a.dvec) + kb + 4 * lane),
-                                         (upd_lds_ptr)(to + Sh::ROWS + Sh::COLS), 4, 0, 0);
-    }
+  // (parts RV + CV - 1 bring the operands, the last one the pivots)
+  auto request = [&](const int part, const int slab, const int stage) {
+    constexpr int SCOPE = LINES ? 0 : FLOW_DEVICE_SCOPE;
+    const unsigned kb = (unsigned)slab * 128u;
+    auto at = [&](const int e) { return lds0 + (unsigned)((stage * Sh::STAGE + e) * (int)sizeof(T)); };
+    if (part < RV)
+      flow_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.row[part]) + kb, roff[part], at((part * LEAF + wave * 8) * BK));
+    else if (part < RV + CV)
+      flow_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.col[part - RV]) + kb, coff[part - RV],
+                             at(Sh::ROWS + ((part - RV) * LEAF + wave * 8) * BK));
+    else if constexpr (!SCALED)       // the slab's pivots: 128 bytes, every wavefront the same, by both halves of it
+      flow_to_lds<4, 0>(reinterpret_cast<const char*>(a.dvec) + kb, 4u * (lane & 31), at(Sh::ROWS + Sh::COLS));
   };
-  auto request_any = [&](const int slab, const int stage) {
-    if (a.lines) request(slab, stage, std::integral_constant<int, 0>{});
-    else request(slab, stage, std::integral_constant<int, FLOW_DEVICE_SCOPE>{});
+  auto request_all = [&](const int slab, const int stage) {
+#pragma unroll
+    for (int part = 0; part < LOADS; ++part) request(part, slab, stage);
   };
 
   const int own_sw = (l16 >> 1) & 7;
@@ -442,31 +457,24 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const Flow
         if (t > 0) arrived(fc[t]);
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < NT) fetch(fc[t + 1], cs + ((t + 1) * SUB + pc) * BK, pc_sw);
-        else if (KIND == 0 || KIND == 3) prefetch(following);          // (behind the last slab: whatever is there)
+        if constexpr (KIND == 0 || KIND == 3) {
+          if (t == NT - 2) prefetch(following);                        // (behind the last slab: whatever is there)
+          if (t == NT - 1) ready();
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < KS; ++e) x[t] = X::mfma(fc[t][e], fr[e], x[t]);
         __builtin_amdgcn_sched_barrier(0);
-        if (t == 0) behind();
+        // (one load at a time: 40 in a row take 640 of a slab's 4096 clocks)
+#pragma unroll
+        for (int part = t; part < LOADS; part += NT) behind(part);
       }
     } else {
-      behind();
-    }
-    if constexpr (KIND == 1) {
 #pragma unroll
-      for (int u = 0; u < 3; ++u)
-        if (u < units.count) {
-          T fr[KS], fc[KS];
-          fetch(fr, rs + (units.row[u] * SUB + l16) * BK, own_sw);
-          fetch(fc, rs + (units.col[u] * SUB + l16) * BK, own_sw);
-          scale(fr, nd);
-#pragma unroll
-          for (int e = 0; e < KS; ++e) s[u] = X::mfma(fr[e], fc[e], s[u]);
-        }
-      prefetch(following);
+      for (int part = 0; part < LOADS; ++part) behind(part);
     }
-    if constexpr (KIND == 2) {
-      const int mine0 = (wave >> 2) * LEAF, other0 = LEAF - mine0;
+    if constexpr (KIND == 1 || KIND == 2) {
+      const int mine0 = KIND == 2 ? (wave >> 2) * LEAF : 0, other0 = KIND == 2 ? LEAF - mine0 : 0;
 #pragma unroll
       for (int u = 0; u < 3; ++u)
         if (u < units.count) {
@@ -479,7 +487,7 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const Flow
         }
       prefetch(following);
     }
-    ready();
+    if (KIND == 1 || KIND == 2 || !sums) ready();
   };
   // All but the newest slab's loads (`late`; or really all) of this wavefront have landed, and behind
   // the barrier those of all.
@@ -499,21 +507,31 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T>& a, const Flow
     if (upto < 0) return false;
     if (upto > nk) upto = nk;
     const int s0 = k * PER_TILE, s1 = upto * PER_TILE;
-    request_any(s0, 0);
-    request_any(s0 + 1, 1);                            // (a tile has at least two slabs)
-    if (s0 + 2 < s1) request_any(s0 + 2, 2);
+    request_all(s0, 0);
+    request_all(s0 + 1, 1);                            // (a tile has at least two slabs)
+    if (s0 + 2 < s1) request_all(s0 + 2, 2);
     landed(s0 + 2 < s1);
     prefetch(0);
     ready();
     // slab by slab; the next one has landed, for all wavefronts after the barrier, which also says
-    // that all are through with the slab before this one: its place takes the third from here
-    for (int slab = s0; slab < s1; slab += FLOW_STAGES) {
+    // that all are through with the slab before this one: its place takes the third from here.
+    // First without a condition on any of it
+    int slab = s0;
+    for (; slab + FLOW_STAGES + 2 < s1; slab += FLOW_STAGES) {
+#pragma unroll
+      for (int q = 0; q < FLOW_STAGES; ++q) {
+        if (q > 0 || slab > s0) landed(true);
+        multiply(q, (q + 1) % FLOW_STAGES,
+                 [&](const int part) { request(part, slab + q + 3, (q + 3) % FLOW_STAGES); });
+      }
+    }
+    for (; slab < s1; slab += FLOW_STAGES) {
 #pragma unroll
       for (int q = 0; q < FLOW_STAGES; ++q) {
         if (PER_TILE % FLOW_STAGES != 0 && q % PER_TILE == 0 && slab + q >= s1) break;
         if (slab + q > s0) landed(slab + q + 2 < s1);
-        multiply(q, (q + 1) % FLOW_STAGES, [&] {
-          if (slab + q + 3 < s1) request_any(slab + q + 3, (q + 3) % FLOW_STAGES);
+        multiply(q, (q + 1) % FLOW_STAGES, [&](const int part) {
+          if (slab + q + 3 < s1) request(part, slab + q + 3, (q + 3) % FLOW_STAGES);
         });
       }
     }
@@ -584,8 +602,8 @@ __device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, cons
 // to memory and, scaled by the pivots, to the copy.  The first through LDS (`out`, this wavefront's), so
 // that a store writes whole rows: in 16-byte pieces as the lanes hold them a row task's 64 KB
 // took 2.9 us to arrive.
-template <typename T>
-__device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, T* array, const int64_t r16, const int col,
+template <typename T, bool LINES>
+__device__ __forceinline__ void flow_store_rows(const FlowArgs<T, LINES>& a, T* array, const int64_t r16, const int col,
                                                 const T (&v)[NSUB][4], T* __restrict__ out, const int lane) {
   using vec_t = typename Mfma<T>::vec_t;
   constexpr int VEC = Mfma<T>::VEC, STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
@@ -624,8 +642,8 @@ __device__ __forceinline__ void flow_store_rows(const FlowArgs<T>& a, T* array, 
 }
 
 // 16 rows of `array` in tile column col, negated, as flow_accumulate collects them.
-template <typename T>
-__device__ __forceinline__ void flow_load_rows(const FlowArgs<T>& a, const T* array, const int64_t r16, const int col,
+template <typename T, bool LINES>
+__device__ __forceinline__ void flow_load_rows(const FlowArgs<T, LINES>& a, const T* array, const int64_t r16, const int col,
                                                typename Mfma<T>::acc_t* x, const int lane) {
   const int l16 = lane & 15, g = lane >> 4;
   const __amdgpu_buffer_rsrc_t from = flow_rsrc(array + r16 * a.ld + (int64_t)col * LEAF);
@@ -695,8 +713,8 @@ __device__ __forceinline__ void flow_gather(const int* __restrict__ perm, const 
     for (int e = 0; e < 4; ++e) x[b][e] = out[l16 * STRIDE + (from[b][e] - (int)first)];
 }
 
-template <typename T, FlowForm FORM>
-__device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pair, const int array, const int j,
+template <typename T, FlowForm FORM, bool LINES>
+__device__ __forceinline__ void flow_row_task(const FlowArgs<T, LINES>& a, const int pair, const int array, const int j,
                                               T* __restrict__ lds, int* shared) {
   using acc_t = typename Mfma<T>::acc_t;
   using Sh = FlowShape<T, FORM>;
@@ -757,8 +775,8 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T>& a, const int pa
 
 // A row task of columns j and j + 1, the tile rows of the pair whole and far from the diagonal: behind the
 // solve of the first column's tiles their products with tile (j + 1, j) come off the second's.
-template <typename T, FlowForm FORM>
-__device__ __forceinline__ void flow_row2_task(const FlowArgs<T>& a, const int pair, const int array, const int j,
+template <typename T, FlowForm FORM, bool LINES>
+__device__ __forceinline__ void flow_row2_task(const FlowArgs<T, LINES>& a, const int pair, const int array, const int j,
                                                T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
@@ -824,12 +842,8 @@ __device__ __forceinline__ void flow_row2_task(const FlowArgs<T>& a, const int p
       const T* from = of.col[1] + (int64_t)rt * a.ld + (int64_t)j * LEAF + chunk * VEC;
 #pragma unroll
       for (int p = 0; p < LEAF / BK; ++p) {
-        if (a.lines)
-          __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
-                                           0, 0);
-        else
-          __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
-                                           0, FLOW_DEVICE_SCOPE);
+        __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
+                                         0, LINES ? 0 : FLOW_DEVICE_SCOPE);
       }
       T d[NSUB][4];                    // the pivots in the order of the product
       if constexpr (!SCALED) {
@@ -929,8 +943,8 @@ __device__ __forceinline__ void flow_solved_slab(T* solved, const int q, const i
 }
 
 // The symmetric forms.
-template <typename T, FlowForm FORM>
-__device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T>& a, const int j, T* __restrict__ lds, int* shared) {
+template <typename T, FlowForm FORM, bool LINES>
+__device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T, LINES>& a, const int j, T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   using Sh = FlowShape<T, FORM>;
@@ -1052,8 +1066,8 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T>& a, const i
 
 // General matrices: P M = L D U of the leaf, and the tiles left of it in both arrays, L's by
 // wavefronts 0 to 3, U^T's by the others.
-template <typename T>
-__device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, const int j, T* __restrict__ lds, int* shared) {
+template <typename T, bool LINES>
+__device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T, LINES>& a, const int j, T* __restrict__ lds, int* shared) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   using Sh = FlowShape<T, FLOW_GENERAL>;
@@ -1160,8 +1174,8 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T>& a, cons
 // Starts on a page: its 47 to 64 KB of instructions nearly fill the instruction cache, and where in a page
 // the code before it made it start moved the pivoted form in fp64 by 1.4 % (n = 6000, the same
 // instructions 0x600 and 0xb00 behind a page's start 2391 and 2426 us, at its start 2392).
-template <typename T, FlowForm FORM>
-__attribute__((aligned(4096))) __global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T> a) {
+template <typename T, FlowForm FORM, bool LINES>
+__attribute__((aligned(4096))) __global__ __launch_bounds__(FLOW_THREADS) void panel_flow_kernel(FlowArgs<T, LINES> a) {
   __shared__ __attribute__((aligned(16))) T lds[FlowShape<T, FORM>::LDS_ELEMS];
   __shared__ int shared[2];
   if (threadIdx.x == 0)

@@ -356,16 +356,10 @@ struct Launcher {
            (w % LEAF == 0 || w == m) && (uint64_t)ld * sizeof(T) * LEAF < (1ull << 31) &&
            flow_order(m, w, arrays, 0).tasks() <= INT32_MAX;
   }
-  int factor_cols_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip) {
-    if (spd && (perm || qoff != 0)) return MDET_EINVAL;
+  template <bool LINES>
+  void launch_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip, FlowSync* from) {
     const int arrays = qoff != 0 ? 2 : 1;
-    const int64_t words = flow_words(m, arrays);
-    if (sync_used + words > sync_words) {
-      hipLaunchKernelGGL(flow_reset_kernel, dim3(1), dim3(1024), 0, st, sync, (int)sync_words);
-      ++launches;
-      sync_used = 0;
-    }
-    FlowArgs<T> a;
+    FlowArgs<T, LINES> a;
     a.P = P;
     a.ld = ld;
     a.m = (int)m;
@@ -379,17 +373,30 @@ struct Launcher {
     a.perm = perm ? perm + d0 : nullptr;
     a.pivot0 = d0;
     a.flags = flags;
-    a.sync = (FlowSync*)(sync + sync_used);
+    a.sync = from;
     // row tasks of two columns while flow_two has pairs of tile rows left for them
     a.order = flow_order(m, w, arrays, flow_two(m, w, arrays));
-    a.lines = ((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0 &&
-              (uint64_t)qoff * sizeof(T) % 128 == 0;
-    sync_used += words;
     const dim3 grid((unsigned)a.order.tasks()), block(FLOW_THREADS);
-    if (qoff != 0) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_GENERAL>), grid, block, 0, st, a);
-    else if (perm) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_PIVOT>), grid, block, 0, st, a);
-    else if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SPD>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SYM>), grid, block, 0, st, a);
+    if (qoff != 0) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_GENERAL, LINES>), grid, block, 0, st, a);
+    else if (perm) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_PIVOT, LINES>), grid, block, 0, st, a);
+    else if (spd) hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SPD, LINES>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((panel_flow_kernel<T, FLOW_SYM, LINES>), grid, block, 0, st, a);
+  }
+  int factor_cols_flow(hipStream_t st, T* P, int64_t ld, int64_t m, int64_t w, int64_t d0, T* Wp, int64_t wskip) {
+    if (spd && (perm || qoff != 0)) return MDET_EINVAL;
+    const int arrays = qoff != 0 ? 2 : 1;
+    const int64_t words = flow_words(m, arrays);
+    if (sync_used + words > sync_words) {
+      hipLaunchKernelGGL(flow_reset_kernel, dim3(1), dim3(1024), 0, st, sync, (int)sync_words);
+      ++launches;
+      sync_used = 0;
+    }
+    sync_used += words;
+    FlowSync* const from = (FlowSync*)(sync + sync_used - words);
+    if (((uintptr_t)P & 127u) == 0 && (uint64_t)ld * sizeof(T) % 128 == 0 && (uint64_t)qoff * sizeof(T) % 128 == 0)
+      launch_flow<true>(st, P, ld, m, w, d0, Wp, wskip, from);
+    else
+      launch_flow<false>(st, P, ld, m, w, d0, Wp, wskip, from);
     fail->check(hipGetLastError());
     ++launches;
     for (int64_t j = 0; j < w; j += LEAF) {
