@@ -157,7 +157,6 @@ static inline FlowOrder flow_order(int64_t m, int64_t w, int arrays, int two) {
 
 // Four consecutive entries past the caches: `base` is the same in all lanes, `off` bytes from it.
 typedef unsigned flow_u4 __attribute__((ext_vector_type(4)));
-constexpr int FLOW_DEVICE_SCOPE = 16;                 // the sc1 bit of a buffer or LDS-direct access
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t flow_rsrc(const void* base) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffffu, 0x00027000);
 }
@@ -165,27 +164,9 @@ template <typename T>
 __device__ __forceinline__ void flow_load4(__amdgpu_buffer_rsrc_t r, unsigned off, T (&v)[4]) {
 #pragma unroll
   for (int h = 0; h < (int)sizeof(T) / 4; ++h) {
-    const flow_u4 u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16 * h), 0, FLOW_DEVICE_SCOPE);
+    const flow_u4 u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16 * h), 0, DEVICE_SCOPE);
     __builtin_memcpy(&v[h * (16 / (int)sizeof(T))], &u, 16);
   }
-}
-// A wavefront's SIZE bytes a lane from base + off (base the same in all lanes) straight to LDS, lane by lane
-// from byte `at` on (the same in all lanes).  Written out because the compiler, told of the load, waits for it in front of the next
-// read of anything in LDS; the caller counts these loads and waits for them by itself (s_waitcnt vmcnt).
-template <int SIZE, int SCOPE>
-__device__ __forceinline__ void flow_to_lds(const char* base, const unsigned off, const unsigned at) {
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)base);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)base >> 32));
-  const unsigned long long from = ((unsigned long long)hi << 32) | lo;
-#define MDET_TO_LDS(WIDTH, BITS)                                                                         \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_" WIDTH " %1, %2" BITS                  \
-               :: "s"(at), "v"(off), "s"(from) : "m0")
-  static_assert((SIZE == 16 || SIZE == 4) && (SCOPE == 0 || SCOPE == FLOW_DEVICE_SCOPE), "forms in use");
-  if constexpr (SIZE == 16 && SCOPE == 0) MDET_TO_LDS("dwordx4", "");
-  else if constexpr (SIZE == 16) MDET_TO_LDS("dwordx4", " sc1");
-  else if constexpr (SCOPE == 0) MDET_TO_LDS("dword", "");
-  else MDET_TO_LDS("dword", " sc1");
-#undef MDET_TO_LDS
 }
 template <typename T, FlowForm FORM>
 struct FlowShape {
@@ -370,16 +351,16 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T, LINES>& a, con
   constexpr int LOADS = RV + CV + (SCALED ? 0 : 1);    // a wavefront's, per slab
   // (parts RV + CV - 1 bring the operands, the last one the pivots)
   auto request = [&](const int part, const int slab, const int stage) {
-    constexpr int SCOPE = LINES ? 0 : FLOW_DEVICE_SCOPE;
+    constexpr int SCOPE = LINES ? 0 : DEVICE_SCOPE;
     const unsigned kb = (unsigned)slab * 128u;
     auto at = [&](const int e) { return lds0 + (unsigned)((stage * Sh::STAGE + e) * (int)sizeof(T)); };
     if (part < RV)
-      flow_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.row[part]) + kb, roff[part], at((part * LEAF + wave * 8) * BK));
+      load_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.row[part]) + kb, roff[part], at((part * LEAF + wave * 8) * BK));
     else if (part < RV + CV)
-      flow_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.col[part - RV]) + kb, coff[part - RV],
+      load_to_lds<16, SCOPE>(reinterpret_cast<const char*>(of.col[part - RV]) + kb, coff[part - RV],
                              at(Sh::ROWS + ((part - RV) * LEAF + wave * 8) * BK));
     else if constexpr (!SCALED)       // the slab's pivots: 128 bytes, every wavefront the same, by both halves of it
-      flow_to_lds<4, 0>(reinterpret_cast<const char*>(a.dvec) + kb, 4u * (lane & 31), at(Sh::ROWS + Sh::COLS));
+      load_to_lds<4, 0>(reinterpret_cast<const char*>(a.dvec) + kb, 4u * (lane & 31), at(Sh::ROWS + Sh::COLS));
   };
   auto request_all = [&](const int slab, const int stage) {
 #pragma unroll
@@ -628,7 +609,7 @@ __device__ __forceinline__ void flow_store_rows(const FlowArgs<T, LINES>& a, T* 
     __builtin_memcpy(&u, &o, 16);
     if (r16 + r < a.m)
       __builtin_amdgcn_raw_buffer_store_b128(u, to, (int)(unsigned)(((int64_t)r * a.ld + c) * (int64_t)sizeof(T)), 0,
-                                             FLOW_DEVICE_SCOPE);
+                                             DEVICE_SCOPE);
   }
   if (a.W != nullptr && r16 + l16 < a.m && r16 + l16 >= a.wskip) {
     T d[NSUB][4];
@@ -843,7 +824,7 @@ __device__ __forceinline__ void flow_row2_task(const FlowArgs<T, LINES>& a, cons
 #pragma unroll
       for (int p = 0; p < LEAF / BK; ++p) {
         __builtin_amdgcn_global_load_lds((upd_global_ptr)(from + p * BK), (upd_lds_ptr)(tile + (p * LEAF + wave * 8) * BK), 16,
-                                         0, LINES ? 0 : FLOW_DEVICE_SCOPE);
+                                         0, LINES ? 0 : DEVICE_SCOPE);
       }
       T d[NSUB][4];                    // the pivots in the order of the product
       if constexpr (!SCALED) {

@@ -17,6 +17,12 @@
 // straight into LDS, double buffered, the next slab's loads in flight while the
 // current one is multiplied.  The scaling by -d is applied to the A fragments as
 // they are read from LDS; the accumulators are seeded with C.
+// Bound by the matrix cores.  The wavefronts of a workgroup meet once a slab, in front of its last strip
+// of products, behind which nothing of the slab is read any more: the next slab's first fragments and
+// the loads of the one after it go out beside those products.  Measured, M = N = 16384, K = 2048, random
+// entries: fp64 73.6 TFLOP/s with scaling, 74.1 without (66.9 and 70.8 with the loads in one piece at the
+// start of a slab and the meeting at its end), fp32 142.8 and 146.0 (133.7, 137.9); of the 78.6 / 157.3 at
+// the matrix cores' peak 4 % go into loading and storing C.
 //
 // Also here, because it ends with the same hand-over of the next leaf: leaf_update_kernel
 // (K = 64, one shot from LDS).
@@ -158,12 +164,34 @@ struct UpdShape {
   using X = Mfma<T>;
   static constexpr int BK = X::BK;                                // K elements per slab: 128 bytes a row
   static constexpr int BM = 32 * TM, BN = 32 * TM;                // block of C per workgroup
-  static constexpr int SLAB_ELEMS = 2 * (BM + BN) * BK;           // both operands, double buffered
+  static constexpr int PIVOTS = 2 * (BM + BN) * BK;               // both operands, double buffered; then
+  static constexpr int SLAB_ELEMS = PIVOTS + 4 * BK;              // the pivots of a slab (twice), likewise
   static constexpr int LDS_ELEMS = SLAB_ELEMS > FACTOR_LDS_ELEMS ? SLAB_ELEMS : FACTOR_LDS_ELEMS;
 };
 
 typedef __attribute__((address_space(1))) const void* upd_global_ptr;
 typedef __attribute__((address_space(3))) void* upd_lds_ptr;
+
+constexpr int DEVICE_SCOPE = 16;                      // the sc1 bit of a buffer or LDS-direct access
+// A wavefront's SIZE bytes a lane from base + off (base the same in all lanes) straight to LDS, lane by lane
+// from byte `at` on (the same in all lanes).  Written out because the compiler, told of the load, waits for
+// it in front of the next read of anything in LDS; the caller counts these loads and waits for them by
+// itself (s_waitcnt vmcnt).
+template <int SIZE, int SCOPE>
+__device__ __forceinline__ void load_to_lds(const char* base, const unsigned off, const unsigned at) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)base);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)base >> 32));
+  const unsigned long long from = ((unsigned long long)hi << 32) | lo;
+#define MDET_TO_LDS(WIDTH, BITS)                                                                         \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_" WIDTH " %1, %2" BITS                  \
+               :: "s"(at), "v"(off), "s"(from) : "m0")
+  static_assert((SIZE == 16 || SIZE == 4) && (SCOPE == 0 || SCOPE == DEVICE_SCOPE), "forms in use");
+  if constexpr (SIZE == 16 && SCOPE == 0) MDET_TO_LDS("dwordx4", "");
+  else if constexpr (SIZE == 16) MDET_TO_LDS("dwordx4", " sc1");
+  else if constexpr (SCOPE == 0) MDET_TO_LDS("dword", "");
+  else MDET_TO_LDS("dword", " sc1");
+#undef MDET_TO_LDS
+}
 
 // One block (bm, bn) of C, by all threads of the workgroup; `lds` = LDS_ELEMS
 // elements.  Every thread returns from it (there are barriers inside), so a
@@ -208,7 +236,8 @@ __device__ __forceinline__ void schur_update_block(
   T (*Bs)[BN * BK] = reinterpret_cast<T (*)[BN * BK]>(lds + 2 * BM * BK);
 
   const int row0 = bm * BM, col0 = bn * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   // a wavefront whose 64 x 64 piece lies strictly above the diagonal has nothing to do
   const bool active = !(lower && (row0 + wm * WT + WT - 1 < col0 + wn * WT));
@@ -232,25 +261,26 @@ __device__ __forceinline__ void schur_update_block(
     aoff[v] = (unsigned)(((int64_t)ar * lda + chunk * VEC) * (int64_t)sizeof(T));
     boff[v] = (unsigned)(((int64_t)br * ldb + chunk * VEC) * (int64_t)sizeof(T));
   }
-  // Two nudges keep these loads in the "scalar base + 32-bit vector offset" form
-  // inside the K loop, instead of one 64-bit induction pointer per lane and load:
-  // the slab's byte offset goes through readfirstlane (it is uniform anyway), and
-  // the per-lane offset through an empty asm, so that its widening is not hoisted
-  // out of the loop.
-  auto pinned = [](unsigned o) { asm volatile("" : "+v"(o)); return o; };
-  auto gload = [&](int kt, int buf) {
-    const unsigned kb = __builtin_amdgcn_readfirstlane((unsigned)kt * (unsigned)(BK * sizeof(T)));
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int blk = __builtin_amdgcn_readfirstlane(4 * v + wave);
-      __builtin_amdgcn_global_load_lds((upd_global_ptr)(Abase + kb + pinned(aoff[v])),
-                                       (upd_lds_ptr)(&As[buf][blk * 8 * BK]), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((upd_global_ptr)(Bbase + kb + pinned(boff[v])),
-                                       (upd_lds_ptr)(&Bs[buf][blk * 8 * BK]), 16, 0, 0);
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(upd_lds_ptr)lds);
+  constexpr int LOADS = 2 * NV + (SCALED ? 0 : 1);            // a wavefront's, per slab
+  auto gload = [&](const int part, const int kt, const int buf) {
+    const unsigned kb = (unsigned)kt * (unsigned)(BK * sizeof(T));
+    auto at = [&](const int e) { return lds0 + (unsigned)(e * (int)sizeof(T)); };
+    if (part < 2 * NV) {
+      const int v = part / 2, rows = 8 * (4 * v + wave);
+      if (part % 2 == 0) load_to_lds<16, 0>(Abase + kb, aoff[v], at((buf * BM + rows) * BK));
+      else load_to_lds<16, 0>(Bbase + kb, boff[v], at(((2 * BM + buf * BN) + rows) * BK));
+    } else if constexpr (!SCALED) {
+      // the slab's pivots, every wavefront the same, by both halves of it
+      load_to_lds<4, 0>(reinterpret_cast<const char*>(d) + kb, 4u * (lane & 31), at(UpdShape<T, TM>::PIVOTS + buf * 2 * BK));
     }
   };
-  // all of this wavefront's loads have landed (the barrier that follows publishes them)
-  auto landed = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+  // all of this wavefront's loads have landed, and behind the barrier those of all
+  auto landed = [] {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
 
   const int r16 = lane & 15, g = lane >> 4;
 
@@ -290,17 +320,11 @@ __device__ __forceinline__ void schur_update_block(
   // (rows 16 apart share the swizzle).
   const int sw = (r16 >> 1) & 7;
   const int c0 = ((2 * g) ^ sw) * VEC, c1 = ((2 * g + 1) ^ sw) * VEC;
-  const T* dlane = d + g * KS;
-  vec_t dcur[2], dnext[2];                            // d of this lane's k's: current slab, next slab
-  auto load_d = [&](vec_t (&dst)[2], int kt) {
-    dst[0] = *reinterpret_cast<const vec_t*>(dlane + (int64_t)kt * BK);
-    dst[1] = *reinterpret_cast<const vec_t*>(dlane + (int64_t)kt * BK + VEC);
-  };
-
-  gload(0, 0);
-  if (!SCALED && active) load_d(dcur, 0);
+#pragma unroll
+  for (int part = 0; part < LOADS; ++part) gload(part, 0, 0);
   landed();
-  __syncthreads();
+#pragma unroll
+  for (int part = 0; part < LOADS; ++part) gload(part, 1, 1);
   {
     // -C, in one go now that the loads have landed (negating each entry as it is
     // loaded would make every load wait for itself)
@@ -312,74 +336,106 @@ __device__ __forceinline__ void schur_update_block(
         for (int r = 0; r < 4; ++r) acc[i][j][r] = -acc[i][j][r];
   }
 
-  // One slab; MORE: another one follows (decided at compile time, so that the
-  // stages of a slab form one straight run of instructions).  The next slab's loads
-  // go out first, into the buffer nobody reads during this slab.
-  auto slab = [&](const int kt, auto more_tag) {
-    constexpr bool MORE = decltype(more_tag)::value;
-    const int buf = kt & 1;
-    if (MORE) gload(kt + 1, buf ^ 1);
-    if (active) {
-      if (!SCALED && MORE) load_d(dnext, kt + 1);
-      T nd[KS];                                         // d, this lane's k's
-      if constexpr (!SCALED) {
+  // Fragments are fetched one 16-row strip at a time, each fetch issued one stage ahead of its first
+  // use, so that LDS latency hides behind the chain of MFMAs of the stage before.  Stage (i, j): all
+  // KS products of accumulator (i, j) back to back.  In front of the last strip's products, when nothing
+  // more is read of this slab, the wavefronts meet: the next slab has landed, whose first fragments
+  // are fetched and scaled beside these products, and this one's place takes the slab after that,
+  // one or two loads behind each group of products.
+  T fa[2][KS], fb[TM][KS], nd[KS];
+  auto fetch = [&](T (&f)[KS], const T* base) {
+    const vec_t v0 = *reinterpret_cast<const vec_t*>(base + c0);
+    const vec_t v1 = *reinterpret_cast<const vec_t*>(base + c1);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { nd[e] = dcur[0][e]; nd[VEC + e] = dcur[1][e]; }
-      }
-      const T* as = &As[buf][(wm * WT + r16) * BK];
-      const T* bs = &Bs[buf][(wn * WT + r16) * BK];
-      // Fragments are fetched one 16-row strip at a time, each fetch issued one
-      // stage ahead of its first use, so that LDS latency hides behind the chain
-      // of MFMAs of the stage before.  Stage (i, j): all KS products of
-      // accumulator (i, j) back to back.
-      T fa[2][KS], fb[TM][KS];
-      auto fetch = [&](T (&f)[KS], const T* base) {
-        const vec_t v0 = *reinterpret_cast<const vec_t*>(base + c0);
-        const vec_t v1 = *reinterpret_cast<const vec_t*>(base + c1);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
-      };
-      auto scale = [&](T (&f)[KS]) {
-        if constexpr (!SCALED) {
-#pragma unroll
-          for (int e = 0; e < KS; ++e) f[e] *= nd[e];
-        }
-      };
-      fetch(fa[0], as);
-      fetch(fb[0], bs);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int j = 0; j < TM; ++j) {
-          if (i == 0 && j + 1 < TM) fetch(fb[j + 1], bs + (j + 1) * 16 * BK);
-          if (j == TM - 1 && i + 1 < TM) fetch(fa[(i + 1) & 1], as + (i + 1) * 16 * BK);
-          if (j == 0) scale(fa[i & 1]);
-          __builtin_amdgcn_sched_barrier(0);   // all of the above goes out before this stage's products
-#pragma unroll
-          for (int e = 0; e < KS; ++e) acc[i][j] = X::mfma(fa[i & 1][e], fb[j][e], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    if (MORE) {
-      landed();
-      if constexpr (!SCALED) {
-        dcur[0] = dnext[0];
-        dcur[1] = dnext[1];
-      }
-    }
-    __syncthreads();
+    for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
   };
-  for (int kt = 0; kt + 1 < nk; ++kt) slab(kt, std::true_type{});
-  slab(nk - 1, std::false_type{});
+  auto fetch_pivots = [&](const int buf) {
+    if constexpr (!SCALED) {
+#pragma unroll
+      for (int h = 0; h < KS / VEC; ++h) {
+        const vec_t v = *reinterpret_cast<const vec_t*>(lds + UpdShape<T, TM>::PIVOTS + buf * 2 * BK + g * KS + h * VEC);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) nd[h * VEC + e] = v[e];
+      }
+    }
+  };
+  auto scale = [&](T (&f)[KS]) {
+    if constexpr (!SCALED) {
+#pragma unroll
+      for (int e = 0; e < KS; ++e) f[e] *= nd[e];
+    }
+  };
+  auto rows_of = [&](const int buf) { return &As[buf][(wm * WT + r16) * BK]; };
+  auto cols_of = [&](const int buf) { return &Bs[buf][(wn * WT + r16) * BK]; };
+  // One slab.  MORE slabs follow: 2 and more, 1 or 0 (decided at compile time, so that the stages of a slab
+  // form one straight run of instructions).
+  auto slab = [&](const int kt, auto buf_tag, auto more_tag) {
+    constexpr int BUF = decltype(buf_tag)::value, MORE = decltype(more_tag)::value;
+    const T* as = rows_of(BUF);
+    const T* bs = cols_of(BUF);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        if (i == 0 && j + 1 < TM) fetch(fb[j + 1], bs + (j + 1) * 16 * BK);
+        if (j == TM - 1 && i + 1 < TM) fetch(fa[(i + 1) & 1], as + (i + 1) * 16 * BK);
+        if (j == 0 && i > 0) scale(fa[i & 1]);
+        if (i == TM - 1 && MORE > 0) {
+          if (j == 0) {
+            landed();
+            fetch(fa[0], rows_of(BUF ^ 1));
+            fetch_pivots(BUF ^ 1);
+          }
+          if (j == 1) fetch(fb[0], cols_of(BUF ^ 1));
+          if (j == TM - 1) scale(fa[0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // all of the above goes out before this stage's products
+#pragma unroll
+        for (int e = 0; e < KS; ++e) acc[i][j] = X::mfma(fa[i & 1][e], fb[j][e], acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i == TM - 1 && MORE > 1) {
+#pragma unroll
+          for (int part = 0; part < LOADS; ++part)
+            if (part * TM / LOADS == j) gload(part, kt + 2, BUF);
+        }
+      }
+    }
+  };
+  using Zero = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  static_assert(TM % 2 == 0, "the last strip is in fa[1], the next slab's first goes to fa[0]");
+  // (K is a multiple of 64: an even number of slabs, at least two)
+  if (active) {
+    fetch(fa[0], rows_of(0));
+    fetch(fb[0], cols_of(0));
+    fetch_pivots(0);
+    scale(fa[0]);
+    int kt = 0;
+    for (; kt + 2 < nk; kt += 2) {
+      slab(kt, Zero{}, Two{});
+      slab(kt + 1, One{}, Two{});
+    }
+    slab(kt, Zero{}, One{});
+    slab(kt + 1, One{}, Zero{});
+  } else {
+    for (int kt = 0; kt + 1 < nk; ++kt) {
+      landed();
+      if (kt + 2 < nk) {
+#pragma unroll
+        for (int part = 0; part < LOADS; ++part) gload(part, kt + 2, kt & 1);
+      }
+    }
+  }
 
   // ---- epilogue: store the reduced block ----------------------------------
   // The workgroup that goes on to factor the leaf at the block's top left hands that
-  // part over in LDS (the operand buffers are free after the last slab's barrier)
+  // part over in LDS (the operand buffers are free behind a barrier)
   // and leaves its write-back to the factorisation.
   const bool fuse = lower && fl.w > 0 && bm == 0 && bn == 0;
   const int wleaf = fuse ? fl.w : 0;
   if (fuse) {
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
