@@ -274,28 +274,93 @@ struct Diag16 {
   }
 };
 
-// v -= sum_k h[k] w_k, w_k in lane k of each row of 16 lanes (the wait covers the instruction
-// that made w, see MDET_STEP)
+// v -= sum_k h[k] w_k for the first 4, 8, 12 or 16 k, w_k in lane k of each row of 16 lanes (the wait
+// covers the instruction that made w, see MDET_STEP)
 #define MDET_APPLY_TERM(K, H) MDET_FMAC " %0, -%1, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
-#define MDET_APPLY16(TYPE)                                                                              \
-  __device__ __forceinline__ void apply16(TYPE& v, const TYPE (&h)[16], TYPE w) {                    \
-    asm("s_nop 1\n\t" MDET_APPLY_TERM("0", "2") MDET_APPLY_TERM("1", "3") MDET_APPLY_TERM("2", "4")              \
-            MDET_APPLY_TERM("3", "5") MDET_APPLY_TERM("4", "6") MDET_APPLY_TERM("5", "7") MDET_APPLY_TERM("6", "8") \
-                MDET_APPLY_TERM("7", "9") MDET_APPLY_TERM("8", "10") MDET_APPLY_TERM("9", "11")                  \
-                    MDET_APPLY_TERM("10", "12") MDET_APPLY_TERM("11", "13") MDET_APPLY_TERM("12", "14")          \
-                        MDET_APPLY_TERM("13", "15") MDET_APPLY_TERM("14", "16") MDET_APPLY_TERM("15", "17")      \
-        : "+v"(v)                                                                                       \
-        : "v"(w), "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3]), "v"(h[4]), "v"(h[5]), "v"(h[6]),          \
-          "v"(h[7]), "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11]), "v"(h[12]), "v"(h[13]), "v"(h[14]),  \
-          "v"(h[15]));                                                                                  \
+#define MDET_APPLY_TERM1(K, H) MDET_FMAC " %1, -%2, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define MDET_APPLY_TERM0(K, H) MDET_FMAC " %0, -%2, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define MDET_APPLY_TERMS4 MDET_APPLY_TERM("0", "2") MDET_APPLY_TERM("1", "3") MDET_APPLY_TERM("2", "4") MDET_APPLY_TERM("3", "5")
+#define MDET_APPLY_TERMS8 \
+  MDET_APPLY_TERMS4 MDET_APPLY_TERM("4", "6") MDET_APPLY_TERM("5", "7") MDET_APPLY_TERM("6", "8") MDET_APPLY_TERM("7", "9")
+#define MDET_APPLY_TERMS12 \
+  MDET_APPLY_TERMS8 MDET_APPLY_TERM("8", "10") MDET_APPLY_TERM("9", "11") MDET_APPLY_TERM("10", "12") MDET_APPLY_TERM("11", "13")
+#define MDET_APPLY_TERMS16 \
+  MDET_APPLY_TERMS12 MDET_APPLY_TERM("12", "14") MDET_APPLY_TERM("13", "15") MDET_APPLY_TERM("14", "16") MDET_APPLY_TERM("15", "17")
+#define MDET_H4 "v"(h[0]), "v"(h[1]), "v"(h[2]), "v"(h[3])
+#define MDET_H8 MDET_H4, "v"(h[4]), "v"(h[5]), "v"(h[6]), "v"(h[7])
+#define MDET_H12 MDET_H8, "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11])
+#define MDET_H16 MDET_H12, "v"(h[12]), "v"(h[13]), "v"(h[14]), "v"(h[15])
+#define MDET_APPLY(TYPE, N) asm("s_nop 1\n\t" MDET_APPLY_TERMS##N : "+v"(v) : "v"(w), MDET_H##N)
+#define MDET_APPLY_ALL(TYPE)                                                                 \
+  template <int N>                                                                           \
+  __device__ __forceinline__ void apply_terms(TYPE& v, const TYPE (&h)[16], TYPE w) {        \
+    static_assert(N == 4 || N == 8 || N == 12 || N == 16, "terms in fours");                 \
+    if constexpr (N == 4) MDET_APPLY(TYPE, 4);                                               \
+    else if constexpr (N == 8) MDET_APPLY(TYPE, 8);                                          \
+    else if constexpr (N == 12) MDET_APPLY(TYPE, 12);                                        \
+    else MDET_APPLY(TYPE, 16);                                                               \
+  }
+// The first 8, 12 or 16 terms, the even k to v0 and the odd ones to v1: a multiply-add waits 11 clocks for the one
+// before it in a sum, and two sums in turn take half as long.
+#define MDET_APPLY_PAIRS8                                                                                   \
+  MDET_APPLY_TERM0("0", "3") MDET_APPLY_TERM1("1", "4") MDET_APPLY_TERM0("2", "5") MDET_APPLY_TERM1("3", "6") \
+  MDET_APPLY_TERM0("4", "7") MDET_APPLY_TERM1("5", "8") MDET_APPLY_TERM0("6", "9") MDET_APPLY_TERM1("7", "10")
+#define MDET_APPLY_PAIRS12                                                                                  \
+  MDET_APPLY_PAIRS8 MDET_APPLY_TERM0("8", "11") MDET_APPLY_TERM1("9", "12") MDET_APPLY_TERM0("10", "13")     \
+  MDET_APPLY_TERM1("11", "14")
+#define MDET_APPLY_PAIRS16                                                                                  \
+  MDET_APPLY_PAIRS12 MDET_APPLY_TERM0("12", "15") MDET_APPLY_TERM1("13", "16") MDET_APPLY_TERM0("14", "17")  \
+  MDET_APPLY_TERM1("15", "18")
+#define MDET_APPLY_PAIR(N) asm("s_nop 1\n\t" MDET_APPLY_PAIRS##N : "+v"(v0), "+v"(v1) : "v"(w), MDET_H##N)
+#define MDET_APPLY_PAIR_ALL(TYPE)                                                                    \
+  template <int N>                                                                                   \
+  __device__ __forceinline__ void apply_pairs(TYPE& v0, TYPE& v1, const TYPE (&h)[16], TYPE w) {     \
+    static_assert(N == 8 || N == 12 || N == 16, "terms in fours");                                   \
+    if constexpr (N == 8) MDET_APPLY_PAIR(8);                                                        \
+    else if constexpr (N == 12) MDET_APPLY_PAIR(12);                                                 \
+    else MDET_APPLY_PAIR(16);                                                                        \
   }
 #define MDET_FMAC "v_fmac_f64_dpp"
-MDET_APPLY16(double)
+MDET_APPLY_ALL(double)
+MDET_APPLY_PAIR_ALL(double)
 #undef MDET_FMAC
 #define MDET_FMAC "v_fmac_f32_dpp"
-MDET_APPLY16(float)
+MDET_APPLY_ALL(float)
+MDET_APPLY_PAIR_ALL(float)
 #undef MDET_FMAC
-#undef MDET_APPLY16
+#undef MDET_APPLY_PAIR_ALL
+#undef MDET_APPLY_PAIR
+#undef MDET_APPLY_PAIRS16
+#undef MDET_APPLY_PAIRS12
+#undef MDET_APPLY_PAIRS8
+#undef MDET_APPLY_ALL
+#undef MDET_APPLY_TERM0
+#undef MDET_APPLY_TERM1
+#undef MDET_APPLY
+#undef MDET_H16
+#undef MDET_H12
+#undef MDET_H8
+#undef MDET_H4
+#undef MDET_APPLY_TERMS16
+#undef MDET_APPLY_TERMS12
+#undef MDET_APPLY_TERMS8
+#undef MDET_APPLY_TERMS4
+// The first j terms (the registers of the others hold zeros): j is known where a loop is unrolled.  With v1
+// the odd ones go there.
+template <typename T>
+__device__ __forceinline__ void apply_first(T& v, T& v1, const T (&h)[16], T w, const int j) {
+  if (j > 12) apply_pairs<16>(v, v1, h, w);
+  else if (j > 8) apply_pairs<12>(v, v1, h, w);
+  else if (j > 4) apply_pairs<8>(v, v1, h, w);
+  else if (j > 0) apply_terms<4>(v, h, w);
+}
+template <typename T>
+__device__ __forceinline__ void apply_first(T& v, const T (&h)[16], T w, const int j) {
+  if (j > 12) apply_terms<16>(v, h, w);
+  else if (j > 8) apply_terms<12>(v, h, w);
+  else if (j > 4) apply_terms<8>(v, h, w);
+  else if (j > 0) apply_terms<4>(v, h, w);
+}
 #undef MDET_APPLY_TERM
 
 // Inverse of a unit-lower 16 x 16 block -> linv (16 x 16, row-major), by one wavefront: nl[k]
@@ -598,9 +663,10 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
 template <typename T>
 using lds_volatile = volatile __attribute__((address_space(3))) T;
 
-// The pivot rule: the lane of `cand` (not empty) whose v is largest in magnitude, the lowest
+// The pivot rule: the lane of `cand` whose v is largest in magnitude, the lowest
 // one on ties.  Magnitudes of IEEE numbers order like their bit patterns without the sign; a
-// NaN is above all others, so that it is taken and reported.  Must be reached by all 64 lanes.
+// NaN is above all others, so that it is taken and reported.  Must be reached by all 64 lanes.  (`cand`
+// empty: the last lane.)
 __device__ __forceinline__ int pick_lane(double v, unsigned long long cand) {
   const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
   const unsigned hi = (unsigned)__double2hiint(v) & 0x7fffffffu;
@@ -613,13 +679,13 @@ __device__ __forceinline__ int pick_lane(double v, unsigned long long cand) {
     const unsigned top_lo = wave_max_u32(level ? lo : 0u);
     hit &= __builtin_amdgcn_ballot_w64(lo == top_lo);
   }
-  return __builtin_ctzll(hit);
+  return __builtin_ctzll(hit | 1ull << 63);
 }
 __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
   const bool mine = __builtin_amdgcn_inverse_ballot_w64(cand);
   const unsigned key = __float_as_uint(v) & 0x7fffffffu;
   const unsigned top = wave_max_u32(mine ? key : 0u);
-  return __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == top) & cand);
+  return __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == top) & cand | 1ull << 63);
 }
 
 // One leaf, P A P^T = L D L^T with P chosen inside the leaf: at every step the largest
@@ -700,7 +766,7 @@ __device__ __forceinline__ void leaf_factor_pivoted_body(
         const T est = rcp_estimate(d);
         const T tail = quotient_tail(d, est);
         left &= ~(1ull << p);
-        if (j > 0) apply16(v, l, lp * dm);
+        apply_first(v, l, lp * dm, j);
         dm = mine == j ? d : dm;
         const T q = v * est;
         l[j] = __builtin_amdgcn_inverse_ballot_w64(left) ? fma(q, tail, q) : T(0);

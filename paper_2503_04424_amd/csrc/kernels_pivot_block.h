@@ -30,6 +30,7 @@
 #include <limits>
 
 #include "kernels_leaf.h"
+#include "kernels_update.h"
 
 namespace mdet {
 
@@ -169,16 +170,18 @@ __global__ __launch_bounds__(PB_THREADS) void pb_step_kernel(
 
 // All steps of a group of up to 64 pivots in one launch of one workgroup, thread i holding
 // row i (w <= NT): its running diagonal and its multipliers of this group stay in registers.
-// Per step: every wavefront's best candidate to LDS (one barrier), its row of S requested in
-// advance; the overall best found by every thread alone; the pivot's row of S read; the thread
-// that holds the pivot puts its multipliers into LDS meanwhile (second barrier); then v, l and
-// the new diagonal as in pb_step_kernel, with the 16 products of a block of multipliers taking
-// the pivot's entries from the lanes of the row (one instruction each).  At the end the group's
-// leaf, in pivot order, with the inverses of its diagonal sub-blocks (as pb_leaf_kernel).  Same
-// rule, same order of the terms, same outputs as a sequence of pb_step_kernel launches, where a
-// launch and its memory round trips made a step 5.7 us; here it is 1.1 us (w = 256, fp64;
-// n = 3000 21.9 -> 5.3 ms).  Bound by a step's chain: search 300 clocks, exchange, row of S
-// 1100, products, quotient.
+// The rows of S that the group is likely to take, those of the largest diagonal entries as it begins,
+// are brought into LDS first, and their multipliers kept there.  Per step: every wavefront's best candidate
+// to LDS; one barrier; the overall best found by every thread alone; its row of S and multipliers from
+// LDS, or from memory and the row's thread where another row than expected is taken; then v, l and the new diagonal as in pb_step_kernel, with
+// the products of a block of multipliers taking the pivot's entries from the lanes of the row (one
+// instruction each).  At the end the group's leaf, in pivot order, with the inverses of its diagonal
+// sub-blocks (as pb_leaf_kernel).  Same rule, same order of the terms as a sequence of
+// pb_step_kernel launches, where a launch and its memory round trips made a step 5.7 us.
+// Bound by a step's chain, w = 256, fp64: search 150 clocks, offer and barrier 140, best of the offers 190, row and
+// multipliers from LDS 150, products 370, quotient and the rest 200: 0.65 us.  A launch of 64 steps 44 us; 71 with the row
+// of S from memory (1100 clocks), a second barrier for the pivot's multipliers and a dozen jumps a step
+// (n = 3000, b = 256 4.89 -> 3.50 ms; where half of the rows taken are not held, 4.82 -> 3.81).
 // The multipliers of 512 rows are what a compute unit's registers hold (128 of 256 per
 // thread in fp64): larger blocks take a launch per step.
 constexpr int PB_GROUP_ROWS = 512;
@@ -189,6 +192,151 @@ __device__ __forceinline__ unsigned long long pb_magnitude(double v) {
 }
 __device__ __forceinline__ unsigned long long pb_magnitude(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
+// A power of two that brings d away from the ends of its range if it is there.
+__device__ __forceinline__ double pb_lift(double d) {
+  const unsigned e = ((unsigned)__double2hiint(d) >> 20) & 0x7ffu;
+  return __hiloint2double(e == 0u ? 0x46700000 : (e > 0x7fbu ? 0x39700000 : 0x3ff00000), 0);      // 2^104, 2^-104, 1
+}
+__device__ __forceinline__ float pb_lift(float d) {
+  const unsigned e = (__float_as_uint(d) >> 23) & 0xffu;
+  return __uint_as_float(e == 0u ? 0x56800000u : (e > 0xfbu ? 0x28800000u : 0x3f800000u));        // 2^46, 2^-46, 1
+}
+
+// What a wavefront offers as the pivot: its value; its row, and its place in LDS (or -1) from bit 16 on;
+// the upper word of its magnitude plus one (no candidate: 0).
+struct alignas(16) PbOffer {
+  unsigned lo, hi;
+  int row;
+  unsigned rank;
+};
+__device__ __forceinline__ PbOffer pb_offer(double v, int row, bool any) {
+  const unsigned hi = (unsigned)__double2hiint(v);
+  return {(unsigned)__double2loint(v), hi, row, any ? (hi & 0x7fffffffu) + 1u : 0u};
+}
+__device__ __forceinline__ PbOffer pb_offer(float v, int row, bool any) {
+  return {0u, __float_as_uint(v), row, any ? (__float_as_uint(v) & 0x7fffffffu) + 1u : 0u};
+}
+__device__ __forceinline__ void pb_value(const PbOffer& o, int q, double& d) {
+  d = __hiloint2double(__builtin_amdgcn_readlane((int)o.hi, q), __builtin_amdgcn_readlane((int)o.lo, q));
+}
+__device__ __forceinline__ void pb_value(const PbOffer& o, int q, float& d) {
+  d = __int_as_float(__builtin_amdgcn_readlane((int)o.hi, q));
+}
+// The best of NW offers, offer l % NW in lane l: larger magnitude wins, the first on ties (which has
+// the smaller row).
+template <typename T, int NW>
+__device__ __forceinline__ int pb_best(const PbOffer& o) {
+  unsigned m = o.rank;
+  m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, false));     // lanes 1 0 3 2 of each four
+  m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, false));     // lanes 2 3 0 1
+  if (NW == 8) m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xF, 0xF, false));   // mirror inside each eight
+  unsigned hit = (unsigned)__builtin_amdgcn_ballot_w64(o.rank == m) & ((1u << NW) - 1u);
+  if (sizeof(T) == 8 && __builtin_expect((hit & (hit - 1u)) != 0u, 0)) {
+    const bool level = __builtin_amdgcn_inverse_ballot_w64((unsigned long long)hit);
+    const unsigned top = wave_max_u32(level ? o.lo : 0u);
+    hit &= (unsigned)__builtin_amdgcn_ballot_w64(o.lo == top);
+  }
+  return __builtin_ctz(hit);
+}
+
+// Rows of S that LDS holds, with their multipliers: all 64 that a group takes where they fit.
+template <typename T, int NT>
+struct PbHeld {
+  static constexpr int ROOM = 156 * 1024 / (int)sizeof(T);
+  static constexpr int HELD = 64 * NT + LEAF * 65 <= ROOM ? 64 : (ROOM - LEAF) / (NT + LEAF) / 2 * 2;
+  static constexpr int STRIDE = HELD + 1;        // (column HELD: of rows that are not held)
+  T rows[HELD * NT];                             // at the end the group's leaf
+  T mult[LEAF * STRIDE];                         // multipliers, by step
+  T other[SUB];                                  // the last ones of a row that is not held
+  PbOffer offer[2][NT / 64];                     // every wavefront's best candidate; two steps in turn
+  int place[HELD];
+};
+
+// A thread's row in a group of steps.
+template <typename T, int NT>
+struct PbRow {
+  using H = PbHeld<T, NT>;
+  static constexpr int NW = NT / 64;
+  H& s;
+  const T* S;
+  const int64_t lds;
+  const T* L;                                    // this group's columns of Lfull
+  const int64_t ldl;
+  const int w, lw;
+  const int i, lane, l16, wave;
+  int place;                                     // in s, or -1
+  T* own;                                        // its column of s.mult
+  T diag;
+  unsigned long long left;                       // the wavefront's rows that are still to be taken
+  int mypos = -1;                                // step at which this row was taken
+  // multipliers of the finished blocks of 16 steps and of the current one (0: not taken yet);
+  // pivots and rows likewise, step k of a block in lane k of each row of lanes
+  T h[3][SUB], cur[SUB], dh[3], dcur;
+  int pcur;
+
+  // 16 steps, the M-th block of them (known at compile time, like the step in it: a jump on either costs
+  // a step some 25 clocks, and there were a dozen)
+  template <int M>
+  __device__ __forceinline__ void block() {
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) cur[k] = T(0);
+    dcur = T(0);
+    pcur = 0;
+    int mine = l16;
+    asm volatile("" : "+v"(mine));               // compared here, not kept as 16 masks in scalar registers
+#pragma unroll
+    for (int j = 0; j < SUB; ++j) {
+      constexpr int J0 = SUB * M;
+      const int par = j & 1;
+      if (J0 + j >= lw) break;
+      const int best = pick_lane(diag, left);
+      // (what the step before last left in these places has been read: its readers are through a barrier)
+      if (lane == best) s.offer[par][wave] = pb_offer(diag, i | (place << 16), left != 0ull);
+      __syncthreads();
+      const PbOffer o = s.offer[par][lane & (NW - 1)];
+      const int win = pb_best<T, NW>(o);
+      T d;
+      pb_value(o, win, d);
+      const int taken = __builtin_amdgcn_readlane(o.row, win);
+      const int p = taken & 0xffff, at = taken >> 16;          // at: -1 if it is not held
+      const int from = at < 0 ? 0 : at;
+      T wk[M + 1], v = s.rows[from * NT + i], v1 = T(0);
+#pragma unroll
+      for (int b = 0; b <= M; ++b) wk[b] = s.mult[(SUB * b + l16) * H::STRIDE + from];
+      if (__builtin_expect(at < 0, 0)) {
+        v = i < w ? S[(int64_t)p * lds + i] : T(0);
+#pragma unroll
+        for (int b = 0; b < M; ++b) wk[b] = L[(int64_t)p * ldl + SUB * b + l16];
+        if (i == p) {
+#pragma unroll
+          for (int k = 0; k < SUB; ++k) s.other[k] = cur[k];
+        }
+        __syncthreads();
+        wk[M] = s.other[l16];
+      }
+      // meanwhile the reciprocal, of a pivot that has been brought away from the ends of the range if
+      // it was there (the reciprocal of one in the last binades is infinite or subnormal)
+      const T lift = pb_lift(d);
+      const T dl = d * lift;
+      const T rd = fast_rcp(dl);
+      mypos = i == p ? J0 + j : mypos;
+      left &= ~(p >> 6 == wave ? 1ull << (p & 63) : 0ull);
+#pragma unroll
+      for (int b = 0; b < M; ++b) apply_pairs<16>(v, v1, h[b], wk[b] * dh[b]);
+      apply_first(v, v1, cur, wk[M] * dcur, j);
+      v += v1;
+      dcur = mine == j ? d : dcur;
+      pcur = mine == j ? p : pcur;
+      // v / d: the product with the reciprocal, and one correction
+      const T vl = v * lift, q = vl * rd;
+      const T l = __builtin_amdgcn_inverse_ballot_w64(left) ? fma(fma(-dl, q, vl), rd, q) : T(0);
+      diag = fma(-l, v, diag);
+      cur[j] = l;
+      own[(J0 + j) * H::STRIDE] = l;
+    }
+  }
+};
+
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, int64_t lds, T* __restrict__ Lfull,
                                                       int64_t ldl, T* __restrict__ dg, int* __restrict__ active,
@@ -196,130 +344,82 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
                                                       T* __restrict__ dinv, int* __restrict__ perm, int w, int c0,
                                                       int lw, long long pivot0, DevFlags* flags,
                                                       T* __restrict__ leaf, T* __restrict__ linv) {
-  constexpr int NW = NT / 64;
+  using H = PbHeld<T, NT>;
+  constexpr int NW = NT / 64, HELD = H::HELD;
   using vec_t = typename Mfma<T>::vec_t;
   constexpr int VEC = Mfma<T>::VEC;
-  constexpr int LINE = 128 / (int)sizeof(T);
-  __shared__ T s_diag[2][NW];                    // every wavefront's best candidate; two steps in turn
-  __shared__ int s_row[2][NW];                   // its row; -1: none
-  __shared__ __attribute__((aligned(16))) T s_mult[2][LEAF];
-  __shared__ T tile[LEAF_TILE];                  // the group's leaf, at the end
-  const int i = threadIdx.x, lane = i & 63, l16 = i & 15;
+  __shared__ __attribute__((aligned(16))) H s;
+  static_assert(HELD * NT >= LEAF_TILE && HELD * sizeof(T) >= 4, "the leaf's place, and the keys'");
+  const int i = threadIdx.x, lane = i & 63;
   const int wave = __builtin_amdgcn_readfirstlane(i >> 6);
-  for (int e = i; e < LEAF_TILE; e += NT) tile[e] = T(0);
-  T diag = i < w ? dg[i] : T(0);
-  bool live = i < w && active[i] != 0;
-  int mypos = -1;                                // step at which this row was taken
-  // multipliers of the finished blocks of 16 steps and of the current one (0: not taken yet);
-  // pivots and rows likewise, step k of a block in lane k of each row of lanes
-  T h[3][SUB], cur[SUB], dh[3], dcur = T(0);
-  int pcur = 0;
+  PbRow<T, NT> r{s, S, lds, Lfull + c0, ldl, w, lw, i, lane, i & 15, wave};
+  r.diag = i < w ? dg[i] : T(0);
+  const bool live = i < w && active[i] != 0;
+  r.left = __builtin_amdgcn_ballot_w64(live);
+  {
+    // places in the order of the magnitudes (their first 22 bits: a guess is all this is)
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    unsigned* const keys = reinterpret_cast<unsigned*>(s.rows);
+    const unsigned top = sizeof(T) == 8 ? (unsigned)((unsigned long long)pb_magnitude(r.diag) >> 32) : (unsigned)pb_magnitude(r.diag);
+    const unsigned key = live ? 0x80000000u | (top >> 9 << 9) | (unsigned)(511 - i) : 0u;
+    keys[i] = key;
+    if (i < HELD) s.place[i] = 0;
+    for (int e = i; e < LEAF * H::STRIDE; e += NT) s.mult[e] = T(0);
+    __syncthreads();
+    int place = 0;
+#pragma unroll 4
+    for (int q = 0; q < NT; q += 4) {
+      const u4 k = *reinterpret_cast<const u4*>(&keys[q]);
+      place += (k[0] > key) + (k[1] > key) + (k[2] > key) + (k[3] > key);
+    }
+    r.place = live && place < HELD ? place : -1;
+    r.own = s.mult + (r.place < 0 ? HELD : place);
+    if (r.place >= 0) s.place[place] = i;
+    __syncthreads();
+    // the rows, whole, in pieces of a wavefront's 1 KB (lds is a multiple of 64: a piece of a lane's is in the row or
+    // behind its end, where it is anything)
+    constexpr int PIECES = NT / (64 * VEC);
+    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(upd_lds_ptr)s.rows);
+    for (int h = wave; h < HELD; h += NW) {
+      const char* row = reinterpret_cast<const char*>(S + (int64_t)__builtin_amdgcn_readfirstlane(s.place[h]) * lds);
 #pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    dh[b] = T(0);
-#pragma unroll
-    for (int k = 0; k < SUB; ++k) h[b][k] = T(0);
-  }
-#pragma unroll 1
-  for (int m = 0; 16 * m < lw; ++m) {
-#pragma unroll
-    for (int k = 0; k < SUB; ++k) cur[k] = T(0);
-    dcur = T(0);
-    int mine = l16;
-    asm volatile("" : "+v"(mine));               // compared here, not kept as 16 masks in scalar registers
-#pragma unroll
-    for (int j = 0; j < SUB; ++j) {
-      const int jj = 16 * m + j, par = j & 1;
-      if (jj < lw) {
-        const unsigned long long cand = __builtin_amdgcn_ballot_w64(live);
-        const int best = cand != 0ull ? pick_lane(diag, cand) : 0;
-        const int brow = 64 * wave + best;
-        // this wavefront's candidate may be the pivot: its row of S on the way to this compute unit
-        const T ahead = S[(int64_t)min(brow, w - 1) * lds + min((lane & (LEAF / 2 - 1)) * LINE, w - 1)];
-        s_diag[par][wave] = lane_value(diag, best);          // (every lane: the same values)
-        s_row[par][wave] = cand != 0ull ? brow : -1;
-        __syncthreads();
-        T cd[NW];
-        int cr[NW];
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-          cd[q] = s_diag[par][q];
-          cr[q] = s_row[par][q];
-        }
-        T d = cd[0];
-        int p = cr[0];
-#pragma unroll
-        for (int q = 1; q < NW; ++q) {
-          // larger magnitude wins, the smaller row on ties
-          const bool better = cr[q] >= 0 && (p < 0 || pb_magnitude(cd[q]) > pb_magnitude(d));
-          d = better ? cd[q] : d;
-          p = better ? cr[q] : p;
-        }
-        p = __builtin_amdgcn_readfirstlane(p);
-        const T sv = i < w ? S[(int64_t)p * lds + i] : T(0);
-        if (i == p) {
-          T* to = s_mult[par];
-          vec_t v;
-#pragma unroll
-          for (int b = 0; b < 3; ++b)
-            if (m > b)
-#pragma unroll
-              for (int k = 0; k < SUB; k += VEC) {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) v[e] = h[b][k + e];
-                *reinterpret_cast<vec_t*>(to + SUB * b + k) = v;
-              }
-#pragma unroll
-          for (int k = 0; k < SUB; k += VEC) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) v[e] = cur[k + e];
-            *reinterpret_cast<vec_t*>(to + SUB * m + k) = v;
-          }
-          mypos = jj;
-          live = false;
-        }
-        // while the row is on its way: the reciprocal, of a pivot that has been lifted out of the
-        // subnormal range if it was there (the reciprocal of one in the last binades is infinite)
-        const T lift = __builtin_fabs((double)d) < (double)std::numeric_limits<T>::min()
-                           ? T(1) / (std::numeric_limits<T>::epsilon() * std::numeric_limits<T>::epsilon()) : T(1);
-        const T dl = d * lift;
-        const T rd = T(1) / dl;
-        __syncthreads();
-        T v = sv;
-        asm volatile("" ::"v"(ahead));
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-          if (m > b) apply16(v, h[b], s_mult[par][SUB * b + l16] * dh[b]);
-        if (j > 0) apply16(v, cur, s_mult[par][SUB * m + l16] * dcur);
-        dcur = mine == j ? d : dcur;
-        pcur = mine == j ? p : pcur;
-        // v / d: the product with the rounded reciprocal, and one correction
-        const T vl = v * lift, q = vl * rd;
-        const T l = live ? fma(fma(-dl, q, vl), rd, q) : T(0);
-        diag = fma(-l, v, diag);
-        cur[j] = l;
+      for (int c = 0; c < PIECES; ++c) {
+        const int col = (c * 64 + lane) * VEC;
+        load_to_lds<16, 0>(row, (unsigned)((col < lds ? col : 0) * (int)sizeof(T)), at + (unsigned)((h * NT + c * 64 * VEC) * (int)sizeof(T)));
       }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    r.dh[b] = T(0);
+#pragma unroll
+    for (int k = 0; k < SUB; ++k) r.h[b][k] = T(0);
+  }
+  // what 16 steps have left, to memory
+  auto out = [&](const int m) {
     if (i < w) {
       T* to = Lfull + (int64_t)i * ldl + c0 + SUB * m;
 #pragma unroll
       for (int k = 0; k < SUB; k += VEC) {
         vec_t v;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = cur[k + e];
+        for (int e = 0; e < VEC; ++e) v[e] = r.cur[k + e];
         *reinterpret_cast<vec_t*>(to + k) = v;
       }
     }
     if (wave == 0) {
-      const int jj = SUB * m + l16;
+      const int jj = SUB * m + r.l16;
+      const T d = r.dcur;
       const bool mine_out = lane < SUB && jj < lw;
-      const bool zero = dcur == T(0);
-      const bool finite = fabs((double)dcur) <= 1.7976931348623157e308;
+      const bool zero = d == T(0);
+      const bool finite = fabs((double)d) <= 1.7976931348623157e308;
       if (mine_out) {
-        piv[c0 + jj] = pcur;
-        dvec[c0 + jj] = dcur;
-        dinv[c0 + jj] = T(1) / dcur;
-        perm[c0 + jj] = (int)pivot0 + pcur;
+        piv[c0 + jj] = r.pcur;
+        dvec[c0 + jj] = d;
+        dinv[c0 + jj] = T(1) / d;
+        perm[c0 + jj] = (int)pivot0 + r.pcur;
       }
       const unsigned long long bad = __builtin_amdgcn_ballot_w64(mine_out && (zero || !finite));
       if (bad != 0ull && lane == __builtin_ctzll(bad)) {
@@ -328,35 +428,49 @@ __global__ __launch_bounds__(NT) void pb_group_kernel(const T* __restrict__ S, i
         if (idx <= old) atomicExch(&flags->bad_kind, zero ? 1ull : 2ull);
       }
     }
-    if (mypos >= 0) {
-      // the rows taken so far are rows of the leaf; multipliers behind a row's own step are zero
+    if (m < 3) {
+      r.dh[m] = r.dcur;
 #pragma unroll
-      for (int k = 0; k < SUB; ++k) tile[mypos * LEAF_PAD + SUB * m + k] = cur[k];
+      for (int k = 0; k < SUB; ++k) r.h[m][k] = r.cur[k];
     }
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-      if (m == b) {
-        dh[b] = dcur;
-#pragma unroll
-        for (int k = 0; k < SUB; ++k) h[b][k] = cur[k];
-      }
+  };
+  r.template block<0>();
+  out(0);
+  if (lw > SUB) {
+    r.template block<1>();
+    out(1);
+  }
+  if (lw > 2 * SUB) {
+    r.template block<2>();
+    out(2);
+  }
+  if (lw > 3 * SUB) {
+    r.template block<3>();
+    out(3);
   }
   if (i < w) {
-    dg[i] = diag;
-    active[i] = live ? 1 : 0;
+    dg[i] = r.diag;
+    active[i] = (int)(r.left >> lane & 1ull);
   }
-  // rows that were taken in a later block than their multipliers
-  if (mypos >= 0) {
+  // the rows taken are rows of the leaf; multipliers behind a row's own step are zero
+  T* const tile = s.rows;
+  __syncthreads();
+  for (int e = i; e < LEAF_TILE; e += NT) tile[e] = T(0);
+  __syncthreads();
+  if (r.mypos >= 0) {
 #pragma unroll
     for (int b = 0; b < 3; ++b)
-      if (mypos >= SUB * (b + 1))
 #pragma unroll
-        for (int k = 0; k < SUB; ++k) tile[mypos * LEAF_PAD + SUB * b + k] = h[b][k];
+      for (int k = 0; k < SUB; ++k) tile[r.mypos * LEAF_PAD + SUB * b + k] = r.h[b][k];
+    if (lw > 3 * SUB) {
+#pragma unroll
+      for (int k = 0; k < SUB; ++k) tile[r.mypos * LEAF_PAD + 3 * SUB + k] = r.cur[k];
+    }
   }
   __syncthreads();
   for (int e = i; e < LEAF * LEAF; e += NT) {
-    const int r = e >> 6, c = e & 63;
-    leaf[e] = c < r ? tile[r * LEAF_PAD + c] : T(0);
+    const int row = e >> 6, col = e & 63;
+    leaf[e] = col < row ? tile[row * LEAF_PAD + col] : T(0);
   }
   if (wave < NSUB) leaf_invert_sub<T>(tile, linv, wave, lane);
 }
