@@ -180,18 +180,16 @@ struct FlowShape {
   static constexpr int LEAF_ELEMS =
       FORM == FLOW_GENERAL ? LU_LDS_ELEMS : (FORM == FLOW_PIVOT ? PIVOT_LDS_ELEMS : FACTOR_LDS_ELEMS);
   static constexpr int TILES = ARRAYS * LEAF * LEAF;
-  // 16 rows of each wavefront on their way out or into another order of columns: behind what a
-  // solve needs in a row task; in a diagonal task behind the solved tile (general matrices: in the
-  // place of the leaf, with barriers in between)
+  // 16 rows of a wavefront on their way out or into another order of columns: behind what a
+  // solve needs in a row task; in a diagonal task behind the solved tile (general matrices: one wavefront's)
   static constexpr int ROW_STRIDE = LEAF + 16 / (int)sizeof(T);
   static constexpr int OUT = SUB * ROW_STRIDE;
-  static constexpr int BEFORE = FORM == FLOW_GENERAL && FLOW_WAVES * OUT > LEAF_ELEMS ? FLOW_WAVES * OUT : LEAF_ELEMS;
-  static constexpr int SOLVED = (BEFORE + 3) / 4 * 4;
+  static constexpr int SOLVED = (LEAF_ELEMS + 3) / 4 * 4;
   static constexpr int ROW_OUT = LeafOperands<T>::ELEMS;
-  static constexpr int DIAG_OUT = FORM == FLOW_GENERAL ? 0 : SOLVED + TILES;
+  static constexpr int DIAG_OUT = SOLVED + TILES;
   static constexpr int ROW_TILE = ROW_OUT + FLOW_WAVES * OUT;     // a tile as a column operand
   static constexpr int LATER_ROW = ROW_TILE + LEAF * LEAF;
-  static constexpr int LATER_DIAG = FORM == FLOW_GENERAL ? SOLVED + TILES : DIAG_OUT + 4 * OUT;
+  static constexpr int LATER_DIAG = DIAG_OUT + (FORM == FLOW_GENERAL ? 1 : 4) * OUT;
   static constexpr int LATER = LATER_ROW > LATER_DIAG ? LATER_ROW : LATER_DIAG;
   // (so much that a compute unit holds one workgroup)
   static constexpr int LDS_ELEMS = SLABS > LATER ? SLABS : LATER;
@@ -527,14 +525,14 @@ __device__ __forceinline__ bool flow_accumulate(const FlowArgs<T, LINES>& a, con
 // operations in the same order as the elimination carries along, and no array of them for every
 // leaf in flight.
 template <typename T>
-__device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, const T* __restrict__ leaf, const int64_t ld,
-                                                const int wave, const int lane) {
+struct FlowStage {
   using L = LeafOperands<T>;
-  constexpr int LOW = L::COUNT - NSUB, VEC = L::VEC;
-  const int c = lane & 15, g = lane >> 4, row = solve_col<T>(c);
-  if (wave < 4) {
-    T nl[SUB], inv[4];
-    const T* mine = leaf + (int64_t)(wave * SUB + c) * ld + wave * SUB;
+  static constexpr int LOW = L::COUNT - NSUB, VEC = L::VEC;
+  const int lane, c, g, row;
+  __device__ __forceinline__ FlowStage(const int lane_) : lane(lane_), c(lane_ & 15), g(lane_ >> 4), row(solve_col<T>(lane_ & 15)) {}
+  // row c of diagonal sub-block b
+  __device__ __forceinline__ void load_diagonal(const T* __restrict__ leaf, const int64_t ld, const int b, T (&nl)[SUB]) const {
+    const T* mine = leaf + (int64_t)(b * SUB + c) * ld + b * SUB;
 #pragma unroll
     for (int k = 0; k < SUB; k += 4) {
       T f[4];
@@ -542,6 +540,10 @@ __device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, cons
 #pragma unroll
       for (int e = 0; e < 4; ++e) nl[k + e] = f[e];
     }
+  }
+  // its inverse to LDS
+  __device__ __forceinline__ void put_inverse(const L& ops, const int b, T (&nl)[SUB]) const {
+    T inv[4];
 #pragma unroll
     for (int k = 0; k < SUB; ++k) nl[k] = c > k ? -nl[k] : T(0);
 #pragma unroll
@@ -551,31 +553,65 @@ __device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, cons
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int k = Mfma<T>::acc_row(lane, s), e = k & 3;
-      ops.lds[(((LOW + wave) * (4 / VEC) + e / VEC) * 64 + (k >> 2) * 16 + row) * VEC + e % VEC] = inv[s];
+      ops.lds[(((LOW + b) * (4 / VEC) + e / VEC) * 64 + (k >> 2) * 16 + row) * VEC + e % VEC] = inv[s];
     }
+  }
+  // this lane's share of the q-th sub-block below the diagonal, and minus it to LDS
+  __device__ __forceinline__ void load_lower(const T* __restrict__ leaf, const int64_t ld, const int q, T (&v)[4]) const {
+    const int b = q < 1 ? 1 : (q < 3 ? 2 : 3);
+    load4(leaf + (int64_t)(b * SUB + row) * ld + (q - L::lower(b, 0)) * SUB + 4 * g, v);
+  }
+  __device__ __forceinline__ void put_lower(const L& ops, const int q, const T (&v)[4]) const {
+#pragma unroll
+    for (int h = 0; h < 4 / VEC; ++h) {
+      typename L::vec_t o;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) o[e] = -v[VEC * h + e];
+      *ops.at(q, h, lane) = o;
+    }
+  }
+};
+template <typename T>
+__device__ __forceinline__ void flow_stage_leaf(const LeafOperands<T>& ops, const T* __restrict__ leaf, const int64_t ld,
+                                                const int wave, const int lane) {
+  using St = FlowStage<T>;
+  const St st(lane);
+  if (wave < 4) {
+    T nl[SUB];
+    st.load_diagonal(leaf, ld, wave, nl);
+    st.put_inverse(ops, wave, nl);
   } else {
     T v[2][4];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int q = 4 * k + wave - 4;
-      if (q < LOW) {
-        const int b = q < 1 ? 1 : (q < 3 ? 2 : 3);
-        load4(leaf + (int64_t)(b * SUB + row) * ld + (q - L::lower(b, 0)) * SUB + 4 * g, v[k]);
-      }
-    }
+    for (int k = 0; k < 2; ++k)
+      if (4 * k + wave - 4 < St::LOW) st.load_lower(leaf, ld, 4 * k + wave - 4, v[k]);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int q = 4 * k + wave - 4;
-      if (q < LOW) {
+    for (int k = 0; k < 2; ++k)
+      if (4 * k + wave - 4 < St::LOW) st.put_lower(ops, 4 * k + wave - 4, v[k]);
+  }
+}
+// The same for a general matrix' L and U^T at once: the inverses by wavefronts 0 to 3, two each, the others by
+// those that have columns to reorder besides.
+template <typename T>
+__device__ __forceinline__ void flow_stage_both(const LeafOperands<T>& opsL, const LeafOperands<T>& opsU,
+                                                const T* __restrict__ L, const T* __restrict__ U, const int64_t ld,
+                                                const int wave, const int lane) {
+  using St = FlowStage<T>;
+  static_assert(2 * St::LOW == 12, "three sub-blocks to a wavefront");
+  const St st(lane);
+  if (wave < 4) {
+    T nl[2][SUB];
+    st.load_diagonal(L, ld, wave, nl[0]);
+    st.load_diagonal(U, ld, wave, nl[1]);
+    st.put_inverse(opsL, wave, nl[0]);
+    st.put_inverse(opsU, wave, nl[1]);
+  } else {
+    T v[3][4];
+    auto of = [&](const int k) { return 4 * k + wave - 4; };
 #pragma unroll
-        for (int h = 0; h < 4 / VEC; ++h) {
-          typename L::vec_t o;
+    for (int k = 0; k < 3; ++k) st.load_lower(of(k) < 6 ? L : U, ld, of(k) < 6 ? of(k) : of(k) - 6, v[k]);
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) o[e] = -v[k][VEC * h + e];
-          *ops.at(q, h, lane) = o;
-        }
-      }
-    }
+    for (int k = 0; k < 3; ++k) st.put_lower(of(k) < 6 ? opsL : opsU, of(k) < 6 ? of(k) : of(k) - 6, v[k]);
   }
 }
 
@@ -675,24 +711,28 @@ __device__ __forceinline__ void flow_solve(const LeafOperands<T>& ops, typename 
 }
 
 // The columns of this wavefront's 16 rows into the order in which the leaf's rows were taken, through
-// `out` (this wavefront's).
-template <typename T>
-__device__ __forceinline__ void flow_gather(const int* __restrict__ perm, const long long first,
-                                            typename Mfma<T>::acc_t* x, T* __restrict__ out, const int lane) {
-  constexpr int STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
-  const int l16 = lane & 15, g = lane >> 4;
+// `out` (this wavefront's).  The order is asked for (ahead of the leaf) and used in two steps.
+struct FlowGather {
   int from[NSUB][4];
+  __device__ __forceinline__ void load(const int* __restrict__ perm, const int lane) {
+    const int g = lane >> 4;
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b) load4(perm + b * SUB + 4 * g, from[b]);
+    for (int b = 0; b < NSUB; ++b) load4(perm + b * SUB + 4 * g, from[b]);
+  }
+  template <typename T>
+  __device__ __forceinline__ void apply(const long long first, typename Mfma<T>::acc_t* x, T* __restrict__ out, const int lane) const {
+    constexpr int STRIDE = FlowShape<T, FLOW_SYM>::ROW_STRIDE;
+    const int l16 = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b)
+    for (int b = 0; b < NSUB; ++b)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) out[l16 * STRIDE + b * SUB + 4 * g + e] = x[b][e];
+      for (int e = 0; e < 4; ++e) out[l16 * STRIDE + b * SUB + 4 * g + e] = x[b][e];
 #pragma unroll
-  for (int b = 0; b < NSUB; ++b)
+    for (int b = 0; b < NSUB; ++b)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[b][e] = out[l16 * STRIDE + (from[b][e] - (int)first)];
-}
+      for (int e = 0; e < 4; ++e) x[b][e] = out[l16 * STRIDE + (from[b][e] - (int)first)];
+  }
+};
 
 template <typename T, FlowForm FORM, bool LINES>
 __device__ __forceinline__ void flow_row_task(const FlowArgs<T, LINES>& a, const int pair, const int array, const int j,
@@ -729,13 +769,14 @@ __device__ __forceinline__ void flow_row_task(const FlowArgs<T, LINES>& a, const
   if (!flow_accumulate<T, FORM, 0>(a, of, j, mine, x, none, lds, shared)) return;
   if (flow_wait_all(a, j, -1, -1, -1, j + 1, shared) < 0) return;
   const LeafOperands<T> ops{lds};
+  const bool gather = FORM == FLOW_PIVOT || (FORM == FLOW_GENERAL && array != 0);
+  FlowGather order;
+  if (gather) order.load((const int*)(a.perm + (int64_t)j * LEAF), lane);
   flow_stage_leaf(ops, (const T*)(cols + (int64_t)j * LEAF * (a.ld + 1)), a.ld, wave, lane);
   T rinv[NSUB][4];
   load_row((const T*)(a.dinv + (int64_t)j * LEAF), lane >> 4, LEAF, rinv);
   T* const out = lds + Sh::ROW_OUT + wave * Sh::OUT;
-  if (FORM == FLOW_PIVOT || (FORM == FLOW_GENERAL && array != 0)) {
-    if (mine) flow_gather((const int*)(a.perm + (int64_t)j * LEAF), a.pivot0 + (long long)j * LEAF, x, out, lane);
-  }
+  if (gather && mine) order.apply(a.pivot0 + (long long)j * LEAF, x, out, lane);
   __syncthreads();
   if (mine) {
     flow_solve(ops, x, lane);
@@ -800,11 +841,12 @@ __device__ __forceinline__ void flow_row2_task(const FlowArgs<T, LINES>& a, cons
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     if (flow_wait_all(a, j + c, -1, -1, -1, j + c + 1, shared) < 0) return;
+    FlowGather order;
+    if (gather) order.load((const int*)(a.perm + (int64_t)(j + c) * LEAF), lane);
     flow_stage_leaf(ops, (const T*)(cols + (int64_t)(j + c) * LEAF * (a.ld + 1)), a.ld, wave, lane);
     T rinv[NSUB][4];
     load_row((const T*)(a.dinv + (int64_t)(j + c) * LEAF), g, LEAF, rinv);
-    if (gather && mine)
-      flow_gather((const int*)(a.perm + (int64_t)(j + c) * LEAF), a.pivot0 + (long long)(j + c) * LEAF, x + c * NSUB, out, lane);
+    if (gather && mine) order.apply(a.pivot0 + (long long)(j + c) * LEAF, x + c * NSUB, out, lane);
     __syncthreads();
     if (mine) {
       flow_solve(ops, x + c * NSUB, lane);
@@ -950,9 +992,19 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T, LINES>& a, 
                     ? -__hip_atomic_load(leaf + (int64_t)grow * a.ld + gcol, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                     : T(0);
     }
+  T v[NSUB][4];                      // the solved rows
+  T* const solved = lds + Sh::SOLVED;
+  T* const out = lds + Sh::DIAG_OUT + (wave & 3) * Sh::OUT;
+  // to memory (wavefront 0's by wavefront 4)
+  auto store_solved = [&] {
+    if (j == 0 || wave < 1 || wave > 4) return;
+    if (wave == 4) {
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b) flow_solved_fetch(solved, 0, b, lane, v[b]);
+    }
+    flow_store_rows(a, a.P, j0 + (wave & 3) * SUB, j - 1, v, out, lane);
+  };
   if (j > 0) {
-    T* const solved = lds + Sh::SOLVED;
-    T* const out = lds + Sh::DIAG_OUT + (wave & 3) * Sh::OUT;
 #pragma unroll
     for (int b = 0; b < NSUB; ++b) x[b] = acc_t{0, 0, 0, 0};
     if (wave < 4) flow_load_rows(a, (const T*)a.P, j0 + wave * SUB, j - 1, x, lane);
@@ -966,7 +1018,10 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T, LINES>& a, 
     if (!flow_accumulate<T, FORM, 1>(a, of, j - 1, true, x, s, lds, shared)) return;
     if (flow_wait_all(a, j - 1, -1, -1, -1, j, shared) < 0) return;
     const LeafOperands<T> ops{lds};
-    flow_stage_leaf(ops, (const T*)(a.P + (j0 - LEAF) * (a.ld + 1)), a.ld, wave, lane);
+    FlowGather order;
+    if (PIVOT && wave < 4) order.load((const int*)(a.perm + j0 - LEAF), lane);
+    // (the wavefronts that have columns to reorder leave the inverses to the others)
+    flow_stage_leaf(ops, (const T*)(a.P + (j0 - LEAF) * (a.ld + 1)), a.ld, PIVOT ? wave ^ 4 : wave, lane);
     T rinv[NSUB][4];
     if (wave < 4) load_row((const T*)(a.dinv + j0 - LEAF), g, LEAF, rinv);
     T d[NSUB][4];                    // the pivots in the order of the product below
@@ -975,22 +1030,21 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T, LINES>& a, 
       for (int q = 0; q < NSUB; ++q)
         load4((const T*)(a.dvec + j0 - LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
     }
-    if (PIVOT && wave < 4) flow_gather((const int*)(a.perm + j0 - LEAF), a.pivot0 + j0 - LEAF, x, out, lane);
+    if (PIVOT && wave < 4) order.apply(a.pivot0 + j0 - LEAF, x, out, lane);
     __syncthreads();
-    T v[NSUB][4];
     if (wave < 4) {
       flow_solve(ops, x, lane);
       // the solved rows go from the wavefronts that hold them to all through LDS
       flow_solved_put(solved, wave, x, rinv, v, lane);
     }
     __syncthreads();
-    // off the chain: the solved tile to memory (wavefront 0's rows by wavefront 4)
-    if (wave >= 1 && wave <= 4) {
-      if (wave == 4) {
-#pragma unroll
-        for (int b = 0; b < NSUB; ++b) flow_solved_fetch(solved, 0, b, lane, v[b]);
-      }
-      flow_store_rows(a, a.P, j0 + (wave & 3) * SUB, j - 1, v, out, lane);
+    // off the chain: the solved tile to memory; with pivoting, where all wavefronts meet before the elimination
+    // begins, beside that, and the multipliers' places cleared here
+    if constexpr (PIVOT) {
+      if (wave >= 1 && wave <= 4)
+        for (int e = LEAF_TILE + tid - 64; e < 2 * LEAF_TILE; e += 256) lds[e] = T(0);
+    } else {
+      store_solved();
     }
     // its product with itself, the columns in the order of a slab
 #pragma unroll
@@ -1008,24 +1062,21 @@ __device__ __forceinline__ void flow_diagonal_task(const FlowArgs<T, LINES>& a, 
     }
   }
   if constexpr (PIVOT) {
-    // the whole leaf has to be there before the first pivot is looked for
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 64) flow_publish(a, j, j);                        // tile (j, j - 1)
+    // (the whole leaf is there behind the first barrier of leaf_factor_pivoted_body, and tile (j, j - 1) in
+    // memory behind its second one)
 #pragma unroll
     for (int u = 0; u < 3; ++u)
       if (u < units.count) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = units.row[u] * SUB + X::acc_row(lane, r), col = units.col[u] * SUB + l16;
-          if (col <= row) {
-            leaf_tile_put<T>(lds, row, col, wl, -s[u][r]);
-            leaf_tile_put<T>(lds, col, row, wl, -s[u][r]);
-          }
+          const T v = row < wl ? -s[u][r] : T(row == col ? 1 : 0);
+          lds[row * LEAF_PAD + (col <= row ? col : LEAF)] = v;   // (or to the padding: no jump)
+          lds[col * LEAF_PAD + (col <= row ? row : LEAF)] = v;
         }
       }
     leaf_factor_pivoted_body<T, true, true>(leaf, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, a.perm + j0, a.pivot0 + j0,
-                                            a.flags, lds);
+                                            a.flags, lds, &a.sync->done[j], (unsigned)j, store_solved, j > 0);
   } else {
     // wavefront 0 goes on with its sub-block at once; the others' are there, and tile (j, j - 1) is
     // in memory, when it is through with that (the first barrier of leaf_factor_body)
@@ -1078,7 +1129,6 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T, LINES>& 
   }
   if (j > 0) {
     T* const solved = lds + Sh::SOLVED;
-    T* const out = lds + Sh::DIAG_OUT + wave * Sh::OUT;
     T* const rows = wave < 4 ? a.P : Q;
     const int64_t r16 = j0 + (wave & 3) * SUB;
     flow_load_rows(a, (const T*)rows, r16, j - 1, x, lane);
@@ -1096,22 +1146,21 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T, LINES>& 
     if (flow_wait_all(a, j - 1, -1, -1, -1, j, shared) < 0) return;
     const LeafOperands<T> opsL{lds}, opsU{lds + LeafOperands<T>::ELEMS};
     const T* const before = a.P + (j0 - LEAF) * (a.ld + 1);
-    flow_stage_leaf(opsL, before, a.ld, wave, lane);
-    flow_stage_leaf(opsU, before + a.qoff, a.ld, wave, lane);
+    FlowGather order;
+    if (wave >= 4) order.load((const int*)(a.perm + j0 - LEAF), lane);
+    flow_stage_both(opsL, opsU, before, before + a.qoff, a.ld, wave, lane);
     T rinv[NSUB][4], d[NSUB][4];
     load_row((const T*)(a.dinv + j0 - LEAF), g, LEAF, rinv);
 #pragma unroll
     for (int q = 0; q < NSUB; ++q)
       load4((const T*)(a.dvec + j0 - LEAF + q / (KS / 4) * BK + g * KS + q % (KS / 4) * 4), d[q]);
     // (the places of the solved tiles are free)
-    if (wave >= 4)
-      flow_gather((const int*)(a.perm + j0 - LEAF), a.pivot0 + j0 - LEAF, x, solved + (wave & 3) * Sh::OUT, lane);
+    if (wave >= 4) order.apply(a.pivot0 + j0 - LEAF, x, solved + (wave & 3) * Sh::OUT, lane);
     __syncthreads();
     flow_solve(wave < 4 ? opsU : opsL, x, lane);
     T v[NSUB][4];
     flow_solved_put(solved, wave, x, rinv, v, lane);
     __syncthreads();
-    flow_store_rows(a, rows, r16, j - 1, v, out, lane);
     // their product, the columns in the order of a slab
     const int mine0 = wave & 4, other0 = 4 - mine0;
 #pragma unroll
@@ -1127,23 +1176,36 @@ __device__ __forceinline__ void flow_diagonal_general(const FlowArgs<T, LINES>& 
         }
     }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 64) {                                               // tiles (j, j - 1)
-    flow_publish(a, j, j);
-    flow_publish(a, a.order.ntr + j, j);
-  }
 #pragma unroll
   for (int u = 0; u < 3; ++u)
     if (u < units.count) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = units.row[u] * SUB + X::acc_row(lane, r), col = units.col[u] * SUB + l16;
-        if (col + low <= row) leaf_tile_put<T>(lds, low ? col : row, low ? row : col, wl, -s[u][r]);
+        const int to_row = low ? col : row, to_col = low ? row : col;
+        lds[to_row * LEAF_PAD + (col + low <= row ? to_col : LEAF)] = row < wl ? -s[u][r] : T(row == col ? 1 : 0);
       }
     }
+  // The solved tiles go to memory beside the elimination, by the wavefront that is through with its columns of
+  // it first: stored before, and waited for so that their counters can say so, they hold it up by 4 us.
+  auto store_solved = [&] {
+    if (j == 0) return;
+    T* const solved = lds + Sh::SOLVED;
+#pragma unroll 1
+    for (int q = 0; q < 2 * NSUB; ++q) {
+      T v[NSUB][4];
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b) flow_solved_fetch(solved, q, b, lane, v[b]);
+      flow_store_rows(a, q < NSUB ? a.P : Q, j0 + (q & (NSUB - 1)) * SUB, j - 1, v, lds + Sh::DIAG_OUT, lane);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) {
+      flow_publish(a, j, j);
+      flow_publish(a, a.order.ntr + j, j);
+    }
+  };
   leaf_lu_body<T, FLOW_WAVES, true, true>(leaf, leaf + a.qoff, a.ld, wl, a.dvec + j0, a.dinv + j0, nullptr, nullptr,
-                                          a.perm + j0, a.pivot0 + j0, a.flags, lds);
+                                          a.perm + j0, a.pivot0 + j0, a.flags, lds, store_solved);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {

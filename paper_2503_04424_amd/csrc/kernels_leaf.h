@@ -33,6 +33,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mfma.h"
 
 namespace mdet {
@@ -290,7 +292,7 @@ struct Diag16 {
 #define MDET_H8 MDET_H4, "v"(h[4]), "v"(h[5]), "v"(h[6]), "v"(h[7])
 #define MDET_H12 MDET_H8, "v"(h[8]), "v"(h[9]), "v"(h[10]), "v"(h[11])
 #define MDET_H16 MDET_H12, "v"(h[12]), "v"(h[13]), "v"(h[14]), "v"(h[15])
-#define MDET_APPLY(TYPE, N) asm("s_nop 1\n\t" MDET_APPLY_TERMS##N : "+v"(v) : "v"(w), MDET_H##N)
+#define MDET_APPLY(TYPE, N) asm("s_nop 1\n\t" MDET_APPLY_TERMS##N : "+&v"(v) : "v"(w), MDET_H##N)
 #define MDET_APPLY_ALL(TYPE)                                                                 \
   template <int N>                                                                           \
   __device__ __forceinline__ void apply_terms(TYPE& v, const TYPE (&h)[16], TYPE w) {        \
@@ -311,7 +313,7 @@ struct Diag16 {
 #define MDET_APPLY_PAIRS16                                                                                  \
   MDET_APPLY_PAIRS12 MDET_APPLY_TERM0("12", "15") MDET_APPLY_TERM1("13", "16") MDET_APPLY_TERM0("14", "17")  \
   MDET_APPLY_TERM1("15", "18")
-#define MDET_APPLY_PAIR(N) asm("s_nop 1\n\t" MDET_APPLY_PAIRS##N : "+v"(v0), "+v"(v1) : "v"(w), MDET_H##N)
+#define MDET_APPLY_PAIR(N) asm("s_nop 1\n\t" MDET_APPLY_PAIRS##N : "+&v"(v0), "+&v"(v1) : "v"(w), MDET_H##N)
 #define MDET_APPLY_PAIR_ALL(TYPE)                                                                    \
   template <int N>                                                                                   \
   __device__ __forceinline__ void apply_pairs(TYPE& v0, TYPE& v1, const TYPE (&h)[16], TYPE w) {     \
@@ -345,8 +347,8 @@ MDET_APPLY_PAIR_ALL(float)
 #undef MDET_APPLY_TERMS12
 #undef MDET_APPLY_TERMS8
 #undef MDET_APPLY_TERMS4
-// The first j terms (the registers of the others hold zeros): j is known where a loop is unrolled.  With v1
-// the odd ones go there.
+// The first j terms (the registers of the others hold zeros): j is known where a loop is unrolled.  From the
+// fifth on the odd ones go to v1.
 template <typename T>
 __device__ __forceinline__ void apply_first(T& v, T& v1, const T (&h)[16], T w, const int j) {
   if (j > 12) apply_pairs<16>(v, v1, h, w);
@@ -354,14 +356,6 @@ __device__ __forceinline__ void apply_first(T& v, T& v1, const T (&h)[16], T w, 
   else if (j > 4) apply_pairs<8>(v, v1, h, w);
   else if (j > 0) apply_terms<4>(v, h, w);
 }
-template <typename T>
-__device__ __forceinline__ void apply_first(T& v, const T (&h)[16], T w, const int j) {
-  if (j > 12) apply_terms<16>(v, h, w);
-  else if (j > 8) apply_terms<12>(v, h, w);
-  else if (j > 4) apply_terms<8>(v, h, w);
-  else if (j > 0) apply_terms<4>(v, h, w);
-}
-#undef MDET_APPLY_TERM
 
 // Inverse of a unit-lower 16 x 16 block -> linv (16 x 16, row-major), by one wavefront: nl[k]
 // of lane (c, g) is minus entry (c, k) of the block below the diagonal (c > k), 0 elsewhere.
@@ -641,10 +635,10 @@ __global__ __launch_bounds__(FACTOR_THREADS) void leaf_factor_kernel(
 // ---------------------------------------------------------------------------
 // leaf factor with pivoting
 // ---------------------------------------------------------------------------
-// Maximum of x over the 64 lanes, delivered in a scalar register: four exchanges inside
-// each row of 16 lanes on the data-parallel-primitive path, then the last lane of a row
-// handed to the next row, and the last lane of the first two rows to the last two; lane
-// 63 then holds the maximum.  Must be reached by all 64 lanes.
+// Maximum of x over the 64 lanes, delivered in a scalar register: four exchanges inside each row of
+// 16 lanes on the data-parallel-primitive path, then the four rows' values through scalar registers (two
+// more exchanges, with the copies that the compiler makes for them, take 25 clocks longer).  Must be reached by
+// all 64 lanes.
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
   int m = (int)x;
   auto take = [&](int other) { m = (int)max((unsigned)m, (unsigned)other); };
@@ -652,9 +646,9 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
   take(__builtin_amdgcn_update_dpp(0, m, 0x4E, 0xF, 0xF, false));    // lanes 2 3 0 1
   take(__builtin_amdgcn_update_dpp(0, m, 0x141, 0xF, 0xF, false));   // mirror inside each eight
   take(__builtin_amdgcn_update_dpp(0, m, 0x140, 0xF, 0xF, false));   // mirror inside each sixteen
-  take(__builtin_amdgcn_update_dpp(m, m, 0x142, 0xA, 0xF, false));   // lane 15 -> rows 1 and 3
-  take(__builtin_amdgcn_update_dpp(m, m, 0x143, 0xC, 0xF, false));   // lane 31 -> rows 2 and 3
-  return (unsigned)__builtin_amdgcn_readlane(m, 63);
+  const unsigned r0 = (unsigned)__builtin_amdgcn_readlane(m, 0), r1 = (unsigned)__builtin_amdgcn_readlane(m, 16);
+  const unsigned r2 = (unsigned)__builtin_amdgcn_readlane(m, 32), r3 = (unsigned)__builtin_amdgcn_readlane(m, 48);
+  return max(max(r0, r1), max(r2, r3));
 }
 
 // LDS that wavefronts exchange without a barrier: accesses stay in the order they are written
@@ -700,18 +694,24 @@ __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
 // into the order in which the rows were taken when they are written to memory.
 // Outputs as leaf_factor_kernel (L and D in pivot order into A, pivots, reciprocals,
 // inverses of the diagonal sub-blocks of L), and perm[j] = pivot0 + (row taken at step j).
-// Bound by the chain of one step (460 clocks: search, row from LDS, its 16 terms, quotient);
-// the three products between cost 2300 clocks each.  Measured, fp64, launches back to back: 20.1 us
-// each (a launch alone 20.6 to 22.6) against 32.3 with the matrix in the registers of four
-// wavefronts and a barrier and an exchange of the pivot row per step (n = 4096 4.41 -> 3.63 ms).
+// Bound by the chain of one step (430 clocks: search 230, row from LDS 100, its terms so far, quotient);
+// the three products between cost 2500 clocks each.  Measured, fp64, inside panel_flow_kernel: 15.5 us a leaf,
+// 24.0 from one leaf to the next (with all 16 terms a step in one sum, and the tile left of the leaf stored and
+// the multipliers' places cleared in front of it, 26.4; n = 4096 1.69 -> 1.60 ms).
 // IN_LDS, THROUGH: as for leaf_factor_body; `lds` has PIVOT_LDS_ELEMS elements, of which with IN_LDS
-// the first LEAF_TILE hold the leaf, both triangles, row stride LEAF_PAD.
+// the first LEAF_TILE hold the leaf, both triangles, row stride LEAF_PAD.  With THROUGH the other
+// wavefronts do what `beside` says during the first 16 steps, and when that is in memory *mid becomes
+// mid_value.  cleared: the multipliers' places (LEAF_TILE behind the leaf) are zero already.
 constexpr int PIVOT_WAVES = 8;
 constexpr int PIVOT_LDS_ELEMS = 2 * LEAF_TILE + 2 * LEAF;
-template <typename T, bool IN_LDS = false, bool THROUGH = false>
+struct LeafBeside {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <typename T, bool IN_LDS = false, bool THROUGH = false, typename Beside = LeafBeside>
 __device__ __forceinline__ void leaf_factor_pivoted_body(
     T* __restrict__ A, int64_t ld, int w, T* __restrict__ dvec, T* __restrict__ dinv,
-    T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags, T* __restrict__ lds) {
+    T* __restrict__ linv, int* __restrict__ perm, long long pivot0, DevFlags* flags, T* __restrict__ lds,
+    unsigned* mid = nullptr, unsigned mid_value = 0u, const Beside& beside = Beside{}, const bool cleared = false) {
   using X = Mfma<T>;
   using acc_t = typename X::acc_t;
   constexpr int NW = PIVOT_WAVES;
@@ -740,13 +740,14 @@ __device__ __forceinline__ void leaf_factor_pivoted_body(
       }
     }
   }
-  for (int e = tid; e < LEAF_TILE; e += 64 * NW) mult[e] = T(0);
+  if (!cleared)
+    for (int e = tid; e < LEAF_TILE; e += 64 * NW) mult[e] = T(0);
   __syncthreads();
   T diag = S[lane * LEAF_PAD + lane];
-  // rows still to be taken: those of the leaf, then (w < 64) those of the padding, whose
-  // pivots are their own ones and eliminate nothing
-  unsigned long long left = ~0ull;
-  const unsigned long long real = w < LEAF ? (1ull << w) - 1ull : ~0ull;
+  // rows still to be taken: those of the leaf, and when there are none left (w < 64) those of the padding,
+  // whose pivots are their own ones and eliminate nothing
+  unsigned long long left = w < LEAF ? (1ull << w) - 1ull : ~0ull;
+  const unsigned long long padding = ~left;
 #pragma unroll 1
   for (int m = 0; m < NSUB; ++m) {
     if (wave == 0) {
@@ -756,28 +757,37 @@ __device__ __forceinline__ void leaf_factor_pivoted_body(
       asm volatile("" : "+v"(mine));         // compared here, not kept as 16 masks in scalar registers
 #pragma unroll
       for (int k = 0; k < SUB; ++k) l[k] = T(0);
+      const T* const terms = mult + (m * SUB + l16) * LEAF_PAD;
+      T* const to = mult + m * SUB * LEAF_PAD + lane;
 #pragma unroll
       for (int j = 0; j < SUB; ++j) {
-        const int jj = m * SUB + j;
-        const int p = pick_lane(diag, left & (jj < w ? real : ~0ull));
-        T v = S[p * LEAF_PAD + lane];
-        const T lp = mult[(m * SUB + l16) * LEAF_PAD + p];
+        left = left != 0ull ? left : padding;
+        const int p = pick_lane(diag, left);
+        T v = S[p * LEAF_PAD + lane], odd = T(0);
+        const T lp = terms[p];
         const T d = lane_value(diag, p);
         const T est = rcp_estimate(d);
         const T tail = quotient_tail(d, est);
         left &= ~(1ull << p);
-        apply_first(v, l, lp * dm, j);
+        apply_first(v, odd, l, lp * dm, j);
+        if (j > 4) v += odd;
         dm = mine == j ? d : dm;
         const T q = v * est;
         l[j] = __builtin_amdgcn_inverse_ballot_w64(left) ? fma(q, tail, q) : T(0);
         diag = fma(-l[j], v, diag);
-        mult[jj * LEAF_PAD + lane] = l[j];
+        to[j * LEAF_PAD] = l[j];
         pm = mine == j ? p : pm;
       }
       dl[m * SUB + l16] = dm;                // (the four rows of lanes: the same values)
       row_of[m * SUB + l16] = pm;
+    } else if (THROUGH && m == 0) {
+      beside();
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
+    if constexpr (THROUGH) {
+      if (m == 0 && tid == 64) __hip_atomic_store(mid, mid_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (m + 1 < NSUB) {
       // S -= L D L^T of these 16 steps, all of it: row p is wanted, whatever p.  Two of the
       // 16 sub-blocks a wavefront, side by side
@@ -884,25 +894,25 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
 // leaf_solve_kernel: rows below in Pl are solved against U^T, rows below in Qu against L
 // with the leaf's row order as their column gather), perm[j] = pivot0 + (row of the leaf
 // taken at step j); flags->odd_leaves is raised by one if that order is an odd permutation.
-// Bound by the owner's chain: search (six exchanges, a ballot), pivot, estimate, quotient,
-// the next column's update, 425 clocks a step.  Measured, fp64: 18.7 us alone, 19.4 in a run
-// of n = 2900, against 33.5 and 34 with a barrier per step and 16 wavefronts of four columns
-// (n = 2900 3.35 -> 2.74 ms, n = 8192 13.2 -> 11.5 ms).
+// Bound by the owner's chain: search 230 clocks (exchanges, a ballot), quotient 70, the next column's
+// update 100.  Measured, fp64, inside panel_flow_kernel: 14.8 us a leaf, 25.6 from one leaf to the next (27.4 with the tiles
+// left of the leaf stored in front of it and the leaves that they are solved against brought to LDS one after
+// the other; n = 2900 1.375 -> 1.282 ms).
 // IN_LDS, THROUGH: as for leaf_factor_body; `lds` has LU_LDS_ELEMS elements, of which with IN_LDS the
-// first LEAF_TILE hold the leaf, row stride LEAF_PAD.
+// first LEAF_TILE hold the leaf, row stride LEAF_PAD.  beside: what the first wavefront is to do when it is through
+// with its columns.
 constexpr int LU_WAVES = 8;
-constexpr int LU_LDS_ELEMS = LEAF_TILE + LEAF * LEAF + 2 * LEAF;
-template <typename T, int NW, bool IN_LDS = false, bool THROUGH = false>
+constexpr int LU_LDS_ELEMS = LEAF_TILE + LEAF * LEAF + LEAF;
+template <typename T, int NW, bool IN_LDS = false, bool THROUGH = false, typename Beside = LeafBeside>
 __device__ __forceinline__ void leaf_lu_body(
     T* __restrict__ Pl, T* __restrict__ Qu, int64_t ld, int w, T* __restrict__ dvec,
     T* __restrict__ dinv, T* __restrict__ linvL, T* __restrict__ linvU, int* __restrict__ perm,
-    long long pivot0, DevFlags* flags, T* __restrict__ lds) {
+    long long pivot0, DevFlags* flags, T* __restrict__ lds, const Beside& beside = Beside{}) {
   constexpr int CW = LEAF / NW;          // columns per wavefront
   static_assert(NW == 2 * NSUB, "one diagonal sub-block of L or U^T to invert per wavefront");
   T* const S = lds;                      // the leaf; afterwards, rows in pivot order: L below, D U on and above
   T (* const mult)[LEAF] = reinterpret_cast<T (*)[LEAF]>(S + LEAF_TILE);   // minus the multipliers of every step, by input row
   int* const row_of = reinterpret_cast<int*>(S + LEAF_TILE + LEAF * LEAF); // row taken at a step; -1: not yet
-  int* const pos = row_of + LEAF;        // step at which a row was taken
   __builtin_amdgcn_s_setprio(2);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -929,67 +939,80 @@ __device__ __forceinline__ void leaf_lu_body(
   T a[CW];
 #pragma unroll
   for (int k = 0; k < CW; ++k) a[k] = S[lane * LEAF_PAD + c0 + k];
-  // rows still to be taken: those of the leaf, then (w < 64) those of the padding, whose
-  // pivots are their own ones and eliminate nothing
-  unsigned long long left = ~0ull;
-  const unsigned long long real = w < LEAF ? (1ull << w) - 1ull : ~0ull;
-  int odd = 0;                           // parity of the row order so far
-  auto take = [&](const int p) {
-    odd ^= __popcll(left & ((1ull << p) - 1ull)) & 1;      // rows still to come that stand before p
-    left &= ~(1ull << p);
-  };
+  // rows still to be taken: those of the leaf, and when there are none left (w < 64) those of the padding,
+  // whose pivots are their own ones and eliminate nothing
+  unsigned long long left = w < LEAF ? (1ull << w) - 1ull : ~0ull;
+  const unsigned long long padding = ~left;
+  int odd = 0;                           // parity of the row order so far (the last wavefront's)
+  auto take = [&](const int p) { left &= ~(1ull << p); };
+  auto refill = [&] { left = left != 0ull ? left : padding; };
+  auto count = [&](const int p) { odd ^= __popcll(left & ((1ull << p) - 1ull)) & 1; };   // rows to come that stand before p
   // the earlier columns' steps
+  auto follow = [&](auto last_tag) {
 #pragma unroll 1
-  for (int j = 0; j < c0; ++j) {
-    lds_volatile<int>* number = (lds_volatile<int>*)&row_of[j];
-    lds_volatile<T>* from = (lds_volatile<T>*)&mult[j][lane];
-    int p;
-    T nl;
-    do {
-      p = *number;
-      nl = *from;
-      p = __builtin_amdgcn_readfirstlane(p);
-    } while (p < 0);
-    T pv[CW];
+    for (int j = 0; j < c0; ++j) {
+      lds_volatile<int>* number = (lds_volatile<int>*)&row_of[j];
+      lds_volatile<T>* from = (lds_volatile<T>*)&mult[j][lane];
+      int p;
+      T nl;
+      do {
+        p = *number;
+        nl = *from;
+        p = __builtin_amdgcn_readfirstlane(p);
+      } while (p < 0);
+      T pv[CW];
 #pragma unroll
-    for (int k = 0; k < CW; ++k) pv[k] = lane_value(a[k], p);
+      for (int k = 0; k < CW; ++k) pv[k] = lane_value(a[k], p);
 #pragma unroll
-    for (int k = 0; k < CW; ++k) a[k] = fma(nl, pv[k], a[k]);
-    take(p);
-  }
+      for (int k = 0; k < CW; ++k) a[k] = fma(nl, pv[k], a[k]);
+      refill();
+      if constexpr (decltype(last_tag)::value) count(p);
+      take(p);
+    }
+  };
+  if (wave == NW - 1) follow(std::true_type{});
+  else follow(std::false_type{});
   // its own
   __builtin_amdgcn_s_setprio(3);
   int ps[CW];
-  unsigned long long mine_left = left;
+  const unsigned long long before = left;
+  lds_volatile<T>* const mult_to = (lds_volatile<T>*)&mult[c0][lane];
+  lds_volatile<int>* const row_to = (lds_volatile<int>*)&row_of[c0];
 #pragma unroll
   for (int jj = 0; jj < CW; ++jj) {
-    const int j = c0 + jj;
     const T cj = a[jj];
-    const unsigned long long cand = mine_left & (j < w ? real : ~0ull);
-    const int p = pick_lane(cj, cand);
-    const T d = lane_value(cj, p);
-    const T est = rcp_estimate(d);
-    mine_left &= ~(1ull << p);
-    const bool below = __builtin_amdgcn_inverse_ballot_w64(cand & ~(1ull << p));
+    refill();
+    // every row's own estimate beside the search, the pivot's out of them
+    const T ests = rcp_estimate(cj), tails = quotient_tail(cj, ests);
+    const int p = pick_lane(cj, left);
+    const T est = lane_value(ests, p), tail = lane_value(tails, p);
+    take(p);
+    const bool below = __builtin_amdgcn_inverse_ballot_w64(left);
     const T np = -(cj * est);
-    const T nl = below ? fma(np, quotient_tail(d, est), np) : T(0);
-    *(lds_volatile<T>*)&mult[j][lane] = nl;
-    *(lds_volatile<int>*)&row_of[j] = p;                   // (every lane: the same value)
-    *(lds_volatile<int>*)&pos[p] = j;
+    const T nl = below ? fma(np, tail, np) : T(0);
+    mult_to[jj * LEAF] = nl;
+    row_to[jj] = p;                                        // (every lane: the same value)
 #pragma unroll
     for (int k = jj + 1; k < CW; ++k) a[k] = fma(nl, lane_value(a[k], p), a[k]);
     a[jj] = below ? -nl : cj;
     ps[jj] = p;
   }
   __builtin_amdgcn_s_setprio(2);
+  if (wave == 0) beside();
   if (wave == NW - 1) {
+    left = before;
 #pragma unroll
-    for (int jj = 0; jj < CW; ++jj) take(ps[jj]);
+    for (int jj = 0; jj < CW; ++jj) {
+      refill();
+      count(ps[jj]);
+      take(ps[jj]);
+    }
     if (lane == 0 && odd) atomicAdd(&flags->odd_leaves, 1ull);
   }
   __syncthreads();
   {
-    const int to = pos[lane];
+    // the step at which this row was taken: every lane's number to the lane of its row
+    const int to = __builtin_amdgcn_ds_permute(4 * row_of[lane], lane);
 #pragma unroll
     for (int k = 0; k < CW; ++k) S[to * LEAF_PAD + c0 + k] = a[k];
   }
