@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels_leaf.h"
+
 namespace mdet {
 
 constexpr int RED_THREADS = 256;
@@ -80,15 +82,30 @@ __device__ __forceinline__ double widen_exact(StoredBF16 v) {
   return (double)__uint_as_float((uint32_t)v.bits << 16);     // bfloat16 = the upper half of a float
 }
 
-// Both in one launch of one workgroup, for calls whose few launches count (FINISH_BLOCKS block columns,
+// The pivots and the permutation to where the caller wants them (either may be null), entry i.
+template <typename T>
+__device__ __forceinline__ void copy_out_entry(const T* __restrict__ d, T* __restrict__ diag, const int* __restrict__ perm,
+                                               int* __restrict__ perm_out, int64_t i, int64_t n) {
+  if (i >= n) return;
+  if (diag) diag[i] = d[i];
+  if (perm_out) perm_out[i] = perm[i];
+}
+
+// Both in one launch, for calls whose few launches count (FINISH_BLOCKS block columns, by the first workgroup,
 // the terms of each in the order of logdet_partial_kernel), with what the host reads of a call
-// written straight into its memory: `host` six words, out and the three flags.  n = 512: two launches
-// and a copy of 48 bytes less, 162 -> 152 us.
+// written straight into its memory: `host` six words, out and the three flags.  Further workgroups copy the
+// pivots and the permutation out.  n = 512: two launches and a copy of 48 bytes less, 162 -> 152 us; the copy out
+// here and the flags reset by the launch that copies the matrix, not by launches of their own: XX us.
 constexpr int FINISH_SETS = 4, FINISH_BLOCKS = 16;
 template <typename T>
 __global__ __launch_bounds__(FINISH_SETS * RED_THREADS) void logdet_finish_kernel(
     const T* __restrict__ d, int64_t n, int64_t bs, int nblk, double* __restrict__ out,
-    const unsigned long long* __restrict__ flags, unsigned long long* __restrict__ host) {
+    const unsigned long long* __restrict__ flags, unsigned long long* __restrict__ host, T* __restrict__ diag,
+    const int* __restrict__ perm, int* __restrict__ perm_out) {
+  if (blockIdx.x != 0) {
+    copy_out_entry(d, diag, perm, perm_out, (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x, n);
+    return;
+  }
   __shared__ double s_log[FINISH_SETS][RED_THREADS];
   __shared__ unsigned s_neg[FINISH_SETS][RED_THREADS], s_zero[FINISH_SETS][RED_THREADS];
   __shared__ double partial[FINISH_BLOCKS][3];
@@ -139,12 +156,31 @@ __global__ __launch_bounds__(FINISH_SETS * RED_THREADS) void logdet_finish_kerne
   __threadfence_system();
 }
 
+// Status words as they are at the start of a call: no bad pivot, no odd leaves, and `words` words for
+// panel_flow_kernel to zero; by all threads of a one-dimensional launch.  A kernel, not a memset: a caller
+// may record the launches of the allocation-free entry point into a graph.
+struct ResetWords {
+  DevFlags* flags;
+  unsigned* sync;
+  int words;
+  __device__ __forceinline__ void operator()() const {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, all = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = t; q < words; q += all) sync[q] = 0u;
+    if (t == 0 && flags) {
+      flags->first_bad = ~0ull;
+      flags->bad_kind = ~0ull;
+      flags->odd_leaves = 0ull;
+    }
+  }
+};
+
 // fp32 / fp16 / bf16 -> fp64 copy of the part of a row-major matrix the factorisation
 // reads: row i up to the end of its 64-column leaf on the diagonal.  Widening is exact.
 template <typename S>
 __global__ __launch_bounds__(256) void widen_lower_kernel(const S* __restrict__ src, int64_t lds,
                                                           double* __restrict__ dst, int64_t ldd,
-                                                          int64_t n) {
+                                                          int64_t n, ResetWords reset) {
+  reset();
   const int64_t i = blockIdx.x;
   int64_t end = (i / 64 + 1) * 64;
   if (end > n) end = n;
@@ -152,11 +188,12 @@ __global__ __launch_bounds__(256) void widen_lower_kernel(const S* __restrict__ 
 }
 
 // The same without a change of type, pieces E of several elements at a time (rows start on whole pieces):
-// half of what copying the square moves.  A row's last elements that make no whole piece go one by
+// half of what copying the square moves.  `also`: what else the launch does (ResetWords).  A row's last elements that make no whole piece go one by
 // one: behind the last row's there need not be any memory.
-template <typename T, typename E>
+template <typename T, typename E, typename... Also>
 __global__ __launch_bounds__(256) void copy_lower_kernel(const T* __restrict__ src, int64_t lds, T* __restrict__ dst,
-                                                         int64_t ldd, int64_t n) {
+                                                         int64_t ldd, int64_t n, Also... also) {
+  (also(), ...);
   constexpr int V = sizeof(E) / sizeof(T);
   const int64_t i = blockIdx.x;
   int64_t end = (i / 64 + 1) * 64;

@@ -1041,16 +1041,8 @@ static void bind_small(Launcher<T>& L, char* base, const SmallArea& sa) {
     L.slots = 2 * cus;
 }
 
-// first_bad = ~0 (none), no odd leaves.  A kernel, not a memset: a caller may record the
-// launches of the allocation-free entry point into a graph.
-__global__ void reset_flags_kernel(DevFlags* f, unsigned* sync, int sync_words) {
-  for (int q = threadIdx.x; q < sync_words; q += blockDim.x) sync[q] = 0u;
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    f->first_bad = ~0ull;
-    f->bad_kind = ~0ull;
-    f->odd_leaves = 0ull;
-  }
-}
+// The same by a launch of its own.
+__global__ void reset_flags_kernel(ResetWords reset) { reset(); }
 
 // The workspace of MDET_FLAG_PIVOT_BLOCK, which follows the small area.
 template <typename T>
@@ -1089,8 +1081,10 @@ static void pivot_block_beside(Launcher<T>& L, hipStream_t st, EventPool& events
 }
 
 template <typename T>
+static ResetWords reset_words(const Launcher<T>& L) { return ResetWords{L.flags, L.sync, (int)L.sync_words}; }
+template <typename T>
 static void reset_flags(Launcher<T>& L, hipStream_t st) {
-  hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(L.sync ? 1024 : 64), 0, st, L.flags, L.sync, (int)L.sync_words);
+  hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(L.sync ? 1024 : 64), 0, st, reset_words(L));
   L.fail->check(hipGetLastError());
 }
 
@@ -1099,10 +1093,7 @@ static void reset_flags(Launcher<T>& L, hipStream_t st) {
 template <typename T>
 __global__ void copy_out_kernel(const T* __restrict__ dvec, T* __restrict__ diag, const int* __restrict__ perm,
                                 int* __restrict__ perm_out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (diag) diag[i] = dvec[i];
-  if (perm_out) perm_out[i] = perm[i];
+  copy_out_entry(dvec, diag, perm, perm_out, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n);
 }
 // (Another device's memory is not for a kernel of this one, which may have no access to it.)
 static bool device_memory(const void* p) {
@@ -1115,11 +1106,15 @@ static bool device_memory(const void* p) {
   return a.type == hipMemoryTypeDevice && a.device == current;
 }
 template <typename T>
+static bool copied_by_kernel(const T* diag, const int32_t* perm_out) {
+  return !((diag && (!device_memory(diag) || (uintptr_t)diag % sizeof(T))) ||
+           (perm_out && (!device_memory(perm_out) || (uintptr_t)perm_out % 4)));
+}
+template <typename T>
 static void copy_out(Launcher<T>& L, hipStream_t st, int64_t n, T* diag, int32_t* perm_out) {
   if (!L.perm) perm_out = nullptr;
   if (n <= 0 || (!diag && !perm_out)) return;
-  if ((diag && (!device_memory(diag) || (uintptr_t)diag % sizeof(T))) ||
-      (perm_out && (!device_memory(perm_out) || (uintptr_t)perm_out % 4))) {
+  if (!copied_by_kernel(diag, perm_out)) {
     if (diag) L.fail->check(hipMemcpyAsync(diag, L.dvec, n * sizeof(T), hipMemcpyDeviceToDevice, st));
     if (perm_out) L.fail->check(hipMemcpyAsync(perm_out, L.perm, n * sizeof(int), hipMemcpyDeviceToDevice, st));
     return;
@@ -1178,13 +1173,13 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
       const dim3 grid((unsigned)pl.n), block(256);
       if (p.dtype == MDET_F16)
         hipLaunchKernelGGL((widen_lower_kernel<StoredF16>), grid, block, 0, s0,
-                           (const StoredF16*)widen_from, ld, (double*)W, ldw, pl.n);
+                           (const StoredF16*)widen_from, ld, (double*)W, ldw, pl.n, reset_words(L));
       else if (p.dtype == MDET_BF16)
         hipLaunchKernelGGL((widen_lower_kernel<StoredBF16>), grid, block, 0, s0,
-                           (const StoredBF16*)widen_from, ld, (double*)W, ldw, pl.n);
+                           (const StoredBF16*)widen_from, ld, (double*)W, ldw, pl.n, reset_words(L));
       else
         hipLaunchKernelGGL((widen_lower_kernel<float>), grid, block, 0, s0, (const float*)widen_from,
-                           ld, (double*)W, ldw, pl.n);
+                           ld, (double*)W, ldw, pl.n, reset_words(L));
       MDET_HIP(fail, hipGetLastError());
     } else if (pl.general) {
       MDET_HIP(fail, hipMemcpy2DAsync(W, ldw * sizeof(T), dA, ld * sizeof(T), pl.n * sizeof(T), pl.n,
@@ -1192,14 +1187,15 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
     } else {
       const dim3 grid((unsigned)pl.n), block(256);
       if (ld % Mfma<T>::VEC == 0)
-        hipLaunchKernelGGL((copy_lower_kernel<T, typename Mfma<T>::vec_t>), grid, block, 0, s0, (const T*)dA, ld, W, ldw,
-                           pl.n);
+        hipLaunchKernelGGL((copy_lower_kernel<T, typename Mfma<T>::vec_t, ResetWords>), grid, block, 0, s0, (const T*)dA, ld, W, ldw,
+                           pl.n, reset_words(L));
       else
-        hipLaunchKernelGGL((copy_lower_kernel<T, T>), grid, block, 0, s0, (const T*)dA, ld, W, ldw, pl.n);
+        hipLaunchKernelGGL((copy_lower_kernel<T, T, ResetWords>), grid, block, 0, s0, (const T*)dA, ld, W, ldw, pl.n, reset_words(L));
       MDET_HIP(fail, hipGetLastError());
     }
   }
-  reset_flags(L, s0);
+  // (a kernel that copies the matrix has reset the flags)
+  if (!pl.need_copy || pl.n == 0 || pl.general) reset_flags(L, s0);
   L.profile_begin(s0);
   T* Q = nullptr;
   const int nb64 = (int)((pl.n + LEAF - 1) / LEAF);
@@ -1232,9 +1228,14 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
     if (!place->p) place.reset();
   }
   if (rc == MDET_OK) {
+    // the pivots and the permutation go out with the results where both are a kernel's
+    int32_t* const perm_out = L.perm ? (int32_t*)p.perm : nullptr;
+    const bool with_out = place && (diag || perm_out) && copied_by_kernel(diag, perm_out);
     if (place) {
-      hipLaunchKernelGGL((logdet_finish_kernel<T>), dim3(1), dim3(FINISH_SETS * RED_THREADS), 0, s0, (const T*)L.dvec, pl.n,
-                         pl.bs, (int)pl.T, out, (const unsigned long long*)L.flags, place->p);
+      const int64_t copiers = with_out ? (pl.n + FINISH_SETS * RED_THREADS - 1) / (FINISH_SETS * RED_THREADS) : 0;
+      hipLaunchKernelGGL((logdet_finish_kernel<T>), dim3((unsigned)(1 + copiers)), dim3(FINISH_SETS * RED_THREADS), 0, s0,
+                         (const T*)L.dvec, pl.n, pl.bs, (int)pl.T, out, (const unsigned long long*)L.flags, place->p,
+                         diag, (const int*)L.perm, (int*)perm_out);
       MDET_HIP(fail, hipGetLastError());
       ++L.launches;
     } else {
@@ -1246,7 +1247,7 @@ static int logdet_device_t(const mdet_params& p, const Plan& plan, T* dA, int64_
                          dim3(256), 0, s0, (const T*)Q, W, ldw, pl.n, nb64, 1);
       MDET_HIP(fail, hipGetLastError());
     }
-    copy_out(L, s0, pl.n, diag, (int32_t*)p.perm);
+    if (!with_out) copy_out(L, s0, pl.n, diag, (int32_t*)p.perm);
   }
   DeviceOut o;
   std::memset(&o, 0, sizeof(o));
