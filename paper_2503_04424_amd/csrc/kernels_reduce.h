@@ -82,28 +82,19 @@ __device__ __forceinline__ double widen_exact(StoredBF16 v) {
   return (double)__uint_as_float((uint32_t)v.bits << 16);     // bfloat16 = the upper half of a float
 }
 
-// The pivots and the permutation to where the caller wants them (either may be null), entry i.
-template <typename T>
-__device__ __forceinline__ void copy_out_entry(const T* __restrict__ d, T* __restrict__ diag, const int* __restrict__ perm,
-                                               int* __restrict__ perm_out, int64_t i, int64_t n) {
-  if (i >= n) return;
-  if (diag) diag[i] = d[i];
-  if (perm_out) perm_out[i] = perm[i];
-}
-
 // Both in one launch, for calls whose few launches count (FINISH_BLOCKS block columns, by the first workgroup,
 // the terms of each in the order of logdet_partial_kernel), with what the host reads of a call
 // written straight into its memory: `host` six words, out and the three flags.  Further workgroups copy the
-// pivots and the permutation out.  n = 512: two launches and a copy of 48 bytes less, 162 -> 152 us; the copy out
-// here and the flags reset by the launch that copies the matrix, not by launches of their own: XX us.
+// pivots out.  n = 512: two launches and a copy of 48 bytes less, 162 -> 152 us; the copy out
+// here and the flags reset by the launch that copies the matrix, not by launches of their own: 147.
 constexpr int FINISH_SETS = 4, FINISH_BLOCKS = 16;
 template <typename T>
 __global__ __launch_bounds__(FINISH_SETS * RED_THREADS) void logdet_finish_kernel(
     const T* __restrict__ d, int64_t n, int64_t bs, int nblk, double* __restrict__ out,
-    const unsigned long long* __restrict__ flags, unsigned long long* __restrict__ host, T* __restrict__ diag,
-    const int* __restrict__ perm, int* __restrict__ perm_out) {
+    const unsigned long long* __restrict__ flags, unsigned long long* __restrict__ host, T* __restrict__ diag) {
   if (blockIdx.x != 0) {
-    copy_out_entry(d, diag, perm, perm_out, (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x, n);
+    const int64_t i = (int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+    if (i < n) diag[i] = d[i];
     return;
   }
   __shared__ double s_log[FINISH_SETS][RED_THREADS];
