@@ -24,10 +24,11 @@
 // elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
 // that.  Between launches the same steps also wait for every workgroup of the launch before and
 // for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
-// against the chain of launches, whole calls that keep their input: symmetric fp64 n = 512 229 -> 152 us,
-// n = 1500 (positive definite) 603 -> 361, n = 5555 (positive definite) 3020 -> 1546, n = 8192 5873 -> 3889, fp32
-// n = 10000 5940 -> 3609; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 183.8 ms; pivots from
-// inside a leaf, n = 4096 3.04 -> 1.69 ms; general n = 2900 2.27 -> 1.38, n = 8192 11.3 -> 8.0 (leaves of 20 us).
+// against the chain of launches, whole calls that keep their input: symmetric fp64 n = 512 229 -> 147 us,
+// n = 1500 (positive definite) 603 -> 360, n = 5555 (positive definite) 3020 -> 1445, n = 8192 5873 -> 3550, fp32
+// n = 10000 5940 -> 3380; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 176.3 ms; pivots from
+// inside a leaf (24 us from leaf to leaf), n = 4096 3.04 -> 1.60 ms; general (26 us) n = 2900 2.27 -> 1.28, n = 8192 11.3 ->
+// 7.1.
 // Where a matrix is large: the
 // matrix cores, in fp64 3.6 us for the 128 x 64 x 64 products of a row task of one column and 7.0 for
 // 128 x 128 x 64 of two (positive-definite form 3.5 and 6.9; 3.4 and 6.8 at their peak; fp32 1.97 and 3.65 of 1.7
@@ -141,14 +142,15 @@ struct FlowOrder {
     return 2 * pair >= top || 2 * pair + 1 < ntr ? FLOW_ROWS : FLOW_NOTHING;
   }
 };
-// Column pairs with row tasks of both: while 28 row tasks of each column are left (general matrices have
-// two to a pair of tile rows, so 14 pairs).  Measured with none, a
-// quarter, 0.4, 0.6, three quarters and all of the pairs: fp64 n = 4096 0.90 0.94 0.89 0.94 0.93 0.98 ms, n
-// = 8192 3.99 3.90 3.90 3.86 3.84 4.18, n = 12300 13.3 12.9 12.5 12.1 12.2 12.4; fp32 n = 10000 4.28 4.02
-// 3.84 3.63 3.60 3.53.
+// Column pairs with row tasks of both: symmetric matrices while 28 pairs of tile rows are left, general ones (two
+// row tasks to each) while 4 are: their leaves take twice as long, so a longer task is waited for less.  Measured
+// (in place, ms): symmetric, 16 20 28 36 pairs, fp64 n = 5555 1.54 1.47 1.52 1.54, n = 8192 3.51 3.59 3.42 3.45, n = 12300
+// 11.1 11.2 11.0 11.1, fp32 n = 10000 3.28 3.31 3.26 3.31; general, 4 6 8 11 14 pairs, fp64 n = 2900 1.25 1.24 1.24 1.24
+// 1.25, n = 5000 2.32 2.35 2.38 2.45 2.57, n = 8192 7.58 7.61 7.59 7.76 8.03, n = 16384 49.8 49.9 49.8 50.1 50.9, fp32 n =
+// 8000 3.61 3.67 3.70 3.73 3.84.
 static inline int flow_two(int64_t m, int64_t w, int arrays) {
   const int64_t pairs = (m + 2 * LEAF - 1) / (2 * LEAF), columns = (w + 2 * LEAF - 1) / (2 * LEAF);
-  const int64_t two = pairs - 28 / arrays;
+  const int64_t two = pairs - (arrays == 2 ? 4 : 28);
   return (int)(two < 0 ? 0 : (two < columns ? two : columns));
 }
 static inline FlowOrder flow_order(int64_t m, int64_t w, int arrays, int two) {
