@@ -795,8 +795,8 @@ static int factor_resident(Launcher<T>& L, const Plan& pl, std::vector<ColRef<T>
 // 82.3 / 156 167 / 38.4 42.1; positive definite 16384 24.3 25.4, 24000 73.4 78.3; pivots from inside a leaf 24000
 // 75.6 83.8; rows off 128-byte lines, whose operands are read past the caches, 8192 3.78 5.39, 16384 25.3
 // 27.4, 24000 76.8 85.1, general 160 173.  The line lies where the plan begins to take pivot-scaled copies of
-// block columns by itself (make_plan).  It is not where the gain ends: 28000 118 124 / 240 259 / 59.8 63.7, 32768
-// 186 181 / 376 380 / 94.9 92.9, 36000 248 256 / 504 536 / 126 131.  16 is how many block columns the
+// block columns by itself (make_plan).  It is not where the gain ends: with
+// the pipelined bulk update 28000 117 122 / 243 249 / - -, 32768 186 180 / 383 367 / 95.4 90.0, 40000 335 337.  16 is how many block columns the
 // library makes of a matrix by itself; a caller who asks for more of them, and for look-ahead between them,
 // gets a launch for every 16 (n = 8192, b = 128, copied: 4.86 ms; without look-ahead, whole, 4.09; the chain
 // of launches took 9.77).  With MDET_FLAG_PROFILE the updates between block columns are what is looked
