@@ -20,8 +20,8 @@
 // Bound by the matrix cores.  The wavefronts of a workgroup meet once a slab, in front of its last strip
 // of products, behind which nothing of the slab is read any more: the next slab's first fragments and
 // the loads of the one after it go out beside those products.  Measured, M = N = 16384, K = 2048, random
-// entries: fp64 73.6 TFLOP/s with scaling, 74.1 without (66.9 and 70.8 with the loads in one piece at the
-// start of a slab and the meeting at its end), fp32 142.8 and 146.0 (133.7, 137.9); of the 78.6 / 157.3 at
+// entries, a launch alone: fp64 73.5 TFLOP/s with scaling, 74.5 without (66.6 and 70.0 with the loads in one piece at the
+// start of a slab and the meeting at its end), fp32 143.3 and 146.3 (132.8, 137.0); of the 78.6 / 157.3 at
 // the matrix cores' peak 4 % go into loading and storing C.
 //
 // Also here, because it ends with the same hand-over of the next leaf: leaf_update_kernel
@@ -193,15 +193,14 @@ __device__ __forceinline__ void load_to_lds(const char* base, const unsigned off
 #undef MDET_TO_LDS
 }
 
-// One block (bm, bn) of C, by all threads of the workgroup; `lds` = LDS_ELEMS
-// elements.  Every thread returns from it (there are barriers inside), so a
-// workgroup may call it for one block after another.
+// One block (bm, bn) of C, by all threads of the workgroup (there are barriers inside); `lds` =
+// LDS_ELEMS elements, which are not read any more when the last thread returns.
 //
 // Staging.  A slab is 128 bytes of K per operand row.  It goes from global memory
 // straight into LDS (global_load_lds_dwordx4: every lane names its own 16 global
 // bytes, and lane l's land at the wavefront's LDS base + 16 l), so it needs no
-// staging registers, no LDS store instructions and no wait before the end of the
-// slab.  One such load fills 1 KB = 8 rows; a workgroup's four wavefronts issue
+// staging registers, no LDS store instructions and no wait before the last strip of
+// the slab before.  One such load fills 1 KB = 8 rows; a workgroup's four wavefronts issue
 // BM/32 of them per operand and slab.  Rows are 128 bytes apart in LDS without
 // padding; instead the eight 16-byte chunks of row r are stored in the order
 // chunk ^ ((r >> 1) & 7), which a lane arranges by choosing what it loads.  The
@@ -282,19 +281,55 @@ __device__ __forceinline__ void schur_update_block(
     asm volatile("" ::: "memory");
   };
 
+  const int nk = K / BK;            // (K is a multiple of 64: an even number of slabs, at least two)
+  __builtin_assume(nk >= 64 / BK);
+  auto first_slabs = [&] {
+#pragma unroll
+    for (int part = 0; part < LOADS; ++part) gload(part, 0, 0);
+    landed();
+#pragma unroll
+    for (int part = 0; part < LOADS; ++part) gload(part, 1, 1);
+  };
+
+  // The workgroup that goes on to factor the leaf at the block's top left hands that part over in LDS
+  // (the operand buffers are free behind a barrier) and leaves its write-back to the factorisation.
+  const bool fuse = lower && fl.w > 0 && bm == 0 && bn == 0;
+  const int wleaf = fuse ? fl.w : 0;
   const int r16 = lane & 15, g = lane >> 4;
 
-  // The accumulators start from (minus) C and the products are added to them in
-  // K order, so every entry is reduced term by term exactly as in the unblocked
-  // recurrence a_ij - sum_k l_ik d_k l_jk; when the Schur complement is much
-  // smaller than a_ij (low-rank Gram matrix plus a small shift) the late roundings
-  // are then relative to the small running value, not to the full sum.
-  acc_t acc[TM][TM];
+  // A wavefront without a piece brings its share of the slabs and keeps the barriers company, on a way of its own
+  // to the end of the block.  Where the two ways met in front of the stores, the accumulators were live on both, and in
+  // fp64 88 registers' worth went to scratch memory (K = 128, M = N = 16384 lower: 0.91 ms, 0.83 without).
+  if (!active) {
+    first_slabs();
+    for (int kt = 0; kt + 1 < nk; ++kt) {
+      landed();
+      if (kt + 2 < nk) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+        for (int part = 0; part < LOADS; ++part) gload(part, kt + 2, kt & 1);
+      }
+    }
+    if (fuse) {
+      __syncthreads();
 #pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
-  if (active) {
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < TM; ++j)
+            leaf_tile_put<T>(lds, wm * WT + i * 16 + X::acc_row(lane, r), wn * WT + j * 16 + r16, wleaf, T(0));
+    }
+  } else {
+    // The accumulators start from (minus) C and the products are added to them in
+    // K order, so every entry is reduced term by term exactly as in the unblocked
+    // recurrence a_ij - sum_k l_ik d_k l_jk; when the Schur complement is much
+    // smaller than a_ij (low-rank Gram matrix plus a small shift) the late roundings
+    // are then relative to the small running value, not to the full sum.
+    acc_t acc[TM][TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -309,104 +344,95 @@ __device__ __forceinline__ void schur_update_block(
         }
       }
     }
-  }
 
-  const int nk = K / BK;
+    // lane group g owns the KS consecutive k's [g*KS, (g+1)*KS) of a slab, i.e. its
+    // logical chunks 2g and 2g+1; MFMA step s multiplies the s-th of them from every
+    // group (any assignment of the slab's k's to steps is valid as long as A and B
+    // use the same one).  Where those chunks sit in a row depends only on the lane
+    // (rows 16 apart share the swizzle).
+    const int sw = (r16 >> 1) & 7;
+    const int c0 = ((2 * g) ^ sw) * VEC, c1 = ((2 * g + 1) ^ sw) * VEC;
+    first_slabs();
+    {
+      // -C, in one go now that the loads have landed (negating each entry as it is
+      // loaded would make every load wait for itself)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[i][j][r] = -acc[i][j][r];
+    }
 
-  // lane group g owns the KS consecutive k's [g*KS, (g+1)*KS) of a slab, i.e. its
-  // logical chunks 2g and 2g+1; MFMA step s multiplies the s-th of them from every
-  // group (any assignment of the slab's k's to steps is valid as long as A and B
-  // use the same one).  Where those chunks sit in a row depends only on the lane
-  // (rows 16 apart share the swizzle).
-  const int sw = (r16 >> 1) & 7;
-  const int c0 = ((2 * g) ^ sw) * VEC, c1 = ((2 * g + 1) ^ sw) * VEC;
+    // Fragments are fetched one 16-row strip at a time, each fetch issued one stage ahead of its first
+    // use, so that LDS latency hides behind the chain of MFMAs of the stage before.  Stage (i, j): all
+    // KS products of accumulator (i, j) back to back.  In front of the last strip's products, when nothing
+    // more is read of this slab, the wavefronts meet: the next slab has landed, whose first fragments
+    // are fetched and scaled beside these products, and this one's place takes the slab after that,
+    // one or two loads behind each group of products.
+    T fa[2][KS], fb[TM][KS], nd[KS];
+    auto fetch = [&](T (&f)[KS], const T* base) {
+      const vec_t v0 = *reinterpret_cast<const vec_t*>(base + c0);
+      const vec_t v1 = *reinterpret_cast<const vec_t*>(base + c1);
 #pragma unroll
-  for (int part = 0; part < LOADS; ++part) gload(part, 0, 0);
-  landed();
+      for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
+    };
+    auto fetch_pivots = [&](const int buf) {
+      if constexpr (!SCALED) {
 #pragma unroll
-  for (int part = 0; part < LOADS; ++part) gload(part, 1, 1);
-  {
-    // -C, in one go now that the loads have landed (negating each entry as it is
-    // loaded would make every load wait for itself)
+        for (int h = 0; h < KS / VEC; ++h) {
+          const vec_t v = *reinterpret_cast<const vec_t*>(lds + UpdShape<T, TM>::PIVOTS + buf * 2 * BK + g * KS + h * VEC);
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = -acc[i][j][r];
-  }
-
-  // Fragments are fetched one 16-row strip at a time, each fetch issued one stage ahead of its first
-  // use, so that LDS latency hides behind the chain of MFMAs of the stage before.  Stage (i, j): all
-  // KS products of accumulator (i, j) back to back.  In front of the last strip's products, when nothing
-  // more is read of this slab, the wavefronts meet: the next slab has landed, whose first fragments
-  // are fetched and scaled beside these products, and this one's place takes the slab after that,
-  // one or two loads behind each group of products.
-  T fa[2][KS], fb[TM][KS], nd[KS];
-  auto fetch = [&](T (&f)[KS], const T* base) {
-    const vec_t v0 = *reinterpret_cast<const vec_t*>(base + c0);
-    const vec_t v1 = *reinterpret_cast<const vec_t*>(base + c1);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) { f[e] = v0[e]; f[VEC + e] = v1[e]; }
-  };
-  auto fetch_pivots = [&](const int buf) {
-    if constexpr (!SCALED) {
-#pragma unroll
-      for (int h = 0; h < KS / VEC; ++h) {
-        const vec_t v = *reinterpret_cast<const vec_t*>(lds + UpdShape<T, TM>::PIVOTS + buf * 2 * BK + g * KS + h * VEC);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) nd[h * VEC + e] = v[e];
+          for (int e = 0; e < VEC; ++e) nd[h * VEC + e] = v[e];
+        }
       }
-    }
-  };
-  auto scale = [&](T (&f)[KS]) {
-    if constexpr (!SCALED) {
+    };
+    auto scale = [&](T (&f)[KS]) {
+      if constexpr (!SCALED) {
 #pragma unroll
-      for (int e = 0; e < KS; ++e) f[e] *= nd[e];
-    }
-  };
-  auto rows_of = [&](const int buf) { return &As[buf][(wm * WT + r16) * BK]; };
-  auto cols_of = [&](const int buf) { return &Bs[buf][(wn * WT + r16) * BK]; };
-  // One slab.  MORE slabs follow: 2 and more, 1 or 0 (decided at compile time, so that the stages of a slab
-  // form one straight run of instructions).
-  auto slab = [&](const int kt, auto buf_tag, auto more_tag) {
-    constexpr int BUF = decltype(buf_tag)::value, MORE = decltype(more_tag)::value;
-    const T* as = rows_of(BUF);
-    const T* bs = cols_of(BUF);
+        for (int e = 0; e < KS; ++e) f[e] *= nd[e];
+      }
+    };
+    auto rows_of = [&](const int buf) { return &As[buf][(wm * WT + r16) * BK]; };
+    auto cols_of = [&](const int buf) { return &Bs[buf][(wn * WT + r16) * BK]; };
+    // One slab.  MORE slabs follow: 2 and more, 1 or 0 (decided at compile time, so that the stages of a slab
+    // form one straight run of instructions).
+    auto slab = [&](const int kt, auto buf_tag, auto more_tag) {
+      constexpr int BUF = decltype(buf_tag)::value, MORE = decltype(more_tag)::value;
+      const T* as = rows_of(BUF);
+      const T* bs = cols_of(BUF);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+      for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        if (i == 0 && j + 1 < TM) fetch(fb[j + 1], bs + (j + 1) * 16 * BK);
-        if (j == TM - 1 && i + 1 < TM) fetch(fa[(i + 1) & 1], as + (i + 1) * 16 * BK);
-        if (j == 0 && i > 0) scale(fa[i & 1]);
-        if (i == TM - 1 && MORE > 0) {
-          if (j == 0) {
-            landed();
-            fetch(fa[0], rows_of(BUF ^ 1));
-            fetch_pivots(BUF ^ 1);
+        for (int j = 0; j < TM; ++j) {
+          if (i == 0 && j + 1 < TM) fetch(fb[j + 1], bs + (j + 1) * 16 * BK);
+          if (j == TM - 1 && i + 1 < TM) fetch(fa[(i + 1) & 1], as + (i + 1) * 16 * BK);
+          if (j == 0 && i > 0) scale(fa[i & 1]);
+          if (i == TM - 1 && MORE > 0) {
+            if (j == 0) {
+              landed();
+              fetch(fa[0], rows_of(BUF ^ 1));
+              fetch_pivots(BUF ^ 1);
+            }
+            if (j == 1) fetch(fb[0], cols_of(BUF ^ 1));
+            if (j == TM - 1) scale(fa[0]);
           }
-          if (j == 1) fetch(fb[0], cols_of(BUF ^ 1));
-          if (j == TM - 1) scale(fa[0]);
-        }
-        __builtin_amdgcn_sched_barrier(0);   // all of the above goes out before this stage's products
+          __builtin_amdgcn_sched_barrier(0);   // all of the above goes out before this stage's products
 #pragma unroll
-        for (int e = 0; e < KS; ++e) acc[i][j] = X::mfma(fa[i & 1][e], fb[j][e], acc[i][j]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i == TM - 1 && MORE > 1) {
+          for (int e = 0; e < KS; ++e) acc[i][j] = X::mfma(fa[i & 1][e], fb[j][e], acc[i][j]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (i == TM - 1 && MORE > 1) {
 #pragma unroll
-          for (int part = 0; part < LOADS; ++part)
-            if (part * TM / LOADS == j) gload(part, kt + 2, BUF);
+            for (int part = 0; part < LOADS; ++part)
+              if (part * TM / LOADS == j) gload(part, kt + 2, BUF);
+          }
         }
       }
-    }
-  };
-  using Zero = std::integral_constant<int, 0>;
-  using One = std::integral_constant<int, 1>;
-  using Two = std::integral_constant<int, 2>;
-  static_assert(TM % 2 == 0, "the last strip is in fa[1], the next slab's first goes to fa[0]");
-  // (K is a multiple of 64: an even number of slabs, at least two)
-  if (active) {
+    };
+    using Zero = std::integral_constant<int, 0>;
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    static_assert(TM % 2 == 0, "the last strip is in fa[1], the next slab's first goes to fa[0]");
     fetch(fa[0], rows_of(0));
     fetch(fb[0], cols_of(0));
     fetch_pivots(0);
@@ -418,44 +444,35 @@ __device__ __forceinline__ void schur_update_block(
     }
     slab(kt, Zero{}, One{});
     slab(kt + 1, One{}, Zero{});
-  } else {
-    for (int kt = 0; kt + 1 < nk; ++kt) {
-      landed();
-      if (kt + 2 < nk) {
-#pragma unroll
-        for (int part = 0; part < LOADS; ++part) gload(part, kt + 2, kt & 1);
-      }
-    }
-  }
 
-  // ---- epilogue: store the reduced block ----------------------------------
-  // The workgroup that goes on to factor the leaf at the block's top left hands that
-  // part over in LDS (the operand buffers are free behind a barrier)
-  // and leaves its write-back to the factorisation.
-  const bool fuse = lower && fl.w > 0 && bm == 0 && bn == 0;
-  const int wleaf = fuse ? fl.w : 0;
-  if (fuse) {
-    __syncthreads();
+    // ---- epilogue: store the reduced block ----------------------------------
+    // (The lane anew where registers are short: the compiler would keep what it knows of C's addresses and bounds
+    // across K, and 40 to 50 of those registers are not there in fp64.  fp32 has them to spare, and is 2.5 % faster
+    // so at K = 128.)
+    int mine = lane;
+    if constexpr (TM == 4 && sizeof(T) == 8) asm volatile("" : "+v"(mine));
+    const int mine16 = mine & 15;
+    if (fuse) {
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-          leaf_tile_put<T>(lds, wm * WT + i * 16 + X::acc_row(lane, r), wn * WT + j * 16 + r16,
-                           wleaf, -acc[i][j][r]);
-  }
-  if (active) {
+          for (int j = 0; j < TM; ++j)
+            leaf_tile_put<T>(lds, wm * WT + i * 16 + X::acc_row(mine, r), wn * WT + j * 16 + mine16,
+                             wleaf, -acc[i][j][r]);
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int grow = row0 + wm * WT + i * 16 + X::acc_row(lane, r);
+        const int grow = row0 + wm * WT + i * 16 + X::acc_row(mine, r);
         if (grow >= M) continue;
         T* crow = C + (int64_t)grow * ldc;
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
-          const int gcol = col0 + wn * WT + j * 16 + r16;
+          const int gcol = col0 + wn * WT + j * 16 + mine16;
           if (gcol < N && (!lower || gcol <= grow) && !(grow < wleaf && gcol < wleaf))
             crow[gcol] = -acc[i][j][r];
         }
