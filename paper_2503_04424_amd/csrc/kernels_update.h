@@ -176,15 +176,15 @@ constexpr int DEVICE_SCOPE = 16;                      // the sc1 bit of a buffer
 // A wavefront's SIZE bytes a lane from base + off (base the same in all lanes) straight to LDS, lane by lane
 // from byte `at` on (the same in all lanes).  Written out because the compiler, told of the load, waits for
 // it in front of the next read of anything in LDS; the caller counts these loads and waits for them by
-// itself (s_waitcnt vmcnt).
+// itself (s_waitcnt vmcnt).  `at` goes into m0 by the compiler's hand, which uses that register too: it knows
+// what is in it, and the instruction in front of the load is the wait that a load has to keep behind a write of m0.
 template <int SIZE, int SCOPE>
 __device__ __forceinline__ void load_to_lds(const char* base, const unsigned off, const unsigned at) {
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)base);
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uintptr_t)base >> 32));
   const unsigned long long from = ((unsigned long long)hi << 32) | lo;
-#define MDET_TO_LDS(WIDTH, BITS)                                                                         \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_" WIDTH " %1, %2" BITS                  \
-               :: "s"(at), "v"(off), "s"(from) : "m0")
+#define MDET_TO_LDS(WIDTH, BITS)                                                                        \
+  asm volatile("s_nop 0\n\tglobal_load_lds_" WIDTH " %1, %2" BITS ::"{m0}"(at), "v"(off), "s"(from))
   static_assert((SIZE == 16 || SIZE == 4) && (SCOPE == 0 || SCOPE == DEVICE_SCOPE), "forms in use");
   if constexpr (SIZE == 16 && SCOPE == 0) MDET_TO_LDS("dwordx4", "");
   else if constexpr (SIZE == 16) MDET_TO_LDS("dwordx4", " sc1");
