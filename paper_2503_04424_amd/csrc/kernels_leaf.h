@@ -279,8 +279,6 @@ struct Diag16 {
 // v -= sum_k h[k] w_k for the first 4, 8, 12 or 16 k, w_k in lane k of each row of 16 lanes (the wait
 // covers the instruction that made w, see MDET_STEP)
 #define MDET_APPLY_TERM(K, H) MDET_FMAC " %0, -%1, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
-#define MDET_APPLY_TERM1(K, H) MDET_FMAC " %1, -%2, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
-#define MDET_APPLY_TERM0(K, H) MDET_FMAC " %0, -%2, %" H " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
 #define MDET_APPLY_TERMS4 MDET_APPLY_TERM("0", "2") MDET_APPLY_TERM("1", "3") MDET_APPLY_TERM("2", "4") MDET_APPLY_TERM("3", "5")
 #define MDET_APPLY_TERMS8 \
   MDET_APPLY_TERMS4 MDET_APPLY_TERM("4", "6") MDET_APPLY_TERM("5", "7") MDET_APPLY_TERM("6", "8") MDET_APPLY_TERM("7", "9")
@@ -302,42 +300,14 @@ struct Diag16 {
     else if constexpr (N == 12) MDET_APPLY(TYPE, 12);                                        \
     else MDET_APPLY(TYPE, 16);                                                               \
   }
-// The first 8, 12 or 16 terms, the even k to v0 and the odd ones to v1: a multiply-add waits 11 clocks for the one
-// before it in a sum, and two sums in turn take half as long.
-#define MDET_APPLY_PAIRS8                                                                                   \
-  MDET_APPLY_TERM0("0", "3") MDET_APPLY_TERM1("1", "4") MDET_APPLY_TERM0("2", "5") MDET_APPLY_TERM1("3", "6") \
-  MDET_APPLY_TERM0("4", "7") MDET_APPLY_TERM1("5", "8") MDET_APPLY_TERM0("6", "9") MDET_APPLY_TERM1("7", "10")
-#define MDET_APPLY_PAIRS12                                                                                  \
-  MDET_APPLY_PAIRS8 MDET_APPLY_TERM0("8", "11") MDET_APPLY_TERM1("9", "12") MDET_APPLY_TERM0("10", "13")     \
-  MDET_APPLY_TERM1("11", "14")
-#define MDET_APPLY_PAIRS16                                                                                  \
-  MDET_APPLY_PAIRS12 MDET_APPLY_TERM0("12", "15") MDET_APPLY_TERM1("13", "16") MDET_APPLY_TERM0("14", "17")  \
-  MDET_APPLY_TERM1("15", "18")
-#define MDET_APPLY_PAIR(N) asm("s_nop 1\n\t" MDET_APPLY_PAIRS##N : "+&v"(v0), "+&v"(v1) : "v"(w), MDET_H##N)
-#define MDET_APPLY_PAIR_ALL(TYPE)                                                                    \
-  template <int N>                                                                                   \
-  __device__ __forceinline__ void apply_pairs(TYPE& v0, TYPE& v1, const TYPE (&h)[16], TYPE w) {     \
-    static_assert(N == 8 || N == 12 || N == 16, "terms in fours");                                   \
-    if constexpr (N == 8) MDET_APPLY_PAIR(8);                                                        \
-    else if constexpr (N == 12) MDET_APPLY_PAIR(12);                                                 \
-    else MDET_APPLY_PAIR(16);                                                                        \
-  }
 #define MDET_FMAC "v_fmac_f64_dpp"
 MDET_APPLY_ALL(double)
-MDET_APPLY_PAIR_ALL(double)
 #undef MDET_FMAC
 #define MDET_FMAC "v_fmac_f32_dpp"
 MDET_APPLY_ALL(float)
-MDET_APPLY_PAIR_ALL(float)
 #undef MDET_FMAC
-#undef MDET_APPLY_PAIR_ALL
-#undef MDET_APPLY_PAIR
-#undef MDET_APPLY_PAIRS16
-#undef MDET_APPLY_PAIRS12
-#undef MDET_APPLY_PAIRS8
 #undef MDET_APPLY_ALL
-#undef MDET_APPLY_TERM0
-#undef MDET_APPLY_TERM1
+#undef MDET_APPLY_TERM
 #undef MDET_APPLY
 #undef MDET_H16
 #undef MDET_H12
@@ -347,13 +317,14 @@ MDET_APPLY_PAIR_ALL(float)
 #undef MDET_APPLY_TERMS12
 #undef MDET_APPLY_TERMS8
 #undef MDET_APPLY_TERMS4
-// The first j terms (the registers of the others hold zeros): j is known where a loop is unrolled.  From the
-// fifth on the odd ones go to v1.
+// The first j terms (the registers of the others hold zeros): j is known where a loop is unrolled.  One sum, which
+// starts from the entry and takes its terms in their order: even and odd terms apart, which would wait less for
+// each other, gain nothing (a leaf 1 % slower, in fp32 6 %) and round to the size of the terms and not of what is left of the entry.
 template <typename T>
-__device__ __forceinline__ void apply_first(T& v, T& v1, const T (&h)[16], T w, const int j) {
-  if (j > 12) apply_pairs<16>(v, v1, h, w);
-  else if (j > 8) apply_pairs<12>(v, v1, h, w);
-  else if (j > 4) apply_pairs<8>(v, v1, h, w);
+__device__ __forceinline__ void apply_first(T& v, const T (&h)[16], T w, const int j) {
+  if (j > 12) apply_terms<16>(v, h, w);
+  else if (j > 8) apply_terms<12>(v, h, w);
+  else if (j > 4) apply_terms<8>(v, h, w);
   else if (j > 0) apply_terms<4>(v, h, w);
 }
 
@@ -696,7 +667,7 @@ __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
 // inverses of the diagonal sub-blocks of L), and perm[j] = pivot0 + (row taken at step j).
 // Bound by the chain of one step (430 clocks: search 230, row from LDS 100, its terms so far, quotient);
 // the three products between cost 2500 clocks each.  Measured, fp64, inside panel_flow_kernel: 15.5 us a leaf,
-// 24.0 from one leaf to the next (with all 16 terms a step in one sum, and the tile left of the leaf stored and
+// 24.0 from one leaf to the next (with all 16 terms a step whatever their number, and the tile left of the leaf stored and
 // the multipliers' places cleared in front of it, 26.4; n = 4096 1.69 -> 1.60 ms).
 // IN_LDS, THROUGH: as for leaf_factor_body; `lds` has PIVOT_LDS_ELEMS elements, of which with IN_LDS
 // the first LEAF_TILE hold the leaf, both triangles, row stride LEAF_PAD.  With THROUGH the other
@@ -763,14 +734,13 @@ __device__ __forceinline__ void leaf_factor_pivoted_body(
       for (int j = 0; j < SUB; ++j) {
         left = left != 0ull ? left : padding;
         const int p = pick_lane(diag, left);
-        T v = S[p * LEAF_PAD + lane], odd = T(0);
+        T v = S[p * LEAF_PAD + lane];
         const T lp = terms[p];
         const T d = lane_value(diag, p);
         const T est = rcp_estimate(d);
         const T tail = quotient_tail(d, est);
         left &= ~(1ull << p);
-        apply_first(v, odd, l, lp * dm, j);
-        if (j > 4) v += odd;
+        apply_first(v, l, lp * dm, j);
         dm = mine == j ? d : dm;
         const T q = v * est;
         l[j] = __builtin_amdgcn_inverse_ballot_w64(left) ? fma(q, tail, q) : T(0);

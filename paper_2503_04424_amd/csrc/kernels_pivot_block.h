@@ -300,7 +300,7 @@ struct PbRow {
       const int taken = __builtin_amdgcn_readlane(o.row, win);
       const int p = taken & 0xffff, at = taken >> 16;          // at: -1 if it is not held
       const int from = at < 0 ? 0 : at;
-      T wk[M + 1], v = s.rows[from * NT + i], v1 = T(0);
+      T wk[M + 1], v = s.rows[from * NT + i];
 #pragma unroll
       for (int b = 0; b <= M; ++b) wk[b] = s.mult[(SUB * b + l16) * H::STRIDE + from];
       if (__builtin_expect(at < 0, 0)) {
@@ -322,9 +322,8 @@ struct PbRow {
       mypos = i == p ? J0 + j : mypos;
       left &= ~(p >> 6 == wave ? 1ull << (p & 63) : 0ull);
 #pragma unroll
-      for (int b = 0; b < M; ++b) apply_pairs<16>(v, v1, h[b], wk[b] * dh[b]);
-      apply_first(v, v1, cur, wk[M] * dcur, j);
-      v += v1;
+      for (int b = 0; b < M; ++b) apply_first(v, h[b], wk[b] * dh[b], SUB);
+      apply_first(v, cur, wk[M] * dcur, j);
       dcur = mine == j ? d : dcur;
       pcur = mine == j ? p : pcur;
       // v / d: the product with the reciprocal, and one correction
