@@ -47,3 +47,31 @@ def test_a_tiny_pivot_and_a_row_coupled_to_it(dtype):
     r, diag, perm = run(a.astype(t), 64)
     assert r.status == 0 and r.sign == 1
     assert list(perm[-2:]) == [4, 9] and list(diag[-2:]) == [4 * tiny, 3 * tiny]
+
+
+# Pivots at the other end of the range, where the reciprocal is subnormal, and on both sides of the line from which on a
+# step scales them down (2^1021, fp32 2^125).
+HUGE = {"f64": (np.float64, (1023, 1021, 1020, 1019)), "f32": (np.float32, (127, 125, 124, 123))}
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,bs", [(20, 64), (300, 320), (600, 640)])
+@pytest.mark.parametrize("k", range(4))
+def test_a_huge_pivot_and_rows_coupled_to_it(n, bs, dtype, k):
+    import paper_2503_04424_amd as M
+    M.load()
+    t, exponents = HUGE[dtype]
+    d = 2.0 ** exponents[k]
+    a = np.eye(n)
+    a[7, 7], a[3, 3] = d, d / 2
+    a[7, 3] = a[3, 7] = 0.75 * d                  # l = 3/4, and d / 2 - 9/16 d is left
+    a[7, 5] = a[5, 7] = 2.0 ** (exponents[k] // 2)    # l = 2^(e / 2 - e), and one less 2^(2 (e / 2) - e)
+    ad = torch.from_numpy(a.astype(t)).cuda()
+    diag = torch.empty(n, dtype=ad.dtype, device="cuda")
+    perm = torch.empty(n, dtype=torch.int32, device="cuda")
+    r = M.mdet_logdet_device(ad, block_size=bs, flags=M.FLAG_PIVOT_BLOCK, diag=diag, perm=perm, overwrite=True,
+                             raise_on_error=False)
+    assert r.status == 0
+    perm, diag, low = list(perm.cpu().numpy()), diag.cpu().numpy().astype(np.float64), ad.cpu().numpy().astype(np.float64)
+    assert perm[:2] == [7, 3] and list(diag[:2]) == [d, -0.0625 * d]
+    assert low[1, 0] == 0.75 and low[perm.index(5), 0] == 2.0 ** (exponents[k] // 2) / d
