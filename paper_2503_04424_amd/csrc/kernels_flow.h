@@ -44,7 +44,7 @@
 // another is written through (stores at device scope) and complete before the tile row's
 // counter says so; a task's own tiles are read past the caches; and finished tiles are read by
 // ordinary loads: they cannot be in any cache from before, as long as no 128-byte line holds
-// entries of two tiles.  Where the array's rows do not start on such lines (`lines` = false) the
+// entries of two tiles.  Where the array's rows do not start on such lines (LINES = false) the
 // operands are read past the caches as well.
 //
 // Order of the products of one entry: k rising in slabs of 128 bytes, inside a slab as
@@ -202,7 +202,6 @@ struct FlowShape {
 // What all tasks of a launch share.  LINES: the arrays' rows start on 128-byte lines.
 template <typename T, bool LINES>
 struct FlowArgs {
-  static constexpr bool lines = LINES;
   T* P;                 // the block column's diagonal entry
   int64_t ld;
   int m, w;             // rows, columns (w a multiple of LEAF, or m = w)

@@ -27,8 +27,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <limits>
-
 #include "kernels_leaf.h"
 #include "kernels_update.h"
 
