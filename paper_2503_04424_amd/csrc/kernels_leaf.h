@@ -952,10 +952,9 @@ __device__ __forceinline__ void leaf_lu_body(
   for (int jj = 0; jj < CW; ++jj) {
     const T cj = a[jj];
     refill();
-    // every row's own estimate beside the search, the pivot's out of them
-    const T ests = rcp_estimate(cj), tails = quotient_tail(cj, ests);
     const int p = pick_lane(cj, left);
-    const T est = lane_value(ests, p), tail = lane_value(tails, p);
+    const T d = lane_value(cj, p);
+    const T est = rcp_estimate(d), tail = quotient_tail(d, est);
     take(p);
     const bool below = __builtin_amdgcn_inverse_ballot_w64(left);
     const T np = -(cj * est);
