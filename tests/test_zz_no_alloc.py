@@ -91,6 +91,35 @@ def test_noalloc_entry_point_other_forms_and_error_reports(M):
                                               C.c_void_p(out.data_ptr()), None) == S.ENOMEM_DEVICE
 
 
+@pytest.mark.parametrize("flags", ["", "FLAG_ASSUME_SPD", "FLAG_PIVOT"])
+def test_noalloc_entry_point_takes_no_device_memory_where_a_call_goes_by_block_columns(M, flags):
+    # from 24576 rows on, an order that ends in part of a leaf: launches per block column, and the trailing updates between
+    # them, which smaller matrices never reach.  rho^|i-j|: log det = (n - 1) log(1 - rho^2)
+    n, ld, bs, rho = 24602, 24608, 2048, 0.5
+    k = torch.arange(n, device="cuda")
+    column = rho ** k.to(torch.float64)
+    a = torch.empty((n, ld), dtype=torch.float64, device="cuda")[:, :n]
+    for r in range(0, n, 2048):
+        a[r:r + 2048] = column[(k[r:r + 2048, None] - k[None, :]).abs()]
+    ref_in = torch.empty((n, ld), dtype=torch.float64, device="cuda")[:, :n].copy_(a)
+    out = torch.zeros(5, dtype=torch.float64, device="cuda")
+    f = getattr(M, flags) if flags else 0
+    # (a first call of any size loads the library's code)
+    assert M.mdet_logdet_device_noalloc(torch.eye(64, dtype=torch.float64, device="cuda"), out) == M.Status.OK
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    assert M.mdet_logdet_device_noalloc(a, out, block_size=bs, flags=f) == M.Status.OK
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free
+    ref = M.mdet_logdet_device(ref_in, block_size=bs, overwrite=True, flags=f | M.FLAG_NO_LOOKAHEAD)
+    got = out.cpu().numpy()
+    assert got[4] == M.Status.OK and got[0] == ref.logabsdet and int(got[1]) == ref.sign == 1
+    assert rel(got[0], (n - 1) * np.log(1 - rho * rho)) <= 1e-10
+    for r in range(0, n, 2048):                                # the stored factor too
+        assert torch.equal(torch.tril(a[r:r + 2048, :r + 2048], r), torch.tril(ref_in[r:r + 2048, :r + 2048], r))
+
+
 def test_noalloc_entry_point_recorded_into_a_graph_and_replayed(M):
     # what the entry point is for: the whole path recorded once into a HIP graph (capture refuses
     # allocations and waits) and replayed on new matrices in the same buffers, with eager work and
