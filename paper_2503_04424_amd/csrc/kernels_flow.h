@@ -24,11 +24,11 @@
 // elimination (leaf_factor_body), 0.7 + 3.2 + 0.9 + 6.7 us in fp64; everything else runs beside
 // that.  Between launches the same steps also wait for every workgroup of the launch before and
 // for the next one to start, and the updates between the leaves lie on the chain as well.  Measured
-// against the chain of launches, whole calls that keep their input: symmetric fp64 n = 512 229 -> 147 us,
+// against the chain of launches, whole calls that keep their input: symmetric fp64 n = 512 229 -> 145 us,
 // n = 1500 (positive definite) 603 -> 360, n = 5555 (positive definite) 3020 -> 1445, n = 8192 5873 -> 3550, fp32
-// n = 10000 5940 -> 3380; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 176.3 ms; pivots from
-// inside a leaf (24 us from leaf to leaf), n = 4096 3.04 -> 1.60 ms; general (26 us) n = 2900 2.27 -> 1.28, n = 8192 11.3 ->
-// 7.1.
+// n = 10000 5940 -> 3380; block columns of 2048 beside a bulk update, n = 32768, 190.9 -> 174.6 ms; pivots from
+// inside a leaf (23 us from leaf to leaf), n = 4096 3.04 -> 1.60 ms; general (25 us) n = 2900 2.27 -> 1.28, n = 8192 11.3 ->
+// 6.9.
 // Where a matrix is large: the
 // matrix cores, in fp64 3.6 us for the 128 x 64 x 64 products of a row task of one column and 7.0 for
 // 128 x 128 x 64 of two (positive-definite form 3.5 and 6.9; 3.4 and 6.8 at their peak; fp32 1.97 and 3.65 of 1.7

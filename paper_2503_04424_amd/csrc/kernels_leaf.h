@@ -667,7 +667,7 @@ __device__ __forceinline__ int pick_lane(float v, unsigned long long cand) {
 // inverses of the diagonal sub-blocks of L), and perm[j] = pivot0 + (row taken at step j).
 // Bound by the chain of one step (430 clocks: search 230, row from LDS 100, its terms so far, quotient);
 // the three products between cost 2500 clocks each.  Measured, fp64, inside panel_flow_kernel: 15.5 us a leaf,
-// 24.0 from one leaf to the next (with all 16 terms a step whatever their number, and the tile left of the leaf stored and
+// 23.1 from one leaf to the next (with all 16 terms a step whatever their number, and the tile left of the leaf stored and
 // the multipliers' places cleared in front of it, 26.4; n = 4096 1.69 -> 1.60 ms).
 // IN_LDS, THROUGH: as for leaf_factor_body; `lds` has PIVOT_LDS_ELEMS elements, of which with IN_LDS
 // the first LEAF_TILE hold the leaf, both triangles, row stride LEAF_PAD.  With THROUGH the other
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(64 * PIVOT_WAVES) void leaf_factor_pivoted_kernel(
 // with the leaf's row order as their column gather), perm[j] = pivot0 + (row of the leaf
 // taken at step j); flags->odd_leaves is raised by one if that order is an odd permutation.
 // Bound by the owner's chain: search 230 clocks (exchanges, a ballot), quotient 70, the next column's
-// update 100.  Measured, fp64, inside panel_flow_kernel: 14.8 us a leaf, 25.6 from one leaf to the next (27.4 with the tiles
+// update 100.  Measured, fp64, inside panel_flow_kernel: 14.8 us a leaf, 25.0 from one leaf to the next (27.4 with the tiles
 // left of the leaf stored in front of it and the leaves that they are solved against brought to LDS one after
 // the other; n = 2900 1.375 -> 1.282 ms).
 // IN_LDS, THROUGH: as for leaf_factor_body; `lds` has LU_LDS_ELEMS elements, of which with IN_LDS the

@@ -177,9 +177,10 @@ __global__ __launch_bounds__(PB_THREADS) void pb_step_kernel(
 // sub-blocks (as pb_leaf_kernel).  Same rule, same order of the terms as a sequence of
 // pb_step_kernel launches, where a launch and its memory round trips made a step 5.7 us.
 // Bound by a step's chain, w = 256, fp64: search 150 clocks, offer and barrier 140, best of the offers 190, row and
-// multipliers from LDS 150, products 370, quotient and the rest 200: 0.65 us.  A launch of 64 steps 44 us; 71 with the row
+// multipliers from LDS 150, products 370, quotient and the rest 200: 0.65 us.  A launch of 64 steps 43.5 us; 71 with the row
 // of S from memory (1100 clocks), a second barrier for the pivot's multipliers and a dozen jumps a step
-// (n = 3000, b = 256 4.89 -> 3.50 ms; where half of the rows taken are not held, 4.82 -> 3.81).
+// (n = 3000, ms, b = 256 and 512: fp64 4.82 -> 3.40, 5.85 -> 4.32, fp32 4.04 -> 2.82, 4.36 -> 3.03; where half of the
+// rows taken are not held, b = 256, 4.82 -> 3.81).
 // The multipliers of 512 rows are what a compute unit's registers hold (128 of 256 per
 // thread in fp64): larger blocks take a launch per step.
 constexpr int PB_GROUP_ROWS = 512;
@@ -237,7 +238,8 @@ __device__ __forceinline__ int pb_best(const PbOffer& o) {
   return __builtin_ctz(hit);
 }
 
-// Rows of S that LDS holds, with their multipliers: all 64 that a group takes where they fit.
+// Rows of S that LDS holds, with their multipliers: all 64 that a group takes where they fit (fp32); in fp64 as many as
+// there is room for, 62 of blocks up to 256 and 34 of wider ones.
 template <typename T, int NT>
 struct PbHeld {
   static constexpr int ROOM = 156 * 1024 / (int)sizeof(T);
